@@ -298,3 +298,91 @@ def tolerance(case):
         # block whose running sum meets eps within their rounding may fall on either side
         return {"rel": 1e-5, "differ": 2e-4}
     return {"rel": 1e-5}  # fp32 sums of products of probabilities
+
+
+# ---- the same outputs in 64 bits, plain torch ------------------------------------------------------------------------
+_EXACT_LOGITS = 1.2e11  # (query, key) pairs that take some 20 s
+
+
+def _attention64(q, k, v, scale, visible=None):
+    """Softmax attention of fp64 queries [n, D] over all keys (or those visible [n, N]), and its log-sum-exp."""
+    s = (q @ k.T) * scale
+    if visible is not None:
+        s = s.masked_fill(~visible, -math.inf)
+    lse = torch.logsumexp(s, 1)
+    return torch.exp(s - lse[:, None]) @ v, lse
+
+
+def _anchor_tokens(c):
+    """Of every token, the token whose query it takes: same frame and column, nearest of the anchor rows (rows under
+    the centres of equal segments, the lower one on a tie); text tokens keep their own."""
+    rows, cols, k = c["rows"], c["cols"], min(c["anchors"], c["rows"])
+    anchor = torch.tensor([(2 * j + 1) * rows // (2 * k) for j in range(k)])
+    row = torch.arange(rows)
+    nearest = anchor[(row[:, None] - anchor[None, :]).abs().argmin(1)]  # argmin: the first of equals
+    shift = ((nearest - row) * cols).repeat_interleave(cols).repeat(c["frames"])
+    own = torch.arange(_tokens(c))
+    own[:shift.numel()] += shift
+    return own.cuda()
+
+
+def exact(case, seed):
+    c = dict(case)
+    B, H, N, D, kind = c["B"], c["H"], _tokens(c), c["D"], c["kind"]
+    if B * H * float(N) * N * (2.0 if kind == HEADS else 1.0) > _EXACT_LOGITS:
+        return None
+    scale, dev = 1.0 / math.sqrt(D), "cuda"
+    step = max(1, int(1.2e8) // N)  # queries at a time
+    if kind in (FORWARD, ATTENTION):
+        q, k, v = _qkv(c, seed)
+        mask, repeat = _mask_and_repeat(c, H, seed + 1)
+        flagged = set()
+        if kind == ATTENTION:
+            flagged = set(np.random.default_rng(seed + 2).permutation(H)[:c["flagged"]].tolist())
+        bq, key_block = c["block_q"], torch.arange(N, device=dev) // c["block_k"]
+        out = torch.empty((B, H, N, D), dtype=torch.float64, device=dev)
+        lse = torch.empty((B, H, N), dtype=torch.float64, device=dev)
+        for b in range(B):
+            for h in range(H):
+                qh, kh, vh = (t[b, h].double() for t in (q, k, v))
+                if h in flagged:
+                    source = _anchor_tokens(c)
+                    visible = None
+                else:
+                    visible = torch.from_numpy(mask[h]).to(dev).bool()
+                    rep = torch.from_numpy(repeat[h]).to(dev).long()
+                    t = torch.arange(N, device=dev)
+                    source = torch.where(rep[t // bq] >= 0, rep[t // bq] * bq + t % bq, t)
+                todo = torch.unique(source)
+                for i in range(0, todo.numel(), step):
+                    at = todo[i:i + step]
+                    see = None if visible is None else visible[at // bq][:, key_block]
+                    out[b, h, at], lse[b, h, at] = _attention64(qh[at], kh, vh, scale, see)
+                out[b, h], lse[b, h] = out[b, h, source], lse[b, h, source]
+        return (out, lse) if c["lse"] and kind == FORWARD else out
+    q, k = _qkv(c, seed, with_v=False)
+    nbq, nbk = _blocks(N, c["block_q"]), _blocks(N, c["block_k"])
+    if kind == MASKS:
+        row_block, key_block = torch.arange(N, device=dev) // c["block_q"], torch.arange(N, device=dev) // c["block_k"]
+        energy = torch.zeros((B, H, nbq, nbk), dtype=torch.float64, device=dev)
+        for b in range(B):
+            for h in range(H):
+                qh, kh = q[b, h].double(), k[b, h].double()
+                for i in range(0, N, step):
+                    p = torch.softmax((qh[i:i + step] @ kh.T) * scale, 1)
+                    mass = torch.zeros((p.shape[0], nbk), dtype=torch.float64, device=dev).index_add_(1, key_block, p)
+                    energy[b, h].index_add_(0, row_block[i:i + step], mass)
+        energy /= torch.bincount(row_block).double()[:, None]
+        return energy, None, None  # a block at the edge of eps has no one answer
+    n_tok = N - c["text"]
+    source = _anchor_tokens(c)[:n_tok]
+    triples = torch.empty((B, H, n_tok, 3), dtype=torch.float64, device=dev)
+    for b in range(B):
+        for h in range(H):
+            qh, kh = q[b, h].double(), k[b, h].double()
+            for i in range(0, n_tok, step):
+                p = torch.softmax((qh[i:min(i + step, n_tok)] @ kh.T) * scale, 1)
+                pa = torch.softmax((qh[source[i:i + step]] @ kh.T) * scale, 1)
+                triples[b, h, i:i + step] = torch.stack([(p * pa).sum(1), (p * p).sum(1), (pa * pa).sum(1)], 1)
+    rows = triples.reshape(B, H, n_tok // c["cols"], c["cols"], 3).sum(3)
+    return (rows[..., 0] / torch.sqrt(rows[..., 1] * rows[..., 2])).mean(2), triples
