@@ -411,6 +411,24 @@ int calibatt_spatial_similarity(const void *q, const void *k, int B, int H, int 
                                 float *workspace, float *score, void *stream);
 
 /*
+ * calibatt_spatial_similarity with scratch memory for the work division:
+ * tokens of one column that share their partner are computed together, with
+ * the partner's row of logits once per group instead of once per token.  The
+ * result has the same bits.
+ *   lists      DEVICE, 16-byte aligned, contents free before and after the
+ *              call; NULL = calibatt_spatial_similarity.  36 * n_tok + 16
+ *              bytes; calibatt_similarity_lists_bytes writes that number, or 0
+ *              where too little work is in the call for grouping to pay.
+ * Errors: as calibatt_spatial_similarity; SHAPE (misaligned lists, a negative
+ * lists_bytes), BUFFER_TOO_SMALL.
+ */
+int calibatt_similarity_lists_bytes(int B, int H, int n_tok, int64_t *bytes);
+int calibatt_spatial_similarity_grouped(const void *q, const void *k, int B, int H, int N, int D,
+                                        const int32_t *partner, int n_tok, int row_len, float scale,
+                                        float *workspace, void *lists, int64_t lists_bytes, float *score,
+                                        void *stream);
+
+/*
  * calibatt_spatial_similarity for callers that cannot allocate device memory
  * or hand a workspace over (code under HIP graph capture, serving loops that
  * forbid hipMalloc): the per-token sums live in a buffer inside the library,

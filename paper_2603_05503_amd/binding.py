@@ -133,6 +133,12 @@ def load_library():
     lib.calibatt_spatial_similarity.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int,
                                                 C.c_void_p, C.c_int, C.c_int, C.c_float, C.c_void_p, C.c_void_p,
                                                 C.c_void_p]
+    lib.calibatt_similarity_lists_bytes.restype = C.c_int
+    lib.calibatt_similarity_lists_bytes.argtypes = [C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int64)]
+    lib.calibatt_spatial_similarity_grouped.restype = C.c_int
+    lib.calibatt_spatial_similarity_grouped.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int,
+                                                        C.c_void_p, C.c_int, C.c_int, C.c_float, C.c_void_p,
+                                                        C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p]
     lib.calibatt_spatial_similarity_static.restype = C.c_int
     lib.calibatt_spatial_similarity_static.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_int,
                                                        C.c_void_p, C.c_int, C.c_int, C.c_float, C.c_void_p, C.c_void_p]
@@ -742,11 +748,18 @@ def spatial_similarity(q, k, partner, row_len: int, scale: float, workspace=None
     if workspace is None:
         workspace = torch.empty((B, H, max(n_tok, 1), 3), dtype=torch.float32, device=q.device)
     score = torch.empty((B, H), dtype=torch.float32, device=q.device)
+    nbytes = C.c_int64(0)
+    lists = None
+    if lib.calibatt_similarity_lists_bytes(B, H, n_tok, C.byref(nbytes)) == 0 and nbytes.value > 0:
+        lists = torch.empty(nbytes.value, dtype=torch.uint8, device=q.device)
+        if stream is not None:  # released on return: its memory must not be reused before that stream is done with it
+            lists.record_stream(torch.cuda.ExternalStream(stream, device=q.device))
     if stream is None:
         stream = torch.cuda.current_stream(q.device).cuda_stream
-    st = lib.calibatt_spatial_similarity(q.data_ptr(), k.data_ptr(), B, H, N, D, partner.data_ptr(), n_tok,
-                                         int(row_len), float(scale), workspace.data_ptr(), score.data_ptr(),
-                                         C.c_void_p(stream))
+    st = lib.calibatt_spatial_similarity_grouped(q.data_ptr(), k.data_ptr(), B, H, N, D, partner.data_ptr(), n_tok,
+                                                 int(row_len), float(scale), workspace.data_ptr(),
+                                                 None if lists is None else lists.data_ptr(), nbytes.value,
+                                                 score.data_ptr(), C.c_void_p(stream))
     if st != 0:
         raise CalibattError(st, "calibatt_spatial_similarity")
     return score

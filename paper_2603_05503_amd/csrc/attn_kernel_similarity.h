@@ -9,15 +9,30 @@
 //     dot[t] = sum_j P[t][j] P[a][j],  nt[t] = sum_j P[t][j]^2,  na[t] = sum_j P[a][j]^2
 // and per spatial row  cos = sum_x dot / sqrt(sum_x nt * sum_x na).
 //
-// Kernel 1: one workgroup per (batch, head, 128 tokens).  A lane owns a token
-// AND its partner: two query operands, two score tiles per key tile
-// (RowBlock::scores twice), ONE pass over all keys: the row sums of both and
-// the three sums of products are kept relative to the running maxima of the
-// two queries and rescaled when a maximum moves (the sums of products by the
-// product of the two factors), exactly as an online softmax keeps its row sum;
-// the normalisers divide out at the end.  Writes the normalised triple of
-// every token.
-// Kernel 2: one wavefront per (batch, head) adds the triples of each spatial
+// Main kernel: one workgroup per (batch, head, 128 lane groups).  A lane holds
+// R + 1 queries - one partner and up to R tokens that share it - and makes ONE
+// pass over all keys: row sums, sums of squares and the R sums of products are
+// kept relative to a reference per query that is moved, and the sums rescaled,
+// only when a logit leaves the safe range above it; the normalisers divide out
+// at the end.  Writes the normalised triple of every token.
+//
+// What bounds it: the vector ALU (per logit an FMA, an exponential, two or
+// three sums) beside the matrix cores, and the power both draw.  A token and
+// its partner alone (R = 1) cost two rows of logits; tokens that share their
+// partner's row cost (R + 1) / R each, and one K operand read from LDS feeds
+// R + 1 MFMAs.  All quantities of a query or pair are computed by the same
+// operations in the same order whatever else the lane and the wave hold, so the
+// bits do not depend on how the tokens were grouped.
+//
+// Measured, 24 heads of 21 x 30 x 52 tokens, D = 128, five anchors, in turn on one box: 14.37 ms with every token
+// beside its own partner and one wavefront per head in the reduction, 10.49 ms as it is here (matrix pipes busy
+// 43 % of the cycles, vector ALU 72 %, at 1.9 GHz).
+//
+// Grouping (similarity_group_kernel): the tokens of one column of the grid in
+// consecutive spatial rows form a run while they have the same partner; a run
+// is cut into groups of R.  Groups are appended to a list in any order.
+//
+// Reduction kernel: one workgroup per (batch, head) adds the triples of each spatial
 // row, forms the cosine and averages over rows in a fixed order.
 #pragma once
 #include "attn_kernel_2wg.h"
@@ -30,150 +45,389 @@ struct SimilarityDims {
 };
 
 constexpr int SIM_BQ = 128;
-constexpr int SIM_BK = 128;
+constexpr int SIM_BK = 64;
 constexpr int SIM_XCDS = 8;
+// Above this many units of 128 tokens the tokens are grouped.  Up to it every unit has a workgroup slot of its own
+// (two on each of 256 CUs) and the pass lasts as long as one unit: two rows of logits per lane, against three or
+// four with the tokens grouped.  Above it there is a second round: four rows against three.
+constexpr int SIM_GROUP_UNITS = 512;
 
+// ---- lists of the grouped form -------------------------------------------------------------------
+// int32 words: [0..2] numbers of 2-token groups, 3-token groups and lone tokens, [4 ..] the 3-token
+// groups (4 words each: partner, tokens; -1 = none), the 2-token groups (likewise) and the lone tokens,
+// room for n_tok of each.  A partner that takes its own triple from this group is stored as ~partner.
+struct SimilarityLists {
+  static constexpr int SEGMENT = 64;  // rows at which a run ends in any case: bounds the walks below
+  static __host__ __device__ long long bytes(int n_tok) { return 16 + 36LL * n_tok; }
+  static __device__ __forceinline__ int4 *groups(int32_t *lists, int n_tok, int R) {
+    return reinterpret_cast<int4 *>(lists + 4) + (R == 3 ? 0 : n_tok);
+  }
+  static __device__ __forceinline__ int32_t *lone(int32_t *lists, int n_tok) { return lists + 4 + 8LL * n_tok; }
+};
+
+__global__ __launch_bounds__(64) void similarity_clear_kernel(int32_t *__restrict__ lists) {
+  if (threadIdx.x < 4) lists[threadIdx.x] = 0;
+}
+
+__device__ __forceinline__ int similarity_partner(const int32_t *__restrict__ partner, int t, int N) {
+  const int a = partner[t];
+  return a < 0 ? 0 : (a < N ? a : N - 1);
+}
+
+// One thread per token.
+__global__ __launch_bounds__(256) void similarity_group_kernel(const int32_t *__restrict__ partner,
+                                                               int32_t *__restrict__ lists, int N, int n_tok,
+                                                               int row_len) {
+  const int t = blockIdx.x * 256 + threadIdx.x;
+  const bool here = t < n_tok;
+  const int a = here ? similarity_partner(partner, t, N) : -1;
+  const int row = here ? t / row_len : 0;
+  const int first_row = row / SimilarityLists::SEGMENT * SimilarityLists::SEGMENT;
+  const int last_row = min(first_row + SimilarityLists::SEGMENT, n_tok / row_len) - 1;
+  // tokens of the run before and behind this one that are not their own partner, and whether the partner is among them
+  int before = 0, behind = 0, next[2] = {-1, -1};
+  bool own = false;
+  if (here) {
+    for (int y = row - 1, u = t - row_len; y >= first_row; --y, u -= row_len) {
+      if (similarity_partner(partner, u, N) != a) break;
+      if (u == a) own = true; else ++before;
+    }
+    for (int y = row + 1, u = t + row_len; y <= last_row; ++y, u += row_len) {
+      if (similarity_partner(partner, u, N) != a) break;
+      if (u == a) {
+        own = true;
+      } else {
+        if (behind < 2) next[behind] = u;
+        ++behind;
+      }
+    }
+  }
+  // appends to a list: one atomic per wavefront
+  auto append = [&](bool mine, int32_t *counter) {
+    const unsigned long long who = __ballot(mine);
+    const int lane = threadIdx.x & 63;
+    int base = 0;
+    if (who && lane == __ffsll(who) - 1) base = atomicAdd(counter, __popcll(who));
+    if (who) base = __shfl(base, __ffsll(who) - 1);
+    return base + __popcll(who & ((1ull << lane) - 1));
+  };
+  const bool grouped = here && a != t;
+  const int stored = before == 0 && own ? ~a : a;
+  const bool starts3 = grouped && before % 3 == 0, starts2 = grouped && before % 2 == 0;
+  const bool lone = here && a == t && before + behind == 0;
+  const int at3 = append(starts3, lists + 1);
+  const int at2 = append(starts2, lists);
+  const int at1 = append(lone, lists + 2);
+  if (starts3) SimilarityLists::groups(lists, n_tok, 3)[at3] = make_int4(stored, t, next[0], next[1]);
+  if (starts2) SimilarityLists::groups(lists, n_tok, 2)[at2] = make_int4(stored, t, next[0], -1);
+  if (lone) SimilarityLists::lone(lists, n_tok)[at1] = t;
+}
+
+// ---- one lane group: partner tok[0] and tokens tok[1..R] against all keys -------------------------
+// The queries of a lane live in registers; with four of them at D = 128 (128 registers beside 64 of scores) the
+// partner's goes to LDS behind the two K tiles, where the lane that wrote it reads it back for every MFMA.
+template <int D, int R>
+struct SimilarityLds {
+  static constexpr bool PARTNER_IN_LDS = D == 128 && R == 3;
+  static constexpr int PARTNER_OFF = 2 * RowBlock<D, SIM_BQ, SIM_BK>::TILE_BYTES;  // [wave][D / 16][lane] x 16 bytes
+  static constexpr int RUN_OFF = PARTNER_OFF + (PARTNER_IN_LDS ? SIM_BQ * D * 2 : 0);  // the third level of sums:
+  static constexpr int BYTES = RUN_OFF + (3 * R + 2) * SIM_BQ * 2 * 4;                 // float[3 R + 2][threads]
+};
+
+template <int D, int R>
+struct SimilaritySums {
+  float l[R + 1], sq[R + 1], dot[R + 1];  // row sum, sum of squares, sum of products with the partner (dot[0] unused)
+};
+
+template <int D, int R>
+__device__ __forceinline__ SimilaritySums<D, R> similarity_pass(
+    const RowBlock<D, SIM_BQ, SIM_BK> &rb, const u32x4 &Kres, const uint16_t *__restrict__ head_q,
+    const int (&tok)[R + 1], const SimilarityDims &p) {
+  using RB = RowBlock<D, SIM_BQ, SIM_BK>;
+  constexpr int KB = RB::KB, DS = RB::DS, ROWB = RB::ROWB, TILE_BYTES = RB::TILE_BYTES, S = R + 1;
+  constexpr float SAFE = 0x1p40f;  // largest partial row sum against the present reference; its square stays in range
+  rb.issue_k_at(Kres, 0, 0);
+  using L = SimilarityLds<D, R>;
+  constexpr int FIRST = L::PARTNER_IN_LDS ? 1 : 0;  // first query in registers
+  using Operand = typename RB::Operand;
+  Operand q[S][DS];
+  Operand *const partner_q = reinterpret_cast<Operand *>(rb.lds + L::PARTNER_OFF) + rb.wave * DS * 64 + rb.lane;
+  if constexpr (L::PARTNER_IN_LDS) {
+    rb.load_q(head_q + (size_t)tok[0] * D, q[0]);
+#pragma unroll
+    for (int d = 0; d < DS; ++d) partner_q[d * 64] = q[0][d];
+  }
+#pragma unroll
+  for (int i = FIRST; i < S; ++i) rb.load_q(head_q + (size_t)tok[i] * D, q[i]);
+
+  const int N = p.N, nbk = p.nbk;
+  const float sc = p.scale_log2e;
+  const bool ragged = (N % SIM_BK) != 0;
+  // Three levels of sums - 16 logits, FLUSH tiles (32 such sums), all - so that no chain of fp32 additions is much
+  // longer than the others: the rounding of a long chain is what the error of the result consists of.  The third
+  // level is touched every FLUSH tiles and lives in LDS, each lane's own words.
+  constexpr int FLUSH = 16;
+  float *const run = reinterpret_cast<float *>(rb.lds + L::RUN_OFF) + rb.tid;
+  auto run_l = [&](int i) -> float & { return run[i * RB::NT]; };
+  auto run_sq = [&](int i) -> float & { return run[(S + i) * RB::NT]; };
+  auto run_dot = [&](int i) -> float & { return run[(2 * S + i - 1) * RB::NT]; };  // i > 0
+  SimilaritySums<D, R> mid;
+  float m[S];
+#pragma unroll
+  for (int i = 0; i < S; ++i) {
+    m[i] = -INFINITY;
+    run_l(i) = run_sq(i) = 0.f;
+    if (i > 0) run_dot(i) = 0.f;
+    mid.l[i] = mid.sq[i] = mid.dot[i] = 0.f;
+  }
+  for (int c = 0; c < nbk; ++c) {
+    wait_vmem<0>();
+    __syncthreads();  // tile c has landed for every wave; everyone is done with the other buffer
+    if (c + 1 < nbk) rb.issue_k_at(Kres, c + 1, ((c + 1) & 1) * TILE_BYTES);
+    const char *const tile = rb.ldsK + (c & 1) * TILE_BYTES;
+#pragma unroll 1
+    for (int kb = 0; kb < KB; ++kb) {
+      const char *const kbuf = tile + kb * 32 * ROWB;
+      f32x16 s[S];
+#pragma unroll
+      for (int i = 0; i < S; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[i][v] = 0.f;
+#pragma unroll
+      for (int d = 0; d < DS; ++d) {
+        const Operand ka = *reinterpret_cast<const Operand *>(kbuf + (rb.k_addr0 ^ (d << 5)));
+        if constexpr (L::PARTNER_IN_LDS) s[0] = Bf16::mfma(ka, partner_q[d * 64], s[0]);
+#pragma unroll
+        for (int i = FIRST; i < S; ++i) s[i] = Bf16::mfma(ka, q[i][d], s[i]);
+      }
+      float sc_t = sc;
+      if (ragged && c == nbk - 1) {  // keys >= N to -inf; the scale is applied up front, multiplier 1 from then on
+        int limit = N - c * SIM_BK - 32 * kb - 8 * rb.g;  // this lane's key offsets below `limit` exist
+        asm volatile("" : "+v"(limit));                   // keeps the comparisons inside this branch
+#pragma unroll
+        for (int i = 0; i < S; ++i)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) s[i][v] = 16 * (v >> 3) + (v & 7) < limit ? s[i][v] * sc : -INFINITY;
+        sc_t = 1.0f;
+      }
+      SimilaritySums<D, R> part;
+      auto sum = [&]() {
+#pragma unroll
+        for (int i = 0; i < S; ++i) part.l[i] = part.sq[i] = part.dot[i] = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          float e[S];
+#pragma unroll
+          for (int i = 0; i < S; ++i) {
+            e[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i][v], sc_t, -m[i]));
+            part.l[i] += e[i];
+            part.sq[i] = __builtin_fmaf(e[i], e[i], part.sq[i]);
+            if (i > 0) part.dot[i] = __builtin_fmaf(e[i], e[0], part.dot[i]);
+          }
+        }
+      };
+      sum();
+      bool bad = false;
+#pragma unroll
+      for (int i = 0; i < S; ++i) bad |= !(part.l[i] < SAFE);
+      if (__any(bad)) {  // always on the first sub-tile, where the references are -inf
+        float alpha[S];
+#pragma unroll
+        for (int i = 0; i < S; ++i) {
+          float m_loc = sc_t >= 0.f ? -INFINITY : INFINITY;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) m_loc = sc_t >= 0.f ? fmaxf(m_loc, s[i][v]) : fminf(m_loc, s[i][v]);
+          // either half of the query's lanes out of range: both move
+          const bool move = !(max_with_other_half(part.l[i] < SAFE ? 0.f : 1.f) < 0.5f);
+          const float m_new = move ? fmaxf(m[i], max_with_other_half(m_loc * sc_t)) : m[i];
+          alpha[i] = move ? __builtin_amdgcn_exp2f(m[i] - m_new) : 1.f;  // 0 on the first sub-tile
+          m[i] = m_new;
+          run_l(i) *= alpha[i];
+          mid.l[i] *= alpha[i];
+          run_sq(i) *= alpha[i] * alpha[i];
+          mid.sq[i] *= alpha[i] * alpha[i];
+          if (i > 0) run_dot(i) *= alpha[i] * alpha[0];
+          if (i > 0) mid.dot[i] *= alpha[i] * alpha[0];
+        }
+        sum();
+      }
+#pragma unroll
+      for (int i = 0; i < S; ++i) {
+        mid.l[i] += part.l[i];
+        mid.sq[i] += part.sq[i];
+        if (i > 0) mid.dot[i] += part.dot[i];
+      }
+    }
+    if (c % FLUSH == FLUSH - 1 || c == nbk - 1) {
+#pragma unroll
+      for (int i = 0; i < S; ++i) {
+        run_l(i) += mid.l[i];
+        run_sq(i) += mid.sq[i];
+        if (i > 0) run_dot(i) += mid.dot[i];
+        mid.l[i] = mid.sq[i] = mid.dot[i] = 0.f;
+      }
+    }
+  }
+  SimilaritySums<D, R> total;
+  float w[S];
+#pragma unroll
+  for (int i = 0; i < S; ++i) {
+    total.l[i] = sum_with_other_half(run_l(i));
+    w[i] = 1.0f / total.l[i];
+    total.sq[i] = sum_with_other_half(run_sq(i)) * w[i] * w[i];
+    total.dot[i] = i > 0 ? sum_with_other_half(run_dot(i)) * w[i] * w[0] : 0.f;
+  }
+  return total;
+}
+
+__device__ __forceinline__ void store_triple(float *__restrict__ head_triples, int t, float dot, float nt, float na) {
+  float *const o = head_triples + (size_t)t * 3;
+  o[0] = dot;
+  o[1] = nt;
+  o[2] = na;
+}
+
+// Position of a workgroup in the sequence of all units (units_per_head of each (batch, head)), cut into one
+// contiguous range per XCD; false when it has none.
+__device__ __forceinline__ bool similarity_unit(const SimilarityDims &p, int units_per_head, int &bh, int &r) {
+  const int xcd = blockIdx.x % SIM_XCDS;
+  const int slot = blockIdx.x / SIM_XCDS;
+  const long long units = (long long)p.B * p.H * units_per_head;
+  const long long lo = units * xcd / SIM_XCDS;
+  const long long hi = units * (xcd + 1) / SIM_XCDS;
+  if (slot >= hi - lo) return false;
+  const int unit = (int)(lo + slot);
+  r = unit % units_per_head;
+  bh = unit / units_per_head;
+  return true;
+}
+
+// Every token with its partner, without lists.
 template <int D>
 __global__ __launch_bounds__(SIM_BQ * 2, 2) void pair_similarity_kernel(
     const uint16_t *__restrict__ gq, const uint16_t *__restrict__ gk, const int32_t *__restrict__ partner,
     float *__restrict__ triples, const SimilarityDims p) {
-  constexpr int BQ = SIM_BQ, BK = SIM_BK;
-  using RB = RowBlock<D, BQ, BK>;
-  constexpr int KB = RB::KB, DS = RB::DS, ROWB = RB::ROWB, TILE_BYTES = RB::TILE_BYTES;
-
+  using RB = RowBlock<D, SIM_BQ, SIM_BK>;
   extern __shared__ __attribute__((aligned(1024))) char lds[];  // two K tiles
-
-  const int xcd = blockIdx.x % SIM_XCDS;
-  const int slot = blockIdx.x / SIM_XCDS;
-  const long long units = (long long)p.B * p.H * p.nbq;
-  const long long lo = units * xcd / SIM_XCDS;
-  const long long hi = units * (xcd + 1) / SIM_XCDS;
-  if (slot >= hi - lo) return;
-  const int unit = (int)(lo + slot);
-  const int r = unit % p.nbq;
-  const int bh = unit / p.nbq;
-
+  int bh, r;
+  if (!similarity_unit(p, p.nbq, bh, r)) return;
   RB rb(lds);
-  const int N = p.N;
-  const size_t head_off = (size_t)bh * (size_t)N * D;
-  const u32x4 Kres = head_rsrc(gk + head_off, (uint32_t)N * ROWB);
-  rb.issue_k_at(Kres, 0, 0);
+  const size_t head_off = (size_t)bh * (size_t)p.N * D;
+  const int tok_raw = r * SIM_BQ + rb.row_in_block();
+  const int t = min(tok_raw, p.n_tok - 1);
+  const int tok[2] = {similarity_partner(partner, t, p.N), t};
+  const SimilaritySums<D, 1> sums =
+      similarity_pass<D, 1>(rb, head_rsrc(gk + head_off, (uint32_t)p.N * RB::ROWB), gq + head_off, tok, p);
+  if (tok_raw < p.n_tok && rb.g == 0)
+    store_triple(triples + (size_t)bh * p.n_tok * 3, t, sums.dot[1], sums.sq[1], sums.sq[0]);
+}
 
-  const int tok_raw = r * BQ + rb.row_in_block();
-  const bool valid = tok_raw < p.n_tok;
-  const int tok = valid ? tok_raw : p.n_tok - 1;
-  int par = partner[tok];
-  par = par < 0 ? 0 : (par < N ? par : N - 1);
-  typename RB::Operand q_t[DS], q_a[DS];
-  rb.load_q(gq + head_off + (size_t)tok * D, q_t);
-  rb.load_q(gq + head_off + (size_t)par * D, q_a);
-
-  const float sc = p.scale_log2e;
-  const bool ragged = (N % BK) != 0;
-  float m_t = -INFINITY, l_t = 0.f, m_a = -INFINITY, l_a = 0.f;
-  float dot = 0.f, nt = 0.f, na = 0.f;
-
-  // largest scaled logit of one query over one tile of raw products (multiplier sc_t still to apply),
-  // folded into the running maximum; returns the factor 2^(old max - new max) for what was summed so far
-  auto fold_max = [&](const f32x16 (&s)[KB], float sc_t, float &m_run) {
-    float m_loc;
-    if (sc_t >= 0.f) {
-      m_loc = -INFINITY;
+template <int D, int R>
+__device__ __forceinline__ void grouped_similarity(char *lds, const uint16_t *__restrict__ gq,
+                                                   const uint16_t *__restrict__ gk, int32_t *__restrict__ lists,
+                                                   float *__restrict__ triples, const SimilarityDims &p, int n_groups,
+                                                   int n_lone) {
+  using RB = RowBlock<D, SIM_BQ, SIM_BK>;
+  const int n_lone_groups = (n_lone + R) / (R + 1);  // R + 1 tokens that are their own partners per lane
+  const int group_units = (n_groups + SIM_BQ - 1) / SIM_BQ;
+  int bh, r;
+  if (!similarity_unit(p, group_units + (n_lone_groups + SIM_BQ - 1) / SIM_BQ, bh, r)) return;
+  RB rb(lds);
+  const bool lone = r >= group_units;
+  const int at = (lone ? r - group_units : r) * SIM_BQ + rb.row_in_block();
+  int id[R + 1];
+  bool own = false;
+  if (lone) {
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) m_loc = fmaxf(m_loc, s[kb][v]);
-    } else {
-      m_loc = INFINITY;
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) m_loc = fminf(m_loc, s[kb][v]);
+    for (int i = 0; i <= R; ++i) {
+      const int j = at * (R + 1) + i;
+      id[i] = j < n_lone ? SimilarityLists::lone(lists, p.n_tok)[j] : -1;
     }
-    const float m_new = fmaxf(m_run, max_with_other_half(m_loc * sc_t));
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);  // 0 on the first tile
-    m_run = m_new;
-    return alpha;
-  };
-  // keys >= N of the ragged last tile to -inf; scales the tile up front
-  auto mask_tail = [&](f32x16 (&s)[KB], int c) {
-    int limit = N - c * BK - 8 * rb.g;  // this lane's key offsets below `limit` exist
-    asm volatile("" : "+v"(limit));      // keeps the comparisons (and their 64 masks) out of the tile loop's prologue
+  } else if (at < n_groups) {
+    const int4 g = SimilarityLists::groups(lists, p.n_tok, R)[at];
+    own = g.x < 0;
+    id[0] = own ? ~g.x : g.x;
+    id[1] = g.y;
+    if constexpr (R > 1) id[2] = g.z;
+    if constexpr (R > 2) id[3] = g.w;
+  } else {
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v)
-        s[kb][v] = 32 * kb + 16 * (v >> 3) + (v & 7) < limit ? s[kb][v] * sc : -INFINITY;
-  };
-
-  // One pass: all five sums are kept relative to the running maxima of the two queries and
-  // rescaled when a maximum moves, like the row sum of an online softmax.  Tile c sits in buffer c & 1.
-  for (int c = 0; c < p.nbk; ++c) {
-    wait_vmem<0>();
-    __syncthreads();  // tile c has landed for every wave; everyone is done with the other buffer
-    if (c + 1 < p.nbk) rb.issue_k_at(Kres, c + 1, ((c + 1) & 1) * TILE_BYTES);
-    f32x16 s_t[KB], s_a[KB];
-    rb.scores((c & 1) * TILE_BYTES, s_t, q_t);
-    rb.scores((c & 1) * TILE_BYTES, s_a, q_a);
-    float sc_t = sc;
-    if (ragged && c == p.nbk - 1) {
-      mask_tail(s_t, c);
-      mask_tail(s_a, c);
-      sc_t = 1.0f;
-    }
-    const float alpha_t = fold_max(s_t, sc_t, m_t);
-    const float alpha_a = fold_max(s_a, sc_t, m_a);
-    float sum_t = 0.f, sum_a = 0.f, sum_ta = 0.f, sum_tt = 0.f, sum_aa = 0.f;
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float et = __builtin_amdgcn_exp2f(__builtin_fmaf(s_t[kb][v], sc_t, -m_t));
-        const float ea = __builtin_amdgcn_exp2f(__builtin_fmaf(s_a[kb][v], sc_t, -m_a));
-        sum_t += et;
-        sum_a += ea;
-        sum_ta = __builtin_fmaf(et, ea, sum_ta);
-        sum_tt = __builtin_fmaf(et, et, sum_tt);
-        sum_aa = __builtin_fmaf(ea, ea, sum_aa);
-      }
-    l_t = __builtin_fmaf(l_t, alpha_t, sum_t);
-    l_a = __builtin_fmaf(l_a, alpha_a, sum_a);
-    dot = __builtin_fmaf(dot, alpha_t * alpha_a, sum_ta);
-    nt = __builtin_fmaf(nt, alpha_t * alpha_t, sum_tt);
-    na = __builtin_fmaf(na, alpha_a * alpha_a, sum_aa);
+    for (int i = 0; i <= R; ++i) id[i] = -1;
   }
-  const float wt = 1.0f / sum_with_other_half(l_t);
-  const float wa = 1.0f / sum_with_other_half(l_a);
-  dot = sum_with_other_half(dot) * wt * wa;
-  nt = sum_with_other_half(nt) * wt * wt;
-  na = sum_with_other_half(na) * wa * wa;
-  if (valid && rb.g == 0) {
-    float *o = triples + ((size_t)bh * p.n_tok + tok) * 3;
-    o[0] = dot;
-    o[1] = nt;
-    o[2] = na;
+  int tok[R + 1];  // slots without a token repeat another one's work
+#pragma unroll
+  for (int i = 0; i <= R; ++i) tok[i] = id[i] >= 0 ? id[i] : max(id[0], 0);
+  const size_t head_off = (size_t)bh * (size_t)p.N * D;
+  const SimilaritySums<D, R> sums =
+      similarity_pass<D, R>(rb, head_rsrc(gk + head_off, (uint32_t)p.N * RB::ROWB), gq + head_off, tok, p);
+  if (rb.g != 0) return;
+  float *const out = triples + (size_t)bh * p.n_tok * 3;
+#pragma unroll
+  for (int i = 0; i <= R; ++i) {
+    if (id[i] < 0) continue;
+    if (lone || (i == 0 && own))
+      store_triple(out, id[i], sums.sq[i], sums.sq[i], sums.sq[i]);
+    else if (i > 0)
+      store_triple(out, id[i], sums.dot[i], sums.sq[i], sums.sq[0]);
   }
 }
 
-// score[b*H + h] = mean over the n_tok / row_len spatial rows of the row's cosine.
-__global__ __launch_bounds__(64) void similarity_reduce_kernel(const float *__restrict__ triples,
-                                                               float *__restrict__ score, int n_tok, int row_len) {
+// Three tokens per group cost fewer rows of logits, two waste fewer lanes on a short last group and are
+// smaller units of work: the form with the fewer rows of logits on the longest queue is taken, counting
+// whole rounds of the `slots` workgroups an XCD holds at a time.
+template <int D>
+__global__ __launch_bounds__(SIM_BQ * 2, 2) void grouped_similarity_kernel(
+    const uint16_t *__restrict__ gq, const uint16_t *__restrict__ gk, int32_t *__restrict__ lists,
+    float *__restrict__ triples, const SimilarityDims p, int slots) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];  // two K tiles
+  const int n2 = lists[0], n3 = lists[1], n_lone = lists[2];
+  auto rows = [&](int groups, int R) {
+    const long long lone = (n_lone + R) / (R + 1);
+    const long long units = (long long)p.B * p.H * ((groups + SIM_BQ - 1) / SIM_BQ + (lone + SIM_BQ - 1) / SIM_BQ);
+    const long long longest = (units + SIM_XCDS - 1) / SIM_XCDS;
+    return (longest + slots - 1) / slots * (R + 1);
+  };
+  if (rows(n3, 3) <= rows(n2, 2))
+    grouped_similarity<D, 3>(lds, gq, gk, lists, triples, p, n3, n_lone);
+  else
+    grouped_similarity<D, 2>(lds, gq, gk, lists, triples, p, n2, n_lone);
+}
+
+// score[b*H + h] = mean over the n_tok / row_len spatial rows of the row's cosine.  A half wavefront adds the
+// triples of one row at a time (lane x takes the columns x, x + 32, ...); the 32 rows in flight of a workgroup and
+// then its half wavefronts are added in a fixed order.
+constexpr int SIM_REDUCE_THREADS = 1024;
+__global__ __launch_bounds__(SIM_REDUCE_THREADS) void similarity_reduce_kernel(const float *__restrict__ triples,
+                                                                               float *__restrict__ score, int n_tok,
+                                                                               int row_len) {
+  constexpr int HALVES = SIM_REDUCE_THREADS / 32;
+  __shared__ float part[HALVES];
   const int bh = blockIdx.x;
   const int n_rows = n_tok / row_len;
-  const float *base = triples + (size_t)bh * n_tok * 3;
+  const int half = threadIdx.x / 32, x0 = threadIdx.x % 32;
+  const float *const base = triples + (size_t)bh * n_tok * 3;
   float acc = 0.f;
-  for (int row = threadIdx.x; row < n_rows; row += 64) {
+  for (int row0 = 0; row0 < n_rows; row0 += HALVES) {  // every lane takes part in the sums of every round
+    const int row = row0 + half;
     float dot = 0.f, nt = 0.f, na = 0.f;
-    for (int x = 0; x < row_len; ++x) {
-      const float *t = base + ((size_t)row * row_len + x) * 3;
-      dot += t[0];
-      nt += t[1];
-      na += t[2];
-    }
-    acc += dot / (sqrtf(nt) * sqrtf(na));
+    if (row < n_rows)
+      for (int x = x0; x < row_len; x += 32) {
+        const float *const t = base + ((size_t)row * row_len + x) * 3;
+        dot += t[0];
+        nt += t[1];
+        na += t[2];
+      }
+    dot = half_wave_sum(dot);
+    nt = half_wave_sum(nt);
+    na = half_wave_sum(na);
+    if (row < n_rows) acc += dot / (sqrtf(nt) * sqrtf(na));
   }
-  acc = wave_sum(acc);
-  if (threadIdx.x == 0) score[bh] = acc / (float)n_rows;
+  if (x0 == 0) part[half] = acc;
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    const float total = wave_sum(threadIdx.x < HALVES ? part[threadIdx.x] : 0.f);
+    if (threadIdx.x == 0) score[bh] = total / (float)n_rows;
+  }
 }
 
 }  // namespace calibatt_dev

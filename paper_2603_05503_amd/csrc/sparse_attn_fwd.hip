@@ -256,18 +256,34 @@ int launch_energy_onepass(const uint16_t *q, const uint16_t *k, float *energy, c
 
 template <int D>
 int launch_similarity(const uint16_t *q, const uint16_t *k, const int32_t *partner, float *triples, float *score,
-                      const SimilarityDims &p, hipStream_t stream) {
-  const long long units = (long long)p.B * p.H * p.nbq;
+                      int32_t *lists, const SimilarityDims &p, hipStream_t stream) {
+  // lists == nullptr: one lane per token, whole grid known here.  Otherwise the device decides how many
+  // workgroups have work: at most one unit per SIM_BQ tokens and one more per head.
+  const long long units = (long long)p.B * p.H * (p.nbq + (lists ? 1 : 0));
   const long long grid = SIM_XCDS * ((units + SIM_XCDS - 1) / SIM_XCDS);
   if (grid > 0x7fffffffLL) return CALIBATT_ERR_SHAPE;
-  constexpr int SMEM = 2 * RowBlock<D, SIM_BQ, SIM_BK>::TILE_BYTES;
-  auto kernel = pair_similarity_kernel<D>;
-  static DevInfo info;
   int slots = 0;
-  if (int st = prepare(kernel, SIM_BQ * 2, SMEM, info, slots)) return st;
-  if (int st = launch_kernel(kernel, (unsigned)grid, SIM_BQ * 2, SMEM, stream, q, k, partner, triples, p)) return st;
-  return launch_kernel(similarity_reduce_kernel, (unsigned)(p.B * p.H), 64, 0, stream, (const float *)triples, score,
-                       p.n_tok, p.row_len);
+  if (!lists) {
+    constexpr int SMEM = SimilarityLds<D, 1>::BYTES;
+    static DevInfo info;
+    if (int st = prepare(pair_similarity_kernel<D>, SIM_BQ * 2, SMEM, info, slots)) return st;
+    if (int st = launch_kernel(pair_similarity_kernel<D>, (unsigned)grid, SIM_BQ * 2, SMEM, stream, q, k, partner,
+                               triples, p))
+      return st;
+  } else {
+    constexpr int SMEM = SimilarityLds<D, 3>::BYTES;  // not less than the two-token form needs
+    static DevInfo info;
+    if (int st = prepare(grouped_similarity_kernel<D>, SIM_BQ * 2, SMEM, info, slots)) return st;
+    if (int st = launch_kernel(similarity_clear_kernel, 1, 64, 0, stream, lists)) return st;
+    if (int st = launch_kernel(similarity_group_kernel, (unsigned)((p.n_tok + 255) / 256), 256, 0, stream, partner,
+                               lists, p.N, p.n_tok, p.row_len))
+      return st;
+    if (int st = launch_kernel(grouped_similarity_kernel<D>, (unsigned)grid, SIM_BQ * 2, SMEM, stream, q, k, lists,
+                               triples, p, std::max(slots / SIM_XCDS, 1)))
+      return st;
+  }
+  return launch_kernel(similarity_reduce_kernel, (unsigned)(p.B * p.H), SIM_REDUCE_THREADS, 0, stream,
+                       (const float *)triples, score, p.n_tok, p.row_len);
 }
 
 }  // namespace
@@ -297,11 +313,29 @@ extern "C" int calibatt_vote_accumulate_device(const uint8_t *mask, int64_t n, u
 extern "C" int calibatt_spatial_similarity(const void *q, const void *k, int B, int H, int N, int D,
                                            const int32_t *partner, int n_tok, int row_len, float scale,
                                            float *workspace, float *score, void *stream) {
+  return calibatt_spatial_similarity_grouped(q, k, B, H, N, D, partner, n_tok, row_len, scale, workspace, nullptr, 0,
+                                             score, stream);
+}
+
+extern "C" int calibatt_similarity_lists_bytes(int B, int H, int n_tok, int64_t *bytes) {
+  if (!bytes) return CALIBATT_ERR_NULL;
+  if (B <= 0 || H <= 0 || n_tok <= 0) return CALIBATT_ERR_SHAPE;
+  const long long units = (long long)B * H * ((n_tok + SIM_BQ - 1) / SIM_BQ);
+  *bytes = units > SIM_GROUP_UNITS ? SimilarityLists::bytes(n_tok) : 0;
+  return CALIBATT_OK;
+}
+
+extern "C" int calibatt_spatial_similarity_grouped(const void *q, const void *k, int B, int H, int N, int D,
+                                                   const int32_t *partner, int n_tok, int row_len, float scale,
+                                                   float *workspace, void *lists, int64_t lists_bytes, float *score,
+                                                   void *stream) {
   if (!q || !k || !partner || !workspace || !score) return CALIBATT_ERR_NULL;
   if (B <= 0 || H <= 0 || N <= 0 || D <= 0 || n_tok <= 0 || row_len <= 0 || n_tok > N || n_tok % row_len)
     return CALIBATT_ERR_SHAPE;
   if (!(D == 64 || D == 128)) return CALIBATT_ERR_UNSUPPORTED;
   if ((size_t)B * H * N * D > 0x7fffffff00ULL) return CALIBATT_ERR_SHAPE;
+  if (lists && (((uintptr_t)lists & 15) || lists_bytes < 0)) return CALIBATT_ERR_SHAPE;
+  if (lists && lists_bytes < SimilarityLists::bytes(n_tok)) return CALIBATT_ERR_BUFFER_TOO_SMALL;
   SimilarityDims p;
   p.B = B;
   p.H = H;
@@ -313,8 +347,10 @@ extern "C" int calibatt_spatial_similarity(const void *q, const void *k, int B, 
   p.scale_log2e = scale * 1.4426950408889634f;
   hipStream_t s = (hipStream_t)stream;
   if (D == 128)
-    return launch_similarity<128>((const uint16_t *)q, (const uint16_t *)k, partner, workspace, score, p, s);
-  return launch_similarity<64>((const uint16_t *)q, (const uint16_t *)k, partner, workspace, score, p, s);
+    return launch_similarity<128>((const uint16_t *)q, (const uint16_t *)k, partner, workspace, score, (int32_t *)lists,
+                                  p, s);
+  return launch_similarity<64>((const uint16_t *)q, (const uint16_t *)k, partner, workspace, score, (int32_t *)lists, p,
+                               s);
 }
 
 // Scratch of calibatt_spatial_similarity_static: one copy per GPU the library runs on, held until

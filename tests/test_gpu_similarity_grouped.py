@@ -1,0 +1,87 @@
+"""The grouped form of the spatial similarity (tokens that share their partner computed together) against the
+form that takes one token per lane: the same bits, for every way the tokens can fall into groups."""
+import ctypes as C
+import math
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _partner(kind, lib, rows, cols, rng):
+    n = rows * cols
+    if kind.startswith("anchors"):
+        return lib.anchor_partner(1, rows, cols, int(kind[7:]))
+    if kind == "self":
+        return np.arange(n, dtype=np.int32)
+    if kind == "random":
+        return rng.integers(0, n, n).astype(np.int32)
+    if kind == "few":  # short runs, some of them their own partner, some with a partner outside the run
+        return (rng.integers(0, 3, n) * (n // 3)).astype(np.int32)
+    if kind == "one":
+        return np.full(n, n // 2, np.int32)
+    assert kind == "wild"  # clamped to [0, N)
+    return rng.choice(np.array([-5, 0, n - 1, n + 3, 1 << 30], np.int32), n).astype(np.int32)
+
+
+# heads, rows, cols, text tokens, D, partner map.  Many heads of one column block: the three-token form
+# (300 units of it against 600 of the two-token form); otherwise the two-token form.
+CASES = [
+    (1, 1, 1, 0, 64, "self"),
+    (2, 7, 5, 3, 128, "anchors2"),
+    (1, 9, 43, 0, 128, "self"),
+    (1, 64, 3, 1, 64, "one"),
+    (1, 130, 3, 7, 128, "anchors1"),  # runs longer than a segment of 64 rows
+    (2, 13, 31, 64, 128, "random"),
+    (2, 13, 31, 0, 64, "few"),
+    (1, 200, 1, 0, 128, "few"),
+    (1, 6, 50, 11, 64, "wild"),
+    (300, 24, 16, 5, 128, "anchors1"),
+    (300, 24, 16, 0, 64, "anchors1"),
+    (300, 25, 16, 0, 128, "one"),
+]
+
+
+@pytest.mark.parametrize("H,rows,cols,text,D,kind", CASES)
+def test_grouped_matches_single_tokens(lib, H, rows, cols, text, D, kind):
+    import torch
+
+    print(f"grouped similarity H={H} rows={rows} cols={cols} text={text} D={D} {kind}", flush=True)
+    raw = lib.load_library()
+    rng = np.random.default_rng(rows * cols + D)
+    n, N = rows * cols, rows * cols + text
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q, k = (torch.randn(1, H, N, D, device="cuda", generator=gen).mul_(2.0).to(torch.bfloat16) for _ in range(2))
+    partner = torch.from_numpy(_partner(kind, lib, rows, cols, rng)).cuda()
+    out = []
+    for lists in (None, torch.full((36 * n + 16,), 0x5A, dtype=torch.uint8, device="cuda")):
+        triples = torch.full((1, H, n, 3), float("nan"), device="cuda")
+        score = torch.full((1, H), float("nan"), device="cuda")
+        st = raw.calibatt_spatial_similarity_grouped(
+            q.data_ptr(), k.data_ptr(), 1, H, N, D, partner.data_ptr(), n, cols, 1 / math.sqrt(D), triples.data_ptr(),
+            None if lists is None else lists.data_ptr(), 0 if lists is None else lists.numel(), score.data_ptr(),
+            C.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert st == 0
+        torch.cuda.synchronize()
+        out.append((triples, score))
+    assert bool(torch.isfinite(out[0][0]).all())
+    assert torch.equal(out[0][0].view(torch.int32), out[1][0].view(torch.int32))
+    assert torch.equal(out[0][1].view(torch.int32), out[1][1].view(torch.int32))
+    # the single-token form against fp64 (tolerance of sums of probabilities whose logits carry fp32 rounding)
+    p = torch.softmax((q[0, -1].double() @ k[0, -1].double().T) / math.sqrt(D), 1)
+    a = partner.clamp(0, N - 1).long()
+    want = torch.stack([(p[:n] * p[a]).sum(1), (p[:n] ** 2).sum(1), (p[a] ** 2).sum(1)], 1)
+    torch.testing.assert_close(out[0][0][0, -1].double(), want, rtol=1e-3, atol=1e-9)
+
+
+def test_grouped_refuses_what_does_not_fit(lib):
+    raw = lib.load_library()
+    one = C.c_void_p(16)
+    f = raw.calibatt_spatial_similarity_grouped
+    assert f(one, one, 1, 1, 8, 64, one, 8, 2, 1.0, one, C.c_void_p(8), 1000, one, None) == -2
+    assert f(one, one, 1, 1, 8, 64, one, 8, 2, 1.0, one, one, -1, one, None) == -2
+    assert f(one, one, 1, 1, 8, 64, one, 8, 2, 1.0, one, one, 36 * 8 + 15, one, None) == -7
+    n = C.c_int64(0)
+    assert raw.calibatt_similarity_lists_bytes(1, 1, 8, C.byref(n)) == 0 and n.value == 0
+    assert raw.calibatt_similarity_lists_bytes(1, 513, 100, C.byref(n)) == 0 and n.value == 3616
