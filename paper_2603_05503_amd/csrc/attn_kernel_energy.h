@@ -142,12 +142,26 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) void block_energy_kern
 // the mass it puts on key block c is only known relative to the running
 // maximum of that moment; its logarithm, t[c][row] = m + log2(sum over the
 // block's keys of 2^(s - m)), needs no reference.  A workgroup keeps these
-// nbk x BQ values in its slice of the workspace (one 128-byte store per wave
-// and tile), and once the row's log-sum-exp L is known reads its own values
-// back: E[r][c] = mean over the rows of 2^(t[c][row] - L[row]).  Every lane
-// reads only what it wrote itself (the two lanes of a row take the even and the
-// odd key blocks).  Half the matrix work of the two-pass
-// kernel; 2 x nbk x BQ x 4 bytes of extra traffic per query block.
+// nbk x QW values in its slice of the workspace and, once the row's
+// log-sum-exp L is known, reads its own values back:
+// E[r][c] = mean over the rows of 2^(t[c][row] - L[row]).  Every lane reads
+// only what it wrote itself.  Half the matrix work of the two-pass kernel;
+// 2 x nbk x BQ x 4 bytes of extra traffic per query block.
+//
+// What bounds it: the vector ALU (FMA, exponential and addition per logit)
+// beside the matrix cores; a 32 x 32 sub-tile is 8 MFMAs and 48 vector
+// instructions per wavefront.  So the wavefront's stream is one step per 32
+// keys in which the MFMAs of step j and the vector instructions of step j - 1
+// are independent (two score buffers), and a wavefront owns PANELS x 32
+// queries: with two panels a K operand read from LDS feeds two MFMAs, and a K
+// tile loaded into LDS serves 256 queries.  The order inside a step is left to
+// the compiler.  Measured, 40 heads of 32 760 tokens at D = 128, blocks of 128,
+// with selection and votes: one panel and no overlap inside a wavefront 11.63
+// ms; two panels 10.53 ms; two panels with an MFMA behind every sixth vector
+// instruction by scheduling directives 11.34; the vector instructions as one
+// block in front of the MFMAs 11.39, with the MFMAs at raised priority 11.5.
+// (The matrix pipes are busy for half of the cycles and the clock is at 1.6-1.8
+// GHz: power is shared with the vector ALU.)
 //
 // Persistent workgroups, no counters: workgroup i serves XCD i mod xcds and
 // takes every (workgroups of that XCD)-th unit of the XCD's contiguous range;
@@ -155,134 +169,229 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) void block_energy_kern
 // to the unit.
 struct EnergyOnePassDims {
   EnergyDims e;
-  int n_wg;  // workgroups launched
-  int xcds;  // 8, or 1 when fewer than 8 workgroups run
+  int n_wg;     // workgroups launched
+  int xcds;     // 8, or 1 when fewer than 8 workgroups run
+  int n_group;  // units per head: ceil(nbq / BLOCKS)
 };
 
-template <int D, int BQ, int BK>
-__global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) void block_energy_onepass_kernel(
+// QW: queries per workgroup, one query block or two.  Two blocks of 64 make a workgroup of four
+// wavefronts instead of two (LDS holds two workgroups on a CU either way), two blocks of 128 one of four
+// wavefronts with two panels each.
+template <int D, int BQ, int BK, int QW>
+struct EnergyOnePass {
+  static constexpr int PANELS = QW / 128 > 1 ? 2 : 1;
+  static constexpr int NW = QW / (32 * PANELS);  // wavefronts per workgroup
+  static constexpr int BLOCKS = QW / BQ;         // query blocks per workgroup
+  using RB = RowBlock<D, NW * 32, BK>;
+  static constexpr int PART_OFF = 2 * RB::TILE_BYTES;  // float[NW][nbk] partial sums behind the two K buffers
+  static __host__ __device__ constexpr long long bytes(int nbk) { return PART_OFF + (long long)NW * nbk * 4; }
+  static_assert(BQ % (32 * PANELS) == 0, "the queries of a wavefront belong to one block");
+};
+
+// Two wavefronts per SIMD in the bounds for every form: with the whole register file to itself a wavefront's scores
+// go to accumulation registers, and on some paths the compiler copies them out before the MFMA that writes them is done.
+template <int D, int BQ, int BK, int QW>
+__global__ __launch_bounds__((EnergyOnePass<D, BQ, BK, QW>::NW * 64), 2) void block_energy_onepass_kernel(
     const uint16_t *__restrict__ gq, const uint16_t *__restrict__ gk, float *__restrict__ gE,
     float *__restrict__ workspace, const EnergyOnePassDims pp) {
-  using RB = RowBlock<D, BQ, BK>;
-  constexpr int NT = RB::NT, NW = RB::NW, KB = RB::KB, ROWB = RB::ROWB, TILE_BYTES = RB::TILE_BYTES;
+  using L = EnergyOnePass<D, BQ, BK, QW>;
+  using RB = typename L::RB;
+  constexpr int PANELS = L::PANELS, NT = RB::NT, NW = L::NW, KB = RB::KB, DS = RB::DS, ROWB = RB::ROWB;
+  constexpr int TILE_BYTES = RB::TILE_BYTES, BLOCKS = L::BLOCKS, WAVES_PER_BLOCK = NW / BLOCKS;
+  static_assert(KB % 2 == 0, "the two score buffers alternate over the steps of a tile");
   const EnergyDims &p = pp.e;
 
-  extern __shared__ __attribute__((aligned(1024))) char lds[];  // EnergyLds::bytes(nbk)
+  extern __shared__ __attribute__((aligned(1024))) char lds[];  // L::bytes(nbk)
 
   const int xcd = blockIdx.x % pp.xcds;
   const int slot = blockIdx.x / pp.xcds;
   const int wgs_here = (pp.n_wg - xcd + pp.xcds - 1) / pp.xcds;  // workgroups serving this XCD's range
-  const long long units = (long long)p.B * p.H * p.nbq;
+  const long long units = (long long)p.B * p.H * pp.n_group;
   const long long lo = units * xcd / pp.xcds;
   const long long hi = units * (xcd + 1) / pp.xcds;
 
   RB rb(lds);
   const int tid = rb.tid;
-  const int N = p.N;
-  float *const part = reinterpret_cast<float *>(lds + EnergyLds<D, BQ, BK>::PART_OFF);
-  float *const mine = workspace + (size_t)blockIdx.x * p.nbk * BQ + rb.row_in_block();  // + c * BQ
+  const int N = p.N, nbk = p.nbk;
+  float *const part = reinterpret_cast<float *>(lds + L::PART_OFF);
+  // this lane's values, + c * QW: one panel: row l32, the halves of the wave take the even and the odd blocks c;
+  // two panels: row l32 of panel g, every block
+  float *const mine = workspace + (size_t)blockIdx.x * nbk * QW + rb.wave * (32 * PANELS) + (PANELS == 1 ? rb.l32 : rb.lane);
   const float sc = p.scale_log2e;
   const bool ragged = (N % BK) != 0;
+  constexpr float SAFE = 0x1p90f;  // largest sum of one step against the present reference
 
   for (long long unit = lo + slot; unit < hi; unit += wgs_here) {
-    const int r = (int)(unit % p.nbq);
-    const long long bh = unit / p.nbq;  // b * H + h
+    const int r0 = (int)(unit % pp.n_group) * BLOCKS;
+    const long long bh = unit / pp.n_group;  // b * H + h
     const size_t head_off = (size_t)bh * (size_t)N * D;
     const u32x4 Kres = head_rsrc(gk + head_off, (uint32_t)N * ROWB);
-    const int rows_valid = min(BQ, N - r * BQ);
-    const bool row_valid = rb.row_in_block() < rows_valid;
+    const int row0 = r0 * BQ + rb.wave * (32 * PANELS) + rb.l32;  // this lane's row of panel 0
 
     // both K buffers are free: every wave is behind the barrier that followed the last tile of the previous unit
     rb.issue_k_at(Kres, 0, 0);
-    rb.begin(gq + head_off + (size_t)(r * BQ + (row_valid ? rb.row_in_block() : 0)) * D);
+    typename RB::Operand q[PANELS][DS];
+#pragma unroll
+    for (int i = 0; i < PANELS; ++i) rb.load_q(gq + head_off + (size_t)min(row0 + 32 * i, N - 1) * D, q[i]);
 
-    float m_run = -INFINITY, l_run = 0.f, t_prev = 0.f;
-    for (int c = 0; c < p.nbk; ++c) {
+    float m_run[PANELS], l_run[PANELS], tile_sum[PANELS];
+#pragma unroll
+    for (int i = 0; i < PANELS; ++i) {
+      m_run[i] = -INFINITY;
+      l_run[i] = tile_sum[i] = 0.f;
+    }
+    f32x16 s[2][PANELS];
+
+    // S of one 32-key sub-tile (kb of the tile at buf_off)
+    auto multiply = [&](uint32_t buf_off, int kb, f32x16 (&dst)[PANELS]) {
+      const char *const kbuf = rb.ldsK + buf_off + kb * 32 * ROWB;
+      typename RB::Operand ka[DS];
+#pragma unroll
+      for (int d = 0; d < DS; ++d) ka[d] = *reinterpret_cast<const typename RB::Operand *>(kbuf + (rb.k_addr0 ^ (d << 5)));
+#pragma unroll
+      for (int i = 0; i < PANELS; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) dst[i][v] = 0.f;
+#pragma unroll
+      for (int d = 0; d < DS; ++d)
+#pragma unroll
+        for (int i = 0; i < PANELS; ++i) dst[i] = Bf16::mfma(ka[d], q[i][d], dst[i]);
+    };
+    // this lane's share of the mass of one sub-tile relative to the present reference
+    auto exp_sum = [&](const f32x16 (&src)[PANELS], float sc_t, float (&psum)[PANELS]) {
+#pragma unroll
+      for (int i = 0; i < PANELS; ++i) {
+        float part[2] = {0.f, 0.f};  // two chains: half the additions behind one another, and their rounding
+#pragma unroll
+        for (int v = 0; v < 16; ++v) part[v >> 3] += __builtin_amdgcn_exp2f(__builtin_fmaf(src[i][v], sc_t, -m_run[i]));
+        psum[i] = part[0] + part[1];
+      }
+    };
+    // The reference m_run of the exponentials only has to keep them in range, it need not be the
+    // maximum: a sub-tile is first summed against the reference as it stands, and only if some
+    // lane's sum leaves the safe range (always on the first sub-tile, where the reference is -inf)
+    // does the wave look for the maximum, move the reference of the rows that need it and sum again.
+    auto fold = [&](const f32x16 (&src)[PANELS], float sc_t, float (&psum)[PANELS]) {
+      bool bad = false;
+#pragma unroll
+      for (int i = 0; i < PANELS; ++i) bad |= !(psum[i] < SAFE);
+      if (__any(bad)) {
+#pragma unroll
+        for (int i = 0; i < PANELS; ++i) {
+          float m_loc = sc_t >= 0.f ? -INFINITY : INFINITY;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) m_loc = sc_t >= 0.f ? fmaxf(m_loc, src[i][v]) : fminf(m_loc, src[i][v]);
+          const bool move = !(sum_with_other_half(psum[i]) < SAFE);  // the same for both halves of a row
+          const float m_new = move ? fmaxf(m_run[i], max_with_other_half(m_loc * sc_t)) : m_run[i];
+          const float alpha = move ? __builtin_amdgcn_exp2f(m_run[i] - m_new) : 1.f;  // 0 on the first sub-tile
+          l_run[i] *= alpha;
+          tile_sum[i] *= alpha;
+          m_run[i] = m_new;
+        }
+        exp_sum(src, sc_t, psum);
+      }
+#pragma unroll
+      for (int i = 0; i < PANELS; ++i) tile_sum[i] += psum[i];
+    };
+    // keys >= N of the ragged last tile to -inf, the scale applied up front (returns the multiplier left: 1)
+    auto mask_tail = [&](f32x16 (&src)[PANELS], int kb) {
+      int limit = N - (nbk - 1) * BK - 32 * kb - 8 * rb.g;  // this lane's key offsets below `limit` exist
+      asm volatile("" : "+v"(limit));                        // keeps the comparisons inside this branch
+      // Twelve wait states between the last MFMA and a read of its result: the compiler's own wait falls short on the
+      // path that enters this branch at once.
+#pragma unroll
+      for (int i = 0; i < PANELS; ++i) asm volatile("s_nop 11" : "+v"(src[i]));
+#pragma unroll
+      for (int i = 0; i < PANELS; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) src[i][v] = 16 * (v >> 3) + (v & 7) < limit ? src[i][v] * sc : -INFINITY;
+      return 1.0f;
+    };
+    // log2 of the rows' mass on block c (-inf when it underflowed: the block then counts as 0) to the workspace
+    auto finish_tile = [&](int c) {
+      float t[PANELS];
+#pragma unroll
+      for (int i = 0; i < PANELS; ++i) {
+        t[i] = m_run[i] + __builtin_amdgcn_logf(sum_with_other_half(tile_sum[i]));
+        l_run[i] += tile_sum[i];
+        tile_sum[i] = 0.f;
+      }
+      if constexpr (PANELS == 1) {
+        if ((c & 1) == rb.g) mine[(size_t)c * QW] = t[0];
+      } else {
+        mine[(size_t)c * QW] = rb.g ? t[PANELS - 1] : t[0];
+      }
+    };
+
+    for (int c = 0; c < nbk; ++c) {
       wait_vmem<0>();
       __syncthreads();  // tile c has landed for every wave; everyone is done with the other buffer
-      // the value of the previous tile goes out here, a whole tile ahead of the next wait for memory
-      if (c > 0 && ((c - 1) & 1) == rb.g) mine[(size_t)(c - 1) * BQ] = t_prev;
-      if (c + 1 < p.nbk) rb.issue_k_at(Kres, c + 1, ((c + 1) & 1) * TILE_BYTES);
-      f32x16 s[KB];
-      rb.scores((c & 1) * TILE_BYTES, s);
-      float sc_t = sc;
-      if (ragged && c == p.nbk - 1) {  // keys >= N sit at -inf; the tile is scaled up front, multiplier 1 from then on
-        int limit = N - c * BK - 8 * rb.g;  // this lane's key offsets below `limit` exist
-        asm volatile("" : "+v"(limit));      // keeps the comparisons (and their 64 masks) inside this branch
+      if (c + 1 < nbk) rb.issue_k_at(Kres, c + 1, ((c + 1) & 1) * TILE_BYTES);
+      const uint32_t buf = (c & 1) * TILE_BYTES;
+      const bool tail = ragged && c == nbk - 1;
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-          for (int v = 0; v < 16; ++v)
-            s[kb][v] = 32 * kb + 16 * (v >> 3) + (v & 7) < limit ? s[kb][v] * sc : -INFINITY;
-        sc_t = 1.0f;
-      }
-      // The reference m_run of the exponentials only has to keep them in range, it need not be the
-      // maximum: the tile is first summed against the reference as it stands, and only if some
-      // lane's sum leaves the safe range (always on the first tile, where the reference is -inf)
-      // does the wave look for the tile's maximum, move the reference and sum again.  The sums
-      // stay below 2^100 per tile, so the row sum cannot overflow.
-      float psum = 0.f;
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) psum += __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][v], sc_t, -m_run));
-      if (__any(!(psum < 0x1p100f))) {
-        float m_loc;
-        if (sc_t >= 0.f) {
-          m_loc = -INFINITY;
-#pragma unroll
-          for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) m_loc = fmaxf(m_loc, s[kb][v]);
-        } else {
-          m_loc = INFINITY;
-#pragma unroll
-          for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) m_loc = fminf(m_loc, s[kb][v]);
+      for (int kb = 0; kb < KB; ++kb) {
+        f32x16(&now)[PANELS] = s[kb & 1];
+        f32x16(&before)[PANELS] = s[(kb & 1) ^ 1];
+        if (kb == 0 && c == 0) {
+          multiply(buf, kb, now);
+          continue;
         }
-        const float m_new = fmaxf(m_run, max_with_other_half(m_loc * sc_t));
-        psum = 0.f;
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) psum += __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][v], sc_t, -m_new));
-        l_run *= __builtin_amdgcn_exp2f(m_run - m_new);  // 0 on the first tile
-        m_run = m_new;
+        float sc_t = sc;
+        if (kb > 0 && tail) sc_t = mask_tail(before, kb - 1);
+        float psum[PANELS];
+        multiply(buf, kb, now);
+        exp_sum(before, sc_t, psum);
+        fold(before, sc_t, psum);
+        if (kb == 0) finish_tile(c - 1);
       }
-      l_run += psum;
-      // log2 of the row's mass on this block (-inf when it underflowed: the block then counts as 0)
-      t_prev = m_run + __builtin_amdgcn_logf(sum_with_other_half(psum));
     }
-    if (((p.nbk - 1) & 1) == rb.g) mine[(size_t)(p.nbk - 1) * BQ] = t_prev;
-    const float lse2 = m_run + __builtin_amdgcn_logf(sum_with_other_half(l_run));
+    {
+      float sc_t = sc, psum[PANELS];
+      if (ragged) sc_t = mask_tail(s[(KB - 1) & 1], KB - 1);
+      exp_sum(s[(KB - 1) & 1], sc_t, psum);
+      fold(s[(KB - 1) & 1], sc_t, psum);
+      finish_tile(nbk - 1);
+    }
+    float lse2[PANELS];
+#pragma unroll
+    for (int i = 0; i < PANELS; ++i) lse2[i] = m_run[i] + __builtin_amdgcn_logf(sum_with_other_half(l_run[i]));
     wait_vmem<0>();
     __syncthreads();  // K buffers free for the next unit; `part` of the previous unit fully consumed
-    // this lane's own values back (blocks c = 2 j + g), 16 loads in flight at a time; each half of
-    // the wave sums its 32 rows
-    for (int c0 = 0; c0 < p.nbk; c0 += 32) {
+    // This lane's own values back, 16 loads in flight at a time, read at L2, where the stores went; the rows
+    // of a wave are summed over the half wave that holds them (one panel) or over the whole wave (two).
+    const float my_lse = PANELS == 1 || rb.g == 0 ? lse2[0] : lse2[PANELS - 1];
+    const bool my_row = row0 + (PANELS == 1 ? 0 : 32 * rb.g) < N;
+    constexpr int HALVES = PANELS == 1 ? 2 : 1;  // blocks c handled per load
+    for (int c0 = 0; c0 < nbk; c0 += 16 * HALVES) {
       float t[16];
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
-        const int c = c0 + 2 * j + rb.g;
-        t[j] = c < p.nbk ? __hip_atomic_load(mine + (size_t)c * BQ, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                         : -INFINITY;  // read at L2, where the stores went
+        const int c = c0 + HALVES * j + (PANELS == 1 ? rb.g : 0);
+        t[j] = c < nbk ? __hip_atomic_load(mine + (size_t)c * QW, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                       : -INFINITY;
       }
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
-        const int c = c0 + 2 * j + rb.g;
-        const float e = half_wave_sum(row_valid ? __builtin_amdgcn_exp2f(t[j] - lse2) : 0.f);
-        if (rb.l32 == 0 && c < p.nbk) part[rb.wave * p.nbk + c] = e;
+        const int c = c0 + HALVES * j + (PANELS == 1 ? rb.g : 0);
+        const float mass = my_row ? __builtin_amdgcn_exp2f(t[j] - my_lse) : 0.f;
+        const float e = PANELS == 1 ? half_wave_sum(mass) : wave_sum(mass);
+        if ((PANELS == 1 ? rb.l32 : rb.lane) == 0 && c < nbk) part[rb.wave * nbk + c] = e;
       }
     }
     __syncthreads();
-    const float inv_rows = 1.0f / (float)rows_valid;
-    float *const out = gE + ((size_t)bh * p.nbq + r) * (size_t)p.nbk;
-    for (int c = tid; c < p.nbk; c += NT) {
-      float e = 0.f;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) e += part[w * p.nbk + c];
-      out[c] = e * inv_rows;
+    for (int j = 0; j < BLOCKS; ++j) {
+      const int r = r0 + j;
+      if (r >= p.nbq) break;
+      const float inv_rows = 1.0f / (float)min(BQ, N - r * BQ);
+      float *const out = gE + ((size_t)bh * p.nbq + r) * (size_t)nbk;
+      for (int c = tid; c < nbk; c += NT) {
+        float e = 0.f;
+#pragma unroll
+        for (int w = 0; w < WAVES_PER_BLOCK; ++w) e += part[(j * WAVES_PER_BLOCK + w) * nbk + c];
+        out[c] = e * inv_rows;
+      }
     }
   }
 }
