@@ -60,11 +60,19 @@ __global__ __launch_bounds__(SELECT_THREADS) void select_blocks_kernel(const flo
     if (tid == 0) {
       double total = 0.0;
       int cut = nbk - 1;
-      for (int i = 0; i < nbk; ++i) {
-        total += (double)key_to_value((uint32_t)(sort_keys[i] >> 32));
-        if (total >= eps) {
-          cut = i;
-          break;
+      // one chain of fp64 additions; the entries are read eight at a time, or each would wait for LDS by itself
+      bool found = false;
+      for (int i0 = 0; i0 < nbk && !found; i0 += 8) {
+        uint32_t key[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) key[j] = (uint32_t)(sort_keys[min(i0 + j, P - 1)] >> 32);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          if (i0 + j < nbk) total += (double)key_to_value(key[j]);
+          if (!found && i0 + j < nbk && total >= eps) {
+            cut = i0 + j;
+            found = true;
+          }
         }
       }
       cut_shared = cut;
