@@ -38,22 +38,24 @@ def build(verbose: bool = True, extra_flags=()) -> str:
     import tempfile
 
     srcs = [os.path.join(CSRC, s) for s in SOURCES]
-    # --save-temps leaves the device assembly of this very compilation in the working directory:
-    # the kernels that name registers by hand are checked on it (csrc/check_named_regs.py).
+    # --save-temps leaves the device assembly of this very compilation in the working directory, which
+    # is checked for what the compiler does not guarantee: that the kernels that name registers by hand
+    # keep them (csrc/check_named_regs.py), and that no MFMA result is read too early (csrc/check_mfma_waits.py).
     cmd = [hipcc(), *HIP_FLAGS, *extra_flags, "--save-temps", "-I", os.path.join(ROOT, "include"), "-I", CSRC, *srcs,
            "-o", LIB_PATH]
     if verbose:
         print(" ".join(cmd), flush=True)
     with tempfile.TemporaryDirectory() as tmp:
         subprocess.run(cmd, check=True, cwd=tmp)
-        spec = importlib.util.spec_from_file_location("check_named_regs", os.path.join(CSRC, "check_named_regs.py"))
+        text = open(os.path.join(tmp, "sparse_attn_fwd-hip-amdgcn-amd-amdhsa-gfx950.s")).read()
+    for name in ("check_named_regs", "check_mfma_waits"):
+        spec = importlib.util.spec_from_file_location(name, os.path.join(CSRC, name + ".py"))
         mod = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(mod)
-        asm = os.path.join(tmp, "sparse_attn_fwd-hip-amdgcn-amd-amdhsa-gfx950.s")
-        problems = mod.check(open(asm).read())
-    if problems:
-        os.remove(LIB_PATH)
-        raise RuntimeError("named-register kernels: the compiler used a reserved register:\n" + "\n".join(problems[:20]))
+        problems = mod.check(text)
+        if problems:
+            os.remove(LIB_PATH)
+            raise RuntimeError(f"{name}.py rejects the compiled kernels:\n" + "\n".join(problems[:20]))
     probe = [hipcc(), *[f for f in HIP_FLAGS if f not in ("-fPIC", "-shared")], "-Wno-unused-value",
              os.path.join(CSRC, "mfma_peak_probe.hip"), "-o", PROBE_PATH]
     if verbose:
