@@ -45,6 +45,10 @@ def _functions(text):
 
 def _early_use(body, used, labels, start, result):
     """Index of an instruction that touches `result` fewer than STATES wait states behind `start`, or None."""
+    def used_as_operand(args):
+        accumulator = _registers(args[3]) & result
+        return (_registers(args[1]) | _registers(args[2])) & result or (accumulator and accumulator != result)
+
     paths, seen = [(start + 1, 0)], set()
     while paths:
         j, waited = paths.pop()
@@ -63,9 +67,8 @@ def _early_use(body, used, labels, start, result):
                 if op.startswith("s_branch"):
                     break
             elif used[j] & result:
-                chained = op.startswith("v_mfma") and _registers(args[0]) == result == _registers(args[3])
-                if chained and not (_registers(args[1]) | _registers(args[2])) & result:
-                    break  # the next accumulation into the same registers: checked by itself
+                if op.startswith("v_mfma") and _registers(args[0]) == result and not used_as_operand(args):
+                    break  # the same registers again, in the matrix cores' own order: checked by itself
                 return j
             waited += 1
             j += 1

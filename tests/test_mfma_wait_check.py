@@ -43,6 +43,7 @@ def test_early_uses_are_reported(body):
 @pytest.mark.parametrize("body", [
     [MFMA, "s_nop 11", READ, "s_endpgm"],
     [MFMA, MFMA, "s_nop 0xb", READ, "s_endpgm"],                                   # accumulation into the same registers
+    [MFMA, "v_mfma_f32_32x32x16_bf16 v[18:33], v[2:5], v[6:9], 0", "s_nop 11", READ, "s_endpgm"],  # or a new sum in them
     [MFMA, "s_nop 9", "s_cbranch_scc1 .LBB0_2", "s_nop 0", ".LBB0_2:", "s_nop 0", READ, "s_endpgm"],
     [MFMA, "v_mul_f32_e32 v3, s59, v17", "v_mul_f32_e32 v34, s59, a18 ; v18", "s_endpgm"],
     [MFMA, "s_nop 3", "s_branch .LBB0_2", ".LBB0_1:", READ, "s_endpgm", ".LBB0_2:", "s_nop 7", "s_branch .LBB0_1"],
