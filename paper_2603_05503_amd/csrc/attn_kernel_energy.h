@@ -148,20 +148,12 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) void block_energy_kern
 // only what it wrote itself.  Half the matrix work of the two-pass kernel;
 // 2 x nbk x BQ x 4 bytes of extra traffic per query block.
 //
-// What bounds it: the vector ALU (FMA, exponential and addition per logit)
-// beside the matrix cores; a 32 x 32 sub-tile is 8 MFMAs and 48 vector
-// instructions per wavefront.  So the wavefront's stream is one step per 32
-// keys in which the MFMAs of step j and the vector instructions of step j - 1
-// are independent (two score buffers), and a wavefront owns PANELS x 32
-// queries: with two panels a K operand read from LDS feeds two MFMAs, and a K
-// tile loaded into LDS serves 256 queries.  The order inside a step is left to
-// the compiler.  Measured, 40 heads of 32 760 tokens at D = 128, blocks of 128,
-// with selection and votes: one panel and no overlap inside a wavefront 11.63
-// ms; two panels 10.53 ms; two panels with an MFMA behind every sixth vector
-// instruction by scheduling directives 11.34; the vector instructions as one
-// block in front of the MFMAs 11.39, with the MFMAs at raised priority 11.5.
-// (The matrix pipes are busy for half of the cycles and the clock is at 1.6-1.8
-// GHz: power is shared with the vector ALU.)
+// The reference of the exponentials only has to keep them in range, it need
+// not be the maximum: a tile is first summed against the reference as it
+// stands, and only if some lane's sum leaves the safe range (always on the
+// first tile, where the reference is -inf) do the 32 rows that a wavefront
+// holds together look for the tile's maximum, move their references and sum
+// again.  The sums stay below 2^100 per tile, so the row sum cannot overflow.
 //
 // Persistent workgroups, no counters: workgroup i serves XCD i mod xcds and
 // takes every (workgroups of that XCD)-th unit of the XCD's contiguous range;
@@ -174,14 +166,177 @@ struct EnergyOnePassDims {
   int n_group;  // units per head: ceil(nbq / BLOCKS)
 };
 
-// QW: queries per workgroup, one query block or two.  Two blocks of 64 make a workgroup of four
-// wavefronts instead of two (LDS holds two workgroups on a CU either way), two blocks of 128 one of four
-// wavefronts with two panels each.
+constexpr float ENERGY_SAFE = 0x1p100f;  // largest sum of one tile against the present reference
+
+// This workgroup's units: lo + slot, lo + slot + step, ... below hi.
+struct EnergyUnits {
+  long long first, hi;
+  int step;
+  __device__ __forceinline__ explicit EnergyUnits(const EnergyOnePassDims &pp) {
+    const int xcd = blockIdx.x % pp.xcds;
+    const long long units = (long long)pp.e.B * pp.e.H * pp.n_group;
+    first = units * xcd / pp.xcds + blockIdx.x / pp.xcds;
+    hi = units * (xcd + 1) / pp.xcds;
+    step = (pp.n_wg - xcd + pp.xcds - 1) / pp.xcds;
+  }
+};
+
+// partial[group][c], one per 32 rows, to the energies of the workgroup's query blocks
+template <int BQ, int BLOCKS, int NT>
+__device__ __forceinline__ void store_energies(const float *partial, float *__restrict__ gE, long long bh, int r0,
+                                               const EnergyDims &p, int tid) {
+#pragma unroll
+  for (int j = 0; j < BLOCKS; ++j) {
+    const int r = r0 + j;
+    if (r >= p.nbq) break;
+    const float inv_rows = 1.0f / (float)min(BQ, p.N - r * BQ);
+    float *const out = gE + ((size_t)bh * p.nbq + r) * (size_t)p.nbk;
+    for (int c = tid; c < p.nbk; c += NT) {
+      float e = 0.f;
+#pragma unroll
+      for (int w = 0; w < BQ / 32; ++w) e += partial[(j * (BQ / 32) + w) * p.nbk + c];
+      out[c] = e * inv_rows;
+    }
+  }
+}
+
+// Narrow form: a wavefront owns 32 queries, QW of them (one query block, or two of 64) make a workgroup.
 template <int D, int BQ, int BK, int QW>
 struct EnergyOnePass {
+  static constexpr int NW = QW / 32;      // wavefronts per workgroup
+  static constexpr int BLOCKS = QW / BQ;  // query blocks per workgroup
+  static constexpr int QUERIES = QW;
+  using RB = RowBlock<D, QW, BK>;
+  static constexpr int PART_OFF = 2 * RB::TILE_BYTES;  // float[NW][nbk] partial sums behind the two K buffers
+  static __host__ __device__ constexpr long long bytes(int nbk) { return PART_OFF + (long long)NW * nbk * 4; }
+};
+
+// Two wavefronts per SIMD in the bounds also where a workgroup has only two: with the whole register file to itself a
+// wavefront's scores go to accumulation registers and are copied out before they are used.
+template <int D, int BQ, int BK, int QW>
+__global__ __launch_bounds__(QW * 2, 2) void block_energy_onepass_kernel(
+    const uint16_t *__restrict__ gq, const uint16_t *__restrict__ gk, float *__restrict__ gE,
+    float *__restrict__ workspace, const EnergyOnePassDims pp) {
+  using L = EnergyOnePass<D, BQ, BK, QW>;
+  using RB = typename L::RB;
+  constexpr int NT = RB::NT, KB = RB::KB, ROWB = RB::ROWB, TILE_BYTES = RB::TILE_BYTES;
+  const EnergyDims &p = pp.e;
+
+  extern __shared__ __attribute__((aligned(1024))) char lds[];  // L::bytes(nbk)
+
+  RB rb(lds);
+  const int N = p.N;
+  float *const part = reinterpret_cast<float *>(lds + L::PART_OFF);
+  float *const mine = workspace + (size_t)blockIdx.x * p.nbk * QW + rb.row_in_block();  // + c * QW
+  const float sc = p.scale_log2e;
+  const bool ragged = (N % BK) != 0;
+
+  const EnergyUnits units(pp);
+  for (long long unit = units.first; unit < units.hi; unit += units.step) {
+    const int r0 = (int)(unit % pp.n_group) * L::BLOCKS;
+    const long long bh = unit / pp.n_group;  // b * H + h
+    const size_t head_off = (size_t)bh * (size_t)N * D;
+    const u32x4 Kres = head_rsrc(gk + head_off, (uint32_t)N * ROWB);
+    const int row = r0 * BQ + rb.row_in_block();
+    const bool row_valid = row < N;
+
+    // both K buffers are free: every wave is behind the barrier that followed the last tile of the previous unit
+    rb.issue_k_at(Kres, 0, 0);
+    // a lane without a row of its own repeats the first row of its block
+    rb.begin(gq + head_off + (size_t)(row_valid ? row : min(row / BQ * BQ, N - 1)) * D);
+
+    float m_run = -INFINITY, l_run = 0.f, t_prev = 0.f;
+    for (int c = 0; c < p.nbk; ++c) {
+      wait_vmem<0>();
+      __syncthreads();  // tile c has landed for every wave; everyone is done with the other buffer
+      // the value of the previous tile goes out here, a whole tile ahead of the next wait for memory
+      if (c > 0 && ((c - 1) & 1) == rb.g) mine[(size_t)(c - 1) * QW] = t_prev;
+      if (c + 1 < p.nbk) rb.issue_k_at(Kres, c + 1, ((c + 1) & 1) * TILE_BYTES);
+      f32x16 s[KB];
+      rb.scores((c & 1) * TILE_BYTES, s);
+      float sc_t = sc;
+      if (ragged && c == p.nbk - 1) {  // keys >= N sit at -inf; the tile is scaled up front, multiplier 1 from then on
+        int limit = N - c * BK - 8 * rb.g;  // this lane's key offsets below `limit` exist
+        asm volatile("" : "+v"(limit));      // keeps the comparisons (and their 64 masks) inside this branch
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+          for (int v = 0; v < 16; ++v)
+            s[kb][v] = 32 * kb + 16 * (v >> 3) + (v & 7) < limit ? s[kb][v] * sc : -INFINITY;
+        sc_t = 1.0f;
+      }
+      float psum = 0.f;
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) psum += __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][v], sc_t, -m_run));
+      if (__any(!(psum < ENERGY_SAFE))) {
+        float m_loc;
+        if (sc_t >= 0.f) {
+          m_loc = -INFINITY;
+#pragma unroll
+          for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) m_loc = fmaxf(m_loc, s[kb][v]);
+        } else {
+          m_loc = INFINITY;
+#pragma unroll
+          for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) m_loc = fminf(m_loc, s[kb][v]);
+        }
+        const float m_new = fmaxf(m_run, max_with_other_half(m_loc * sc_t));
+        psum = 0.f;
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) psum += __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][v], sc_t, -m_new));
+        l_run *= __builtin_amdgcn_exp2f(m_run - m_new);  // 0 on the first tile
+        m_run = m_new;
+      }
+      l_run += psum;
+      // log2 of the row's mass on this block (-inf when it underflowed: the block then counts as 0)
+      t_prev = m_run + __builtin_amdgcn_logf(sum_with_other_half(psum));
+    }
+    if (((p.nbk - 1) & 1) == rb.g) mine[(size_t)(p.nbk - 1) * QW] = t_prev;
+    const float lse2 = m_run + __builtin_amdgcn_logf(sum_with_other_half(l_run));
+    wait_vmem<0>();
+    __syncthreads();  // K buffers free for the next unit; `part` of the previous unit fully consumed
+    // this lane's own values back (blocks c = 2 j + g), 16 loads in flight at a time; each half of
+    // the wave sums its 32 rows
+    for (int c0 = 0; c0 < p.nbk; c0 += 32) {
+      float t[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int c = c0 + 2 * j + rb.g;
+        t[j] = c < p.nbk ? __hip_atomic_load(mine + (size_t)c * QW, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                         : -INFINITY;  // read at L2, where the stores went
+      }
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int c = c0 + 2 * j + rb.g;
+        const float e = half_wave_sum(row_valid ? __builtin_amdgcn_exp2f(t[j] - lse2) : 0.f);
+        if (rb.l32 == 0 && c < p.nbk) part[rb.wave * p.nbk + c] = e;
+      }
+    }
+    __syncthreads();
+    store_energies<BQ, L::BLOCKS, NT>(part, gE, bh, r0, p, rb.tid);
+  }
+}
+
+// Wide form: a wavefront owns two panels of 32 queries, four of them make a workgroup of two query blocks of 128.
+//
+// What bounds the pass: the vector ALU (FMA, exponential and addition per logit) beside the matrix cores; a 32 x 32
+// sub-tile is 8 MFMAs and 48 vector instructions per wavefront.  So the wavefront's stream is one step per 32 keys in
+// which the MFMAs of step j and the vector instructions of step j - 1 are independent (two score buffers); with two
+// panels a K operand read from LDS feeds two MFMAs, and a K tile loaded into LDS serves 256 queries.  The order inside a
+// step is left to the compiler.
+template <int D, int BQ, int BK, int QW>
+struct EnergyPanels {
   static constexpr int PANELS = QW / 128 > 1 ? 2 : 1;
   static constexpr int NW = QW / (32 * PANELS);  // wavefronts per workgroup
   static constexpr int BLOCKS = QW / BQ;         // query blocks per workgroup
+  static constexpr int QUERIES = QW;
   using RB = RowBlock<D, NW * 32, BK>;
   static constexpr int PART_OFF = 2 * RB::TILE_BYTES;  // float[NW][nbk] partial sums behind the two K buffers
   static __host__ __device__ constexpr long long bytes(int nbk) { return PART_OFF + (long long)NW * nbk * 4; }
@@ -191,10 +346,10 @@ struct EnergyOnePass {
 // Two wavefronts per SIMD in the bounds for every form: with the whole register file to itself a wavefront's scores
 // go to accumulation registers, and on some paths the compiler copies them out before the MFMA that writes them is done.
 template <int D, int BQ, int BK, int QW>
-__global__ __launch_bounds__((EnergyOnePass<D, BQ, BK, QW>::NW * 64), 2) void block_energy_onepass_kernel(
+__global__ __launch_bounds__((EnergyPanels<D, BQ, BK, QW>::NW * 64), 2) void block_energy_panels_kernel(
     const uint16_t *__restrict__ gq, const uint16_t *__restrict__ gk, float *__restrict__ gE,
     float *__restrict__ workspace, const EnergyOnePassDims pp) {
-  using L = EnergyOnePass<D, BQ, BK, QW>;
+  using L = EnergyPanels<D, BQ, BK, QW>;
   using RB = typename L::RB;
   constexpr int PANELS = L::PANELS, NT = RB::NT, NW = L::NW, KB = RB::KB, DS = RB::DS, ROWB = RB::ROWB;
   constexpr int TILE_BYTES = RB::TILE_BYTES, BLOCKS = L::BLOCKS, WAVES_PER_BLOCK = NW / BLOCKS;

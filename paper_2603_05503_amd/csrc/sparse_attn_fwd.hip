@@ -229,26 +229,23 @@ int launch_energy(const uint16_t *q, const uint16_t *k, float *energy, const Ene
   return launch_kernel(kernel, (unsigned)grid, BQ * 2, (int)smem, stream, q, k, energy, p);
 }
 
-// One-pass energy kernel with QW queries per workgroup: as many persistent workgroups as the
-// device holds at a time, the workspace has slices for, and there are units.  Fills in
-// the launch without launching (n_wg = 0 when this form cannot run at all).
-template <int D, int BQ, int BK, int QW>
-int plan_energy_onepass(const EnergyDims &p, long long workspace_bytes, EnergyOnePassDims &pp, int &slots) {
-  using L = EnergyOnePass<D, BQ, BK, QW>;
+// One-pass energies in one of their forms (EnergyOnePass or EnergyPanels with its kernel): as many persistent
+// workgroups as the device holds at a time, the workspace has slices for, and there are units.  Fills in the launch
+// without launching.
+template <typename Form, typename Kernel>
+int plan_energy_onepass(Kernel kernel, const EnergyDims &p, long long workspace_bytes, EnergyOnePassDims &pp, int &slots) {
   pp.e = p;
-  pp.n_group = (p.nbq + L::BLOCKS - 1) / L::BLOCKS;
-  pp.n_wg = slots = 0;
+  pp.n_group = (p.nbq + Form::BLOCKS - 1) / Form::BLOCKS;
   const long long units = (long long)p.B * p.H * pp.n_group;
-  const long long smem = L::bytes(p.nbk);
+  const long long smem = Form::bytes(p.nbk);
   if (smem > ENERGY_MAX_LDS) return CALIBATT_ERR_UNSUPPORTED;
-  const long long slice = (long long)p.nbk * QW * 4;
+  const long long slice = (long long)p.nbk * Form::QUERIES * 4;
   if (workspace_bytes < slice) return CALIBATT_ERR_BUFFER_TOO_SMALL;
-  auto kernel = block_energy_onepass_kernel<D, BQ, BK, QW>;
   static DevReady state;
   int dev = 0, cus = 0, per_cu = 0;
   if (int st = register_lds(kernel, ENERGY_MAX_LDS, state, dev)) return st;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kernel, L::NW * 64, (size_t)smem) !=
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kernel, Form::NW * 64, (size_t)smem) !=
           hipSuccess ||
       cus <= 0 || per_cu <= 0)
     return CALIBATT_ERR_LAUNCH;
@@ -264,22 +261,34 @@ int launch_energy_onepass(const uint16_t *q, const uint16_t *k, float *energy, c
   // Two query blocks per workgroup where the workspace has a slice for every workgroup that fits the device, and
   //  - blocks of 128 (two panels per wavefront): from two rounds of such workgroups on.  A unit takes 1.8 times as long
   //    as one of the narrow form, so with fewer rounds the coarser last one costs more than the panels give;
-  //  - blocks of 64 (four wavefronts for two): as soon as the narrow form needs a second round.  10 heads of 10 400
-  //    tokens at D = 128: 564 us with the narrow form only, 387 us.
+  //  - blocks of 64 (four wavefronts for two): as soon as the narrow form needs a second round.
+  constexpr int WIDE = 2 * BQ;
   EnergyOnePassDims pp;
   int slots = 0;
-  constexpr int WIDE = 2 * BQ;
-  using W = EnergyOnePass<D, BQ, BK, WIDE>;
-  if (plan_energy_onepass<D, BQ, BK, WIDE>(p, workspace_bytes, pp, slots) == CALIBATT_OK) {
-    const long long units = (long long)p.B * p.H * pp.n_group;
-    if (pp.n_wg == std::min<long long>(units, slots) && (W::PANELS == 2 ? units >= 2LL * slots : 2 * units > slots))
-      return launch_kernel(block_energy_onepass_kernel<D, BQ, BK, WIDE>, (unsigned)pp.n_wg, W::NW * 64,
-                           (int)W::bytes(p.nbk), stream, q, k, energy, workspace, pp);
+  auto launch = [&](auto kernel, auto form) {
+    using Form = decltype(form);
+    return launch_kernel(kernel, (unsigned)pp.n_wg, Form::NW * 64, (int)Form::bytes(p.nbk), stream, q, k, energy,
+                         workspace, pp);
+  };
+  if constexpr (BQ == 128) {
+    using Form = EnergyPanels<D, BQ, BK, WIDE>;
+    auto kernel = block_energy_panels_kernel<D, BQ, BK, WIDE>;
+    if (plan_energy_onepass<Form>(kernel, p, workspace_bytes, pp, slots) == CALIBATT_OK) {
+      const long long units = (long long)p.B * p.H * pp.n_group;
+      if (pp.n_wg == slots && units >= 2LL * slots) return launch(kernel, Form{});
+    }
+  } else {
+    using Form = EnergyOnePass<D, BQ, BK, WIDE>;
+    auto kernel = block_energy_onepass_kernel<D, BQ, BK, WIDE>;
+    if (plan_energy_onepass<Form>(kernel, p, workspace_bytes, pp, slots) == CALIBATT_OK) {
+      const long long units = (long long)p.B * p.H * pp.n_group;
+      if (pp.n_wg == std::min<long long>(units, slots) && 2 * units > slots) return launch(kernel, Form{});
+    }
   }
-  using L = EnergyOnePass<D, BQ, BK, BQ>;
-  if (int st = plan_energy_onepass<D, BQ, BK, BQ>(p, workspace_bytes, pp, slots)) return st;
-  return launch_kernel(block_energy_onepass_kernel<D, BQ, BK, BQ>, (unsigned)pp.n_wg, L::NW * 64,
-                       (int)L::bytes(p.nbk), stream, q, k, energy, workspace, pp);
+  using Form = EnergyOnePass<D, BQ, BK, BQ>;
+  auto kernel = block_energy_onepass_kernel<D, BQ, BK, BQ>;
+  if (int st = plan_energy_onepass<Form>(kernel, p, workspace_bytes, pp, slots)) return st;
+  return launch(kernel, Form{});
 }
 
 template <int D>
