@@ -155,6 +155,11 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) void block_energy_kern
 // holds together look for the tile's maximum, move their references and sum
 // again.  The sums stay below 2^100 per tile, so the row sum cannot overflow.
 //
+// Two forms with the same bits: the same additions in the same order in a
+// lane, the same 32 rows that move their references together and whose masses
+// are added as one partial.  Which one runs, on how many workgroups, is a
+// matter of speed alone.
+//
 // Persistent workgroups, no counters: workgroup i serves XCD i mod xcds and
 // takes every (workgroups of that XCD)-th unit of the XCD's contiguous range;
 // all units cost the same.  The workspace slice belongs to the workgroup, not
@@ -331,78 +336,63 @@ __global__ __launch_bounds__(QW * 2, 2) void block_energy_onepass_kernel(
 // which the MFMAs of step j and the vector instructions of step j - 1 are independent (two score buffers); with two
 // panels a K operand read from LDS feeds two MFMAs, and a K tile loaded into LDS serves 256 queries.  The order inside a
 // step is left to the compiler.
-template <int D, int BQ, int BK, int QW>
+//
+// The scores of a tile are gone when its sum turns out to be out of range; they are then multiplied again from K in
+// memory.  That is rare, as the references start at the maximum of the first tile, which is multiplied once more for it.
+template <int D, int BK>
 struct EnergyPanels {
-  static constexpr int PANELS = QW / 128 > 1 ? 2 : 1;
-  static constexpr int NW = QW / (32 * PANELS);  // wavefronts per workgroup
-  static constexpr int BLOCKS = QW / BQ;         // query blocks per workgroup
-  static constexpr int QUERIES = QW;
+  static constexpr int BQ = 128, PANELS = 2, NW = 4, BLOCKS = 2, QUERIES = 256;
   using RB = RowBlock<D, NW * 32, BK>;
-  static constexpr int PART_OFF = 2 * RB::TILE_BYTES;  // float[NW][nbk] partial sums behind the two K buffers
-  static __host__ __device__ constexpr long long bytes(int nbk) { return PART_OFF + (long long)NW * nbk * 4; }
-  static_assert(BQ % (32 * PANELS) == 0, "the queries of a wavefront belong to one block");
+  // float[NW * PANELS][nbk] partial sums over the second K buffer, which the next unit's loads reach behind a barrier
+  static constexpr int PART_OFF = RB::TILE_BYTES;
+  static __host__ __device__ constexpr long long bytes(int nbk) {
+    const long long part = (long long)NW * PANELS * nbk * 4;
+    return PART_OFF + (part > RB::TILE_BYTES ? part : RB::TILE_BYTES);
+  }
 };
 
-// Two wavefronts per SIMD in the bounds for every form: with the whole register file to itself a wavefront's scores
-// go to accumulation registers, and on some paths the compiler copies them out before the MFMA that writes them is done.
-template <int D, int BQ, int BK, int QW>
-__global__ __launch_bounds__((EnergyPanels<D, BQ, BK, QW>::NW * 64), 2) void block_energy_panels_kernel(
+template <int D, int BK>
+__global__ __launch_bounds__(256, 2) void block_energy_panels_kernel(
     const uint16_t *__restrict__ gq, const uint16_t *__restrict__ gk, float *__restrict__ gE,
     float *__restrict__ workspace, const EnergyOnePassDims pp) {
-  using L = EnergyPanels<D, BQ, BK, QW>;
+  using L = EnergyPanels<D, BK>;
   using RB = typename L::RB;
-  constexpr int PANELS = L::PANELS, NT = RB::NT, NW = L::NW, KB = RB::KB, DS = RB::DS, ROWB = RB::ROWB;
-  constexpr int TILE_BYTES = RB::TILE_BYTES, BLOCKS = L::BLOCKS, WAVES_PER_BLOCK = NW / BLOCKS;
+  constexpr int PANELS = L::PANELS, NT = RB::NT, KB = RB::KB, DS = RB::DS, ROWB = RB::ROWB, BQ = L::BQ, QW = L::QUERIES;
+  constexpr int TILE_BYTES = RB::TILE_BYTES;
   static_assert(KB % 2 == 0, "the two score buffers alternate over the steps of a tile");
+  using Operand = typename RB::Operand;
+  using Scores = f32x16[PANELS];
   const EnergyDims &p = pp.e;
 
   extern __shared__ __attribute__((aligned(1024))) char lds[];  // L::bytes(nbk)
 
-  const int xcd = blockIdx.x % pp.xcds;
-  const int slot = blockIdx.x / pp.xcds;
-  const int wgs_here = (pp.n_wg - xcd + pp.xcds - 1) / pp.xcds;  // workgroups serving this XCD's range
-  const long long units = (long long)p.B * p.H * pp.n_group;
-  const long long lo = units * xcd / pp.xcds;
-  const long long hi = units * (xcd + 1) / pp.xcds;
-
   RB rb(lds);
-  const int tid = rb.tid;
   const int N = p.N, nbk = p.nbk;
   float *const part = reinterpret_cast<float *>(lds + L::PART_OFF);
-  // this lane's values, + c * QW: one panel: row l32, the halves of the wave take the even and the odd blocks c;
-  // two panels: row l32 of panel g, every block
-  float *const mine = workspace + (size_t)blockIdx.x * nbk * QW + rb.wave * (32 * PANELS) + (PANELS == 1 ? rb.l32 : rb.lane);
+  float *const mine = workspace + (size_t)blockIdx.x * nbk * QW + rb.wave * 64 + rb.lane;  // + c * QW: row l32 of panel g
   const float sc = p.scale_log2e;
   const bool ragged = (N % BK) != 0;
-  constexpr float SAFE = 0x1p90f;  // largest sum of one step against the present reference
 
-  for (long long unit = lo + slot; unit < hi; unit += wgs_here) {
-    const int r0 = (int)(unit % pp.n_group) * BLOCKS;
+  const EnergyUnits units(pp);
+  for (long long unit = units.first; unit < units.hi; unit += units.step) {
+    const int r0 = (int)(unit % pp.n_group) * L::BLOCKS;
     const long long bh = unit / pp.n_group;  // b * H + h
     const size_t head_off = (size_t)bh * (size_t)N * D;
-    const u32x4 Kres = head_rsrc(gk + head_off, (uint32_t)N * ROWB);
-    const int row0 = r0 * BQ + rb.wave * (32 * PANELS) + rb.l32;  // this lane's row of panel 0
+    const uint16_t *const head_k = gk + head_off;
+    const u32x4 Kres = head_rsrc(head_k, (uint32_t)N * ROWB);
+    const int row0 = r0 * BQ + rb.wave * 64 + rb.l32;  // this lane's row of panel 0; of panel 1: + 32
 
     // both K buffers are free: every wave is behind the barrier that followed the last tile of the previous unit
     rb.issue_k_at(Kres, 0, 0);
-    typename RB::Operand q[PANELS][DS];
+    Operand q[PANELS][DS];
 #pragma unroll
-    for (int i = 0; i < PANELS; ++i) rb.load_q(gq + head_off + (size_t)min(row0 + 32 * i, N - 1) * D, q[i]);
-
-    float m_run[PANELS], l_run[PANELS], tile_sum[PANELS];
-#pragma unroll
-    for (int i = 0; i < PANELS; ++i) {
-      m_run[i] = -INFINITY;
-      l_run[i] = tile_sum[i] = 0.f;
+    for (int i = 0; i < PANELS; ++i) {  // a lane without a row of its own repeats the first row of its block
+      const int row = row0 + 32 * i;
+      rb.load_q(gq + head_off + (size_t)(row < N ? row : min(row / BQ * BQ, N - 1)) * D, q[i]);
     }
-    f32x16 s[2][PANELS];
 
-    // S of one 32-key sub-tile (kb of the tile at buf_off)
-    auto multiply = [&](uint32_t buf_off, int kb, f32x16 (&dst)[PANELS]) {
-      const char *const kbuf = rb.ldsK + buf_off + kb * 32 * ROWB;
-      typename RB::Operand ka[DS];
-#pragma unroll
-      for (int d = 0; d < DS; ++d) ka[d] = *reinterpret_cast<const typename RB::Operand *>(kbuf + (rb.k_addr0 ^ (d << 5)));
+    // S of one 32-key sub-tile against the K operands of its DS slabs
+    auto products = [&](const Operand (&ka)[DS], Scores &dst) {
 #pragma unroll
       for (int i = 0; i < PANELS; ++i)
 #pragma unroll
@@ -412,48 +402,27 @@ __global__ __launch_bounds__((EnergyPanels<D, BQ, BK, QW>::NW * 64), 2) void blo
 #pragma unroll
         for (int i = 0; i < PANELS; ++i) dst[i] = Bf16::mfma(ka[d], q[i][d], dst[i]);
     };
-    // this lane's share of the mass of one sub-tile relative to the present reference
-    auto exp_sum = [&](const f32x16 (&src)[PANELS], float sc_t, float (&psum)[PANELS]) {
+    auto multiply = [&](uint32_t buf_off, int kb, Scores &dst) {  // kb of the tile at buf_off
+      const char *const kbuf = rb.ldsK + buf_off + kb * 32 * ROWB;
+      Operand ka[DS];
 #pragma unroll
-      for (int i = 0; i < PANELS; ++i) {
-        float part[2] = {0.f, 0.f};  // two chains: half the additions behind one another, and their rounding
-#pragma unroll
-        for (int v = 0; v < 16; ++v) part[v >> 3] += __builtin_amdgcn_exp2f(__builtin_fmaf(src[i][v], sc_t, -m_run[i]));
-        psum[i] = part[0] + part[1];
-      }
+      for (int d = 0; d < DS; ++d) ka[d] = *reinterpret_cast<const Operand *>(kbuf + (rb.k_addr0 ^ (d << 5)));
+      products(ka, dst);
     };
-    // The reference m_run of the exponentials only has to keep them in range, it need not be the
-    // maximum: a sub-tile is first summed against the reference as it stands, and only if some
-    // lane's sum leaves the safe range (always on the first sub-tile, where the reference is -inf)
-    // does the wave look for the maximum, move the reference of the rows that need it and sum again.
-    auto fold = [&](const f32x16 (&src)[PANELS], float sc_t, float (&psum)[PANELS]) {
-      bool bad = false;
+    auto multiply_again = [&](int c, int kb, Scores &dst) {  // the same from memory
+      const int key = c * BK + kb * 32 + ((rb.l32 & 0x13) | ((rb.l32 & 4) << 1) | ((rb.l32 & 8) >> 1));
+      const uint16_t *const krow = head_k + (size_t)min(key, N - 1) * D + 8 * rb.g;
+      Operand ka[DS];
 #pragma unroll
-      for (int i = 0; i < PANELS; ++i) bad |= !(psum[i] < SAFE);
-      if (__any(bad)) {
-#pragma unroll
-        for (int i = 0; i < PANELS; ++i) {
-          float m_loc = sc_t >= 0.f ? -INFINITY : INFINITY;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) m_loc = sc_t >= 0.f ? fmaxf(m_loc, src[i][v]) : fminf(m_loc, src[i][v]);
-          const bool move = !(sum_with_other_half(psum[i]) < SAFE);  // the same for both halves of a row
-          const float m_new = move ? fmaxf(m_run[i], max_with_other_half(m_loc * sc_t)) : m_run[i];
-          const float alpha = move ? __builtin_amdgcn_exp2f(m_run[i] - m_new) : 1.f;  // 0 on the first sub-tile
-          l_run[i] *= alpha;
-          tile_sum[i] *= alpha;
-          m_run[i] = m_new;
-        }
-        exp_sum(src, sc_t, psum);
-      }
-#pragma unroll
-      for (int i = 0; i < PANELS; ++i) tile_sum[i] += psum[i];
+      for (int d = 0; d < DS; ++d) ka[d] = *reinterpret_cast<const Operand *>(krow + 16 * d);
+      products(ka, dst);
     };
     // keys >= N of the ragged last tile to -inf, the scale applied up front (returns the multiplier left: 1)
-    auto mask_tail = [&](f32x16 (&src)[PANELS], int kb) {
+    auto mask_tail = [&](Scores &src, int kb) {
       int limit = N - (nbk - 1) * BK - 32 * kb - 8 * rb.g;  // this lane's key offsets below `limit` exist
       asm volatile("" : "+v"(limit));                        // keeps the comparisons inside this branch
       // Twelve wait states between the last MFMA and a read of its result: the compiler's own wait falls short on the
-      // path that enters this branch at once.
+      // path that enters this branch at once (the build checks the distance).
 #pragma unroll
       for (int i = 0; i < PANELS; ++i) asm volatile("s_nop 11" : "+v"(src[i]));
 #pragma unroll
@@ -462,92 +431,133 @@ __global__ __launch_bounds__((EnergyPanels<D, BQ, BK, QW>::NW * 64), 2) void blo
         for (int v = 0; v < 16; ++v) src[i][v] = 16 * (v >> 3) + (v & 7) < limit ? src[i][v] * sc : -INFINITY;
       return 1.0f;
     };
-    // log2 of the rows' mass on block c (-inf when it underflowed: the block then counts as 0) to the workspace
-    auto finish_tile = [&](int c) {
+    // largest scaled logit so far: the largest product, or the smallest under a negative scale
+    float m_run[PANELS], l_run[PANELS], psum[PANELS], m_loc[PANELS];
+    auto fold_max = [&](const Scores &src, float sc_t) {
+#pragma unroll
+      for (int i = 0; i < PANELS; ++i) {
+        float m = sc_t >= 0.f ? -INFINITY : INFINITY;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) m = sc_t >= 0.f ? fmaxf(m, src[i][v]) : fminf(m, src[i][v]);
+        m_loc[i] = fmaxf(m_loc[i], m * sc_t);
+      }
+    };
+    // this lane's share of the mass of one sub-tile relative to the present reference
+    auto exp_sum = [&](const Scores &src, float sc_t) {
+#pragma unroll
+      for (int i = 0; i < PANELS; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) psum[i] += __builtin_amdgcn_exp2f(__builtin_fmaf(src[i][v], sc_t, -m_run[i]));
+      // keeps the sums in their step: the compiler would move those of a whole tile behind its last MFMA
+      asm volatile("" : "+v"(psum[0]), "+v"(psum[1]));
+    };
+    // tile c is summed: its logarithm (-inf when the mass underflowed: the block then counts as 0) to the workspace
+    auto finish_tile = [&](int c, Scores &tmp) {
+      bool moves[PANELS];
+#pragma unroll
+      for (int i = 0; i < PANELS; ++i) moves[i] = __any(!(psum[i] < ENERGY_SAFE));
+      if (moves[0] || moves[1]) {
+        const bool tail = ragged && c == nbk - 1;
+        float sum_before[PANELS];
+#pragma unroll
+        for (int i = 0; i < PANELS; ++i) {
+          sum_before[i] = psum[i];
+          m_loc[i] = -INFINITY;
+          psum[i] = 0.f;
+        }
+#pragma unroll 1
+        for (int kb = 0; kb < KB; ++kb) {
+          multiply_again(c, kb, tmp);
+          fold_max(tmp, tail ? mask_tail(tmp, kb) : sc);
+        }
+#pragma unroll
+        for (int i = 0; i < PANELS; ++i) {
+          const float m_new = moves[i] ? fmaxf(m_run[i], max_with_other_half(m_loc[i])) : m_run[i];
+          l_run[i] *= moves[i] ? __builtin_amdgcn_exp2f(m_run[i] - m_new) : 1.f;
+          m_run[i] = m_new;
+        }
+#pragma unroll 1
+        for (int kb = 0; kb < KB; ++kb) {
+          multiply_again(c, kb, tmp);
+          exp_sum(tmp, tail ? mask_tail(tmp, kb) : sc);
+        }
+#pragma unroll
+        for (int i = 0; i < PANELS; ++i) psum[i] = moves[i] ? psum[i] : sum_before[i];
+      }
       float t[PANELS];
 #pragma unroll
       for (int i = 0; i < PANELS; ++i) {
-        t[i] = m_run[i] + __builtin_amdgcn_logf(sum_with_other_half(tile_sum[i]));
-        l_run[i] += tile_sum[i];
-        tile_sum[i] = 0.f;
+        t[i] = m_run[i] + __builtin_amdgcn_logf(sum_with_other_half(psum[i]));
+        l_run[i] += psum[i];
+        psum[i] = 0.f;
       }
-      if constexpr (PANELS == 1) {
-        if ((c & 1) == rb.g) mine[(size_t)c * QW] = t[0];
-      } else {
-        mine[(size_t)c * QW] = rb.g ? t[PANELS - 1] : t[0];
-      }
+      mine[(size_t)c * QW] = rb.g ? t[1] : t[0];
     };
 
+    Scores s[2];
+#pragma unroll
+    for (int i = 0; i < PANELS; ++i) {
+      l_run[i] = psum[i] = 0.f;
+      m_loc[i] = -INFINITY;
+    }
     for (int c = 0; c < nbk; ++c) {
       wait_vmem<0>();
       __syncthreads();  // tile c has landed for every wave; everyone is done with the other buffer
       if (c + 1 < nbk) rb.issue_k_at(Kres, c + 1, ((c + 1) & 1) * TILE_BYTES);
       const uint32_t buf = (c & 1) * TILE_BYTES;
       const bool tail = ragged && c == nbk - 1;
+      if (c == 0) {
+#pragma unroll 1
+        for (int kb = 0; kb < KB; ++kb) {
+          multiply(buf, kb, s[0]);
+          fold_max(s[0], tail ? mask_tail(s[0], kb) : sc);
+        }
+#pragma unroll
+        for (int i = 0; i < PANELS; ++i) m_run[i] = max_with_other_half(m_loc[i]);
+      }
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb) {
-        f32x16(&now)[PANELS] = s[kb & 1];
-        f32x16(&before)[PANELS] = s[(kb & 1) ^ 1];
+        Scores &now = s[kb & 1], &before = s[(kb & 1) ^ 1];
         if (kb == 0 && c == 0) {
           multiply(buf, kb, now);
           continue;
         }
         float sc_t = sc;
         if (kb > 0 && tail) sc_t = mask_tail(before, kb - 1);
-        float psum[PANELS];
         multiply(buf, kb, now);
-        exp_sum(before, sc_t, psum);
-        fold(before, sc_t, psum);
-        if (kb == 0) finish_tile(c - 1);
+        exp_sum(before, sc_t);
+        if (kb == 0) finish_tile(c - 1, before);
       }
     }
     {
-      float sc_t = sc, psum[PANELS];
-      if (ragged) sc_t = mask_tail(s[(KB - 1) & 1], KB - 1);
-      exp_sum(s[(KB - 1) & 1], sc_t, psum);
-      fold(s[(KB - 1) & 1], sc_t, psum);
-      finish_tile(nbk - 1);
+      Scores &last = s[(KB - 1) & 1];
+      exp_sum(last, ragged ? mask_tail(last, KB - 1) : sc);
+      finish_tile(nbk - 1, last);
     }
     float lse2[PANELS];
 #pragma unroll
     for (int i = 0; i < PANELS; ++i) lse2[i] = m_run[i] + __builtin_amdgcn_logf(sum_with_other_half(l_run[i]));
     wait_vmem<0>();
-    __syncthreads();  // K buffers free for the next unit; `part` of the previous unit fully consumed
-    // This lane's own values back, 16 loads in flight at a time, read at L2, where the stores went; the rows
-    // of a wave are summed over the half wave that holds them (one panel) or over the whole wave (two).
-    const float my_lse = PANELS == 1 || rb.g == 0 ? lse2[0] : lse2[PANELS - 1];
-    const bool my_row = row0 + (PANELS == 1 ? 0 : 32 * rb.g) < N;
-    constexpr int HALVES = PANELS == 1 ? 2 : 1;  // blocks c handled per load
-    for (int c0 = 0; c0 < nbk; c0 += 16 * HALVES) {
+    __syncthreads();  // every wave is done with the K buffers
+    // this lane's own values back, 16 loads in flight at a time, read at L2, where the stores went; each half of the
+    // wave sums the rows of its panel
+    const float my_lse = rb.g ? lse2[1] : lse2[0];
+    const bool my_row = row0 + 32 * rb.g < N;
+    for (int c0 = 0; c0 < nbk; c0 += 16) {
       float t[16];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int c = c0 + HALVES * j + (PANELS == 1 ? rb.g : 0);
-        t[j] = c < nbk ? __hip_atomic_load(mine + (size_t)c * QW, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                       : -INFINITY;
-      }
+      for (int j = 0; j < 16; ++j)
+        t[j] = c0 + j < nbk
+                   ? __hip_atomic_load(mine + (size_t)(c0 + j) * QW, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                   : -INFINITY;
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
-        const int c = c0 + HALVES * j + (PANELS == 1 ? rb.g : 0);
-        const float mass = my_row ? __builtin_amdgcn_exp2f(t[j] - my_lse) : 0.f;
-        const float e = PANELS == 1 ? half_wave_sum(mass) : wave_sum(mass);
-        if ((PANELS == 1 ? rb.l32 : rb.lane) == 0 && c < nbk) part[rb.wave * nbk + c] = e;
+        const float e = half_wave_sum(my_row ? __builtin_amdgcn_exp2f(t[j] - my_lse) : 0.f);
+        if (rb.l32 == 0 && c0 + j < nbk) part[(rb.wave * PANELS + rb.g) * nbk + c0 + j] = e;
       }
     }
     __syncthreads();
-#pragma unroll
-    for (int j = 0; j < BLOCKS; ++j) {
-      const int r = r0 + j;
-      if (r >= p.nbq) break;
-      const float inv_rows = 1.0f / (float)min(BQ, N - r * BQ);
-      float *const out = gE + ((size_t)bh * p.nbq + r) * (size_t)nbk;
-      for (int c = tid; c < nbk; c += NT) {
-        float e = 0.f;
-#pragma unroll
-        for (int w = 0; w < WAVES_PER_BLOCK; ++w) e += part[(j * WAVES_PER_BLOCK + w) * nbk + c];
-        out[c] = e * inv_rows;
-      }
-    }
+    store_energies<BQ, L::BLOCKS, NT>(part, gE, bh, r0, p, rb.tid);
   }
 }
 

@@ -271,8 +271,8 @@ int launch_energy_onepass(const uint16_t *q, const uint16_t *k, float *energy, c
                          workspace, pp);
   };
   if constexpr (BQ == 128) {
-    using Form = EnergyPanels<D, BQ, BK, WIDE>;
-    auto kernel = block_energy_panels_kernel<D, BQ, BK, WIDE>;
+    using Form = EnergyPanels<D, BK>;
+    auto kernel = block_energy_panels_kernel<D, BK>;
     if (plan_energy_onepass<Form>(kernel, p, workspace_bytes, pp, slots) == CALIBATT_OK) {
       const long long units = (long long)p.B * p.H * pp.n_group;
       if (pp.n_wg == slots && units >= 2LL * slots) return launch(kernel, Form{});

@@ -1,11 +1,30 @@
 """The one-pass block energies where the call is large enough for workgroups of 256 queries, at ragged lengths and
-odd numbers of query blocks, against fp64 and against the same call with a workspace that only the 128-query form
-(or the 64-query one) fits.  Tolerance: fp32 sums of fp32 exponentials of logits below 64 (2^-18 in the exponent)."""
+odd numbers of query blocks, against fp64, and bit for bit against the same call with a workspace that only the
+128-query form (or the 64-query one) fits, and against one head alone.  Tolerance: fp32 sums of fp32 exponentials of
+logits below 64 (2^-18 in the exponent).  A second test has logits that outgrow the reference of the exponentials late
+in a row: up to 2^8 in the exponent, sums of D products in fp32, so 2^-14 with a few ulps, and 2e-4 relative."""
 import math
 
 import pytest
 
 pytestmark = pytest.mark.gpu
+
+
+def _same_bits(a, b):
+    import torch
+
+    assert torch.equal(a.contiguous().view(torch.int32), b.contiguous().view(torch.int32))
+
+
+def _energy64(q, k, bq, bk, scale):
+    import torch
+
+    N = q.shape[0]
+    p = torch.softmax((q.double() @ k.double().T) * scale, 1)
+    rows = torch.arange(N, device="cuda")
+    e = torch.zeros(N, -(-N // bk), dtype=torch.float64, device="cuda").index_add_(1, rows // bk, p)
+    e = torch.zeros(-(-N // bq), e.shape[1], dtype=torch.float64, device="cuda").index_add_(0, rows // bq, e)
+    return e / torch.bincount(rows // bq)[:, None]
 
 
 @pytest.mark.parametrize("N", [129, 640, 901])
@@ -26,11 +45,36 @@ def test_block_energy_wide_workgroups(lib, D, bq, bk, N):
     narrow = lib.block_energy(q, k, bq, bk, scale, workspace=small)
     torch.cuda.synchronize()
     assert torch.equal(got, again)
-    torch.testing.assert_close(got, narrow, rtol=2e-5, atol=1e-9)
+    _same_bits(got, narrow)
     for h in (0, H // 2, H - 1):
-        p = torch.softmax((q[0, h].double() @ k[0, h].double().T) * scale, 1)
-        rows = torch.arange(N, device="cuda")
-        e = torch.zeros(N, -(-N // bk), dtype=torch.float64, device="cuda").index_add_(1, rows // bk, p)
-        e = torch.zeros(-(-N // bq), e.shape[1], dtype=torch.float64, device="cuda").index_add_(0, rows // bq, e)
-        e /= torch.bincount(rows // bq)[:, None]
-        torch.testing.assert_close(got[0, h].double(), e, rtol=2e-5, atol=1e-9)
+        _same_bits(got[:, h:h + 1], lib.block_energy(q[:, h:h + 1].contiguous(), k[:, h:h + 1].contiguous(), bq, bk, scale,
+                                                     workspace=full))
+        torch.testing.assert_close(got[0, h].double(), _energy64(q[0, h], k[0, h], bq, bk, scale), rtol=2e-5, atol=1e-9)
+
+
+# the first key that outgrows the keys before it by more than the safe range: in the second tile, around the edges of
+# tiles and sub-tiles, in the ragged last tile only
+@pytest.mark.parametrize("N,late", [(700, 130), (700, 255), (700, 256), (700, 415), (675, 640), (675, 674)])
+@pytest.mark.parametrize("D,bk", [(128, 128), (128, 64), (64, 128), (64, 64)])
+def test_block_energy_late_large_logits(lib, D, bk, N, late):
+    import torch
+
+    print(f"energy late logits D={D} bk={bk} N={N} late={late}", flush=True)
+    H = 4200 // -(-N // 256)
+    gen = torch.Generator(device="cuda").manual_seed(N + D + bk + late)
+    q, k = (torch.randn(1, H, N, D, device="cuda", generator=gen) for _ in range(2))
+    # rows of very different reach: some move their references more than once, others never, in either half of 64
+    reach = torch.tensor([0.05, 1.0, 6.0, 12.0], device="cuda")[torch.randint(0, 4, (1, H, -(-N // 32), 1), device="cuda",
+                                                                              generator=gen)]
+    q *= reach.repeat_interleave(32, 2)[:, :, :N]
+    k[:, :, :late] *= 0.2
+    q, k = q.to(torch.bfloat16), k.to(torch.bfloat16)
+    scale = (-1 if late == 255 else 1) * 2.5 / math.sqrt(D)
+    nbytes = lib.block_energy_workspace_bytes(N, 128, bk)
+    full, small = (torch.full((b // 4,), float("nan"), device="cuda") for b in (nbytes, nbytes // 1024 * 300))
+    got = lib.block_energy(q, k, 128, bk, scale, workspace=full)
+    narrow = lib.block_energy(q, k, 128, bk, scale, workspace=small)
+    torch.cuda.synchronize()
+    _same_bits(got, narrow)
+    for h in (0, 1, H - 1):
+        torch.testing.assert_close(got[0, h].double(), _energy64(q[0, h], k[0, h], 128, bk, scale), rtol=2e-4, atol=1e-9)
