@@ -486,8 +486,13 @@ int calibatt_block_energy(const void *q, const void *k, float *energy, int B, in
  *                    bytes) up: the kernel runs as many workgroups as there
  *                    are slices, the GPU holds at a time, and there are query
  *                    blocks.  calibatt_block_energy_workspace_bytes (host, no
- *                    GPU needed) returns 1024 slices, enough for every
- *                    supported shape on a 256-CU part.
+ *                    GPU needed) returns 1024 slices.
+ * Large calls run with two query blocks and two slices per workgroup (so 1024
+ * slices are two such workgroups on each of 256 CUs); the energies have the
+ * same bits whatever the size of the workspace and the number of heads.
+ * calibatt_block_energy_onepass_queries (host) writes how many queries a
+ * workgroup of such a call takes on the current device: block_q, or twice as
+ * many.
  * Other arguments, supported shapes and errors as calibatt_block_energy, plus
  * BUFFER_TOO_SMALL (less than one slice).
  */
@@ -495,6 +500,8 @@ int calibatt_block_energy_workspace_bytes(int N, int block_q, int block_k, int64
 int calibatt_block_energy_onepass(const void *q, const void *k, float *energy, int B, int H, int N, int D,
                                   int block_q, int block_k, float scale, void *workspace,
                                   int64_t workspace_bytes, void *stream);
+int calibatt_block_energy_onepass_queries(int B, int H, int N, int D, int block_q, int block_k,
+                                          int64_t workspace_bytes, int32_t *queries);
 
 /*
  * calibatt_select_blocks (Eq. 6): for each of n_rows block-rows of nbk

@@ -18,6 +18,7 @@ from .binding import (  # noqa: F401
     anchor_map,
     anchor_partner,
     block_energy,
+    block_energy_onepass_queries,
     block_energy_workspace_bytes,
     compile_pattern,
     encode_intervals,

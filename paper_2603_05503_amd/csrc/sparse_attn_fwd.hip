@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "attn_kernel_2wg.h"
 #include "attn_kernel_anchor.h"
@@ -233,7 +234,7 @@ int launch_energy(const uint16_t *q, const uint16_t *k, float *energy, const Ene
 // workgroups as the device holds at a time, the workspace has slices for, and there are units.  Fills in the launch
 // without launching.
 template <typename Form, typename Kernel>
-int plan_energy_onepass(Kernel kernel, const EnergyDims &p, long long workspace_bytes, EnergyOnePassDims &pp, int &slots) {
+int plan_energy_form(Kernel kernel, const EnergyDims &p, long long workspace_bytes, EnergyOnePassDims &pp, int &cus) {
   pp.e = p;
   pp.n_group = (p.nbq + Form::BLOCKS - 1) / Form::BLOCKS;
   const long long units = (long long)p.B * p.H * pp.n_group;
@@ -242,53 +243,84 @@ int plan_energy_onepass(Kernel kernel, const EnergyDims &p, long long workspace_
   const long long slice = (long long)p.nbk * Form::QUERIES * 4;
   if (workspace_bytes < slice) return CALIBATT_ERR_BUFFER_TOO_SMALL;
   static DevReady state;
-  int dev = 0, cus = 0, per_cu = 0;
+  int dev = 0, per_cu = 0;
   if (int st = register_lds(kernel, ENERGY_MAX_LDS, state, dev)) return st;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
       hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kernel, Form::NW * 64, (size_t)smem) !=
           hipSuccess ||
       cus <= 0 || per_cu <= 0)
     return CALIBATT_ERR_LAUNCH;
-  slots = cus * per_cu;
-  pp.n_wg = (int)std::min<long long>({units, (long long)slots, workspace_bytes / slice, 1 << 20});
+  pp.n_wg = (int)std::min<long long>({units, (long long)cus * per_cu, workspace_bytes / slice, 1 << 20});
   pp.xcds = pp.n_wg >= ENERGY_XCDS ? ENERGY_XCDS : 1;
+  return CALIBATT_OK;
+}
+
+// How long the longest XCD is at it, in turns of one workgroup on one CU: its workgroups go through its units in
+// rounds, and a round takes a CU one turn per workgroup that it holds.
+long long energy_turns(const EnergyOnePassDims &pp, int cus) {
+  const long long units = (long long)pp.e.B * pp.e.H * pp.n_group, here = std::max(cus / pp.xcds, 1);
+  long long longest = 0;
+  for (int x = 0; x < pp.xcds; ++x) {
+    const long long n = units * (x + 1) / pp.xcds - units * x / pp.xcds;  // as EnergyUnits has it
+    const long long wgs = (pp.n_wg - x + pp.xcds - 1) / pp.xcds;
+    longest = std::max(longest, n / wgs * ((wgs + here - 1) / here) + (n % wgs + here - 1) / here);
+  }
+  return longest;
+}
+
+// Chooses and plans the form: with two query blocks per workgroup (`wide`) where its turns, longer by a measured
+// factor, take less time than those of the narrow form.  The factors are the times of full rounds at 5120 tokens,
+// D = 128 / 64, us per key block and workgroup of a CU:
+//  - blocks of 128, two panels per wavefront: 1.10 -> 1.98 with key blocks of 128, 1.10 -> 2.08 of 64; D = 64: 0.77 ->
+//    1.41 and 0.78 -> 1.56, twice as long: not built.  Below one workgroup per CU the panels gain nothing;
+//  - blocks of 64, four wavefronts instead of two: 0.87 -> 1.13 with key blocks of 128 at D = 128.  Elsewhere LDS does
+//    not keep the narrow form's wavefronts down, and the factor (1.5) decides between calls that do not fill the device:
+//    both forms have as many wavefronts in flight in full rounds and the wide one reads K half as often (N = 10400, 10
+//    heads, D = 128: 399 -> 364 us).
+// Either side of the line, 128 / 128 / 128: 32 heads of 5120 tokens (1280 narrow units on 512 workgroups, 3 rounds, the
+// last half full) 222 us narrow, 217 wide; 35 heads 260 and 225; 40 heads (2 wide rounds against 3 and a few) 288 and 312.
+template <int D, int BQ, int BK>
+int plan_energy_onepass(const EnergyDims &p, long long workspace_bytes, EnergyOnePassDims &pp, bool &wide) {
+  using Narrow = EnergyOnePass<D, BQ, BK, BQ>;
+  int cus = 0;
+  wide = false;
+  if (int st = plan_energy_form<Narrow>(block_energy_onepass_kernel<D, BQ, BK, BQ>, p, workspace_bytes, pp, cus))
+    return st;
+  if constexpr (BQ == 64 || D == 128 || BK == 128) {
+    EnergyOnePassDims w;
+    int st;
+    if constexpr (BQ == 64)
+      st = plan_energy_form<EnergyOnePass<D, BQ, BK, 128>>(block_energy_onepass_kernel<D, BQ, BK, 128>, p,
+                                                           workspace_bytes, w, cus);
+    else
+      st = plan_energy_form<EnergyPanels<D, BK>>(block_energy_panels_kernel<D, BK>, p, workspace_bytes, w, cus);
+    constexpr int PERCENT = BQ == 64 ? (D == 128 && BK == 128 ? 130 : 150) : BK == 64 ? 190 : D == 128 ? 180 : 185;
+    if (st == CALIBATT_OK && (BQ == 64 || (long long)p.B * p.H * w.n_group > cus) &&
+        energy_turns(w, cus) * PERCENT <= energy_turns(pp, cus) * 100) {
+      wide = true;
+      pp = w;
+    }
+  }
   return CALIBATT_OK;
 }
 
 template <int D, int BQ, int BK>
 int launch_energy_onepass(const uint16_t *q, const uint16_t *k, float *energy, const EnergyDims &p, float *workspace,
                           long long workspace_bytes, hipStream_t stream) {
-  // Two query blocks per workgroup where the workspace has a slice for every workgroup that fits the device, and
-  //  - blocks of 128 (two panels per wavefront): from two rounds of such workgroups on.  A unit takes 1.8 times as long
-  //    as one of the narrow form, so with fewer rounds the coarser last one costs more than the panels give;
-  //  - blocks of 64 (four wavefronts for two): as soon as the narrow form needs a second round.
-  constexpr int WIDE = 2 * BQ;
   EnergyOnePassDims pp;
-  int slots = 0;
+  bool wide = false;
+  if (int st = plan_energy_onepass<D, BQ, BK>(p, workspace_bytes, pp, wide)) return st;
   auto launch = [&](auto kernel, auto form) {
     using Form = decltype(form);
     return launch_kernel(kernel, (unsigned)pp.n_wg, Form::NW * 64, (int)Form::bytes(p.nbk), stream, q, k, energy,
                          workspace, pp);
   };
-  if constexpr (BQ == 128) {
-    using Form = EnergyPanels<D, BK>;
-    auto kernel = block_energy_panels_kernel<D, BK>;
-    if (plan_energy_onepass<Form>(kernel, p, workspace_bytes, pp, slots) == CALIBATT_OK) {
-      const long long units = (long long)p.B * p.H * pp.n_group;
-      if (pp.n_wg == slots && units >= 2LL * slots) return launch(kernel, Form{});
-    }
-  } else {
-    using Form = EnergyOnePass<D, BQ, BK, WIDE>;
-    auto kernel = block_energy_onepass_kernel<D, BQ, BK, WIDE>;
-    if (plan_energy_onepass<Form>(kernel, p, workspace_bytes, pp, slots) == CALIBATT_OK) {
-      const long long units = (long long)p.B * p.H * pp.n_group;
-      if (pp.n_wg == std::min<long long>(units, slots) && 2 * units > slots) return launch(kernel, Form{});
-    }
+  if constexpr (BQ == 64) {
+    if (wide) return launch(block_energy_onepass_kernel<D, BQ, BK, 128>, EnergyOnePass<D, BQ, BK, 128>{});
+  } else if constexpr (D == 128 || BK == 128) {
+    if (wide) return launch(block_energy_panels_kernel<D, BK>, EnergyPanels<D, BK>{});
   }
-  using Form = EnergyOnePass<D, BQ, BK, BQ>;
-  auto kernel = block_energy_onepass_kernel<D, BQ, BK, BQ>;
-  if (int st = plan_energy_onepass<Form>(kernel, p, workspace_bytes, pp, slots)) return st;
-  return launch(kernel, Form{});
+  return launch(block_energy_onepass_kernel<D, BQ, BK, BQ>, EnergyOnePass<D, BQ, BK, BQ>{});
 }
 
 template <int D>
@@ -463,37 +495,50 @@ extern "C" int calibatt_block_energy_workspace_bytes(int N, int block_q, int blo
   return CALIBATT_OK;
 }
 
+namespace {
+// Calls f(integral constants D, block_q, block_k) for the shapes that the one-pass energies are built for.
+template <typename F>
+int energy_shape(int D, int block_q, int block_k, F f) {
+  auto with_d = [&](auto d) {
+    auto with_q = [&](auto bq) {
+      return block_k == 128 ? f(d, bq, std::integral_constant<int, 128>{}) : f(d, bq, std::integral_constant<int, 64>{});
+    };
+    return block_q == 128 ? with_q(std::integral_constant<int, 128>{}) : with_q(std::integral_constant<int, 64>{});
+  };
+  if (!(D == 64 || D == 128) || !(block_q == 64 || block_q == 128) || !(block_k == 64 || block_k == 128))
+    return CALIBATT_ERR_UNSUPPORTED;
+  return D == 128 ? with_d(std::integral_constant<int, 128>{}) : with_d(std::integral_constant<int, 64>{});
+}
+}  // namespace
+
 extern "C" int calibatt_block_energy_onepass(const void *q, const void *k, float *energy, int B, int H, int N, int D,
                                              int block_q, int block_k, float scale, void *workspace,
                                              int64_t workspace_bytes, void *stream) {
   if (!q || !k || !energy || !workspace) return CALIBATT_ERR_NULL;
   if (B <= 0 || H <= 0 || N <= 0 || D <= 0 || block_q <= 0 || block_k <= 0 || workspace_bytes < 0)
     return CALIBATT_ERR_SHAPE;
-  if (!(D == 64 || D == 128) || !(block_q == 64 || block_q == 128) || !(block_k == 64 || block_k == 128))
-    return CALIBATT_ERR_UNSUPPORTED;
-  if ((size_t)B * H * N * D > 0x7fffffff00ULL || ((uintptr_t)workspace & 3)) return CALIBATT_ERR_SHAPE;
-  EnergyDims p;
-  p.B = B;
-  p.H = H;
-  p.N = N;
-  p.nbq = (N + block_q - 1) / block_q;
-  p.nbk = (N + block_k - 1) / block_k;
-  p.scale_log2e = scale * 1.4426950408889634f;
-  const uint16_t *qq = (const uint16_t *)q, *kk = (const uint16_t *)k;
-  hipStream_t s = (hipStream_t)stream;
-#define CALIBATT_CASE(d, bq, bk)                        \
-  if (D == d && block_q == bq && block_k == bk)         \
-    return launch_energy_onepass<d, bq, bk>(qq, kk, energy, p, (float *)workspace, workspace_bytes, s);
-  CALIBATT_CASE(128, 128, 128)
-  CALIBATT_CASE(128, 128, 64)
-  CALIBATT_CASE(128, 64, 128)
-  CALIBATT_CASE(128, 64, 64)
-  CALIBATT_CASE(64, 128, 128)
-  CALIBATT_CASE(64, 128, 64)
-  CALIBATT_CASE(64, 64, 128)
-  CALIBATT_CASE(64, 64, 64)
-#undef CALIBATT_CASE
-  return CALIBATT_ERR_UNSUPPORTED;
+  return energy_shape(D, block_q, block_k, [&](auto d, auto bq, auto bk) -> int {
+    if ((size_t)B * H * N * D > 0x7fffffff00ULL || ((uintptr_t)workspace & 3)) return CALIBATT_ERR_SHAPE;
+    const EnergyDims p = {B, H, N, (N + block_q - 1) / block_q, (N + block_k - 1) / block_k, scale * 1.4426950408889634f};
+    return launch_energy_onepass<d, bq, bk>((const uint16_t *)q, (const uint16_t *)k, energy, p, (float *)workspace,
+                                            workspace_bytes, (hipStream_t)stream);
+  });
+}
+
+extern "C" int calibatt_block_energy_onepass_queries(int B, int H, int N, int D, int block_q, int block_k,
+                                                     int64_t workspace_bytes, int32_t *queries) {
+  if (!queries) return CALIBATT_ERR_NULL;
+  if (B <= 0 || H <= 0 || N <= 0 || D <= 0 || block_q <= 0 || block_k <= 0 || workspace_bytes < 0)
+    return CALIBATT_ERR_SHAPE;
+  return energy_shape(D, block_q, block_k, [&](auto d, auto bq, auto bk) -> int {
+    if ((size_t)B * H * N * D > 0x7fffffff00ULL) return CALIBATT_ERR_SHAPE;
+    const EnergyDims p = {B, H, N, (N + block_q - 1) / block_q, (N + block_k - 1) / block_k, 1.0f};
+    EnergyOnePassDims pp;
+    bool wide = false;
+    if (int st = plan_energy_onepass<d, bq, bk>(p, workspace_bytes, pp, wide)) return st;
+    *queries = wide ? 2 * block_q : block_q;
+    return CALIBATT_OK;
+  });
 }
 
 extern "C" int calibatt_anchor_attn_fwd(const void *q, const void *k, const void *v, void *out, int B, int H,

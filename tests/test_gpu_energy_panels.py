@@ -1,8 +1,9 @@
-"""The one-pass block energies where the call is large enough for workgroups of 256 queries, at ragged lengths and
-odd numbers of query blocks, against fp64, and bit for bit against the same call with a workspace that only the
-128-query form (or the 64-query one) fits, and against one head alone.  Tolerance: fp32 sums of fp32 exponentials of
-logits below 64 (2^-18 in the exponent).  A second test has logits that outgrow the reference of the exponentials late
-in a row: up to 2^8 in the exponent, sums of D products in fp32, so 2^-14 with a few ulps, and 2e-4 relative."""
+"""The one-pass block energies where the call is large enough for workgroups of two query blocks, at ragged lengths
+and odd numbers of query blocks, against fp64, and bit for bit against the form with one query block (a workspace of
+one slice) and against one head alone; the form that a call takes is asserted.  Tolerance: fp32 sums of fp32
+exponentials of logits below 64 (2^-18 in the exponent).  A second test has logits that outgrow the reference of the
+exponentials late in a row: up to 2^8 in the exponent, sums of D products in fp32, so 2^-14 with a few ulps, and 2e-4
+relative."""
 import math
 
 import pytest
@@ -16,6 +17,18 @@ def _same_bits(a, b):
     assert torch.equal(a.contiguous().view(torch.int32), b.contiguous().view(torch.int32))
 
 
+def _workspaces(lib, B, H, N, D, bq, bk):
+    """Workspaces of the recommended size, of one slice (one narrow workgroup) and of four times the recommended size,
+    NaN-filled, after a look at the form that each gives."""
+    import torch
+
+    nbytes = lib.block_energy_workspace_bytes(N, bq, bk)
+    sizes = nbytes, nbytes // 1024, 4 * nbytes
+    twice = 1 if (D, bq, bk) == (64, 128, 64) else 2
+    assert [lib.block_energy_onepass_queries(B, H, N, D, bq, bk, n) for n in sizes] == [twice * bq, bq, twice * bq]
+    return [torch.full((n // 4,), float("nan"), device="cuda") for n in sizes]
+
+
 def _energy64(q, k, bq, bk, scale):
     import torch
 
@@ -27,25 +40,22 @@ def _energy64(q, k, bq, bk, scale):
     return e / torch.bincount(rows // bq)[:, None]
 
 
-@pytest.mark.parametrize("N", [129, 640, 901])
+# 4096 units of 256 queries: whole rounds of 512 workgroups, two per CU.  With blocks of 128, D = 64 and key blocks of 64
+# the wide form is not built.
+@pytest.mark.parametrize("N,H", [(129, 4096), (901, 1024), (2100, 455)])
 @pytest.mark.parametrize("D,bq,bk", [(128, 128, 128), (128, 128, 64), (128, 64, 128), (128, 64, 64),
                                      (64, 128, 128), (64, 128, 64), (64, 64, 128), (64, 64, 64)])
-def test_block_energy_wide_workgroups(lib, D, bq, bk, N):
+def test_block_energy_wide_workgroups(lib, D, bq, bk, N, H):
     import torch
 
     print(f"energy panels D={D} bq={bq} bk={bk} N={N}", flush=True)
-    H = 4200 // -(-N // 256)  # 256-query units: more than twice the workgroups of a 256-CU device at four per CU
     gen = torch.Generator(device="cuda").manual_seed(N + D + bq + bk)
     q, k = (torch.randn(1, H, N, D, device="cuda", generator=gen).mul_(1.5).to(torch.bfloat16) for _ in range(2))
-    scale = -1 / math.sqrt(D) if N == 640 else 1 / math.sqrt(D)
-    nbytes = lib.block_energy_workspace_bytes(N, bq, bk)
-    full, small = (torch.full((b // 4,), float("nan"), device="cuda") for b in (nbytes, nbytes // 1024 * 300))
+    scale = -1 / math.sqrt(D) if N == 901 else 1 / math.sqrt(D)
+    full, narrow, big = _workspaces(lib, 1, H, N, D, bq, bk)
     got = lib.block_energy(q, k, bq, bk, scale, workspace=full)
-    again = lib.block_energy(q, k, bq, bk, scale, workspace=full)
-    narrow = lib.block_energy(q, k, bq, bk, scale, workspace=small)
-    torch.cuda.synchronize()
-    assert torch.equal(got, again)
-    _same_bits(got, narrow)
+    for workspace in (full, narrow, big):
+        _same_bits(got, lib.block_energy(q, k, bq, bk, scale, workspace=workspace))
     for h in (0, H // 2, H - 1):
         _same_bits(got[:, h:h + 1], lib.block_energy(q[:, h:h + 1].contiguous(), k[:, h:h + 1].contiguous(), bq, bk, scale,
                                                      workspace=full))
@@ -55,12 +65,12 @@ def test_block_energy_wide_workgroups(lib, D, bq, bk, N):
 # the first key that outgrows the keys before it by more than the safe range: in the second tile, around the edges of
 # tiles and sub-tiles, in the ragged last tile only
 @pytest.mark.parametrize("N,late", [(700, 130), (700, 255), (700, 256), (700, 415), (675, 640), (675, 674)])
-@pytest.mark.parametrize("D,bk", [(128, 128), (128, 64), (64, 128), (64, 64)])
+@pytest.mark.parametrize("D,bk", [(128, 128), (128, 64), (64, 128)])
 def test_block_energy_late_large_logits(lib, D, bk, N, late):
     import torch
 
     print(f"energy late logits D={D} bk={bk} N={N} late={late}", flush=True)
-    H = 4200 // -(-N // 256)
+    H = 1365  # x 3 units
     gen = torch.Generator(device="cuda").manual_seed(N + D + bk + late)
     q, k = (torch.randn(1, H, N, D, device="cuda", generator=gen) for _ in range(2))
     # rows of very different reach: some move their references more than once, others never, in either half of 64
@@ -70,11 +80,8 @@ def test_block_energy_late_large_logits(lib, D, bk, N, late):
     k[:, :, :late] *= 0.2
     q, k = q.to(torch.bfloat16), k.to(torch.bfloat16)
     scale = (-1 if late == 255 else 1) * 2.5 / math.sqrt(D)
-    nbytes = lib.block_energy_workspace_bytes(N, 128, bk)
-    full, small = (torch.full((b // 4,), float("nan"), device="cuda") for b in (nbytes, nbytes // 1024 * 300))
+    full, narrow, _ = _workspaces(lib, 1, H, N, D, 128, bk)
     got = lib.block_energy(q, k, 128, bk, scale, workspace=full)
-    narrow = lib.block_energy(q, k, 128, bk, scale, workspace=small)
-    torch.cuda.synchronize()
-    _same_bits(got, narrow)
+    _same_bits(got, lib.block_energy(q, k, 128, bk, scale, workspace=narrow))
     for h in (0, 1, H - 1):
         torch.testing.assert_close(got[0, h].double(), _energy64(q[0, h], k[0, h], 128, bk, scale), rtol=2e-4, atol=1e-9)
