@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import threading
 from dataclasses import dataclass
 from typing import Optional
 
@@ -319,8 +320,10 @@ class DevicePattern:
             c.head_map = self.tensors["head_map"].data_ptr()
         else:
             c.head_map = None
-        # int32[16] workspace of the persistent-workgroup scheduler (kept zero between calls)
-        self.counter = torch.zeros(16, dtype=torch.int32, device=device) if persistent else None
+        # int32[16] workspace of the persistent-workgroup scheduler (kept zero between calls), and as many for
+        # further streams, cleared here so that no call has to (128 bytes apart: a cache line each)
+        counters = torch.zeros((8, 32), dtype=torch.int32, device=device)[:, :16] if persistent else None
+        self.counter = counters[0] if persistent else None
         c.work_counter = self.counter.data_ptr() if persistent else None
         c.n_groups = hp.n_groups
         gp = hp.group_ptr if hp.group_ptr is not None else np.array([0] + [hp.n_work] * 8, np.int32)
@@ -329,23 +332,33 @@ class DevicePattern:
         self.c = c
         self._stream_of_c = None   # stream handle that uses self.c
         self._per_stream = {}      # other streams: (clone of the struct, its own counters)
+        self._spare = [] if counters is None else list(counters[1:])
+        self._lock = threading.Lock()
 
     def c_for(self, stream_handle: int):
         """The C struct to pass for a call on ``stream_handle``.  Calls on different streams may overlap on
         the GPU, and overlapping calls must not share the scheduler's work counters: every stream after the
         first gets a clone of the struct that points at counters of its own (the index arrays are shared)."""
-        if self.counter is None or self._stream_of_c is None or self._stream_of_c == stream_handle:
-            self._stream_of_c = stream_handle
+        if self.counter is None or self._stream_of_c == stream_handle:
             return self.c
-        if stream_handle not in self._per_stream:
-            import torch
+        with self._lock:
+            if self._stream_of_c is None:
+                self._stream_of_c = stream_handle
+            if self._stream_of_c == stream_handle:
+                return self.c
+            if stream_handle not in self._per_stream:
+                import torch
 
-            clone = _CPattern()
-            C.memmove(C.byref(clone), C.byref(self.c), C.sizeof(_CPattern))
-            counter = torch.zeros(16, dtype=torch.int32, device=self.counter.device)
-            clone.work_counter = counter.data_ptr()
-            self._per_stream[stream_handle] = (clone, counter)
-        return self._per_stream[stream_handle][0]
+                clone = _CPattern()
+                C.memmove(C.byref(clone), C.byref(self.c), C.sizeof(_CPattern))
+                if self._spare:
+                    counter = self._spare.pop()
+                else:  # cleared on the stream that uses it: nothing orders a fill on another one before the call
+                    with torch.cuda.stream(torch.cuda.ExternalStream(stream_handle, device=self.counter.device)):
+                        counter = torch.zeros(16, dtype=torch.int32, device=self.counter.device)
+                clone.work_counter = counter.data_ptr()
+                self._per_stream[stream_handle] = (clone, counter)
+            return self._per_stream[stream_handle][0]
 
     @property
     def nnz(self) -> int:

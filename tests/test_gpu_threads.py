@@ -65,3 +65,32 @@ def test_four_threads_four_streams(lib, kernel):
         t.join()
     torch.cuda.synchronize()
     assert not errors, errors
+
+
+def test_first_calls_on_streams_do_not_wait_for_another(lib):
+    """A pattern that is in use gets cleared work counters for every further stream, also while the stream that was
+    current when the call was made is busy and its free memory holds other values."""
+    import torch
+
+    print("first calls on ten streams", flush=True)
+    B, H, N, D, blk = 2, 16, 3000, 128, 128
+    nb = -(-N // blk)
+    tq, tk, tv = (to_dev(x) for x in _qkv(900, B, H, N, D, 2.0))
+    mask, repeat = random_mask(901, H, nb, nb, 0.3, 0.2, tail_partial=True)
+    dp = lib.compile_pattern(mask, repeat, H, N, blk, blk, 3).to_device(persistent=True)
+    assert dp.host.n_work * B > 512  # more items than workgroups: the counters are used
+    want = lib.sparse_attn_fwd(tq, tk, tv, torch.empty_like(tq), dp, 0.09).view(torch.int16).clone()
+    streams = [torch.cuda.Stream() for _ in range(10)]
+    outs = [torch.full_like(tq, float("nan")) for _ in streams]
+    for _ in range(64):
+        torch.full((16,), 1 << 24, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    torch.cuda._sleep(200_000_000)
+    for out, s in zip(outs, streams):
+        for _ in range(2):
+            lib.sparse_attn_fwd(tq, tk, tv, out, dp, 0.09, stream=s.cuda_stream)
+    for s in streams:
+        s.synchronize()
+    torch.cuda.synchronize()
+    for i, out in enumerate(outs):
+        assert torch.equal(out.view(torch.int16), want), i
