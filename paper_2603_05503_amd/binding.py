@@ -509,6 +509,34 @@ def anchor_attn_fwd(q, k, v, out, head_ids, amap: DeviceAnchorMap, scale: float,
     return out
 
 
+def _stream_of(stream, device):
+    """(handle, other): the stream handle of a call (None = torch's current stream), and that stream as a torch stream
+    where it is not the current one.  What a call allocates is allocated under ``torch.cuda.stream(other)`` (None = the
+    current one): free memory of the current stream may still be in use by work of its last owner there, which nothing
+    orders before another stream."""
+    import torch
+
+    current = torch.cuda.current_stream(device).cuda_stream
+    if stream is None or int(stream) == current:
+        return current, None
+    return int(stream), torch.cuda.ExternalStream(int(stream), device=device)
+
+
+def _empty(shape, dtype, device, other, returned=False):
+    """An uninitialised tensor of the call's stream (see ``_stream_of``); one that is returned may be read and released
+    on the current stream."""
+    import torch
+
+    if other is None:
+        return torch.empty(shape, dtype=dtype, device=device)
+    current = torch.cuda.current_stream(device)
+    with torch.cuda.stream(other):
+        t = torch.empty(shape, dtype=dtype, device=device)
+    if returned:
+        t.record_stream(current)
+    return t
+
+
 def block_energy_workspace_bytes(N: int, block_q: int, block_k: int) -> int:
     lib = load_library()
     n = C.c_int64(0)
@@ -542,12 +570,11 @@ def block_energy(q, k, block_q: int, block_k: int, scale: float, out=None, strea
         raise ValueError("q and k must have the same shape")
     B, H, N, D = q.shape
     shape = (B, H, -(-N // block_q), -(-N // block_k))
+    stream, other = _stream_of(stream, q.device)
     if out is None:
-        out = torch.empty(shape, dtype=torch.float32, device=q.device)
+        out = _empty(shape, torch.float32, q.device, other, returned=True)
     elif not (out.is_cuda and out.dtype == torch.float32 and out.is_contiguous() and tuple(out.shape) == shape):
         raise ValueError(f"out must be a contiguous fp32 CUDA tensor of shape {shape}")
-    if stream is None:
-        stream = torch.cuda.current_stream(q.device).cuda_stream
     if workspace is not None:
         if not (workspace.is_cuda and workspace.is_contiguous() and workspace.device == q.device):
             raise ValueError("workspace must be a contiguous CUDA tensor on the tensors' device")
@@ -570,13 +597,12 @@ def select_blocks_device(energy, eps: float, out=None, stream=None):
     lib = load_library()
     if not (energy.is_cuda and energy.dtype == torch.float32 and energy.is_contiguous() and energy.dim() >= 1):
         raise ValueError("energy must be a contiguous fp32 CUDA tensor [..., nbk]")
+    stream, other = _stream_of(stream, energy.device)
     if out is None:
-        out = torch.empty(energy.shape, dtype=torch.uint8, device=energy.device)
+        out = _empty(energy.shape, torch.uint8, energy.device, other, returned=True)
     elif not (out.is_cuda and out.dtype == torch.uint8 and out.is_contiguous() and out.shape == energy.shape):
         raise ValueError("out must be a contiguous uint8 CUDA tensor of the energies' shape")
     nbk = energy.shape[-1]
-    if stream is None:
-        stream = torch.cuda.current_stream(energy.device).cuda_stream
     st = lib.calibatt_select_blocks_device(energy.data_ptr(), energy.numel() // max(nbk, 1), nbk, float(eps),
                                            out.data_ptr(), C.c_void_p(stream))
     if st != 0:
@@ -770,17 +796,14 @@ def spatial_similarity(q, k, partner, row_len: int, scale: float, workspace=None
         raise ValueError("partner must be a contiguous 1-d int32 CUDA tensor")
     B, H, N, D = q.shape
     n_tok = partner.numel()
+    stream, other = _stream_of(stream, q.device)
     if workspace is None:
-        workspace = torch.empty((B, H, max(n_tok, 1), 3), dtype=torch.float32, device=q.device)
-    score = torch.empty((B, H), dtype=torch.float32, device=q.device)
+        workspace = _empty((B, H, max(n_tok, 1), 3), torch.float32, q.device, other)
+    score = _empty((B, H), torch.float32, q.device, other, returned=True)
     nbytes = C.c_int64(0)
     lists = None
     if lib.calibatt_similarity_lists_bytes(B, H, n_tok, C.byref(nbytes)) == 0 and nbytes.value > 0:
-        lists = torch.empty(nbytes.value, dtype=torch.uint8, device=q.device)
-        if stream is not None:  # released on return: its memory must not be reused before that stream is done with it
-            lists.record_stream(torch.cuda.ExternalStream(stream, device=q.device))
-    if stream is None:
-        stream = torch.cuda.current_stream(q.device).cuda_stream
+        lists = _empty(nbytes.value, torch.uint8, q.device, other)
     st = lib.calibatt_spatial_similarity_grouped(q.data_ptr(), k.data_ptr(), B, H, N, D, partner.data_ptr(), n_tok,
                                                  int(row_len), float(scale), workspace.data_ptr(),
                                                  None if lists is None else lists.data_ptr(), nbytes.value,

@@ -198,12 +198,12 @@ class CalibAttention:
         calls on one stream run in order and may share it, calls on different streams may overlap."""
         import torch
 
-        handle = torch.cuda.current_stream(q.device).cuda_stream if stream is None else int(stream)
+        handle, other = _b._stream_of(stream, q.device)
         key = (q.shape[0], n_heads, handle)
         if key not in self._anchor_workspace:
             with torch.cuda.device(q.device):
                 n_split, nbytes = _b.anchor_split_plan(q.shape[0], self.N, self.D, n_heads, self.amap.n_q)
-            self._anchor_workspace[key] = (torch.empty(nbytes // 4, dtype=torch.float32, device=q.device)
+            self._anchor_workspace[key] = (_b._empty(nbytes // 4, torch.float32, q.device, other)
                                            if n_split > 1 else None)
         return self._anchor_workspace[key]
 

@@ -85,3 +85,38 @@ def test_grouped_refuses_what_does_not_fit(lib):
     n = C.c_int64(0)
     assert raw.calibatt_similarity_lists_bytes(1, 1, 8, C.byref(n)) == 0 and n.value == 0
     assert raw.calibatt_similarity_lists_bytes(1, 513, 100, C.byref(n)) == 0 and n.value == 3616
+
+
+def test_temporaries_belong_to_the_stream_of_the_call(lib):
+    """What the binding allocates for a call on another stream comes from that stream's memory: a block of the current
+    stream may still be in use by earlier work there."""
+    import torch
+
+    n, cols, H, D = 65536, 256, 2, 64
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q, k = (torch.randn(1, H, n, D, device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2))
+    partner = torch.from_numpy(lib.anchor_partner(2, n // 2 // cols, cols, 9)).cuda()
+    triples = torch.empty((1, H, n, 3), device="cuda")
+    nbytes = C.c_int64(0)
+    assert lib.load_library().calibatt_similarity_lists_bytes(1, H, n, C.byref(nbytes)) == 0 and nbytes.value > 1 << 21
+    want = lib.spatial_similarity(q, k, partner, cols, 0.1, workspace=triples)
+    want_triples = triples.clone()
+    torch.cuda.synchronize()
+    q2, k2 = (x[:, :, :512].contiguous() for x in (q, k))
+    side = torch.cuda.Stream()
+    triples.fill_(0)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+
+    def segments():
+        return [s for s in torch.cuda.memory_snapshot() if s["stream"] == side.cuda_stream]
+
+    before = sum(s["total_size"] for s in segments())
+    score = lib.spatial_similarity(q, k, partner, cols, 0.1, workspace=triples, stream=side.cuda_stream)
+    assert sum(s["total_size"] for s in segments()) - before >= nbytes.value  # the lists: more than a segment of small blocks
+    energy = lib.block_energy(q2, k2, 128, 128, 0.1, stream=side.cuda_stream)
+    mask = lib.select_blocks_device(energy, 0.9, stream=side.cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(score, want) and torch.equal(triples, want_triples)
+    for t in (score, energy, mask):
+        assert any(s["address"] <= t.data_ptr() < s["address"] + s["total_size"] for s in segments())
