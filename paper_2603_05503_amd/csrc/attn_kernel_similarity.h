@@ -17,7 +17,8 @@
 // at the end.  Writes the normalised triple of every token.
 //
 // What bounds it: the vector ALU (per logit an FMA, an exponential, two or
-// three sums) beside the matrix cores, and the power both draw.  A token and
+// three sums) beside the matrix cores, and the power both draw; where a
+// workgroup has its CU to itself, the chain of one wavefront.  A token and
 // its partner alone (R = 1) cost two rows of logits; tokens that share their
 // partner's row cost (R + 1) / R each, and one K operand read from LDS feeds
 // R + 1 MFMAs.  All quantities of a query or pair are computed by the same
@@ -27,6 +28,10 @@
 // Measured, 24 heads of 21 x 30 x 52 tokens, D = 128, five anchors, in turn on one box: 14.37 ms with every token
 // beside its own partner and one wavefront per head in the reduction, 10.49 ms as it is here (matrix pipes busy
 // 43 % of the cycles, vector ALU 72 %, at 1.9 GHz).
+//
+// Without groups, us with one score buffer (and before it, with whole tiles of 128 keys) -> with two: 210 units of 3840
+// keys, D = 128 95 (92) -> 81, D = 64 78 (73) -> 69; 480 units 148 (156) -> 141; 1800 units of 9600 keys 1299 (1427) ->
+// 1296.
 //
 // Grouping (similarity_group_kernel): the tokens of one column of the grid in
 // consecutive spatial rows form a run while they have the same partner; a run
@@ -145,11 +150,16 @@ __device__ __forceinline__ SimilaritySums<D, R> similarity_pass(
     const int (&tok)[R + 1], const SimilarityDims &p) {
   using RB = RowBlock<D, SIM_BQ, SIM_BK>;
   constexpr int KB = RB::KB, DS = RB::DS, ROWB = RB::ROWB, TILE_BYTES = RB::TILE_BYTES, S = R + 1;
+  // With two queries per lane there are registers for two score buffers: the MFMAs of a sub-tile then stand beside the
+  // sums of the one before.
+  constexpr bool PIPE = R == 1;
+  static_assert(KB % 2 == 0, "the two score buffers alternate over the sub-tiles of a tile");
   constexpr float SAFE = 0x1p40f;  // largest partial row sum against the present reference; its square stays in range
   rb.issue_k_at(Kres, 0, 0);
   using L = SimilarityLds<D, R>;
   constexpr int FIRST = L::PARTNER_IN_LDS ? 1 : 0;  // first query in registers
   using Operand = typename RB::Operand;
+  using Scores = f32x16[S];
   Operand q[S][DS];
   Operand *const partner_q = reinterpret_cast<Operand *>(rb.lds + L::PARTNER_OFF) + rb.wave * DS * 64 + rb.lane;
   if constexpr (L::PARTNER_IN_LDS) {
@@ -180,84 +190,81 @@ __device__ __forceinline__ SimilaritySums<D, R> similarity_pass(
     if (i > 0) run_dot(i) = 0.f;
     mid.l[i] = mid.sq[i] = mid.dot[i] = 0.f;
   }
-  for (int c = 0; c < nbk; ++c) {
-    wait_vmem<0>();
-    __syncthreads();  // tile c has landed for every wave; everyone is done with the other buffer
-    if (c + 1 < nbk) rb.issue_k_at(Kres, c + 1, ((c + 1) & 1) * TILE_BYTES);
-    const char *const tile = rb.ldsK + (c & 1) * TILE_BYTES;
-#pragma unroll 1
-    for (int kb = 0; kb < KB; ++kb) {
-      const char *const kbuf = tile + kb * 32 * ROWB;
-      f32x16 s[S];
+  // S of one 32-key sub-tile of the K tile at `tile`
+  auto multiply = [&](const char *tile, int kb, Scores &s) {
+    const char *const kbuf = tile + kb * 32 * ROWB;
 #pragma unroll
-      for (int i = 0; i < S; ++i)
+    for (int i = 0; i < S; ++i)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) s[i][v] = 0.f;
+      for (int v = 0; v < 16; ++v) s[i][v] = 0.f;
 #pragma unroll
-      for (int d = 0; d < DS; ++d) {
-        const Operand ka = *reinterpret_cast<const Operand *>(kbuf + (rb.k_addr0 ^ (d << 5)));
-        if constexpr (L::PARTNER_IN_LDS) s[0] = Bf16::mfma(ka, partner_q[d * 64], s[0]);
+    for (int d = 0; d < DS; ++d) {
+      const Operand ka = *reinterpret_cast<const Operand *>(kbuf + (rb.k_addr0 ^ (d << 5)));
+      if constexpr (L::PARTNER_IN_LDS) s[0] = Bf16::mfma(ka, partner_q[d * 64], s[0]);
 #pragma unroll
-        for (int i = FIRST; i < S; ++i) s[i] = Bf16::mfma(ka, q[i][d], s[i]);
-      }
-      float sc_t = sc;
-      if (ragged && c == nbk - 1) {  // keys >= N to -inf; the scale is applied up front, multiplier 1 from then on
-        int limit = N - c * SIM_BK - 32 * kb - 8 * rb.g;  // this lane's key offsets below `limit` exist
-        asm volatile("" : "+v"(limit));                   // keeps the comparisons inside this branch
+      for (int i = FIRST; i < S; ++i) s[i] = Bf16::mfma(ka, q[i][d], s[i]);
+    }
+  };
+  // keys >= N to -inf; the scale is applied up front, multiplier 1 from then on
+  auto mask_tail = [&](Scores &s, int kb) {
+    int limit = N - (nbk - 1) * SIM_BK - 32 * kb - 8 * rb.g;  // this lane's key offsets below `limit` exist
+    asm volatile("" : "+v"(limit));                             // keeps the comparisons inside this branch
 #pragma unroll
-        for (int i = 0; i < S; ++i)
+    for (int i = 0; i < S; ++i)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) s[i][v] = 16 * (v >> 3) + (v & 7) < limit ? s[i][v] * sc : -INFINITY;
-        sc_t = 1.0f;
-      }
-      SimilaritySums<D, R> part;
-      auto sum = [&]() {
+      for (int v = 0; v < 16; ++v) s[i][v] = 16 * (v >> 3) + (v & 7) < limit ? s[i][v] * sc : -INFINITY;
+    return 1.0f;
+  };
+  auto fold = [&](const Scores &s, float sc_t) {
+    SimilaritySums<D, R> part;
+    auto sum = [&]() {
 #pragma unroll
-        for (int i = 0; i < S; ++i) part.l[i] = part.sq[i] = part.dot[i] = 0.f;
+      for (int i = 0; i < S; ++i) part.l[i] = part.sq[i] = part.dot[i] = 0.f;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          float e[S];
-#pragma unroll
-          for (int i = 0; i < S; ++i) {
-            e[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i][v], sc_t, -m[i]));
-            part.l[i] += e[i];
-            part.sq[i] = __builtin_fmaf(e[i], e[i], part.sq[i]);
-            if (i > 0) part.dot[i] = __builtin_fmaf(e[i], e[0], part.dot[i]);
-          }
-        }
-      };
-      sum();
-      bool bad = false;
-#pragma unroll
-      for (int i = 0; i < S; ++i) bad |= !(part.l[i] < SAFE);
-      if (__any(bad)) {  // always on the first sub-tile, where the references are -inf
-        float alpha[S];
+      for (int v = 0; v < 16; ++v) {
+        float e[S];
 #pragma unroll
         for (int i = 0; i < S; ++i) {
-          float m_loc = sc_t >= 0.f ? -INFINITY : INFINITY;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) m_loc = sc_t >= 0.f ? fmaxf(m_loc, s[i][v]) : fminf(m_loc, s[i][v]);
-          // either half of the query's lanes out of range: both move
-          const bool move = !(max_with_other_half(part.l[i] < SAFE ? 0.f : 1.f) < 0.5f);
-          const float m_new = move ? fmaxf(m[i], max_with_other_half(m_loc * sc_t)) : m[i];
-          alpha[i] = move ? __builtin_amdgcn_exp2f(m[i] - m_new) : 1.f;  // 0 on the first sub-tile
-          m[i] = m_new;
-          run_l(i) *= alpha[i];
-          mid.l[i] *= alpha[i];
-          run_sq(i) *= alpha[i] * alpha[i];
-          mid.sq[i] *= alpha[i] * alpha[i];
-          if (i > 0) run_dot(i) *= alpha[i] * alpha[0];
-          if (i > 0) mid.dot[i] *= alpha[i] * alpha[0];
+          e[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i][v], sc_t, -m[i]));
+          part.l[i] += e[i];
+          part.sq[i] = __builtin_fmaf(e[i], e[i], part.sq[i]);
+          if (i > 0) part.dot[i] = __builtin_fmaf(e[i], e[0], part.dot[i]);
         }
-        sum();
       }
+    };
+    sum();
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < S; ++i) bad |= !(part.l[i] < SAFE);
+    if (__any(bad)) {  // always on the first sub-tile, where the references are -inf
+      float alpha[S];
 #pragma unroll
       for (int i = 0; i < S; ++i) {
-        mid.l[i] += part.l[i];
-        mid.sq[i] += part.sq[i];
-        if (i > 0) mid.dot[i] += part.dot[i];
+        float m_loc = sc_t >= 0.f ? -INFINITY : INFINITY;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) m_loc = sc_t >= 0.f ? fmaxf(m_loc, s[i][v]) : fminf(m_loc, s[i][v]);
+        // either half of the query's lanes out of range: both move
+        const bool move = !(max_with_other_half(part.l[i] < SAFE ? 0.f : 1.f) < 0.5f);
+        const float m_new = move ? fmaxf(m[i], max_with_other_half(m_loc * sc_t)) : m[i];
+        alpha[i] = move ? __builtin_amdgcn_exp2f(m[i] - m_new) : 1.f;  // 0 on the first sub-tile
+        m[i] = m_new;
+        run_l(i) *= alpha[i];
+        mid.l[i] *= alpha[i];
+        run_sq(i) *= alpha[i] * alpha[i];
+        mid.sq[i] *= alpha[i] * alpha[i];
+        if (i > 0) run_dot(i) *= alpha[i] * alpha[0];
+        if (i > 0) mid.dot[i] *= alpha[i] * alpha[0];
       }
+      sum();
     }
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+      mid.l[i] += part.l[i];
+      mid.sq[i] += part.sq[i];
+      if (i > 0) mid.dot[i] += part.dot[i];
+    }
+  };
+  auto flush = [&](int c) {
     if (c % FLUSH == FLUSH - 1 || c == nbk - 1) {
 #pragma unroll
       for (int i = 0; i < S; ++i) {
@@ -267,6 +274,40 @@ __device__ __forceinline__ SimilaritySums<D, R> similarity_pass(
         mid.l[i] = mid.sq[i] = mid.dot[i] = 0.f;
       }
     }
+  };
+  Scores s[PIPE ? 2 : 1];
+  for (int c = 0; c < nbk; ++c) {
+    wait_vmem<0>();
+    __syncthreads();  // tile c has landed for every wave; everyone is done with the other buffer
+    if (c + 1 < nbk) rb.issue_k_at(Kres, c + 1, ((c + 1) & 1) * TILE_BYTES);
+    const char *const tile = rb.ldsK + (c & 1) * TILE_BYTES;
+    const bool tail = ragged && c == nbk - 1;
+    if constexpr (PIPE) {
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) {
+        Scores &now = s[kb & 1], &before = s[(kb & 1) ^ 1];
+        if (kb == 0 && c == 0) {
+          multiply(tile, kb, now);
+          continue;
+        }
+        float sc_t = sc;
+        if (kb > 0 && tail) sc_t = mask_tail(before, kb - 1);
+        multiply(tile, kb, now);
+        fold(before, sc_t);
+        if (kb == 0) flush(c - 1);
+      }
+    } else {
+#pragma unroll 1
+      for (int kb = 0; kb < KB; ++kb) {
+        multiply(tile, kb, s[0]);
+        fold(s[0], tail ? mask_tail(s[0], kb) : sc);
+      }
+      flush(c);
+    }
+  }
+  if constexpr (PIPE) {
+    fold(s[(KB - 1) & 1], ragged ? mask_tail(s[(KB - 1) & 1], KB - 1) : sc);
+    flush(nbk - 1);
   }
   SimilaritySums<D, R> total;
   float w[S];
