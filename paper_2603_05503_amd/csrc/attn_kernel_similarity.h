@@ -154,7 +154,11 @@ __device__ __forceinline__ SimilaritySums<D, R> similarity_pass(
   // sums of the one before.
   constexpr bool PIPE = R == 1;
   static_assert(KB % 2 == 0, "the two score buffers alternate over the sub-tiles of a tile");
-  constexpr float SAFE = 0x1p40f;  // largest partial row sum against the present reference; its square stays in range
+  // Largest partial row sum against the present reference.  The further the reference lags behind the logits, the larger
+  // the arguments of the exponentials that matter, and their rounding: with 2^40 the sums of rows whose first 64 keys
+  // lie 40 powers of two below the rest were off by 3.6e-7 (rms), with 2^12 by 2.2e-7, relative to the true maximum by
+  // 2.4e-7.  2^12 takes the same time; 2^8 up to 8 % more, because references then move in more steps.
+  constexpr float SAFE = 0x1p12f;
   rb.issue_k_at(Kres, 0, 0);
   using L = SimilarityLds<D, R>;
   constexpr int FIRST = L::PARTNER_IN_LDS ? 1 : 0;  // first query in registers

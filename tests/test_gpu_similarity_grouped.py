@@ -75,6 +75,56 @@ def test_grouped_matches_single_tokens(lib, H, rows, cols, text, D, kind):
     torch.testing.assert_close(out[0][0][0, -1].double(), want, rtol=1e-3, atol=1e-9)
 
 
+def _both_forms(lib, q, k, partner, cols, scale):
+    """Triples of the form without and with groups, which have the same bits."""
+    import torch
+
+    raw = lib.load_library()
+    _, H, N, D = q.shape
+    n = partner.numel()
+    out = []
+    for nbytes in (0, 36 * n + 16):
+        lists = torch.empty(max(nbytes, 1), dtype=torch.uint8, device="cuda")
+        triples = torch.full((1, H, n, 3), float("nan"), device="cuda")
+        score = torch.empty((1, H), device="cuda")
+        st = raw.calibatt_spatial_similarity_grouped(
+            q.data_ptr(), k.data_ptr(), 1, H, N, D, partner.data_ptr(), n, cols, scale, triples.data_ptr(),
+            lists.data_ptr() if nbytes else None, nbytes, score.data_ptr(),
+            C.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert st == 0
+        torch.cuda.synchronize()
+        out.append(triples)
+    assert torch.equal(out[0].view(torch.int32), out[1].view(torch.int32))
+    return out[0][0]
+
+
+def _triples64(q, k, partner, scale):
+    import torch
+
+    a = partner.long()
+    p = [torch.softmax((q[0, h].double() @ k[0, h].double().T) * scale, 1)[:a.numel()] for h in range(q.shape[1])]
+    return torch.stack([torch.stack([(x * x[a]).sum(1), (x ** 2).sum(1), (x[a] ** 2).sum(1)], 1) for x in p])
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_late_large_logits(lib, D):
+    """Logits that are exact in fp32 and whose first 64 keys lie some 40 powers of two below the rest.  Relative error of
+    the sums, rms: 2.6e-7 (D = 128) with sums relative to the true maximum and one addition after the other, which the
+    sums here stay below; an argument of an exponential that is 32 too large alone adds a rounding of 2^-20 / sqrt(3)."""
+    import torch
+
+    print(f"similarity late logits D={D}", flush=True)
+    H, N, cols = 4, 2048, 32
+    gen = torch.Generator(device="cuda").manual_seed(N + D)
+    q, k = (torch.randint(-3, 4, (1, H, N, D), device="cuda", generator=gen).float() for _ in range(2))
+    q[..., 0] = 4.0
+    k[..., 0] = torch.where(torch.arange(N, device="cuda") < 64, -72.0 if D == 128 else -50.0, 0.0)
+    q, k = q.to(torch.bfloat16), k.to(torch.bfloat16)
+    partner = torch.from_numpy(lib.anchor_partner(2, 32, cols, 5)).cuda()
+    got, want = _both_forms(lib, q, k, partner, cols, 1 / math.sqrt(D)), _triples64(q, k, partner, 1 / math.sqrt(D))
+    assert float((got.double() / want - 1).pow(2).mean().sqrt()) < 3e-7
+
+
 def test_grouped_refuses_what_does_not_fit(lib):
     raw = lib.load_library()
     one = C.c_void_p(16)
