@@ -42,6 +42,8 @@
 #pragma once
 #include "attn_kernel_2wg.h"
 
+#include <float.h>
+
 namespace calibatt_dev {
 
 struct SimilarityDims {
@@ -249,7 +251,8 @@ __device__ __forceinline__ SimilaritySums<D, R> similarity_pass(
         for (int v = 0; v < 16; ++v) m_loc = sc_t >= 0.f ? fmaxf(m_loc, s[i][v]) : fminf(m_loc, s[i][v]);
         // either half of the query's lanes out of range: both move
         const bool move = !(max_with_other_half(part.l[i] < SAFE ? 0.f : 1.f) < 0.5f);
-        const float m_new = move ? fmaxf(m[i], max_with_other_half(m_loc * sc_t)) : m[i];
+        // finite also where every logit so far is -inf, so that their exponentials are 0
+        const float m_new = move ? fmaxf(fmaxf(m[i], max_with_other_half(m_loc * sc_t)), -FLT_MAX) : m[i];
         alpha[i] = move ? __builtin_amdgcn_exp2f(m[i] - m_new) : 1.f;  // 0 on the first sub-tile
         m[i] = m_new;
         run_l(i) *= alpha[i];

@@ -125,6 +125,25 @@ def test_late_large_logits(lib, D):
     assert float((got.double() / want - 1).pow(2).mean().sqrt()) < 3e-7
 
 
+@pytest.mark.parametrize("n_out", [32, 40, 64, 200])
+@pytest.mark.parametrize("D", [64, 128])
+def test_first_keys_at_minus_infinity(lib, D, n_out):
+    """The logits of the first keys overflow to -inf: they have no mass, like keys that are not there."""
+    import torch
+
+    print(f"similarity -inf D={D} n_out={n_out}", flush=True)
+    H, N, cols = 2, 333, 37
+    gen = torch.Generator(device="cuda").manual_seed(N + D)
+    q, k = (torch.randn(1, H, N, D, device="cuda", generator=gen) for _ in range(2))
+    q[..., 0] = 2.0 ** 70
+    k[..., 0] = 0.0
+    k[:, :, :n_out, 0] = -2.0 ** 70
+    q, k = q.to(torch.bfloat16), k.to(torch.bfloat16)
+    partner = torch.from_numpy(lib.anchor_partner(1, 9, cols, 2)).cuda()
+    got, want = _both_forms(lib, q, k, partner, cols, 1 / math.sqrt(D)), _triples64(q, k, partner, 1 / math.sqrt(D))
+    torch.testing.assert_close(got.double(), want, rtol=1e-4, atol=1e-12)
+
+
 def test_grouped_refuses_what_does_not_fit(lib):
     raw = lib.load_library()
     one = C.c_void_p(16)
