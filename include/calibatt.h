@@ -418,7 +418,8 @@ int calibatt_spatial_similarity(const void *q, const void *k, int B, int H, int 
  *   lists      DEVICE, 16-byte aligned, contents free before and after the
  *              call; NULL = calibatt_spatial_similarity.  36 * n_tok + 16
  *              bytes; calibatt_similarity_lists_bytes writes that number, or 0
- *              where too little work is in the call for grouping to pay.
+ *              where too little work is in the call for grouping to pay on the
+ *              current device.
  * Errors: as calibatt_spatial_similarity; SHAPE (misaligned lists, a negative
  * lists_bytes), BUFFER_TOO_SMALL.
  */

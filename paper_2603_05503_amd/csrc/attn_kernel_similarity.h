@@ -25,9 +25,8 @@
 // operations in the same order whatever else the lane and the wave hold, so the
 // bits do not depend on how the tokens were grouped.
 //
-// Measured, 24 heads of 21 x 30 x 52 tokens, D = 128, five anchors, in turn on one box: 14.37 ms with every token
-// beside its own partner and one wavefront per head in the reduction, 10.49 ms as it is here (matrix pipes busy
-// 43 % of the cycles, vector ALU 72 %, at 1.9 GHz).
+// Measured, 24 heads of 21 x 30 x 52 tokens, D = 128, five anchors, in turn on one box: 13.87 ms with every token
+// beside its own partner over whole tiles and one wavefront per head in the reduction, 9.84 ms as it is here.
 //
 // Without groups, us with one score buffer (and before it, with whole tiles of 128 keys) -> with two: 210 units of 3840
 // keys, D = 128 95 (92) -> 81, D = 64 78 (73) -> 69; 480 units 148 (156) -> 141; 1800 units of 9600 keys 1299 (1427) ->
@@ -54,10 +53,13 @@ struct SimilarityDims {
 constexpr int SIM_BQ = 128;
 constexpr int SIM_BK = 64;
 constexpr int SIM_XCDS = 8;
-// Above this many units of 128 tokens the tokens are grouped.  Up to it every unit has a workgroup slot of its own
-// (two on each of 256 CUs) and the pass lasts as long as one unit: two rows of logits per lane, against three or
-// four with the tokens grouped.  Above it there is a second round: four rows against three.
-constexpr int SIM_GROUP_UNITS = 512;
+// The tokens are grouped where the pair form has more than SIM_GROUP_TURNS units of 128 tokens per CU and a head has more
+// than SIM_GROUP_TOKENS tokens.  Up to two units per CU even the best groups save a CU only one of four rows of logits,
+// which a single workgroup on it takes about as long for, and the lists cost 6-10 us: 16 heads of 3840 tokens, D = 128,
+// 135 us in pairs, 140 grouped; 18 heads 189 and 177.  In heads of a few units the groups save no whole unit: 200 heads of
+// 384 tokens 28 us in pairs, 38 grouped; 220 heads of 640 tokens 62 and 50.
+constexpr int SIM_GROUP_TURNS = 2;
+constexpr int SIM_GROUP_TOKENS = 512;
 
 // ---- lists of the grouped form -------------------------------------------------------------------
 // int32 words: [0..2] numbers of 2-token groups, 3-token groups and lone tokens, [4 ..] the 3-token
@@ -352,11 +354,10 @@ __device__ __forceinline__ bool similarity_unit(const SimilarityDims &p, int uni
 
 // Every token with its partner, without lists.
 template <int D>
-__global__ __launch_bounds__(SIM_BQ * 2, 2) void pair_similarity_kernel(
-    const uint16_t *__restrict__ gq, const uint16_t *__restrict__ gk, const int32_t *__restrict__ partner,
-    float *__restrict__ triples, const SimilarityDims p) {
+__device__ __forceinline__ void pair_similarity(char *lds, const uint16_t *__restrict__ gq,
+                                                const uint16_t *__restrict__ gk, const int32_t *__restrict__ partner,
+                                                float *__restrict__ triples, const SimilarityDims &p) {
   using RB = RowBlock<D, SIM_BQ, SIM_BK>;
-  extern __shared__ __attribute__((aligned(1024))) char lds[];  // two K tiles
   int bh, r;
   if (!similarity_unit(p, p.nbq, bh, r)) return;
   RB rb(lds);
@@ -368,6 +369,14 @@ __global__ __launch_bounds__(SIM_BQ * 2, 2) void pair_similarity_kernel(
       similarity_pass<D, 1>(rb, head_rsrc(gk + head_off, (uint32_t)p.N * RB::ROWB), gq + head_off, tok, p);
   if (tok_raw < p.n_tok && rb.g == 0)
     store_triple(triples + (size_t)bh * p.n_tok * 3, t, sums.dot[1], sums.sq[1], sums.sq[0]);
+}
+
+template <int D>
+__global__ __launch_bounds__(SIM_BQ * 2, 2) void pair_similarity_kernel(
+    const uint16_t *__restrict__ gq, const uint16_t *__restrict__ gk, const int32_t *__restrict__ partner,
+    float *__restrict__ triples, const SimilarityDims p) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];  // SimilarityLds<D, 1>::BYTES
+  pair_similarity<D>(lds, gq, gk, partner, triples, p);
 }
 
 template <int D, int R>
@@ -420,25 +429,35 @@ __device__ __forceinline__ void grouped_similarity(char *lds, const uint16_t *__
   }
 }
 
-// Three tokens per group cost fewer rows of logits, two waste fewer lanes on a short last group and are
-// smaller units of work: the form with the fewer rows of logits on the longest queue is taken, counting
-// whole rounds of the `slots` workgroups an XCD holds at a time.
+// Three tokens per group cost the fewest rows of logits, two waste fewer lanes on a short last group and are smaller
+// units of work, tokens that share nothing are best off in pairs: the form with the fewest rows of logits on the CU that
+// has the most to do is taken, two tokens before three (at D = 128 those keep the partner in LDS) and groups before pairs
+// where that is the same.  `cus`: compute units of an XCD.  D = 128, ms in pairs / twos / threes (rows on the busiest CU):
+//   24 heads of 21 x 30 x 52 tokens, five anchors   12.64 (48) /  9.84 (36) / 10.00 (36);  D = 64  9.39 / 7.41 / 7.23
+//   5 heads of 21 x 45 x 80 tokens, three anchors   14.81 (24) / 11.71 (18) / 10.73 (16)
+//   24 heads of 8 x 30 x 40 tokens, five anchors     1.23 (16) /  0.99 (12) /  1.00 (12), random partners 1.22 / 1.90 / 2.55
+//   18 heads of 4 x 30 x 32 tokens, five anchors    0.196 (6)  / 0.203 (6)  / 0.176 (4)
 template <int D>
 __global__ __launch_bounds__(SIM_BQ * 2, 2) void grouped_similarity_kernel(
-    const uint16_t *__restrict__ gq, const uint16_t *__restrict__ gk, int32_t *__restrict__ lists,
-    float *__restrict__ triples, const SimilarityDims p, int slots) {
-  extern __shared__ __attribute__((aligned(1024))) char lds[];  // two K tiles
+    const uint16_t *__restrict__ gq, const uint16_t *__restrict__ gk, const int32_t *__restrict__ partner,
+    int32_t *__restrict__ lists, float *__restrict__ triples, const SimilarityDims p, int cus) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];  // SimilarityLds<D, 3>::BYTES
   const int n2 = lists[0], n3 = lists[1], n_lone = lists[2];
-  auto rows = [&](int groups, int R) {
-    const long long lone = (n_lone + R) / (R + 1);
-    const long long units = (long long)p.B * p.H * ((groups + SIM_BQ - 1) / SIM_BQ + (lone + SIM_BQ - 1) / SIM_BQ);
-    const long long longest = (units + SIM_XCDS - 1) / SIM_XCDS;
-    return (longest + slots - 1) / slots * (R + 1);
+  auto rows = [&](int units_per_head, int queries) {
+    const long long units = (long long)p.B * p.H * units_per_head;
+    return ((units + SIM_XCDS - 1) / SIM_XCDS + cus - 1) / cus * queries;
   };
-  if (rows(n3, 3) <= rows(n2, 2))
-    grouped_similarity<D, 3>(lds, gq, gk, lists, triples, p, n3, n_lone);
-  else
+  auto grouped_rows = [&](int groups, int R) {
+    const int lone = (n_lone + R) / (R + 1);
+    return rows((groups + SIM_BQ - 1) / SIM_BQ + (lone + SIM_BQ - 1) / SIM_BQ, R + 1);
+  };
+  const long long rows3 = grouped_rows(n3, 3), rows2 = grouped_rows(n2, 2), rows1 = rows(p.nbq, 2);
+  if (rows1 < min(rows2, rows3))
+    pair_similarity<D>(lds, gq, gk, partner, triples, p);
+  else if (rows2 <= rows3)
     grouped_similarity<D, 2>(lds, gq, gk, lists, triples, p, n2, n_lone);
+  else
+    grouped_similarity<D, 3>(lds, gq, gk, lists, triples, p, n3, n_lone);
 }
 
 // score[b*H + h] = mean over the n_tok / row_len spatial rows of the row's cosine.  A half wavefront adds the

@@ -323,6 +323,19 @@ int launch_energy_onepass(const uint16_t *q, const uint16_t *k, float *energy, c
   return launch(block_energy_onepass_kernel<D, BQ, BK, BQ>, EnergyOnePass<D, BQ, BK, BQ>{});
 }
 
+// compute units of the current device, looked up once
+int device_cus(int &cus) {
+  static DevInfo info;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return CALIBATT_ERR_LAUNCH;
+  cus = info.slots[dev].load(std::memory_order_acquire);
+  if (cus > 0) return CALIBATT_OK;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+    return CALIBATT_ERR_LAUNCH;
+  info.slots[dev].store(cus, std::memory_order_release);
+  return CALIBATT_OK;
+}
+
 template <int D>
 int launch_similarity(const uint16_t *q, const uint16_t *k, const int32_t *partner, float *triples, float *score,
                       int32_t *lists, const SimilarityDims &p, hipStream_t stream) {
@@ -347,8 +360,10 @@ int launch_similarity(const uint16_t *q, const uint16_t *k, const int32_t *partn
     if (int st = launch_kernel(similarity_group_kernel, (unsigned)((p.n_tok + 255) / 256), 256, 0, stream, partner,
                                lists, p.N, p.n_tok, p.row_len))
       return st;
-    if (int st = launch_kernel(grouped_similarity_kernel<D>, (unsigned)grid, SIM_BQ * 2, SMEM, stream, q, k, lists,
-                               triples, p, std::max(slots / SIM_XCDS, 1)))
+    int cus = 0;
+    if (int st = device_cus(cus)) return st;
+    if (int st = launch_kernel(grouped_similarity_kernel<D>, (unsigned)grid, SIM_BQ * 2, SMEM, stream, q, k, partner,
+                               lists, triples, p, std::max(cus / SIM_XCDS, 1)))
       return st;
   }
   return launch_kernel(similarity_reduce_kernel, (unsigned)(p.B * p.H), SIM_REDUCE_THREADS, 0, stream,
@@ -389,8 +404,10 @@ extern "C" int calibatt_spatial_similarity(const void *q, const void *k, int B, 
 extern "C" int calibatt_similarity_lists_bytes(int B, int H, int n_tok, int64_t *bytes) {
   if (!bytes) return CALIBATT_ERR_NULL;
   if (B <= 0 || H <= 0 || n_tok <= 0) return CALIBATT_ERR_SHAPE;
+  int cus = 0;
+  if (int st = device_cus(cus)) return st;
   const long long units = (long long)B * H * ((n_tok + SIM_BQ - 1) / SIM_BQ);
-  *bytes = units > SIM_GROUP_UNITS ? SimilarityLists::bytes(n_tok) : 0;
+  *bytes = units > (long long)SIM_GROUP_TURNS * cus && n_tok > SIM_GROUP_TOKENS ? SimilarityLists::bytes(n_tok) : 0;
   return CALIBATT_OK;
 }
 

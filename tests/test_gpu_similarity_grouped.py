@@ -1,5 +1,5 @@
-"""The grouped form of the spatial similarity (tokens that share their partner computed together) against the
-form that takes one token per lane: the same bits, for every way the tokens can fall into groups."""
+"""The grouped call of the spatial similarity (tokens that share their partner computed together) against the form that
+takes one token per lane: the same bits, for every way the tokens can fall into groups of three, of two, and pairs."""
 import ctypes as C
 import math
 
@@ -21,30 +21,66 @@ def _partner(kind, lib, rows, cols, rng):
         return (rng.integers(0, 3, n) * (n // 3)).astype(np.int32)
     if kind == "one":
         return np.full(n, n // 2, np.int32)
+    if kind.startswith("period"):  # of p rows the first p - 1 have the first one as their partner, the last is its own
+        p, row = int(kind[6:]), np.arange(n) // cols
+        return (np.arange(n) - np.where(row % p == p - 1, 0, row % p * cols)).astype(np.int32)
+    if kind.startswith("runs"):  # runs of these lengths, with a partner inside, in another column or outside [0, n)
+        out = np.empty((rows, cols), np.int32)
+        for x in range(cols):
+            y = 0
+            while y < rows:
+                length = int(rng.choice([int(c) for c in kind[4:]]))
+                inside = (y + int(rng.integers(min(length, rows - y)))) * cols + x
+                out[y:y + length, x] = rng.choice([inside, rng.integers(n), n + 2])
+                y += length
+        return out.reshape(-1)
     assert kind == "wild"  # clamped to [0, N)
     return rng.choice(np.array([-5, 0, n - 1, n + 3, 1 << 30], np.int32), n).astype(np.int32)
 
 
-# heads, rows, cols, text tokens, D, partner map.  Many heads of one column block: the three-token form
-# (300 units of it against 600 of the two-token form); otherwise the two-token form.
+# heads, rows, cols, text tokens, D, partner map, tokens per group in the form that the device chooses (1: pairs)
 CASES = [
-    (1, 1, 1, 0, 64, "self"),
-    (2, 7, 5, 3, 128, "anchors2"),
-    (1, 9, 43, 0, 128, "self"),
-    (1, 64, 3, 1, 64, "one"),
-    (1, 130, 3, 7, 128, "anchors1"),  # runs longer than a segment of 64 rows
-    (2, 13, 31, 64, 128, "random"),
-    (2, 13, 31, 0, 64, "few"),
-    (1, 200, 1, 0, 128, "few"),
-    (1, 6, 50, 11, 64, "wild"),
-    (300, 24, 16, 5, 128, "anchors1"),
-    (300, 24, 16, 0, 64, "anchors1"),
-    (300, 25, 16, 0, 128, "one"),
+    (1, 1, 1, 0, 64, "self", 1),
+    (2, 7, 5, 3, 128, "anchors2", 1),
+    (300, 9, 43, 0, 128, "self", 3),
+    (300, 9, 43, 2, 64, "self", 3),
+    (200, 64, 11, 1, 64, "one", 3),
+    (300, 130, 3, 7, 128, "anchors1", 2),  # runs longer than a segment of 64 rows
+    (256, 130, 5, 0, 64, "anchors1", 3),
+    (300, 13, 31, 64, 128, "random", 1),
+    (300, 13, 31, 0, 64, "few", 1),
+    (300, 6, 70, 11, 64, "wild", 1),
+    (300, 24, 16, 5, 128, "anchors1", 3),
+    (300, 24, 16, 0, 64, "anchors1", 3),
+    (300, 25, 16, 0, 128, "one", 2),
+    (100, 47, 33, 3, 128, "runs123456789", 2),
+    (256, 47, 33, 0, 64, "runs3369", 3),
+    (256, 47, 33, 3, 128, "runs34569", 3),
+    (100, 47, 33, 3, 128, "runs24", 2),
+    (100, 47, 33, 0, 64, "runs24", 2),
+    (100, 50, 33, 0, 128, "period5", 3),  # groups of three and lone tokens
+    (100, 49, 33, 1, 64, "period5", 3),
+    (256, 49, 33, 1, 128, "period4", 2),  # groups of two and lone tokens
+    (256, 48, 33, 0, 64, "period4", 2),
 ]
 
 
-@pytest.mark.parametrize("H,rows,cols,text,D,kind", CASES)
-def test_grouped_matches_single_tokens(lib, H, rows, cols, text, D, kind):
+def _form(lists, H, n, cus):
+    """Tokens per group in the form that the device takes, from the numbers of groups that it left behind."""
+    n2, n3, lone = np.frombuffer(lists[:12].cpu().numpy().tobytes(), np.int32).tolist()
+
+    def up(a, b):
+        return -(-a // b)
+
+    def rows(groups, lanes, queries):
+        return up(up(H * (up(groups, 128) + up(up(lone, lanes), 128)), 8), cus) * queries
+
+    rows1, rows2, rows3 = up(up(H * up(n, 128), 8), cus) * 2, rows(n2, 3, 3), rows(n3, 4, 4)
+    return 1 if rows1 < min(rows2, rows3) else 2 if rows2 <= rows3 else 3
+
+
+@pytest.mark.parametrize("H,rows,cols,text,D,kind,form", CASES)
+def test_grouped_matches_single_tokens(lib, H, rows, cols, text, D, kind, form):
     import torch
 
     print(f"grouped similarity H={H} rows={rows} cols={cols} text={text} D={D} {kind}", flush=True)
@@ -65,6 +101,7 @@ def test_grouped_matches_single_tokens(lib, H, rows, cols, text, D, kind):
         assert st == 0
         torch.cuda.synchronize()
         out.append((triples, score))
+    assert _form(lists, H, n, torch.cuda.get_device_properties(0).multi_processor_count // 8) == form
     assert bool(torch.isfinite(out[0][0]).all())
     assert torch.equal(out[0][0].view(torch.int32), out[1][0].view(torch.int32))
     assert torch.equal(out[0][1].view(torch.int32), out[1][1].view(torch.int32))
@@ -145,6 +182,8 @@ def test_first_keys_at_minus_infinity(lib, D, n_out):
 
 
 def test_grouped_refuses_what_does_not_fit(lib):
+    import torch
+
     raw = lib.load_library()
     one = C.c_void_p(16)
     f = raw.calibatt_spatial_similarity_grouped
@@ -152,8 +191,10 @@ def test_grouped_refuses_what_does_not_fit(lib):
     assert f(one, one, 1, 1, 8, 64, one, 8, 2, 1.0, one, one, -1, one, None) == -2
     assert f(one, one, 1, 1, 8, 64, one, 8, 2, 1.0, one, one, 36 * 8 + 15, one, None) == -7
     n = C.c_int64(0)
-    assert raw.calibatt_similarity_lists_bytes(1, 1, 8, C.byref(n)) == 0 and n.value == 0
-    assert raw.calibatt_similarity_lists_bytes(1, 513, 100, C.byref(n)) == 0 and n.value == 3616
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for H, n_tok, want in ((1, 8, 0), (2 * cus, 100, 0), (2 * cus + 1, 100, 0), (2 * cus, 512, 0), (2 * cus, 513, 18484),
+                           (2, 128 * cus, 0), (2, 128 * cus + 1, 36 * (128 * cus + 1) + 16)):
+        assert raw.calibatt_similarity_lists_bytes(1, H, n_tok, C.byref(n)) == 0 and n.value == want
 
 
 def test_temporaries_belong_to_the_stream_of_the_call(lib):
