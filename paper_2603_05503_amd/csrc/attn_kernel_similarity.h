@@ -158,10 +158,13 @@ __device__ __forceinline__ SimilaritySums<D, R> similarity_pass(
   // sums of the one before.
   constexpr bool PIPE = R == 1;
   static_assert(KB % 2 == 0, "the two score buffers alternate over the sub-tiles of a tile");
-  // Largest partial row sum against the present reference.  The further the reference lags behind the logits, the larger
-  // the arguments of the exponentials that matter, and their rounding: with 2^40 the sums of rows whose first 64 keys
-  // lie 40 powers of two below the rest were off by 3.6e-7 (rms), with 2^12 by 2.2e-7, relative to the true maximum by
-  // 2.4e-7.  2^12 takes the same time; 2^8 up to 8 % more, because references then move in more steps.
+  // A query's reference is put SLACK above its largest logit so far and moves when a partial row sum against it reaches
+  // SAFE, some 20 powers of two later; the arguments of the exponentials that matter, and so their rounding, stay as
+  // small as those around a reference that lags by 10.  Error of the sums of rows whose first 64 keys lie 40 powers of two
+  // below the rest (rms, D = 64 / 128) and time on activations with a positional component (30 heads of 2400 tokens, D =
+  // 128): relative to the true maximum 2.4 / 2.6e-7; no slack and 2^40 3.6 / 3.4e-7, 119 us; no slack and 2^12 2.2 /
+  // 2.3e-7, 154 us (references move in many steps); 2^10 and 2^12 2.1 / 2.3e-7, 119 us.
+  constexpr float SLACK = 10.f;
   constexpr float SAFE = 0x1p12f;
   rb.issue_k_at(Kres, 0, 0);
   using L = SimilarityLds<D, R>;
@@ -254,7 +257,7 @@ __device__ __forceinline__ SimilaritySums<D, R> similarity_pass(
         // either half of the query's lanes out of range: both move
         const bool move = !(max_with_other_half(part.l[i] < SAFE ? 0.f : 1.f) < 0.5f);
         // finite also where every logit so far is -inf, so that their exponentials are 0
-        const float m_new = move ? fmaxf(fmaxf(m[i], max_with_other_half(m_loc * sc_t)), -FLT_MAX) : m[i];
+        const float m_new = move ? fmaxf(fmaxf(m[i], max_with_other_half(m_loc * sc_t) + SLACK), -FLT_MAX) : m[i];
         alpha[i] = move ? __builtin_amdgcn_exp2f(m[i] - m_new) : 1.f;  // 0 on the first sub-tile
         m[i] = m_new;
         run_l(i) *= alpha[i];
