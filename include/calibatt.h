@@ -491,9 +491,10 @@ int calibatt_block_energy(const void *q, const void *k, float *energy, int B, in
  * Large calls run with two query blocks and two slices per workgroup (so 1024
  * slices are two such workgroups on each of 256 CUs); the energies have the
  * same bits whatever the size of the workspace and the number of heads.
- * calibatt_block_energy_onepass_queries (host) writes how many queries a
- * workgroup of such a call takes on the current device: block_q, or twice as
- * many.
+ * calibatt_block_energy_onepass_form (host) writes the form that such a call
+ * takes on the current device: CALIBATT_ENERGY_ONE_BLOCK per workgroup,
+ * CALIBATT_ENERGY_TWO_BLOCKS, or CALIBATT_ENERGY_OVERLAPPED (128 queries; the
+ * products of a step beside the sums of the one before).
  * Other arguments, supported shapes and errors as calibatt_block_energy, plus
  * BUFFER_TOO_SMALL (less than one slice).
  */
@@ -501,8 +502,9 @@ int calibatt_block_energy_workspace_bytes(int N, int block_q, int block_k, int64
 int calibatt_block_energy_onepass(const void *q, const void *k, float *energy, int B, int H, int N, int D,
                                   int block_q, int block_k, float scale, void *workspace,
                                   int64_t workspace_bytes, void *stream);
-int calibatt_block_energy_onepass_queries(int B, int H, int N, int D, int block_q, int block_k,
-                                          int64_t workspace_bytes, int32_t *queries);
+enum { CALIBATT_ENERGY_ONE_BLOCK = 0, CALIBATT_ENERGY_TWO_BLOCKS = 1, CALIBATT_ENERGY_OVERLAPPED = 2 };
+int calibatt_block_energy_onepass_form(int B, int H, int N, int D, int block_q, int block_k,
+                                       int64_t workspace_bytes, int32_t *form);
 
 /*
  * calibatt_select_blocks (Eq. 6): for each of n_rows block-rows of nbk

@@ -5,6 +5,9 @@ torch is used for device buffers and streams.  There is no fallback: if the
 library has not been built, loading fails with an error.
 """
 from .binding import (  # noqa: F401
+    ENERGY_ONE_BLOCK,
+    ENERGY_OVERLAPPED,
+    ENERGY_TWO_BLOCKS,
     KERNEL_AUTO,
     KERNEL_INTERLEAVED,
     KERNEL_TWO_WORKGROUPS,
@@ -18,7 +21,7 @@ from .binding import (  # noqa: F401
     anchor_map,
     anchor_partner,
     block_energy,
-    block_energy_onepass_queries,
+    block_energy_onepass_form,
     block_energy_workspace_bytes,
     compile_pattern,
     encode_intervals,

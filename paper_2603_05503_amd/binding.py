@@ -30,6 +30,7 @@ class _CFwdOptions(C.Structure):
 
 
 KERNEL_AUTO, KERNEL_TWO_WORKGROUPS, KERNEL_INTERLEAVED = 0, 1, 2
+ENERGY_ONE_BLOCK, ENERGY_TWO_BLOCKS, ENERGY_OVERLAPPED = 0, 1, 2  # forms of the one-pass block energies
 
 
 class _CPattern(C.Structure):
@@ -159,8 +160,8 @@ def load_library():
     lib.calibatt_anchor_split_plan.argtypes = [C.c_int] * 5 + [C.POINTER(C.c_int32), C.POINTER(C.c_int64)]
     lib.calibatt_block_energy_workspace_bytes.restype = C.c_int
     lib.calibatt_block_energy_workspace_bytes.argtypes = [C.c_int, C.c_int, C.c_int, C.POINTER(C.c_int64)]
-    lib.calibatt_block_energy_onepass_queries.restype = C.c_int
-    lib.calibatt_block_energy_onepass_queries.argtypes = [C.c_int] * 6 + [C.c_int64, C.POINTER(C.c_int32)]
+    lib.calibatt_block_energy_onepass_form.restype = C.c_int
+    lib.calibatt_block_energy_onepass_form.argtypes = [C.c_int] * 6 + [C.c_int64, C.POINTER(C.c_int32)]
     lib.calibatt_block_energy_onepass.restype = C.c_int
     lib.calibatt_block_energy_onepass.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p] + [C.c_int] * 6 + [
         C.c_float, C.c_void_p, C.c_int64, C.c_void_p]
@@ -546,13 +547,13 @@ def block_energy_workspace_bytes(N: int, block_q: int, block_k: int) -> int:
     return n.value
 
 
-def block_energy_onepass_queries(B: int, H: int, N: int, D: int, block_q: int, block_k: int, workspace_bytes: int) -> int:
-    """calibatt_block_energy_onepass_queries: queries per workgroup on the current device, block_q or twice as many."""
+def block_energy_onepass_form(B: int, H: int, N: int, D: int, block_q: int, block_k: int, workspace_bytes: int) -> int:
+    """calibatt_block_energy_onepass_form: the form of such a call on the current device, ENERGY_*."""
     lib = load_library()
     n = C.c_int32(0)
-    st = lib.calibatt_block_energy_onepass_queries(B, H, N, D, block_q, block_k, workspace_bytes, C.byref(n))
+    st = lib.calibatt_block_energy_onepass_form(B, H, N, D, block_q, block_k, workspace_bytes, C.byref(n))
     if st != 0:
-        raise CalibattError(st, "calibatt_block_energy_onepass_queries")
+        raise CalibattError(st, "calibatt_block_energy_onepass_form")
     return n.value
 
 

@@ -155,7 +155,7 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) void block_energy_kern
 // holds together look for the tile's maximum, move their references and sum
 // again.  The sums stay below 2^100 per tile, so the row sum cannot overflow.
 //
-// Two forms with the same bits: the same additions in the same order in a
+// All forms give the same bits: the same additions in the same order in a
 // lane, the same 32 rows that move their references together and whose masses
 // are added as one partial.  Which one runs, on how many workgroups, is a
 // matter of speed alone.
@@ -329,19 +329,21 @@ __global__ __launch_bounds__(QW * 2, 2) void block_energy_onepass_kernel(
   }
 }
 
-// Wide form: a wavefront owns two panels of 32 queries, four of them make a workgroup of two query blocks of 128.
+// Overlapped form: a wavefront owns one or two panels of 32 queries, four of them make a workgroup.
 //
 // What bounds the pass: the vector ALU (FMA, exponential and addition per logit) beside the matrix cores; a 32 x 32
 // sub-tile is 8 MFMAs and 48 vector instructions per wavefront.  So the wavefront's stream is one step per 32 keys in
 // which the MFMAs of step j and the vector instructions of step j - 1 are independent (two score buffers); with two
 // panels a K operand read from LDS feeds two MFMAs, and a K tile loaded into LDS serves 256 queries.  The order inside a
-// step is left to the compiler.
+// step is left to the compiler.  With one panel a lone workgroup on its CU is faster than the narrow form's (522 units of
+// 33325 keys, D = 128: 852 -> 780 us), two on a CU, which overlap one another anyway, are slower (480 units of 2560 keys
+// 47.5 -> 50.3 us).
 //
 // The scores of a tile are gone when its sum turns out to be out of range; they are then multiplied again from K in
 // memory.  That is rare, as the references start at the maximum of the first tile, which is multiplied once more for it.
-template <int D, int BK>
+template <int D, int BQ, int BK, int PANELS>
 struct EnergyPanels {
-  static constexpr int BQ = 128, PANELS = 2, NW = 4, BLOCKS = 2, QUERIES = 256;
+  static constexpr int NW = 4, QUERIES = NW * 32 * PANELS, BLOCKS = QUERIES / BQ;
   using RB = RowBlock<D, NW * 32, BK>;
   // float[NW * PANELS][nbk] partial sums over the second K buffer, which the next unit's loads reach behind a barrier
   static constexpr int PART_OFF = RB::TILE_BYTES;
@@ -351,14 +353,14 @@ struct EnergyPanels {
   }
 };
 
-template <int D, int BK>
+template <int D, int BQ, int BK, int PANELS>
 __global__ __launch_bounds__(256, 2) void block_energy_panels_kernel(
     const uint16_t *__restrict__ gq, const uint16_t *__restrict__ gk, float *__restrict__ gE,
     float *__restrict__ workspace, const EnergyOnePassDims pp) {
-  using L = EnergyPanels<D, BK>;
+  using L = EnergyPanels<D, BQ, BK, PANELS>;
   using RB = typename L::RB;
-  constexpr int PANELS = L::PANELS, NT = RB::NT, KB = RB::KB, DS = RB::DS, ROWB = RB::ROWB, BQ = L::BQ, QW = L::QUERIES;
-  constexpr int TILE_BYTES = RB::TILE_BYTES;
+  constexpr int NT = RB::NT, KB = RB::KB, DS = RB::DS, ROWB = RB::ROWB, QW = L::QUERIES;
+  constexpr int TILE_BYTES = RB::TILE_BYTES, LAST = PANELS - 1;
   static_assert(KB % 2 == 0, "the two score buffers alternate over the steps of a tile");
   using Operand = typename RB::Operand;
   using Scores = f32x16[PANELS];
@@ -369,7 +371,9 @@ __global__ __launch_bounds__(256, 2) void block_energy_panels_kernel(
   RB rb(lds);
   const int N = p.N, nbk = p.nbk;
   float *const part = reinterpret_cast<float *>(lds + L::PART_OFF);
-  float *const mine = workspace + (size_t)blockIdx.x * nbk * QW + rb.wave * 64 + rb.lane;  // + c * QW: row l32 of panel g
+  // this lane's values, + c * QW: row l32 of panel g of every block c, or of the only panel and every second block
+  const int half = PANELS == 1 ? 0 : rb.g;
+  float *const mine = workspace + (size_t)blockIdx.x * nbk * QW + rb.wave * 32 * PANELS + 32 * half + rb.l32;
   const float sc = p.scale_log2e;
   const bool ragged = (N % BK) != 0;
 
@@ -380,7 +384,7 @@ __global__ __launch_bounds__(256, 2) void block_energy_panels_kernel(
     const size_t head_off = (size_t)bh * (size_t)N * D;
     const uint16_t *const head_k = gk + head_off;
     const u32x4 Kres = head_rsrc(head_k, (uint32_t)N * ROWB);
-    const int row0 = r0 * BQ + rb.wave * 64 + rb.l32;  // this lane's row of panel 0; of panel 1: + 32
+    const int row0 = r0 * BQ + rb.wave * 32 * PANELS + rb.l32;  // this lane's row of panel 0; of panel 1: + 32
 
     // both K buffers are free: every wave is behind the barrier that followed the last tile of the previous unit
     rb.issue_k_at(Kres, 0, 0);
@@ -449,14 +453,14 @@ __global__ __launch_bounds__(256, 2) void block_energy_panels_kernel(
 #pragma unroll
         for (int v = 0; v < 16; ++v) psum[i] += __builtin_amdgcn_exp2f(__builtin_fmaf(src[i][v], sc_t, -m_run[i]));
       // keeps the sums in their step: the compiler would move those of a whole tile behind its last MFMA
-      asm volatile("" : "+v"(psum[0]), "+v"(psum[1]));
+      asm volatile("" : "+v"(psum[0]), "+v"(psum[LAST]));
     };
     // tile c is summed: its logarithm (-inf when the mass underflowed: the block then counts as 0) to the workspace
     auto finish_tile = [&](int c, Scores &tmp) {
       bool moves[PANELS];
 #pragma unroll
       for (int i = 0; i < PANELS; ++i) moves[i] = __any(!(psum[i] < ENERGY_SAFE));
-      if (moves[0] || moves[1]) {
+      if (moves[0] || moves[LAST]) {
         const bool tail = ragged && c == nbk - 1;
         float sum_before[PANELS];
 #pragma unroll
@@ -491,7 +495,7 @@ __global__ __launch_bounds__(256, 2) void block_energy_panels_kernel(
         l_run[i] += psum[i];
         psum[i] = 0.f;
       }
-      mine[(size_t)c * QW] = rb.g ? t[1] : t[0];
+      if (PANELS == 2 || (c & 1) == rb.g) mine[(size_t)c * QW] = half ? t[LAST] : t[0];
     };
 
     Scores s[2];
@@ -540,20 +544,23 @@ __global__ __launch_bounds__(256, 2) void block_energy_panels_kernel(
     wait_vmem<0>();
     __syncthreads();  // every wave is done with the K buffers
     // this lane's own values back, 16 loads in flight at a time, read at L2, where the stores went; each half of the
-    // wave sums the rows of its panel
-    const float my_lse = rb.g ? lse2[1] : lse2[0];
-    const bool my_row = row0 + 32 * rb.g < N;
-    for (int c0 = 0; c0 < nbk; c0 += 16) {
+    // wave sums the 32 rows of its panel, or those of the only one for every second block
+    const float my_lse = half ? lse2[LAST] : lse2[0];
+    const bool my_row = row0 + 32 * half < N;
+    constexpr int STEP = PANELS == 1 ? 2 : 1;  // blocks c that the wave takes per load
+    for (int c0 = 0; c0 < nbk; c0 += 16 * STEP) {
       float t[16];
 #pragma unroll
-      for (int j = 0; j < 16; ++j)
-        t[j] = c0 + j < nbk
-                   ? __hip_atomic_load(mine + (size_t)(c0 + j) * QW, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                   : -INFINITY;
+      for (int j = 0; j < 16; ++j) {
+        const int c = c0 + STEP * j + (STEP == 2 ? rb.g : 0);
+        t[j] = c < nbk ? __hip_atomic_load(mine + (size_t)c * QW, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                       : -INFINITY;
+      }
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
+        const int c = c0 + STEP * j + (STEP == 2 ? rb.g : 0);
         const float e = half_wave_sum(my_row ? __builtin_amdgcn_exp2f(t[j] - my_lse) : 0.f);
-        if (rb.l32 == 0 && c0 + j < nbk) part[(rb.wave * PANELS + rb.g) * nbk + c0 + j] = e;
+        if (rb.l32 == 0 && c < nbk) part[(rb.wave * PANELS + half) * nbk + c] = e;
       }
     }
     __syncthreads();

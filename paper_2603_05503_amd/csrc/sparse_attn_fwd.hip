@@ -268,22 +268,27 @@ long long energy_turns(const EnergyOnePassDims &pp, int cus) {
   return longest;
 }
 
-// Chooses and plans the form: with two query blocks per workgroup (`wide`) where its turns, longer by a measured
-// factor, take less time than those of the narrow form.  The factors are the times of full rounds at 5120 tokens,
-// D = 128 / 64, us per key block and workgroup of a CU:
-//  - blocks of 128, two panels per wavefront: 1.10 -> 1.98 with key blocks of 128, 1.10 -> 2.08 of 64; D = 64: 0.77 ->
-//    1.41 and 0.78 -> 1.56, twice as long: not built.  Below one workgroup per CU the panels gain nothing;
+// Chooses and plans the form (CALIBATT_ENERGY_*).  Two query blocks per workgroup where its turns, longer by a measured
+// factor, take less time than those of the narrow form.  The factors are the times of full rounds at 5120 tokens, D = 128 /
+// 64, us per key block and workgroup of a CU:
+//  - blocks of 128, two panels per wavefront: 1.10 -> 1.98 with key blocks of 128, 1.10 -> 2.08 of 64 (in calls of
+//    milliseconds 2.2); D = 64: 0.77 -> 1.41 and 0.78 -> 1.56, twice as long: not built.  Below one workgroup per CU the
+//    panels gain nothing;
 //  - blocks of 64, four wavefronts instead of two: 0.87 -> 1.13 with key blocks of 128 at D = 128.  Elsewhere LDS does
 //    not keep the narrow form's wavefronts down, and the factor (1.5) decides between calls that do not fill the device:
 //    both forms have as many wavefronts in flight in full rounds and the wide one reads K half as often (N = 10400, 10
 //    heads, D = 128: 399 -> 364 us).
 // Either side of the line, 128 / 128 / 128: 32 heads of 5120 tokens (1280 narrow units on 512 workgroups, 3 rounds, the
 // last half full) 222 us narrow, 217 wide; 35 heads 260 and 225; 40 heads (2 wide rounds against 3 and a few) 288 and 312.
+// The overlapped form with one panel: at D = 128 with key blocks of 128 where one full round is followed by lone
+// workgroups on their CUs (three turns).  8 heads of 10400 tokens 274 -> 259 us, 2 of 33325 852 -> 780; blocks of 64, 8
+// heads of 10400 274 -> 264.
 template <int D, int BQ, int BK>
-int plan_energy_onepass(const EnergyDims &p, long long workspace_bytes, EnergyOnePassDims &pp, bool &wide) {
+int plan_energy_onepass(const EnergyDims &p, long long workspace_bytes, EnergyOnePassDims &pp, int &form) {
   using Narrow = EnergyOnePass<D, BQ, BK, BQ>;
+  constexpr bool OVERLAPPED = D == 128 && BK == 128;
   int cus = 0;
-  wide = false;
+  form = CALIBATT_ENERGY_ONE_BLOCK;
   if (int st = plan_energy_form<Narrow>(block_energy_onepass_kernel<D, BQ, BK, BQ>, p, workspace_bytes, pp, cus))
     return st;
   if constexpr (BQ == 64 || D == 128 || BK == 128) {
@@ -293,12 +298,23 @@ int plan_energy_onepass(const EnergyDims &p, long long workspace_bytes, EnergyOn
       st = plan_energy_form<EnergyOnePass<D, BQ, BK, 128>>(block_energy_onepass_kernel<D, BQ, BK, 128>, p,
                                                            workspace_bytes, w, cus);
     else
-      st = plan_energy_form<EnergyPanels<D, BK>>(block_energy_panels_kernel<D, BK>, p, workspace_bytes, w, cus);
-    constexpr int PERCENT = BQ == 64 ? (D == 128 && BK == 128 ? 130 : 150) : BK == 64 ? 190 : D == 128 ? 180 : 185;
+      st = plan_energy_form<EnergyPanels<D, BQ, BK, 2>>(block_energy_panels_kernel<D, BQ, BK, 2>, p, workspace_bytes, w,
+                                                        cus);
+    constexpr int PERCENT = BQ == 64 ? (D == 128 && BK == 128 ? 130 : 150) : BK == 64 ? 200 : D == 128 ? 180 : 185;
     if (st == CALIBATT_OK && (BQ == 64 || (long long)p.B * p.H * w.n_group > cus) &&
         energy_turns(w, cus) * PERCENT <= energy_turns(pp, cus) * 100) {
-      wide = true;
+      form = CALIBATT_ENERGY_TWO_BLOCKS;
       pp = w;
+    }
+  }
+  if constexpr (OVERLAPPED) {
+    if (form == (BQ == 64 ? CALIBATT_ENERGY_TWO_BLOCKS : CALIBATT_ENERGY_ONE_BLOCK) && energy_turns(pp, cus) == 3) {
+      EnergyOnePassDims w;
+      if (plan_energy_form<EnergyPanels<D, BQ, BK, 1>>(block_energy_panels_kernel<D, BQ, BK, 1>, p, workspace_bytes, w,
+                                                       cus) == CALIBATT_OK && w.n_wg == pp.n_wg) {
+        form = CALIBATT_ENERGY_OVERLAPPED;
+        pp = w;
+      }
     }
   }
   return CALIBATT_OK;
@@ -308,17 +324,23 @@ template <int D, int BQ, int BK>
 int launch_energy_onepass(const uint16_t *q, const uint16_t *k, float *energy, const EnergyDims &p, float *workspace,
                           long long workspace_bytes, hipStream_t stream) {
   EnergyOnePassDims pp;
-  bool wide = false;
-  if (int st = plan_energy_onepass<D, BQ, BK>(p, workspace_bytes, pp, wide)) return st;
+  int which = 0;
+  if (int st = plan_energy_onepass<D, BQ, BK>(p, workspace_bytes, pp, which)) return st;
   auto launch = [&](auto kernel, auto form) {
     using Form = decltype(form);
     return launch_kernel(kernel, (unsigned)pp.n_wg, Form::NW * 64, (int)Form::bytes(p.nbk), stream, q, k, energy,
                          workspace, pp);
   };
+  if constexpr (D == 128 && BK == 128) {
+    if (which == CALIBATT_ENERGY_OVERLAPPED)
+      return launch(block_energy_panels_kernel<D, BQ, BK, 1>, EnergyPanels<D, BQ, BK, 1>{});
+  }
   if constexpr (BQ == 64) {
-    if (wide) return launch(block_energy_onepass_kernel<D, BQ, BK, 128>, EnergyOnePass<D, BQ, BK, 128>{});
+    if (which == CALIBATT_ENERGY_TWO_BLOCKS)
+      return launch(block_energy_onepass_kernel<D, BQ, BK, 128>, EnergyOnePass<D, BQ, BK, 128>{});
   } else if constexpr (D == 128 || BK == 128) {
-    if (wide) return launch(block_energy_panels_kernel<D, BK>, EnergyPanels<D, BK>{});
+    if (which == CALIBATT_ENERGY_TWO_BLOCKS)
+      return launch(block_energy_panels_kernel<D, BQ, BK, 2>, EnergyPanels<D, BQ, BK, 2>{});
   }
   return launch(block_energy_onepass_kernel<D, BQ, BK, BQ>, EnergyOnePass<D, BQ, BK, BQ>{});
 }
@@ -542,18 +564,18 @@ extern "C" int calibatt_block_energy_onepass(const void *q, const void *k, float
   });
 }
 
-extern "C" int calibatt_block_energy_onepass_queries(int B, int H, int N, int D, int block_q, int block_k,
-                                                     int64_t workspace_bytes, int32_t *queries) {
-  if (!queries) return CALIBATT_ERR_NULL;
+extern "C" int calibatt_block_energy_onepass_form(int B, int H, int N, int D, int block_q, int block_k,
+                                                  int64_t workspace_bytes, int32_t *form) {
+  if (!form) return CALIBATT_ERR_NULL;
   if (B <= 0 || H <= 0 || N <= 0 || D <= 0 || block_q <= 0 || block_k <= 0 || workspace_bytes < 0)
     return CALIBATT_ERR_SHAPE;
   return energy_shape(D, block_q, block_k, [&](auto d, auto bq, auto bk) -> int {
     if ((size_t)B * H * N * D > 0x7fffffff00ULL) return CALIBATT_ERR_SHAPE;
     const EnergyDims p = {B, H, N, (N + block_q - 1) / block_q, (N + block_k - 1) / block_k, 1.0f};
     EnergyOnePassDims pp;
-    bool wide = false;
-    if (int st = plan_energy_onepass<d, bq, bk>(p, workspace_bytes, pp, wide)) return st;
-    *queries = wide ? 2 * block_q : block_q;
+    int which = 0;
+    if (int st = plan_energy_onepass<d, bq, bk>(p, workspace_bytes, pp, which)) return st;
+    *form = which;
     return CALIBATT_OK;
   });
 }

@@ -24,8 +24,8 @@ def _workspaces(lib, B, H, N, D, bq, bk):
 
     nbytes = lib.block_energy_workspace_bytes(N, bq, bk)
     sizes = nbytes, nbytes // 1024, 4 * nbytes
-    twice = 1 if (D, bq, bk) == (64, 128, 64) else 2
-    assert [lib.block_energy_onepass_queries(B, H, N, D, bq, bk, n) for n in sizes] == [twice * bq, bq, twice * bq]
+    one, two = lib.ENERGY_ONE_BLOCK, lib.ENERGY_ONE_BLOCK if (D, bq, bk) == (64, 128, 64) else lib.ENERGY_TWO_BLOCKS
+    assert [lib.block_energy_onepass_form(B, H, N, D, bq, bk, n) for n in sizes] == [two, one, two]
     return [torch.full((n // 4,), float("nan"), device="cuda") for n in sizes]
 
 
@@ -40,9 +40,9 @@ def _energy64(q, k, bq, bk, scale):
     return e / torch.bincount(rows // bq)[:, None]
 
 
-# 4096 units of 256 queries: whole rounds of 512 workgroups, two per CU.  With blocks of 128, D = 64 and key blocks of 64
+# 3800-4100 units of 256 queries: rounds of 512 workgroups, two per CU.  With blocks of 128, D = 64 and key blocks of 64
 # the wide form is not built.
-@pytest.mark.parametrize("N,H", [(129, 4096), (901, 1024), (2100, 455)])
+@pytest.mark.parametrize("N,H", [(129, 4096), (901, 1024), (4100, 225)])
 @pytest.mark.parametrize("D,bq,bk", [(128, 128, 128), (128, 128, 64), (128, 64, 128), (128, 64, 64),
                                      (64, 128, 128), (64, 128, 64), (64, 64, 128), (64, 64, 64)])
 def test_block_energy_wide_workgroups(lib, D, bq, bk, N, H):
@@ -60,6 +60,34 @@ def test_block_energy_wide_workgroups(lib, D, bq, bk, N, H):
         _same_bits(got[:, h:h + 1], lib.block_energy(q[:, h:h + 1].contiguous(), k[:, h:h + 1].contiguous(), bq, bk, scale,
                                                      workspace=full))
         torch.testing.assert_close(got[0, h].double(), _energy64(q[0, h], k[0, h], bq, bk, scale), rtol=2e-5, atol=1e-9)
+
+
+# 576 units of 128 queries: one round of 512 workgroups and lone ones behind it
+@pytest.mark.parametrize("N,H,bq", [(1100, 64, 128), (1024, 72, 128), (260, 192, 128), (1100, 64, 64), (140, 288, 64)])
+@pytest.mark.parametrize("late", [0, 129])
+def test_block_energy_overlapped(lib, N, H, bq, late):
+    import torch
+
+    print(f"energy overlapped N={N} H={H} bq={bq} late={late}", flush=True)
+    D = bk = 128
+    gen = torch.Generator(device="cuda").manual_seed(N + bq + late)
+    q, k = (torch.randn(1, H, N, D, device="cuda", generator=gen) for _ in range(2))
+    if late:
+        q *= torch.tensor([0.05, 1.0, 6.0, 12.0], device="cuda")[torch.randint(0, 4, (1, H, N, 1), device="cuda",
+                                                                               generator=gen)]
+        k[:, :, :late] *= 0.2
+    q, k = q.to(torch.bfloat16), k.to(torch.bfloat16)
+    scale = (2.5 if late else 1.5) / math.sqrt(D)
+    nbytes = lib.block_energy_workspace_bytes(N, bq, bk)
+    assert lib.block_energy_onepass_form(1, H, N, D, bq, bk, nbytes) == lib.ENERGY_OVERLAPPED
+    assert lib.block_energy_onepass_form(1, H, N, D, bq, bk, nbytes // 1024) == lib.ENERGY_ONE_BLOCK
+    full, narrow = (torch.full((n // 4,), float("nan"), device="cuda") for n in (nbytes, nbytes // 1024))
+    got = lib.block_energy(q, k, bq, bk, scale, workspace=full)
+    _same_bits(got, lib.block_energy(q, k, bq, bk, scale, workspace=narrow))
+    _same_bits(got, lib.block_energy(q, k, bq, bk, scale, workspace=full))
+    for h in (0, H - 1):
+        torch.testing.assert_close(got[0, h].double(), _energy64(q[0, h], k[0, h], bq, bk, scale),
+                                   rtol=2e-4 if late else 2e-5, atol=1e-9)
 
 
 # the first key that outgrows the keys before it by more than the safe range: in the second tile, around the edges of
