@@ -1,9 +1,9 @@
 // Device side of the mask calibration that follows the block-energy kernel
 // (paper, Section 3.2): Eq. 6, the smallest set of key blocks of a block-row
 // whose energies sum to at least eps, and the per-block vote counters behind
-// Eq. 8-9.  Small kernels next to the energy kernel's 20 ms; they exist so
+// Eq. 8-9.  Small kernels next to the energy kernel's 10 ms; they exist so
 // that a calibration step never leaves the GPU (the same selection on the host
-// costs five times the energy kernel in sorting alone).
+// costs ten times the energy kernel in sorting alone).
 //
 // The selection is an integer decision taken on floating-point data, so it is
 // defined exactly and matches the host routine bit for bit: order the row by
