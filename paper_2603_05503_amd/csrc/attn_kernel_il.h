@@ -15,7 +15,7 @@
 // their phases happen to fall.  But an MFMA occupies the pipe for 32 cycles
 // and its wavefront can issue a few other instructions meanwhile.  So here a
 // kept key block is cut into sub-tiles of 64 keys (32 where the block is not
-// a multiple of 64 or is 64 keys itself), a row's kept blocks become one
+// a multiple of 64, or LDS is short: il_sub), a row's kept blocks become one
 // stream of sub-tiles, and in every STAGE a wavefront issues, interleaved
 // instruction by instruction,
 //     the MFMAs of  O += P V  of the sub-tile before the previous one,
@@ -58,20 +58,32 @@ constexpr int IL_VGPRS = 72;  // arch VGPRs left to the compiler; the named ones
 constexpr int IL_STAGES = 6;  // operand staging slots
 constexpr int IL_AHEAD = 4;   // MFMAs between the issue of an operand's LDS reads and its use
 
-// Keys per sub-tile for a key block of BK keys: the block is a whole number of sub-tiles (two for
-// the power-of-two widths; three or five for 96, 160 and 192).
-constexpr __host__ __device__ int il_sub(int bk) { return bk >= 128 && bk % 64 == 0 ? 64 : 32; }
+// Keys per sub-tile for a key block of BK keys: the block is a whole number of sub-tiles (one, two or three of 64
+// keys; three or five of 32 for 96 and 160).  A stage costs a barrier and, where few wavefronts are in flight, the
+// latency of its tile loads, however short it is: with sub-tiles of 64 instead of 32 keys, key blocks of 64 at 128
+// queries take 2.77 instead of 2.96 ms (20 heads of 32 760 tokens, D = 128) and 1.72 instead of 1.89 (D = 64), and one
+// row of blocks by itself on its CU four fifths of the time.  64-query blocks at D = 128 with key blocks of 64 keep 32: a
+// workgroup of two wavefronts then takes 32 KB of LDS, four of them fill a CU's eight wavefronts, and 3.35 ms become
+// 4.14 with 64 (D = 64 takes half the LDS).
+constexpr __host__ __device__ int il_sub(int d, int bq, int bk) {
+  return bk % 64 != 0 || (bq == 64 && d == 128 && bk == 64) ? 32 : 64;
+}
+
+// Columns of a row in interval form that are expanded into LDS at a time.  With 64-query blocks the list stays in 4 KB,
+// so that four workgroups fit on a CU: 8 KB leave room for three, 2.04 -> 1.84 ms at D = 64, 3.74 -> 3.35 at D = 128
+// (20 heads of 32 760 tokens, key blocks of 64).
+constexpr __host__ __device__ int il_iv_cols(int bq) { return bq == 64 ? 1024 : IV_COLS; }
 
 // The base class lays out LDS and lanes for a window of two sub-tiles of K and of V.
 template <int D, int BQ, int BK, typename T = Bf16>
-struct IlRow : RowBlock<D, BQ, 2 * il_sub(BK), T> {
-  using RB = RowBlock<D, BQ, 2 * il_sub(BK), T>;
+struct IlRow : RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T> {
+  using RB = RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T>;
   using RB::DB;
   using RB::DS;
   using RB::ROWB;
-  static constexpr int SUB = il_sub(BK);         // keys per sub-tile
+  static constexpr int SUB = il_sub(D, BQ, BK);         // keys per sub-tile
   static constexpr int SPB = BK / SUB;           // sub-tiles per key block
-  static_assert(BK % SUB == 0 && SPB >= 2, "a key block is a whole number of sub-tiles");
+  static_assert(BK % SUB == 0, "a key block is a whole number of sub-tiles");
   static constexpr int KBS = SUB / 32;           // 32-key sub-blocks per sub-tile
   static_assert(KBS >= 1, "sub-tiles of at least 32 keys");
   static constexpr int EL = 16 * KBS;            // S^T elements per lane and sub-tile
@@ -315,7 +327,8 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
     int32_t *counter, const FwdDims p, const int32_t *__restrict__ iv_ptr, const uint32_t *__restrict__ iv,
     const int32_t *__restrict__ head_map, float *__restrict__ lse) {
   using Row = IlRow<D, BQ, BK, T>;
-  constexpr int NT = Row::NT, CH = Row::CH, ROWB = Row::ROWB, OST = Row::OST, LDS_BYTES = Row::LDS_BYTES, SUB = Row::SUB;
+  constexpr int NT = Row::NT, CH = Row::CH, ROWB = Row::ROWB, OST = Row::OST, LDS_BYTES = Row::LDS_BYTES, SUB = Row::SUB,
+                COLS = il_iv_cols(BQ);
   il_claim_registers();
 
   // [K window: 2 sub-tiles][V window: 2 sub-tiles] (reused as the output staging tile), work-item mailbox,
@@ -381,7 +394,7 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
 
     const int cbeg = row_ptr[id];
     int n_tiles = row_ptr[id + 1] - cbeg;
-    // IV: entries [chunk_lo, chunk_lo + IV_COLS) of the row's list are expanded from its runs of
+    // IV: entries [chunk_lo, chunk_lo + COLS) of the row's list are expanded from its runs of
     // consecutive key blocks into LDS; every thread takes runs tid, tid + NT, ...
     int chunk_lo = 0;
     auto expand_runs = [&]() {
@@ -389,7 +402,7 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
       for (int i = ib + tid; i < ie; i += NT) {
         const uint32_t w = iv[i], w_next = iv[i + 1];
         const int start = (int)(w & 0xffffu), before = (int)(w >> 16), len = (int)(w_next >> 16) - before;
-        const int j0 = max(0, chunk_lo - before), j1 = min(len, chunk_lo + IV_COLS - before);
+        const int j0 = max(0, chunk_lo - before), j1 = min(len, chunk_lo + COLS - before);
         for (int j = j0; j < j1; ++j) cols[before + j - chunk_lo] = start + j;
       }
       __syncthreads();
@@ -411,14 +424,14 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
     }
 
     if (n_tiles > 0) {
-      // The row's kept blocks as a stream of sub-tiles u_0, u_1, ... (SPB per block, an odd total is
-      // padded with one sub-tile beyond the sequence, all of whose keys are masked).  Stage k:
+      // The row's kept blocks as a stream of sub-tiles u_0, u_1, ... (SPB per block; a lone one is
+      // padded with one beyond the sequence, all of whose keys are masked).  Stage k:
       // O += P V of u_(k-2), S = K Q^T of u_k, softmax of u_(k-1); at its start the loads of V of u_(k-1)
       // and K of u_(k+1) are issued into the slots the stage before has finished with, and they land by
       // its end.  Stages alternate between the two slots of the windows and the two S buffers.
       constexpr int SPB = Row::SPB;
       const int n_sub = n_tiles * SPB;
-      const int n_stream = (n_sub + 1) & ~1;
+      const int n_stream = max(n_sub, 2);
       // First key row of the next sub-tile of the stream (N beyond its end: rows there read as zeros
       // and the keys are masked); called once per sub-tile, in order.
       int nx_entry = 0, nx_part = 0, nx_col = col_of(0);
@@ -430,7 +443,7 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
           ++nx_entry;
           if ((nx_entry & 63) == 0 && nx_entry < n_tiles) {
             if constexpr (IV) {
-              if (nx_entry % IV_COLS == 0) {  // every wave has taken its entries of the chunk that is replaced
+              if (nx_entry % COLS == 0) {  // every wave has taken its entries of the chunk that is replaced
                 chunk_lo = nx_entry;
                 expand_runs();
               }
@@ -464,8 +477,9 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
       CALIBATT_IL_MASK(1, r1)
       wait_vmem<0>();
       __syncthreads();
+      bool odd_end = false;
       for (int k = 2; k < n_stream; k += 2) {
-        // stage k: loads inside the stream: V of u_(k-1), K of u_(k+1)
+        // stage k: loads inside the stream: V of u_(k-1), K of u_(k+1) (beyond the stream: zeros into a slot nobody reads)
         const int row_c = next_rows();
         IL_PROF(3);
         rb.template stage<0, true, true, true, true>(Vres, row_a, Kres, row_c);
@@ -475,7 +489,9 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
         IL_PROF(1);
         __syncthreads();
         IL_PROF(2);
-        // stage k + 1: V of u_k, K of u_(k+2) (beyond the stream: zeros into a slot nobody reads)
+        odd_end = k + 1 == n_stream;
+        if (odd_end) break;
+        // stage k + 1: V of u_k, K of u_(k+2)
         const int row_d = next_rows();
         IL_PROF(3);
         rb.template stage<1, true, true, true, true>(Vres, row_b, Kres, row_d);
@@ -490,12 +506,20 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
       }
 #undef CALIBATT_IL_MASK
       // stage n_stream: V of the last sub-tile; O += P V of u_(n_stream-2), softmax of u_(n_stream-1)
-      rb.issue_v_sub(Vres, row_a, 1);
-      rb.template stage<0, true, false, true>();
-      wait_vmem<0>();
-      __syncthreads();
-      // stage n_stream + 1: O += P V of u_(n_stream-1)
-      rb.template stage<1, true, false, false>();
+      // and stage n_stream + 1: O += P V of u_(n_stream-1)
+      if (odd_end) {
+        rb.issue_v_sub(Vres, row_b, 0);
+        rb.template stage<1, true, false, true>();
+        wait_vmem<0>();
+        __syncthreads();
+        rb.template stage<0, true, false, false>();
+      } else {
+        rb.issue_v_sub(Vres, row_a, 1);
+        rb.template stage<0, true, false, true>();
+        wait_vmem<0>();
+        __syncthreads();
+        rb.template stage<1, true, false, false>();
+      }
     }
 
     // ---- normalise, stage in LDS, store to the block and its repeat targets ----

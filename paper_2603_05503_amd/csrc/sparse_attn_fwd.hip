@@ -97,7 +97,7 @@ int launch_typed(const FwdPtrs &a, const FwdDims &p, int which, hipStream_t stre
   int slots = 0;
   if (which != CALIBATT_KERNEL_TWO_WORKGROUPS) {
     static DevInfo info;
-    constexpr int SMEM = IlRow<D, BQ, BK, T>::LDS_BYTES + 64 + (IV ? IV_COLS * 4 : 0);
+    constexpr int SMEM = IlRow<D, BQ, BK, T>::LDS_BYTES + 64 + (IV ? il_iv_cols(BQ) * 4 : 0);
     auto kernel = sparse_attn_fwd_il_kernel<D, BQ, BK, IV, T>;
     if (int st = prepare(kernel, BQ * 2, SMEM, info, slots)) return st;
     return enqueue(kernel, BQ * 2, SMEM, slots, a, p, stream);
