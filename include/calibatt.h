@@ -268,6 +268,61 @@ int calibatt_sparse_attn_fwd_ex(const void *q, const void *k, const void *v, voi
                                 const calibatt_fwd_options *options, void *stream);
 
 /*
+ * The forward with its rows cut along the keys (Section 2, Eq. 3-4: the sums of
+ * an online softmax over disjoint key sets combine exactly).  A query block's
+ * kept key blocks are a chain that one workgroup walks; a call of few rows, or
+ * of a few long ones, lasts as long as its longest chain while most of the GPU
+ * idles.  Here every row is cut into parts of about equal length, one workgroup
+ * takes a part, and the last of a row's parts to finish adds up their sums in
+ * the order of the keys.  Same result up to fp32 rounding, the same bits on
+ * every run and for every schedule order of the pattern.
+ *
+ * calibatt_plan_split (HOST): the parts of a pattern for batch B.
+ *   pattern     as calibatt_compile_pattern filled it (HOST pointers row_ptr,
+ *               work, fan_ptr and, or NULL, col_idx, which only decides what an
+ *               XCD's workgroups find in its L2); for the interval form also
+ *               iv_ptr (HOST), as calibatt_encode_intervals wrote it.
+ *   max_blocks  longest part in key blocks, 0 = chosen by estimated time.  A row
+ *               is cut into at most 16 parts.
+ *   parts       HOST int32 [cap_parts][12], or NULL to learn the counts; copied
+ *               to the GPU by the caller, like the arrays of the pattern.
+ *   split       receives B and the counts; the pointers are set to NULL.
+ *               n_parts == 0: whole rows are the better choice (a call long
+ *               enough to fill the GPU), the forward ignores the split.
+ * Errors: NULL, SHAPE, BUFFER_TOO_SMALL (cap_parts), NOMEM.
+ * calibatt_split_workspace_bytes: workspace of a call with that plan.
+ *
+ * calibatt_sparse_attn_fwd_split: calibatt_sparse_attn_fwd_ex with
+ *   split            HOST struct of the plan for this pattern and B, its parts
+ *                    and arrivals pointing to DEVICE memory: parts 16-byte
+ *                    aligned; arrivals int32 [n_rows], all zero before the
+ *                    first call and zero again after every call.  NULL: the
+ *                    call is calibatt_sparse_attn_fwd_ex.  pattern->work_counter
+ *                    is not used.
+ *   workspace        DEVICE, 16-byte aligned, contents irrelevant before and
+ *                    undefined after (NULL is allowed for 0 bytes).
+ *   workspace_bytes  at least calibatt_split_workspace_bytes.
+ * Calls that may overlap need arrivals and workspaces of their own.  Errors: as
+ * calibatt_sparse_attn_fwd_ex; PATTERN_MISMATCH (another B, counts no plan has),
+ * UNSUPPORTED (CALIBATT_KERNEL_TWO_WORKGROUPS), BUFFER_TOO_SMALL (workspace).
+ */
+typedef struct calibatt_split {
+  int32_t B;            /* batch the plan is for */
+  int32_t n_parts;      /* records of `parts`, a multiple of CALIBATT_GROUPS (some empty) */
+  int32_t n_rows;       /* rows that are cut, over the batch */
+  int32_t n_slots;      /* parts of cut rows */
+  const int32_t *parts; /* record i goes to XCD i % CALIBATT_GROUPS */
+  int32_t *arrivals;    /* parts of a cut row that have finished */
+} calibatt_split;
+int calibatt_plan_split(const calibatt_pattern *pattern, int B, int max_blocks, int32_t *parts, int64_t cap_parts,
+                        calibatt_split *split);
+int64_t calibatt_split_workspace_bytes(const calibatt_split *split, int block_q, int D);
+int calibatt_sparse_attn_fwd_split(const void *q, const void *k, const void *v, void *out, int B, int H, int N, int D,
+                                   int block_q, int block_k, const calibatt_pattern *pattern, float scale,
+                                   const calibatt_fwd_options *options, const calibatt_split *split, void *workspace,
+                                   int64_t workspace_bytes, void *stream);
+
+/*
  * Spatial-row anchor scheme (Section 3.3; "Inference stage" of Section 3.4:
  * heads flagged as spatially repetitive run dense attention on a reduced query
  * set and broadcast the result).

@@ -1,6 +1,7 @@
 """ctypes marshalling for include/calibatt.h."""
 from __future__ import annotations
 
+import contextlib
 import ctypes as C
 import os
 import threading
@@ -48,6 +49,11 @@ class _CPattern(C.Structure):
         ("iv_ptr", C.c_void_p), ("iv", C.c_void_p),
         ("head_map", C.c_void_p),
     ]
+
+
+class _CSplit(C.Structure):
+    _fields_ = [("B", C.c_int32), ("n_parts", C.c_int32), ("n_rows", C.c_int32), ("n_slots", C.c_int32),
+                ("parts", C.c_void_p), ("arrivals", C.c_void_p)]
 
 
 def library_path() -> str:
@@ -150,6 +156,13 @@ def load_library():
         C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int,
         C.POINTER(_CPattern), C.c_float, C.POINTER(_CFwdOptions), C.c_void_p,
     ]
+    lib.calibatt_plan_split.restype = C.c_int
+    lib.calibatt_plan_split.argtypes = [C.POINTER(_CPattern), C.c_int, C.c_int, i32p, C.c_int64, C.POINTER(_CSplit)]
+    lib.calibatt_split_workspace_bytes.restype = C.c_int64
+    lib.calibatt_split_workspace_bytes.argtypes = [C.POINTER(_CSplit), C.c_int, C.c_int]
+    lib.calibatt_sparse_attn_fwd_split.restype = C.c_int
+    lib.calibatt_sparse_attn_fwd_split.argtypes = lib.calibatt_sparse_attn_fwd_ex.argtypes[:-1] + [
+        C.POINTER(_CSplit), C.c_void_p, C.c_int64, C.c_void_p]
     lib.calibatt_anchor_attn_fwd_strided.restype = C.c_int
     lib.calibatt_anchor_attn_fwd_strided.argtypes = lib.calibatt_anchor_attn_fwd.argtypes[:-1] + [
         C.POINTER(_CStrides), C.POINTER(_CStrides), C.c_void_p]
@@ -246,6 +259,26 @@ class HostPattern:
         ``head_map`` (one tensor head per pattern head) makes the pattern act on a subset of heads."""
         return DevicePattern(self, device, persistent, intervals, head_map)
 
+    def plan_split(self, B: int, max_blocks: int = 0, iv_ptr=None):
+        """calibatt_plan_split for batch ``B``: (struct without device pointers, int32 records [n_parts, 12]), or None
+        where whole rows are the better choice.  ``max_blocks``: longest part in key blocks, 0 = the library's choice."""
+        lib = load_library()
+        c = _CPattern()
+        for f in ("H", "N", "block_q", "block_k", "nbq", "nbk", "n_work", "n_repeat", "order", "max_row", "nnz"):
+            setattr(c, f, getattr(self, f))
+        c.row_ptr, c.work, c.fan_ptr, c.col_idx = (
+            a.ctypes.data for a in (self.row_ptr, self.work, self.fan_ptr, self.col_idx))
+        if iv_ptr is not None:
+            c.iv_ptr = iv_ptr.ctypes.data
+        split = _CSplit()
+        st = lib.calibatt_plan_split(C.byref(c), B, max_blocks, None, 0, C.byref(split))
+        if st == 0 and split.n_parts:
+            parts = np.empty((split.n_parts, 12), np.int32)
+            st = lib.calibatt_plan_split(C.byref(c), B, max_blocks, _ptr(parts, C.c_int32), split.n_parts, C.byref(split))
+        if st != 0:
+            raise CalibattError(st, "calibatt_plan_split")
+        return (split, parts) if split.n_parts else None
+
     def encode_intervals(self):
         """(iv_ptr int32 [rows + 1], iv uint32 words) via calibatt_encode_intervals."""
         return encode_intervals(self.row_ptr, self.col_idx)
@@ -293,6 +326,7 @@ class DevicePattern:
         self.host = hp
         self.tensors = {}
         self.intervals = bool(intervals)
+        self._iv_ptr = None
         for name in self._NAMES:
             if intervals and name == "col_idx":
                 continue
@@ -308,6 +342,7 @@ class DevicePattern:
             iv_ptr, iv = hp.encode_intervals()
             self.tensors["iv_ptr"] = torch.from_numpy(iv_ptr).to(device)
             self.tensors["iv"] = torch.from_numpy(iv.view(np.int32)).to(device)
+            self._iv_ptr = iv_ptr
             c.iv_ptr = self.tensors["iv_ptr"].data_ptr()
             c.iv = self.tensors["iv"].data_ptr()
         else:
@@ -321,45 +356,76 @@ class DevicePattern:
             c.head_map = self.tensors["head_map"].data_ptr()
         else:
             c.head_map = None
-        # int32[16] workspace of the persistent-workgroup scheduler (kept zero between calls), and as many for
-        # further streams, cleared here so that no call has to (128 bytes apart: a cache line each)
-        counters = torch.zeros((8, 32), dtype=torch.int32, device=device)[:, :16] if persistent else None
-        self.counter = counters[0] if persistent else None
-        c.work_counter = self.counter.data_ptr() if persistent else None
+        self.device = device
+        self.c = c
+        self._plan(persistent)
         c.n_groups = hp.n_groups
         gp = hp.group_ptr if hp.group_ptr is not None else np.array([0] + [hp.n_work] * 8, np.int32)
         for i in range(9):
             c.group_ptr[i] = int(gp[i])
-        self.c = c
-        self._stream_of_c = None   # stream handle that uses self.c
-        self._per_stream = {}      # other streams: (clone of the struct, its own counters)
-        self._spare = [] if counters is None else list(counters[1:])
+
+    def _plan(self, persistent, max_blocks=0):
+        """Plans of the calls cut along the keys (batches of one and, for two guidance branches, two), and the counters:
+        per stream an int32[16] workspace of the persistent-workgroup scheduler and the arrivals of the cut rows' parts,
+        both kept zero between calls, here for eight streams, cleared so that no call has to."""
+        import torch
+
+        self._plans = {}
+        if persistent:
+            for B in (1, 2):
+                plan = self.host.plan_split(B, max_blocks, self._iv_ptr)
+                if plan:
+                    self._plans[B] = (plan[0], torch.from_numpy(plan[1]).to(self.device))
+        # the arrivals behind the scheduler's words, whole cache lines for every stream
+        arrivals = max((p.n_rows for p, _ in self._plans.values()), default=0)
+        self._words = 32 + -(-arrivals // 32) * 32
+        self._spare = list(torch.zeros((8, self._words), dtype=torch.int32, device=self.device)) if persistent else []
+        words = self._spare.pop(0) if persistent else None
+        self.counter = words[:16] if persistent else None
+        self.c.work_counter = self.counter.data_ptr() if persistent else None
+        self._stream_of_c = None  # stream handle that uses self.c
+        self._own = (self.c, words, self._splits_with(words))
+        self._per_stream = {}     # other streams: (clone of the struct, its own words, splits with its own arrivals)
         self._lock = threading.Lock()
 
-    def c_for(self, stream_handle: int):
-        """The C struct to pass for a call on ``stream_handle``.  Calls on different streams may overlap on
-        the GPU, and overlapping calls must not share the scheduler's work counters: every stream after the
-        first gets a clone of the struct that points at counters of its own (the index arrays are shared)."""
+    def _splits_with(self, words):
+        """{B: struct of the planned split whose arrivals are counted behind the scheduler's ``words``}"""
+        out = {}
+        for B, (plan, parts) in self._plans.items():
+            out[B] = _CSplit(plan.B, plan.n_parts, plan.n_rows, plan.n_slots, parts.data_ptr(), words.data_ptr() + 32 * 4)
+        return out
+
+    def _for_stream(self, stream_handle: int):
         if self.counter is None or self._stream_of_c == stream_handle:
-            return self.c
+            return self._own
         with self._lock:
             if self._stream_of_c is None:
                 self._stream_of_c = stream_handle
             if self._stream_of_c == stream_handle:
-                return self.c
+                return self._own
             if stream_handle not in self._per_stream:
                 import torch
 
                 clone = _CPattern()
                 C.memmove(C.byref(clone), C.byref(self.c), C.sizeof(_CPattern))
                 if self._spare:
-                    counter = self._spare.pop()
+                    words = self._spare.pop()
                 else:  # cleared on the stream that uses it: nothing orders a fill on another one before the call
                     with torch.cuda.stream(torch.cuda.ExternalStream(stream_handle, device=self.counter.device)):
-                        counter = torch.zeros(16, dtype=torch.int32, device=self.counter.device)
-                clone.work_counter = counter.data_ptr()
-                self._per_stream[stream_handle] = (clone, counter)
-            return self._per_stream[stream_handle][0]
+                        words = torch.zeros(self._words, dtype=torch.int32, device=self.counter.device)
+                clone.work_counter = words.data_ptr()
+                self._per_stream[stream_handle] = (clone, words, self._splits_with(words))
+            return self._per_stream[stream_handle]
+
+    def c_for(self, stream_handle: int):
+        """The C struct to pass for a call on ``stream_handle``.  Calls on different streams may overlap on
+        the GPU, and overlapping calls must not share the scheduler's work counters: every stream after the
+        first gets a clone of the struct that points at counters of its own (the index arrays are shared)."""
+        return self._for_stream(stream_handle)[0]
+
+    def split_for(self, stream_handle: int, B: int):
+        """The split of a call of batch ``B`` on ``stream_handle`` (None: whole rows)."""
+        return self._for_stream(stream_handle)[2].get(B)
 
     @property
     def nnz(self) -> int:
@@ -380,8 +446,9 @@ def sparse_attn_fwd(q, k, v, out, pattern: DevicePattern, scale: float,
     slices of a fused [B, N, 3, H, D] projection) as long as D is contiguous and q, k, v share their
     strides.  ``lse``: optional contiguous fp32 CUDA tensor [B, H, N] that receives the log-sum-exp of
     every query's kept logits.  ``kernel``: KERNEL_AUTO, KERNEL_TWO_WORKGROUPS or KERNEL_INTERLEAVED (the
-    ``kernel`` field of calibatt_fwd_options).  Packed bf16 calls without ``lse`` and with the automatic
-    kernel choice go through calibatt_sparse_attn_fwd, everything else through calibatt_sparse_attn_fwd_ex."""
+    ``kernel`` field of calibatt_fwd_options).  Calls that the pattern has a split for (``DevicePattern``)
+    go through calibatt_sparse_attn_fwd_split, other packed bf16 calls without ``lse`` and with the automatic
+    kernel choice through calibatt_sparse_attn_fwd, everything else through calibatt_sparse_attn_fwd_ex."""
     import torch
 
     lib = load_library()
@@ -398,20 +465,31 @@ def sparse_attn_fwd(q, k, v, out, pattern: DevicePattern, scale: float,
         raise ValueError("lse must be a contiguous fp32 CUDA tensor [B, H, N]")
     bq = pattern.host.block_q if block_q is None else block_q
     bk = pattern.host.block_k if block_k is None else block_k
-    if stream is None:
-        stream = torch.cuda.current_stream(q.device).cuda_stream
+    stream, other = _stream_of(stream, q.device)
+    pointers = (q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr())
     packed = all(t.is_contiguous() for t in (q, k, v, out))
-    if packed and lse is None and q.dtype == torch.bfloat16 and kernel == KERNEL_AUTO:
-        st = lib.calibatt_sparse_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
-                                          B, H, N, D, bq, bk, C.byref(pattern.c_for(int(stream))), float(scale), C.c_void_p(stream))
+    c, split = C.byref(pattern.c_for(stream)), None
+    if kernel != KERNEL_TWO_WORKGROUPS:
+        split = pattern.split_for(stream, B)
+    if split is None and packed and lse is None and q.dtype == torch.bfloat16 and kernel == KERNEL_AUTO:
+        st = lib.calibatt_sparse_attn_fwd(*pointers, B, H, N, D, bq, bk, c, float(scale), stream)
     else:
         si = _CStrides(q.stride(0), q.stride(1), q.stride(2))
         so = _CStrides(out.stride(0), out.stride(1), out.stride(2))
         opt = _CFwdOptions(None if packed else C.pointer(si), None if packed else C.pointer(so),
                            0 if q.dtype == torch.bfloat16 else 1, None if lse is None else lse.data_ptr(), int(kernel))
-        st = lib.calibatt_sparse_attn_fwd_ex(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(),
-                                             B, H, N, D, bq, bk, C.byref(pattern.c_for(int(stream))), float(scale),
-                                             C.byref(opt), C.c_void_p(stream))
+        if split is None:
+            st = lib.calibatt_sparse_attn_fwd_ex(*pointers, B, H, N, D, bq, bk, c, float(scale), C.byref(opt), stream)
+        else:
+            nbytes = lib.calibatt_split_workspace_bytes(C.byref(split), bq, D)
+            workspace = _empty(nbytes // 4, torch.float32, q.device, other)
+            with contextlib.nullcontext() if other is None else torch.cuda.stream(other):
+                # a captured call counts in memory of its own graph: replays may overlap calls of the stream it is captured on
+                if torch.cuda.is_current_stream_capturing():
+                    arrivals = torch.zeros(max(split.n_rows, 1), dtype=torch.int32, device=q.device)
+                    split = _CSplit(B, split.n_parts, split.n_rows, split.n_slots, split.parts, arrivals.data_ptr())
+            st = lib.calibatt_sparse_attn_fwd_split(*pointers, B, H, N, D, bq, bk, c, float(scale), C.byref(opt),
+                                                    C.byref(split), workspace.data_ptr(), nbytes, stream)
     if st != 0:
         raise CalibattError(st, "calibatt_sparse_attn_fwd")
     return out

@@ -37,13 +37,8 @@ struct FwdDims {
 template <int N_OUTSTANDING>
 __device__ __forceinline__ void wait_vmem() {
   // waits until at most N_OUTSTANDING vector-memory operations of this wave are in flight
-  static_assert(N_OUTSTANDING == 0 || N_OUTSTANDING == 2 || N_OUTSTANDING == 4 || N_OUTSTANDING == 8 ||
-                N_OUTSTANDING == 16, "add the immediate below");
-  if constexpr (N_OUTSTANDING == 0) asm volatile("s_waitcnt vmcnt(0)");
-  else if constexpr (N_OUTSTANDING == 2) asm volatile("s_waitcnt vmcnt(2)");
-  else if constexpr (N_OUTSTANDING == 4) asm volatile("s_waitcnt vmcnt(4)");
-  else if constexpr (N_OUTSTANDING == 8) asm volatile("s_waitcnt vmcnt(8)");
-  else asm volatile("s_waitcnt vmcnt(16)");
+  static_assert(N_OUTSTANDING >= 0 && N_OUTSTANDING <= 63, "vmcnt is a 6-bit counter");
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N_OUTSTANDING));
 }
 
 // 16-byte-chunk XOR swizzles of the LDS tiles.  CH = chunks per row (D/8); one
@@ -79,12 +74,16 @@ __device__ __forceinline__ u32x4 head_rsrc(const uint16_t *base, uint32_t bytes)
 // inline asm so that the compiler keeps no record of LDS being written by an
 // in-flight vector-memory operation (it would otherwise drain vmcnt before
 // every LDS read); completion is tracked by hand with wait_vmem<>().
+// The scalar copy of soff is the wait state between the M0 write and the LDS-DMA that reads it, and the memory
+// instruction then reads a register that the scalar unit wrote: one that the compiler has just brought back from a vector
+// lane would need five wait states (csrc/check_sgpr_waits.py fails the build where they are missing).
 __device__ __forceinline__ void dma_16B_per_lane(const u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds_off) {
+  uint32_t copy;
   asm volatile(
-      "s_mov_b32 m0, %0\n\t"
-      "s_nop 0\n\t"  // one wait state between the M0 write and the LDS-DMA that reads it
-      "buffer_load_dwordx4 %1, %2, %3 offen lds"
-      :
+      "s_mov_b32 m0, %1\n\t"
+      "s_mov_b32 %0, %4\n\t"
+      "buffer_load_dwordx4 %2, %3, %0 offen lds"
+      : "=&s"(copy)
       : "s"(lds_off), "v"(voff), "s"(rsrc), "s"(soff)
       : "m0");
 }

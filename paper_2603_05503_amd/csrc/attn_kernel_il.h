@@ -45,6 +45,8 @@
 // instructions later; a dot product's result is read by another kind of
 // instruction only behind an s_nop.
 #pragma once
+#include <float.h>
+
 #include "attn_kernel_2wg.h"
 #include "attn_named_regs.h"
 
@@ -81,7 +83,7 @@ struct IlRow : RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T> {
   using RB::DB;
   using RB::DS;
   using RB::ROWB;
-  static constexpr int SUB = il_sub(D, BQ, BK);         // keys per sub-tile
+  static constexpr int SUB = il_sub(D, BQ, BK);  // keys per sub-tile
   static constexpr int SPB = BK / SUB;           // sub-tiles per key block
   static_assert(BK % SUB == 0, "a key block is a whole number of sub-tiles");
   static constexpr int KBS = SUB / 32;           // 32-key sub-blocks per sub-tile
@@ -111,7 +113,7 @@ struct IlRow : RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T> {
     for (int db = 0; db < DB; ++db) v_base[db] = lds_base + RB::TILE_BYTES + this->v_addr[db];
   }
 
-  // K / V rows [row0, row0 + SUB) of the head into slot `slot` (0 or 1) of the K / V window
+  // K / V rows [row0, row0 + SUB) of the head into slot `slot` of the K / V window
   __device__ __forceinline__ void issue_k_sub(const u32x4 &Kres, int row0, int slot) const {
     LoadKs::issue(Kres, row0, this->ldsK_wave + slot * SUB_BYTES, this->tid, this->k_lane_off, this->kv_row_bytes);
   }
@@ -160,7 +162,7 @@ struct IlRow : RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T> {
   // of this sub-tile and the decision about the reference: m_run is the value subtracted in the
   // exponent; any value works as long as the exponentials stay in range, since numerator and
   // denominator carry the same factor.  It moves up to the running maximum only when that exceeds
-  // it by more than IL_REF_SLACK (always on a row's first sub-tile, whose reference is -inf); then
+  // it by more than IL_REF_SLACK (always on a row's first sub-tile, whose reference is the lowest float); then
   // alpha = 2^(old - new) < 1 and O and the row sum are rescaled at the end of the stage, else
   // alpha = 1 and they are left alone (O sits in AGPRs, where rescaling costs three instructions
   // per element).  Then, per group of 8 keys: 8 x (sc * s - m_run), 8 x exp2, 4 x round-and-pack
@@ -268,23 +270,25 @@ struct IlRow : RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T> {
     });
   }
 
-  // Start a row: Q^T operand into the AGPRs (lane (query l32, half g) holds d = 16 s + 8 g + [0,8) of
-  // k-slab s), negated when the scale is negative; zero accumulators; empty running state.
+  // Start a row: empty running state, zero accumulators, and the loads of the Q^T operand into the AGPRs (lane (query
+  // l32, half g) holds d = 16 s + 8 g + [0,8) of k-slab s), in flight on return.  finish_q, behind their wait, folds a
+  // negative scale into the operand's sign.
   __device__ __forceinline__ void begin_row(const uint16_t *qrow_ptr, float scale_log2e) {
-    const uint32_t flip = scale_log2e < 0.f ? 0x80008000u : 0u;
-    const uint16_t *qp = qrow_ptr + 8 * this->g;
-    static_unroll<DS / 2>([&](auto pair) {  // two k-slabs at a time: few registers in flight
-      const typename RB::Operand q0 = *reinterpret_cast<const typename RB::Operand *>(qp + 32 * pair);
-      const typename RB::Operand q1 = *reinterpret_cast<const typename RB::Operand *>(qp + 32 * pair + 16);
-      static_unroll<4>([&](auto i) { acc_write<A_Q + 8 * pair + i>(__builtin_bit_cast(float, q0[(int)i] ^ flip)); });
-      static_unroll<4>([&](auto i) { acc_write<A_Q + 8 * pair + 4 + i>(__builtin_bit_cast(float, q1[(int)i] ^ flip)); });
-    });
+    const uint16_t *const qp = qrow_ptr + 8 * this->g;
+    static_unroll<DS>([&](auto s) { global_to_acc_b128<A_Q + 4 * s, 32 * s>(qp); });
     static_unroll<16 * DB>([&](auto i) { acc_write<A_O + i>(0.f); });
     // a scale of exactly zero would turn the -inf of masked keys into NaN
     sc = fmaxf(fabsf(scale_log2e), 1e-30f);
-    this->m_run = -INFINITY;
+    this->m_run = -FLT_MAX;  // finite: leading keys at -inf have no weight, wherever a row's part begins
     this->l_run = 0.f;
     alpha = 1.f;
+  }
+  __device__ __forceinline__ void finish_q(float scale_log2e) const {
+    if (scale_log2e < 0.f)
+      static_unroll<4 * DS>([&](auto i) {
+        const uint32_t x = __builtin_bit_cast(uint32_t, acc_read<A_Q + i>());
+        acc_write<A_Q + i>(__builtin_bit_cast(float, x ^ 0x80008000u));
+      });
   }
 
   // Normalised rows as packed element pairs into the staging tile (row i at tile + i * OST).
@@ -318,6 +322,146 @@ __device__ __forceinline__ void il_claim_registers() {
 #undef CALIBATT_R10
 }
 
+// Runs one row of key blocks, or a part of one, from its first loads to the last O += P V.  col_at(i): key block of entry
+// i < n_tiles of the row's list; expand(i): called before entries of the next COLS are asked for, from entry i on (IV).
+// On return the sums lie in the registers and other waves may still read the tile windows.
+template <int BK, bool IV, int COLS, typename Row, typename ColAt, typename Expand>
+__device__ __forceinline__ void il_run_row(Row &rb, const uint16_t *qrow_ptr, const u32x4 &Kres, const u32x4 &Vres,
+                                           int N, int n_tiles, float scale_log2e, ColAt col_at, Expand expand) {
+  constexpr int SUB = Row::SUB, SPB = Row::SPB, LOADS = Row::LOADS_PER_WAVE;
+  // kept key blocks of the row, 64 at a time in one VGPR (lane j = entry j of the current 64)
+  int col_cache = n_tiles > 0 ? col_at(min(rb.lane, n_tiles - 1)) : 0;
+  auto col_of = [&](int t) {  // t inside the cached 64
+    return __builtin_amdgcn_readlane(col_cache, t & 63);
+  };
+  rb.begin_row(qrow_ptr, scale_log2e);
+  if (n_tiles <= 0) {
+    wait_vmem<0>();
+    return;
+  }
+  // The row's kept blocks as a stream of sub-tiles u_0, u_1, ... (SPB per block; a lone one is
+  // padded with one beyond the sequence, all of whose keys are masked).  Stage k:
+  // O += P V of u_(k-2), S = K Q^T of u_k, softmax of u_(k-1); at its start the loads of V of u_(k-1)
+  // and K of u_(k+1) are issued into the slots the stage before has finished with, and they land by
+  // its end.  Stages alternate between the two slots of the windows and the two S buffers.
+  const int n_sub = n_tiles * SPB;
+  const int n_stream = max(n_sub, 2);
+  // First key row of the next sub-tile of the stream (N beyond its end: rows there read as zeros
+  // and the keys are masked); called once per sub-tile, in order.
+  int nx_entry = 0, nx_part = 0, nx_col = col_of(0);
+  auto next_rows = [&]() {
+    if (nx_entry >= n_tiles) return N;
+    const int row0 = nx_col * BK + nx_part * SUB;
+    if (++nx_part == SPB) {
+      nx_part = 0;
+      ++nx_entry;
+      if ((nx_entry & 63) == 0 && nx_entry < n_tiles) {
+        if constexpr (IV) {
+          if (nx_entry % COLS == 0) expand(nx_entry);  // every wave has taken its entries of the piece that is replaced
+        }
+        col_cache = col_at(min(nx_entry + rb.lane, n_tiles - 1));
+      }
+      if (nx_entry < n_tiles) nx_col = col_of(nx_entry);
+    }
+    return __builtin_amdgcn_readfirstlane(row0);  // the loads take it from a scalar register
+  };
+  // keys of a sub-tile that starts at key row row0 and lie beyond the sequence get -inf
+#define CALIBATT_IL_MASK(PAR, row0) \
+  if ((row0) + SUB > N) rb.template mask_tail<PAR>(N - (row0) - 8 * rb.g);
+  // the loads of Q, K of u_0 and u_1 and V of u_0 go out together; stage 0 waits for the first two
+  const int r0 = next_rows();
+  const int r1 = next_rows();
+  rb.issue_k_sub(Kres, r0, 0);
+  rb.issue_k_sub(Kres, r1, 1);
+  rb.issue_v_sub(Vres, r0, 0);
+  wait_vmem<2 * LOADS>();
+  rb.finish_q(scale_log2e);
+  __syncthreads();
+  // stage 0: S of u_0
+  rb.template stage<0, false, true, false>();
+  CALIBATT_IL_MASK(0, r0)
+  wait_vmem<0>();
+  __syncthreads();
+  // stage 1: K of u_2; S of u_1, softmax of u_0
+  int row_a = r1;            // of u_(k-1) at the start of stage k (k even below)
+  int row_b = next_rows();   // of u_k
+  rb.issue_k_sub(Kres, row_b, 0);
+  rb.template stage<1, false, true, true>();
+  CALIBATT_IL_MASK(1, r1)
+  wait_vmem<0>();
+  __syncthreads();
+  bool odd_end = false;
+  for (int k = 2; k < n_stream; k += 2) {
+    // stage k: loads inside the stream: V of u_(k-1), K of u_(k+1) (beyond the stream: zeros into a slot nobody reads)
+    const int row_c = next_rows();
+    rb.template stage<0, true, true, true, true>(Vres, row_a, Kres, row_c);
+    CALIBATT_IL_MASK(0, row_b)
+    wait_vmem<0>();
+    __syncthreads();
+    odd_end = k + 1 == n_stream;
+    if (odd_end) break;
+    // stage k + 1: V of u_k, K of u_(k+2)
+    const int row_d = next_rows();
+    rb.template stage<1, true, true, true, true>(Vres, row_b, Kres, row_d);
+    CALIBATT_IL_MASK(1, row_c)
+    wait_vmem<0>();
+    __syncthreads();
+    row_a = row_c;
+    row_b = row_d;
+  }
+#undef CALIBATT_IL_MASK
+  // stage n_stream: V of the last sub-tile; O += P V of u_(n_stream-2), softmax of u_(n_stream-1)
+  // and stage n_stream + 1: O += P V of u_(n_stream-1)
+  if (odd_end) {
+    rb.issue_v_sub(Vres, row_b, 0);
+    rb.template stage<1, true, false, true>();
+    wait_vmem<0>();
+    __syncthreads();
+    rb.template stage<0, true, false, false>();
+  } else {
+    rb.issue_v_sub(Vres, row_a, 1);
+    rb.template stage<0, true, false, true>();
+    wait_vmem<0>();
+    __syncthreads();
+    rb.template stage<1, true, false, false>();
+  }
+}
+
+// The rows of block r, normalised and rounded, through LDS to the block itself and to the blocks [fan, fan + n_fan) that
+// repeat it; their log-sum-exps likewise.
+template <typename Row>
+__device__ __forceinline__ void il_store_row(const Row &rb, char *lds, const FwdDims &p, int b, int ht, int r,
+                                             const int32_t *fan, int n_fan, uint16_t *__restrict__ gout,
+                                             float *__restrict__ lse) {
+  constexpr int NT = Row::NT, CH = Row::CH, OST = Row::OST, BQ = NT / 2;
+  const int N = p.N;
+  __syncthreads();  // every wave is done with the tile windows
+  const float row_lse = rb.stage_rows(lds);
+  __syncthreads();
+  if (lse && rb.g == 0) {
+    float *const lse_head = lse + ((size_t)b * p.H + ht) * (size_t)N;
+    for (int f = -1; f < n_fan; ++f) {
+      const int row = (f < 0 ? r : fan[f]) * BQ + rb.row_in_block();
+      if (row < N) lse_head[row] = row_lse;
+    }
+  }
+  uint16_t *const out_head = gout + (size_t)b * p.out.b + (size_t)ht * p.out.h;
+  for (int f = -1; f < n_fan; ++f) {
+    const int rd = f < 0 ? r : fan[f];
+    const int rows_valid = min(BQ, N - rd * BQ);
+    uint16_t *dst = out_head + (size_t)rd * BQ * p.out.n;
+#pragma unroll 2
+    for (int L = rb.tid; L < BQ * CH; L += NT) {
+      const int row = L / CH;
+      const int cc = L % CH;
+      if (row < rows_valid) {
+        const u32x4 val = *reinterpret_cast<const u32x4 *>(lds + row * OST + cc * 16);
+        *reinterpret_cast<u32x4 *>(dst + (size_t)row * p.out.n + cc * 8) = val;
+      }
+    }
+  }
+}
+
 // Arguments and work distribution exactly as sparse_attn_fwd_kernel (attn_kernel_2wg.h).
 template <int D, int BQ, int BK, bool IV = false, typename T = Bf16>
 __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_num_vgpr(IL_VGPRS))) void sparse_attn_fwd_il_kernel(
@@ -327,8 +471,7 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
     int32_t *counter, const FwdDims p, const int32_t *__restrict__ iv_ptr, const uint32_t *__restrict__ iv,
     const int32_t *__restrict__ head_map, float *__restrict__ lse) {
   using Row = IlRow<D, BQ, BK, T>;
-  constexpr int NT = Row::NT, CH = Row::CH, ROWB = Row::ROWB, OST = Row::OST, LDS_BYTES = Row::LDS_BYTES, SUB = Row::SUB,
-                COLS = il_iv_cols(BQ);
+  constexpr int NT = Row::NT, ROWB = Row::ROWB, LDS_BYTES = Row::LDS_BYTES, COLS = il_iv_cols(BQ);
   il_claim_registers();
 
   // [K window: 2 sub-tiles][V window: 2 sub-tiles] (reused as the output staging tile), work-item mailbox,
@@ -337,7 +480,6 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
   int *const cols = reinterpret_cast<int *>(lds + LDS_BYTES + 64);
   Row rb(lds, (uint32_t)p.in.n * 2);
   const int tid = rb.tid;
-  const int lane = rb.lane;
   const int N = p.N;
   const int n_items = p.n_work * p.B;
   volatile int *const mailbox = reinterpret_cast<volatile int *>(lds + LDS_BYTES);
@@ -346,19 +488,6 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
     cur_group = __builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) % p.n_groups;  // HW_REG_XCC_ID[3:0]
   ResidencyClock residency;
   residency.start();
-#ifdef IL_PROFILE
-  // cycles of one wavefront in: full stages, waits for the tile loads, barriers, everything else
-  unsigned long long prof[4] = {0, 0, 0, 0};
-  unsigned long long prof_t = __builtin_amdgcn_s_memtime();
-#define IL_PROF(i)                                                \
-  {                                                               \
-    const unsigned long long now_ = __builtin_amdgcn_s_memtime(); \
-    prof[i] += now_ - prof_t;                                     \
-    prof_t = now_;                                                \
-  }
-#else
-#define IL_PROF(i)
-#endif
   for (int wg_item = blockIdx.x;;) {
     if (counter) {
       if (tid == 0) {
@@ -397,7 +526,8 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
     // IV: entries [chunk_lo, chunk_lo + COLS) of the row's list are expanded from its runs of
     // consecutive key blocks into LDS; every thread takes runs tid, tid + NT, ...
     int chunk_lo = 0;
-    auto expand_runs = [&]() {
+    auto expand_runs = [&](int from) {
+      chunk_lo = from;
       const int ib = iv_ptr[id], ie = iv_ptr[id + 1] - 1;  // the last word only terminates the row
       for (int i = ib + tid; i < ie; i += NT) {
         const uint32_t w = iv[i], w_next = iv[i + 1];
@@ -409,157 +539,20 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
     };
     if constexpr (IV) {
       n_tiles = (int)(iv[iv_ptr[id + 1] - 1] >> 16);
-      expand_runs();  // the previous item's readers are behind the barrier that ended it
+      expand_runs(0);  // the previous item's readers are behind the barrier that ended it
     }
     auto col_at = [&](int entry) { return IV ? cols[entry - chunk_lo] : col_idx[cbeg + entry]; };
-    // kept key blocks of the row, 64 at a time in one VGPR (lane j = entry j of the current 64)
-    int col_cache = n_tiles > 0 ? col_at(min(lane, n_tiles - 1)) : 0;
-    auto col_of = [&](int t) {  // t inside the cached 64
-      return __builtin_amdgcn_readlane(col_cache, t & 63);
-    };
-    {
-      int qrow = r * BQ + rb.row_in_block();
-      qrow = qrow < N ? qrow : N - 1;
-      rb.begin_row(gq + head_off + (size_t)qrow * p.in.n, p.scale_log2e);
-    }
-
-    if (n_tiles > 0) {
-      // The row's kept blocks as a stream of sub-tiles u_0, u_1, ... (SPB per block; a lone one is
-      // padded with one beyond the sequence, all of whose keys are masked).  Stage k:
-      // O += P V of u_(k-2), S = K Q^T of u_k, softmax of u_(k-1); at its start the loads of V of u_(k-1)
-      // and K of u_(k+1) are issued into the slots the stage before has finished with, and they land by
-      // its end.  Stages alternate between the two slots of the windows and the two S buffers.
-      constexpr int SPB = Row::SPB;
-      const int n_sub = n_tiles * SPB;
-      const int n_stream = max(n_sub, 2);
-      // First key row of the next sub-tile of the stream (N beyond its end: rows there read as zeros
-      // and the keys are masked); called once per sub-tile, in order.
-      int nx_entry = 0, nx_part = 0, nx_col = col_of(0);
-      auto next_rows = [&]() {
-        if (nx_entry >= n_tiles) return N;
-        const int row0 = nx_col * BK + nx_part * SUB;
-        if (++nx_part == SPB) {
-          nx_part = 0;
-          ++nx_entry;
-          if ((nx_entry & 63) == 0 && nx_entry < n_tiles) {
-            if constexpr (IV) {
-              if (nx_entry % COLS == 0) {  // every wave has taken its entries of the chunk that is replaced
-                chunk_lo = nx_entry;
-                expand_runs();
-              }
-            }
-            col_cache = col_at(min(nx_entry + lane, n_tiles - 1));
-          }
-          if (nx_entry < n_tiles) nx_col = col_of(nx_entry);
-        }
-        return row0;
-      };
-      // keys of a sub-tile that starts at key row row0 and lie beyond the sequence get -inf
-#define CALIBATT_IL_MASK(PAR, row0) \
-  if ((row0) + SUB > N) rb.template mask_tail<PAR>(N - (row0) - 8 * rb.g);
-      const int r0 = next_rows();
-      rb.issue_k_sub(Kres, r0, 0);
-      wait_vmem<0>();
-      __syncthreads();
-      // stage 0: K of u_1 streams in; S of u_0
-      const int r1 = next_rows();
-      rb.issue_k_sub(Kres, r1, 1);
-      rb.template stage<0, false, true, false>();
-      CALIBATT_IL_MASK(0, r0)
-      wait_vmem<0>();
-      __syncthreads();
-      // stage 1: V of u_0, K of u_2; S of u_1, softmax of u_0
-      rb.issue_v_sub(Vres, r0, 0);
-      int row_a = r1;            // of u_(k-1) at the start of stage k (k even below)
-      int row_b = next_rows();   // of u_k
-      rb.issue_k_sub(Kres, row_b, 0);
-      rb.template stage<1, false, true, true>();
-      CALIBATT_IL_MASK(1, r1)
-      wait_vmem<0>();
-      __syncthreads();
-      bool odd_end = false;
-      for (int k = 2; k < n_stream; k += 2) {
-        // stage k: loads inside the stream: V of u_(k-1), K of u_(k+1) (beyond the stream: zeros into a slot nobody reads)
-        const int row_c = next_rows();
-        IL_PROF(3);
-        rb.template stage<0, true, true, true, true>(Vres, row_a, Kres, row_c);
-        IL_PROF(0);
-        CALIBATT_IL_MASK(0, row_b)
-        wait_vmem<0>();
-        IL_PROF(1);
-        __syncthreads();
-        IL_PROF(2);
-        odd_end = k + 1 == n_stream;
-        if (odd_end) break;
-        // stage k + 1: V of u_k, K of u_(k+2)
-        const int row_d = next_rows();
-        IL_PROF(3);
-        rb.template stage<1, true, true, true, true>(Vres, row_b, Kres, row_d);
-        IL_PROF(0);
-        CALIBATT_IL_MASK(1, row_c)
-        wait_vmem<0>();
-        IL_PROF(1);
-        __syncthreads();
-        IL_PROF(2);
-        row_a = row_c;
-        row_b = row_d;
-      }
-#undef CALIBATT_IL_MASK
-      // stage n_stream: V of the last sub-tile; O += P V of u_(n_stream-2), softmax of u_(n_stream-1)
-      // and stage n_stream + 1: O += P V of u_(n_stream-1)
-      if (odd_end) {
-        rb.issue_v_sub(Vres, row_b, 0);
-        rb.template stage<1, true, false, true>();
-        wait_vmem<0>();
-        __syncthreads();
-        rb.template stage<0, true, false, false>();
-      } else {
-        rb.issue_v_sub(Vres, row_a, 1);
-        rb.template stage<0, true, false, true>();
-        wait_vmem<0>();
-        __syncthreads();
-        rb.template stage<1, true, false, false>();
-      }
-    }
-
-    // ---- normalise, stage in LDS, store to the block and its repeat targets ----
-    __syncthreads();  // every wave is done with the tile windows
-    const float row_lse = rb.stage_rows(lds);
-    __syncthreads();
+    const int qrow = min(r * BQ + rb.row_in_block(), N - 1);
+    il_run_row<BK, IV, COLS>(rb, gq + head_off + (size_t)qrow * p.in.n, Kres, Vres, N, n_tiles, p.scale_log2e, col_at,
+                             expand_runs);
     const int fbeg = fan_ptr[item];
-    const int fend = fan_ptr[item + 1];
-    if (lse && head_ok && rb.g == 0) {
-      float *const lse_head = lse + ((size_t)b * p.H + ht) * (size_t)N;
-      for (int f = fbeg - 1; f < fend; ++f) {
-        const int row = (f < fbeg ? r : fan_dst[f]) * BQ + rb.row_in_block();
-        if (row < N) lse_head[row] = row_lse;
-      }
-    }
-    uint16_t *const out_head = gout + (size_t)b * p.out.b + (size_t)ht * p.out.h;
-    for (int f = fbeg - 1; head_ok && f < fend; ++f) {
-      const int rd = f < fbeg ? r : fan_dst[f];
-      const int rows_valid = min(BQ, N - rd * BQ);
-      uint16_t *dst = out_head + (size_t)rd * BQ * p.out.n;
-#pragma unroll 2
-      for (int L = tid; L < BQ * CH; L += NT) {
-        const int row = L / CH;
-        const int cc = L % CH;
-        if (row < rows_valid) {
-          const u32x4 val = *reinterpret_cast<const u32x4 *>(lds + row * OST + cc * 16);
-          *reinterpret_cast<u32x4 *>(dst + (size_t)row * p.out.n + cc * 8) = val;
-        }
-      }
-    }
+    const int n_fan = fan_ptr[item + 1] - fbeg;
+    if (head_ok) il_store_row(rb, lds, p, b, ht, r, fan_dst + fbeg, n_fan, gout, lse);
     if (!counter) break;
     __syncthreads();  // staging tile fully read before the next item's loads overwrite it
   }  // work-item loop
 
   if (counter && blockIdx.x == 0 && tid == 0) residency.store(counter);
-#ifdef IL_PROFILE
-  if (counter && blockIdx.x == 2 && tid == 0)
-    for (int i = 0; i < 4; ++i) counter[12 + i] = (int32_t)(prof[i] >> 6);
-#endif
-#undef IL_PROF
   // Last workgroup out re-arms the counters for the next launch.
   if (counter && tid == 0) {
     __threadfence();

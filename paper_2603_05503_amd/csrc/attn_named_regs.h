@@ -123,4 +123,24 @@ __device__ __forceinline__ void global_to_acc_b128(const void *ptr) {
   asm volatile("global_load_dwordx4 a[%1:%2], %0, off offset:%3" : : "v"(ptr), "n"(DST), "n"(DST + 3), "n"(OFF));
 }
 
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+// a pair of floats at agent scope (8-byte aligned)
+__device__ __forceinline__ f32x2 agent_load_f32x2(const float *at) {
+  return __builtin_bit_cast(f32x2, __hip_atomic_load((const uint64_t *)at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ __forceinline__ void agent_store_f32x2(float *at, f32x2 x) {
+  __hip_atomic_store((uint64_t *)at, __builtin_bit_cast(uint64_t, x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// 16 bytes of global memory at base (wave-uniform) + off into arch VGPRs DST..DST+3, and out of AGPRs SRC..SRC+3, at agent
+// scope: the load is not served from what this XCD's caches hold, the store goes through them.  The wait states are those
+// of a base that a vector instruction has just put into scalar registers (csrc/check_sgpr_waits.py).
+template <int DST>
+__device__ __forceinline__ void agent_load_named_b128(const void *base, uint32_t off) {
+  asm volatile("s_nop 4\n\tglobal_load_dwordx4 v[%2:%3], %0, %1 sc1" : : "v"(off), "s"(base), "n"(DST), "n"(DST + 3) : "memory");
+}
+template <int SRC>
+__device__ __forceinline__ void agent_store_acc_b128(void *base, uint32_t off) {
+  asm volatile("s_nop 4\n\tglobal_store_dwordx4 %0, a[%2:%3], %1 sc1" : : "v"(off), "s"(base), "n"(SRC), "n"(SRC + 3) : "memory");
+}
+
 }  // namespace calibatt_dev

@@ -14,45 +14,12 @@
 #include "calibration_kernels.h"
 #include "attn_kernel_il.h"
 #include "calibatt.h"
+#include "launch.h"
+#include "split_plan.h"
 
 namespace {
 using namespace calibatt_dev;
-
-struct FwdPtrs {
-  const uint16_t *q, *k, *v;
-  uint16_t *out;
-  const int32_t *row_ptr, *col_idx, *work, *fan_ptr, *fan_dst;
-  int32_t *counter;
-  const int32_t *iv_ptr;  // interval form of the kept-block lists, or NULL
-  const uint32_t *iv;
-  const int32_t *head_map;  // tensor head of each pattern head, or NULL
-  float *lse;               // log-sum-exp output, or NULL
-  int dtype;                // CALIBATT_BF16 or CALIBATT_F16
-};
-
-// Per-device launch facts of one kernel: how many workgroups the whole device holds at a time.
-// Looked up on the first call per device.  Concurrent first calls all compute the same figure, so
-// the slot is a plain atomic (0 = not known yet) and no lock is taken.
-struct DevInfo {
-  std::atomic<int> slots[64];
-};
-
-template <typename Kernel>
-int prepare(Kernel kernel, int threads, int smem, DevInfo &info, int &slots) {
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return CALIBATT_ERR_LAUNCH;
-  slots = info.slots[dev].load(std::memory_order_acquire);
-  if (slots > 0) return CALIBATT_OK;
-  int cus = 0, per_cu = 0;
-  if (hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kernel, threads, smem) != hipSuccess ||
-      cus <= 0 || per_cu <= 0)
-    return CALIBATT_ERR_LAUNCH;
-  slots = cus * per_cu;
-  info.slots[dev].store(slots, std::memory_order_release);
-  return CALIBATT_OK;
-}
+using namespace calibatt_host;
 
 // Registers a kernel's dynamic LDS ceiling once per device (same scheme as above).
 struct DevReady {
@@ -66,16 +33,6 @@ int register_lds(Kernel kernel, int smem, DevReady &state, int &dev) {
     return CALIBATT_ERR_LAUNCH;
   state.ready[dev].store(1, std::memory_order_release);
   return CALIBATT_OK;
-}
-
-// Launches through the call that reports its own status: the runtime's "last error" may still hold
-// an unrelated error left by earlier calls of the host program.
-template <typename Kernel, typename... Args>
-int launch_kernel(Kernel kernel, unsigned grid, int threads, int smem, hipStream_t stream, Args... args) {
-  void *argv[] = {(void *)&args...};
-  return hipLaunchKernel((const void *)kernel, dim3(grid), dim3(threads), argv, smem, stream) == hipSuccess
-             ? CALIBATT_OK
-             : CALIBATT_ERR_LAUNCH;
 }
 
 // Grid of the two-workgroup kernel: persistent workgroups popping from the counters when there are
@@ -695,6 +652,15 @@ extern "C" int calibatt_sparse_attn_fwd_ex(const void *q, const void *k, const v
                                            int N, int D, int block_q, int block_k,
                                            const calibatt_pattern *pattern, float scale,
                                            const calibatt_fwd_options *options, void *stream) {
+  return calibatt_sparse_attn_fwd_split(q, k, v, out, B, H, N, D, block_q, block_k, pattern, scale, options, nullptr,
+                                        nullptr, 0, stream);
+}
+
+extern "C" int calibatt_sparse_attn_fwd_split(const void *q, const void *k, const void *v, void *out, int B, int H,
+                                              int N, int D, int block_q, int block_k,
+                                              const calibatt_pattern *pattern, float scale,
+                                              const calibatt_fwd_options *options, const calibatt_split *split,
+                                              void *workspace, int64_t workspace_bytes, void *stream) {
   if (!options) return CALIBATT_ERR_NULL;
   if (options->dtype != CALIBATT_BF16 && options->dtype != CALIBATT_F16) return CALIBATT_ERR_UNSUPPORTED;
   if (options->kernel != CALIBATT_KERNEL_AUTO && options->kernel != CALIBATT_KERNEL_TWO_WORKGROUPS &&
@@ -729,6 +695,18 @@ extern "C" int calibatt_sparse_attn_fwd_ex(const void *q, const void *k, const v
   if (intervals && nbk > 65535) return CALIBATT_ERR_UNSUPPORTED;
   if (!strides_ok(*in_strides, B, H, N, D) || !strides_ok(*out_strides, B, H, N, D)) return CALIBATT_ERR_SHAPE;
   if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out) & 15) return CALIBATT_ERR_SHAPE;
+  if (split && split->n_parts == 0) split = nullptr;  // nothing to gain: whole rows
+  if (split) {
+    if (options->kernel == CALIBATT_KERNEL_TWO_WORKGROUPS) return CALIBATT_ERR_UNSUPPORTED;
+    if (split->B != B || split->n_parts < 0 || split->n_parts % CALIBATT_GROUPS || split->n_rows < 0 ||
+        split->n_slots < 0)
+      return CALIBATT_ERR_PATTERN_MISMATCH;
+    if (!split->parts || (split->n_slots > 0 && (!split->arrivals || !workspace))) return CALIBATT_ERR_NULL;
+    if ((((uintptr_t)split->parts | (uintptr_t)workspace) & 15) || ((uintptr_t)split->arrivals & 3))
+      return CALIBATT_ERR_SHAPE;
+    if (workspace_bytes < calibatt_split_workspace_bytes(split, block_q, D))
+      return CALIBATT_ERR_BUFFER_TOO_SMALL;
+  }
 
   FwdPtrs a;
   a.q = (const uint16_t *)q;
@@ -760,7 +738,8 @@ extern "C" int calibatt_sparse_attn_fwd_ex(const void *q, const void *k, const v
   p.out = Strides{out_strides->b, out_strides->h, out_strides->n};
   hipStream_t s = (hipStream_t)stream;
 #define CALIBATT_CASE(d, bq, bk) \
-  if (D == d && block_q == bq && block_k == bk) return launch<d, bq, bk>(a, p, options->kernel, s);
+  if (D == d && block_q == bq && block_k == bk)                 \
+    return split ? launch_split<d, bq, bk>(a, p, *split, (float *)workspace, s) : launch<d, bq, bk>(a, p, options->kernel, s);
   CALIBATT_CASE(128, 128, 128)
   CALIBATT_CASE(128, 128, 64)
   CALIBATT_CASE(128, 128, 96)

@@ -1,0 +1,158 @@
+// Plan of a forward whose rows of kept blocks are cut along the keys (calibatt_plan_split): which part of which row
+// every workgroup takes.  Integer and cost arithmetic on the host, no device calls.
+#include "split_plan.h"
+
+#include <algorithm>
+#include <new>
+#include <vector>
+
+#include "calibatt.h"
+
+namespace {
+
+struct Part {
+  int32_t item, id, first, count, part, n_parts, slot, row, b;
+};
+
+// Costs in stages of 64 keys, fitted to sweeps of the longest part over 41 shapes (1 to 40 heads of 1 024 to 35 100
+// tokens, densities 0.15 to 0.9, every block size and head dimension): what a part costs beside its stages (its start, its
+// sums to memory and back) and how the longest part weighs against an even share of the whole.  The lengths chosen
+// take 1.6 % more time than the best ones of the sweeps, 14 % at most.
+constexpr double PART_COST = 8.0, CHAIN_WEIGHT = 0.4;
+// Workgroups that the device holds at a time: 256 CUs, two each of 128 queries, four of 64.
+constexpr int slots_of(int block_q) { return block_q >= 128 ? 512 : 1024; }
+// Above so many stages per slot whole rows are the better choice: their workgroups pop from queues that keep an XCD at one head,
+// and their tail is small beside the call.  128-key blocks, us whole / by plan: 44 000 blocks (172 stages a slot) 470 /
+// 369, 59 600 514 / 491, 70 300 636 / 641, 141 000 1 112 / 1 123; 64-query blocks: 117 000 833 / 742.
+constexpr int64_t MAX_STAGES_PER_SLOT = 270;
+
+int32_t parts_of(int32_t len, int32_t longest) {
+  return std::max(1, std::min<int32_t>(CALIBATT_MAX_PARTS, len / longest + (len % longest != 0)));
+}
+
+// The longest part, in key blocks, whose estimated time is least: an even share of all work and the longest part,
+// whichever is larger, smoothly.  Rows stay whole where cutting them promises less than 3 %: the estimate does not see
+// that 512 equal rows fill the device exactly (4 heads of 16 380 tokens, all blocks kept: 483 us, cut in two 496).
+int32_t choose_longest(const std::vector<int32_t> &rows_of_length, int B, double stages, int slots) {
+  const int32_t max_row = (int32_t)rows_of_length.size() - 1;
+  int32_t best = max_row;
+  double best_cost = 0.0;
+  for (int32_t longest = max_row;; longest = longest * 7 / 8) {
+    double parts = 0.0, blocks = 0.0, chain = 0.0;
+    for (int32_t len = 0; len <= max_row; ++len) {
+      if (!rows_of_length[(size_t)len]) continue;
+      const int32_t k = parts_of(len, longest);
+      parts += (double)k * rows_of_length[(size_t)len];
+      blocks += (double)len * rows_of_length[(size_t)len];
+      chain = std::max(chain, (double)((len + k - 1) / k));
+    }
+    const double share = B * (blocks * stages + PART_COST * parts) / slots, cost = share * share +
+        CHAIN_WEIGHT * chain * stages * CHAIN_WEIGHT * chain * stages;
+    if (longest == max_row) best_cost = 0.97 * 0.97 * cost;
+    else if (cost < best_cost) best = longest, best_cost = cost;
+    if (longest <= 1) return best;
+  }
+}
+
+}  // namespace
+
+extern "C" int calibatt_plan_split(const calibatt_pattern *pattern, int B, int max_blocks, int32_t *parts,
+                                   int64_t cap_parts, calibatt_split *split) {
+  if (!pattern || !split || !pattern->row_ptr || !pattern->work || !pattern->fan_ptr) return CALIBATT_ERR_NULL;
+  if (B <= 0 || max_blocks < 0 || cap_parts < 0 || pattern->n_work < 0 || pattern->block_k <= 0 || pattern->nbq <= 0) return CALIBATT_ERR_SHAPE;
+  *split = calibatt_split{};
+  split->B = B;
+  const int n = pattern->n_work;
+  const double stages = pattern->block_k / 64.0;
+  const int slots = slots_of(pattern->block_q);
+  if (n == 0 || (int64_t)n * B > 1 << 20 || (max_blocks == 0 && (double)pattern->nnz * B * stages > (double)MAX_STAGES_PER_SLOT * slots))
+    return CALIBATT_OK;
+  const int32_t *const row_ptr = pattern->row_ptr;
+  auto length = [&](int32_t id) { return row_ptr[id + 1] - row_ptr[id]; };
+  try {
+    // rows in the order of heads and query blocks
+    std::vector<std::pair<int32_t, int32_t>> rows((size_t)n);
+    int32_t max_row = 1;
+    for (int i = 0; i < n; ++i) {
+      rows[(size_t)i] = {pattern->work[i], i};
+      max_row = std::max(max_row, length(pattern->work[i]));
+    }
+    std::sort(rows.begin(), rows.end());
+    int32_t longest = max_blocks;
+    if (longest == 0) {
+      std::vector<int32_t> rows_of_length((size_t)max_row + 1, 0);
+      for (const auto &r : rows) ++rows_of_length[(size_t)length(r.first)];
+      longest = choose_longest(rows_of_length, B, stages, slots);
+    }
+    // cut into parts of nearly equal length
+    std::vector<Part> all;
+    int32_t n_slots = 0, n_rows = 0;
+    double total = 0.0;
+    auto cost = [&](const Part &p) { return p.count * stages + PART_COST; };
+    for (int b = 0; b < B; ++b)
+      for (const auto &r : rows) {
+        const int32_t len = length(r.first), k = parts_of(len, longest);
+        for (int32_t j = 0; j < k; ++j) {
+          const int32_t lo = (int32_t)((int64_t)len * j / k), hi = (int32_t)((int64_t)len * (j + 1) / k);
+          all.push_back({r.second, r.first, lo, hi - lo, j, k, k > 1 ? n_slots : 0, k > 1 ? n_rows : 0, b});
+          total += cost(all.back());
+        }
+        if (k > 1) n_slots += k, ++n_rows;
+      }
+    // eight ranges of equal cost, one per XCD, of the parts ordered by batch, head and the keys in their middle, so that
+    // an XCD's workgroups share keys in its L2; in each the longest parts first
+    if (pattern->col_idx) {
+      auto middle = [&](const Part &p) {
+        return p.count ? pattern->col_idx[row_ptr[p.id] + p.first + p.count / 2] : 0;
+      };
+      const int nbq = pattern->nbq;
+      std::stable_sort(all.begin(), all.end(), [&](const Part &a, const Part &b) {
+        if (a.b != b.b) return a.b < b.b;
+        return a.id / nbq != b.id / nbq ? a.id / nbq < b.id / nbq : middle(a) < middle(b);
+      });
+    }
+    std::vector<Part> list[CALIBATT_GROUPS];
+    double before = 0.0;
+    for (const Part &p : all) {
+      const int x = (int)((before + 0.5 * cost(p)) * CALIBATT_GROUPS / total);
+      list[std::min(x, CALIBATT_GROUPS - 1)].push_back(p);
+      before += cost(p);
+    }
+    size_t most = 0;
+    for (auto &l : list) {
+      std::stable_sort(l.begin(), l.end(), [](const Part &a, const Part &b) { return a.count > b.count; });
+      most = std::max(most, l.size());
+    }
+    const int64_t n_parts = (int64_t)most * CALIBATT_GROUPS;
+    if (n_parts > 0x7fffffffLL / CALIBATT_PART_WORDS) return CALIBATT_ERR_SHAPE;
+    split->n_parts = (int32_t)n_parts;
+    split->n_rows = n_rows;
+    split->n_slots = n_slots;
+    if (!parts) return CALIBATT_OK;
+    if (cap_parts < n_parts) return CALIBATT_ERR_BUFFER_TOO_SMALL;
+    // one part of every XCD's list in turn, as workgroups are dealt to the XCDs; a list that has ended gives -1
+    const int32_t *const iv_ptr = pattern->iv_ptr;
+    for (size_t i = 0; i < most; ++i)
+      for (int x = 0; x < CALIBATT_GROUPS; ++x) {
+        int32_t *const rec = parts + (i * CALIBATT_GROUPS + (size_t)x) * CALIBATT_PART_WORDS;
+        if (i >= list[x].size()) {
+          std::fill(rec, rec + CALIBATT_PART_WORDS, -1);
+          continue;
+        }
+        const Part &p = list[x][i];
+        const int32_t fan = pattern->fan_ptr[p.item];
+        const int32_t words[CALIBATT_PART_WORDS] = {
+            p.id, p.first, p.count, row_ptr[p.id] + p.first,
+            iv_ptr ? iv_ptr[p.id] : 0, iv_ptr ? iv_ptr[p.id + 1] - 1 : 0, fan, pattern->fan_ptr[p.item + 1] - fan,
+            p.part | p.n_parts << 16, p.b, p.slot, p.row};
+        std::copy(words, words + CALIBATT_PART_WORDS, rec);
+      }
+  } catch (const std::bad_alloc &) {
+    return CALIBATT_ERR_NOMEM;
+  }
+  return CALIBATT_OK;
+}
+
+extern "C" int64_t calibatt_split_workspace_bytes(const calibatt_split *split, int block_q, int D) {
+  return split ? (int64_t)split->n_slots * calibatt_part_bytes(block_q, D) : 0;
+}

@@ -1,0 +1,81 @@
+"""The plan of a split forward: every kept block of every computed row in exactly one part, in order."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+from paper_2603_05503_amd import binding
+from workloads import random_mask
+
+
+def _records(plan):
+    split, parts = plan
+    assert parts.shape == (split.n_parts, 12) and split.n_parts % 8 == 0
+    live = parts[parts[:, 0] >= 0]
+    assert (parts[parts[:, 0] < 0] == -1).all()
+    return split, live
+
+
+@pytest.mark.parametrize("H,N,bq,bk,density,order", [(1, 1, 128, 128, 1.0, 4), (3, 1000, 64, 64, 0.4, 1), (2, 5000, 128, 96, 0.7, 4),
+                                                     (9, 3000, 128, 192, 0.2, 3), (5, 4000, 64, 128, 1.0, 0)])
+@pytest.mark.parametrize("max_blocks", [0, 1, 2, 3, 7, 1000])
+@pytest.mark.parametrize("intervals", [False, True])
+def test_parts_cover_every_row(lib, H, N, bq, bk, density, order, max_blocks, intervals):
+    nbq, nbk = -(-N // bq), -(-N // bk)
+    mask, repeat = random_mask(N + bk, H, nbq, nbk, density, 0.2 if nbq > 3 else 0.0, tail_partial=N % bq != 0)
+    mask[0, nbq // 2, :] = 0  # an empty row
+    hp = lib.compile_pattern(mask, repeat, H, N, bq, bk, order)
+    iv_ptr = hp.encode_intervals()[0] if intervals else None
+    split, rec = _records(hp.plan_split(2, max_blocks, iv_ptr))
+    assert split.B == 2
+    item_of = {int(i): w for w, i in enumerate(hp.work)}
+    slots, cut_rows = [], []
+    assert sorted(set(rec[:, 0].tolist())) == sorted(item_of)
+    for b, row in ((b, row) for b in range(2) for row in item_of):
+        mine = rec[(rec[:, 0] == row) & (rec[:, 9] == b)]
+        parts, of = mine[:, 8] & 0xffff, mine[:, 8] >> 16
+        mine, of = mine[np.argsort(parts)], of[np.argsort(parts)]
+        n, length = len(mine), int(hp.row_ptr[row + 1] - hp.row_ptr[row])
+        assert sorted(parts.tolist()) == list(range(n)) and (of == n).all() and n <= 16
+        ends = np.append(mine[:, 1], length)
+        assert ends[0] == 0 and (ends[1:] - ends[:-1] == mine[:, 2]).all()
+        assert n == 1 or (mine[:, 2] > 0).all()
+        if max_blocks:
+            assert n == max(1, min(16, -(-length // max_blocks)))
+        assert (mine[:, 3] == hp.row_ptr[row] + mine[:, 1]).all()
+        assert (mine[:, 4:6] == ([iv_ptr[row], iv_ptr[row + 1] - 1] if intervals else [0, 0])).all()
+        w = item_of[row]
+        assert (mine[:, 6:8] == [hp.fan_ptr[w], hp.fan_ptr[w + 1] - hp.fan_ptr[w]]).all()
+        if n > 1:
+            assert len(set(mine[:, 10])) == 1 and len(set(mine[:, 11])) == 1
+            slots += range(mine[0, 10], mine[0, 10] + n)
+            cut_rows.append(int(mine[0, 11]))
+    assert sorted(slots) == list(range(split.n_slots))
+    assert sorted(cut_rows) == list(range(split.n_rows))
+
+
+def test_same_cuts_for_every_order_and_no_plan_for_long_calls(lib):
+    mask, repeat = random_mask(5, 6, 40, 40, 0.5, 0.2, keep_diagonal=True)
+    cuts = []
+    for order in range(5):
+        _, rec = _records(lib.compile_pattern(mask, repeat, 6, 40 * 128, 128, 128, order).plan_split(1))
+        cuts.append(sorted(map(tuple, rec[:, [0, 1, 2, 8, 9]].tolist())))
+    assert all(c == cuts[0] for c in cuts)
+    hp = lib.compile_pattern(np.ones((8, 100, 100), np.uint8), None, 8, 100 * 128, 128, 128)
+    assert hp.plan_split(1) is None  # 312 stages of work per workgroup that the device holds
+    assert lib.compile_pattern(np.ones((6, 100, 100), np.uint8), None, 6, 100 * 128, 128, 128).plan_split(1) is not None
+
+
+def test_workspace_and_refusals(lib):
+    raw = lib.load_library()
+    hp = lib.compile_pattern(np.ones((2, 10, 10), np.uint8), None, 2, 1280, 128, 128)
+    split, _ = hp.plan_split(2, 4)
+    assert (split.n_rows, split.n_slots) == (40, 120)
+    assert raw.calibatt_split_workspace_bytes(C.byref(split), 128, 128) == 120 * (128 * 128 + 256 * 2) * 4
+    for B, max_blocks, status in ((0, 0, -2), (1, -1, -2), (1, 4, -7)):
+        c, out = binding._CPattern(), binding._CSplit()
+        c.n_work, c.block_k, c.nnz, c.nbq = hp.n_work, 128, hp.nnz, 10
+        c.row_ptr, c.work, c.fan_ptr = (a.ctypes.data for a in (hp.row_ptr, hp.work, hp.fan_ptr))
+        buf = np.empty(12, np.int32)
+        assert raw.calibatt_plan_split(C.byref(c), B, max_blocks, binding._ptr(buf, C.c_int32), 1, C.byref(out)) == status
+    assert raw.calibatt_plan_split(None, 1, 0, None, 0, C.byref(out)) == -1
