@@ -64,12 +64,10 @@ constexpr int IL_AHEAD = 4;   // MFMAs between the issue of an operand's LDS rea
 // keys; three or five of 32 for 96 and 160).  A stage costs a barrier and, where few wavefronts are in flight, the
 // latency of its tile loads, however short it is: with sub-tiles of 64 instead of 32 keys, key blocks of 64 at 128
 // queries take 2.77 instead of 2.96 ms (20 heads of 32 760 tokens, D = 128) and 1.72 instead of 1.89 (D = 64), and one
-// row of blocks by itself on its CU four fifths of the time.  64-query blocks at D = 128 with key blocks of 64 keep 32: a
-// workgroup of two wavefronts then takes 32 KB of LDS, four of them fill a CU's eight wavefronts, and 3.35 ms become
-// 4.14 with 64 (D = 64 takes half the LDS).
-constexpr __host__ __device__ int il_sub(int d, int bq, int bk) {
-  return bk % 64 != 0 || (bq == 64 && d == 128 && bk == 64) ? 32 : 64;
-}
+// row of blocks by itself on its CU four fifths of the time.  64-query blocks at D = 128 take 32: a workgroup of two
+// wavefronts then has 32 KB of LDS, and four of them fill a CU's eight wavefronts, instead of two with 64: 3.39 ms
+// instead of 4.08 with key blocks of 128, 3.35 instead of 4.14 with 64 (D = 64 takes half the LDS).
+constexpr __host__ __device__ int il_sub(int d, int bq, int bk) { return bk % 64 != 0 || (bq == 64 && d == 128) ? 32 : 64; }
 
 // Columns of a row in interval form that are expanded into LDS at a time.  With 64-query blocks the list stays in 4 KB,
 // so that four workgroups fit on a CU: 8 KB leave room for three, 2.04 -> 1.84 ms at D = 64, 3.74 -> 3.35 at D = 128
