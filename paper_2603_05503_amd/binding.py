@@ -1,8 +1,8 @@
 """ctypes marshalling for include/calibatt.h."""
 from __future__ import annotations
 
-import contextlib
 import ctypes as C
+import functools
 import os
 import threading
 from dataclasses import dataclass
@@ -314,6 +314,13 @@ def compile_pattern(mask, repeat, H, N, block_q, block_k, order=4) -> HostPatter
     )
 
 
+class _StreamState:
+    """What the calls of one stream use of a pattern."""
+
+    def __init__(self, c, words, splits):
+        self.c, self.c_ref, self.words, self.splits = c, C.byref(c), words, splits
+
+
 class DevicePattern:
     """The six index arrays as int32 torch tensors on the GPU plus the C struct
     that points at them."""
@@ -384,8 +391,8 @@ class DevicePattern:
         self.counter = words[:16] if persistent else None
         self.c.work_counter = self.counter.data_ptr() if persistent else None
         self._stream_of_c = None  # stream handle that uses self.c
-        self._own = (self.c, words, self._splits_with(words))
-        self._per_stream = {}     # other streams: (clone of the struct, its own words, splits with its own arrivals)
+        self._own = _StreamState(self.c, words, self._splits_with(words))
+        self._per_stream = {}     # other streams: clone of the struct, its own words, splits with its own arrivals
         self._lock = threading.Lock()
 
     def _splits_with(self, words):
@@ -414,18 +421,14 @@ class DevicePattern:
                     with torch.cuda.stream(torch.cuda.ExternalStream(stream_handle, device=self.counter.device)):
                         words = torch.zeros(self._words, dtype=torch.int32, device=self.counter.device)
                 clone.work_counter = words.data_ptr()
-                self._per_stream[stream_handle] = (clone, words, self._splits_with(words))
+                self._per_stream[stream_handle] = _StreamState(clone, words, self._splits_with(words))
             return self._per_stream[stream_handle]
 
     def c_for(self, stream_handle: int):
         """The C struct to pass for a call on ``stream_handle``.  Calls on different streams may overlap on
         the GPU, and overlapping calls must not share the scheduler's work counters: every stream after the
         first gets a clone of the struct that points at counters of its own (the index arrays are shared)."""
-        return self._for_stream(stream_handle)[0]
-
-    def split_for(self, stream_handle: int, B: int):
-        """The split of a call of batch ``B`` on ``stream_handle`` (None: whole rows)."""
-        return self._for_stream(stream_handle)[2].get(B)
+        return self._for_stream(stream_handle).c
 
     @property
     def nnz(self) -> int:
@@ -452,47 +455,64 @@ def sparse_attn_fwd(q, k, v, out, pattern: DevicePattern, scale: float,
     import torch
 
     lib = load_library()
-    for t in (q, k, v, out):
-        if not (t.is_cuda and t.dtype in (torch.bfloat16, torch.float16) and t.dim() == 4 and t.stride(3) == 1):
-            raise ValueError("q, k, v, out must be bf16 or fp16 CUDA tensors [B, H, N, D] with contiguous D")
-        if t.shape != q.shape or t.dtype != q.dtype:
-            raise ValueError("q, k, v, out must have the same shape and element type")
-    if not (q.stride() == k.stride() == v.stride()):
+    shape, dtype, strides, out_strides = q.shape, q.dtype, q.stride(), out.stride()
+    if not (len(shape) == 4 and dtype in (torch.bfloat16, torch.float16) and strides[3] == 1 and len(out_strides) == 4
+            and out_strides[3] == 1 and q.is_cuda and k.is_cuda and v.is_cuda and out.is_cuda
+            and k.dtype == dtype and v.dtype == dtype and out.dtype == dtype
+            and k.shape == shape and v.shape == shape and out.shape == shape
+            and k.stride() == strides and v.stride() == strides):
+        for t in (q, k, v, out):
+            if not (t.is_cuda and t.dtype in (torch.bfloat16, torch.float16) and t.dim() == 4 and t.stride(3) == 1):
+                raise ValueError("q, k, v, out must be bf16 or fp16 CUDA tensors [B, H, N, D] with contiguous D")
+            if t.shape != q.shape or t.dtype != q.dtype:
+                raise ValueError("q, k, v, out must have the same shape and element type")
         raise ValueError("q, k, v must share their strides")
-    B, H, N, D = q.shape
+    B, H, N, D = shape
     if lse is not None and not (lse.is_cuda and lse.dtype == torch.float32 and lse.is_contiguous()
                                 and tuple(lse.shape) == (B, H, N)):
         raise ValueError("lse must be a contiguous fp32 CUDA tensor [B, H, N]")
     bq = pattern.host.block_q if block_q is None else block_q
     bk = pattern.host.block_k if block_k is None else block_k
     stream, other = _stream_of(stream, q.device)
-    pointers = (q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr())
-    packed = all(t.is_contiguous() for t in (q, k, v, out))
-    c, split = C.byref(pattern.c_for(stream)), None
-    if kernel != KERNEL_TWO_WORKGROUPS:
-        split = pattern.split_for(stream, B)
-    if split is None and packed and lse is None and q.dtype == torch.bfloat16 and kernel == KERNEL_AUTO:
-        st = lib.calibatt_sparse_attn_fwd(*pointers, B, H, N, D, bq, bk, c, float(scale), stream)
+    state = pattern._for_stream(stream)
+    split = None if kernel == KERNEL_TWO_WORKGROUPS else state.splits.get(B)
+    packed = q.is_contiguous() and out.is_contiguous()
+    args = (q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), B, H, N, D, bq, bk, state.c_ref, float(scale))
+    if split is None and packed and lse is None and dtype == torch.bfloat16 and kernel == KERNEL_AUTO:
+        st = lib.calibatt_sparse_attn_fwd(*args, stream)
     else:
-        si = _CStrides(q.stride(0), q.stride(1), q.stride(2))
-        so = _CStrides(out.stride(0), out.stride(1), out.stride(2))
+        si, so = _CStrides(*strides[:3]), _CStrides(*out_strides[:3])
         opt = _CFwdOptions(None if packed else C.pointer(si), None if packed else C.pointer(so),
-                           0 if q.dtype == torch.bfloat16 else 1, None if lse is None else lse.data_ptr(), int(kernel))
+                           0 if dtype == torch.bfloat16 else 1, None if lse is None else lse.data_ptr(), int(kernel))
         if split is None:
-            st = lib.calibatt_sparse_attn_fwd_ex(*pointers, B, H, N, D, bq, bk, c, float(scale), C.byref(opt), stream)
+            st = lib.calibatt_sparse_attn_fwd_ex(*args, C.byref(opt), stream)
+        elif other is None:
+            st = _split_call(lib, args, opt, split, bq, D, q.device, stream)
         else:
-            nbytes = lib.calibatt_split_workspace_bytes(C.byref(split), bq, D)
-            workspace = _empty(nbytes // 4, torch.float32, q.device, other)
-            with contextlib.nullcontext() if other is None else torch.cuda.stream(other):
-                # a captured call counts in memory of its own graph: replays may overlap calls of the stream it is captured on
-                if torch.cuda.is_current_stream_capturing():
-                    arrivals = torch.zeros(max(split.n_rows, 1), dtype=torch.int32, device=q.device)
-                    split = _CSplit(B, split.n_parts, split.n_rows, split.n_slots, split.parts, arrivals.data_ptr())
-            st = lib.calibatt_sparse_attn_fwd_split(*pointers, B, H, N, D, bq, bk, c, float(scale), C.byref(opt),
-                                                    C.byref(split), workspace.data_ptr(), nbytes, stream)
+            with torch.cuda.stream(other):
+                st = _split_call(lib, args, opt, split, bq, D, q.device, stream)
     if st != 0:
         raise CalibattError(st, "calibatt_sparse_attn_fwd")
     return out
+
+
+def _split_call(lib, args, opt, split, block_q, D, device, stream):
+    """calibatt_sparse_attn_fwd_split with a workspace of torch's current stream, which is the call's."""
+    import torch
+
+    nbytes = split.n_slots * _part_bytes(block_q, D)
+    workspace = torch.empty(nbytes // 4, dtype=torch.float32, device=device)
+    if torch.cuda.is_current_stream_capturing():
+        # a captured call counts in memory of its own graph: replays may overlap calls of the stream it is captured on
+        arrivals = torch.zeros(max(split.n_rows, 1), dtype=torch.int32, device=device)
+        split = _CSplit(split.B, split.n_parts, split.n_rows, split.n_slots, split.parts, arrivals.data_ptr())
+    return lib.calibatt_sparse_attn_fwd_split(*args, C.byref(opt), C.byref(split), workspace.data_ptr(), nbytes, stream)
+
+
+@functools.lru_cache(maxsize=16)
+def _part_bytes(block_q: int, D: int) -> int:
+    """Workspace of one part of a cut row (calibatt_split_workspace_bytes)."""
+    return load_library().calibatt_split_workspace_bytes(C.byref(_CSplit(1, 0, 0, 1, None, None)), block_q, D)
 
 
 @dataclass
@@ -595,7 +615,8 @@ def _stream_of(stream, device):
     orders before another stream."""
     import torch
 
-    current = torch.cuda.current_stream(device).cuda_stream
+    index = device.index  # the raw handle: a stream object costs 2 us, as much as half a launch
+    current = torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
     if stream is None or int(stream) == current:
         return current, None
     return int(stream), torch.cuda.ExternalStream(int(stream), device=device)
