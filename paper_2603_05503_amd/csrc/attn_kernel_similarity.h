@@ -26,7 +26,7 @@
 // bits do not depend on how the tokens were grouped.
 //
 // Measured, 24 heads of 21 x 30 x 52 tokens, D = 128, five anchors, in turn on one box: 13.87 ms with every token
-// beside its own partner over whole tiles and one wavefront per head in the reduction, 9.84 ms as it is here.
+// beside its own partner over whole tiles and one wavefront per head in the reduction, 9.84 ms in twos, 5 % less mixed.
 //
 // Without groups, us with one score buffer (and before it, with whole tiles of 128 keys) -> with two: 210 units of 3840
 // keys, D = 128 95 (92) -> 81, D = 64 78 (73) -> 69; 480 units 148 (156) -> 141; 1800 units of 9600 keys 1299 (1427) ->
@@ -34,7 +34,7 @@
 //
 // Grouping (similarity_group_kernel): the tokens of one column of the grid in
 // consecutive spatial rows form a run while they have the same partner; a run
-// is cut into groups of R.  Groups are appended to a list in any order.
+// is cut into groups of R, or of three and two.  Groups are appended to a list in any order.
 //
 // Reduction kernel: one workgroup per (batch, head) adds the triples of each spatial
 // row, forms the cosine and averages over rows in a fixed order.
@@ -61,21 +61,35 @@ constexpr int SIM_XCDS = 8;
 constexpr int SIM_GROUP_TURNS = 2;
 constexpr int SIM_GROUP_TOKENS = 512;
 
+// The mixed form is taken where the busiest CU has less than 96 % of the rows of the best other form to do, a row of
+// threes counted 1.15 times (their partner's operand comes from LDS).  Either side, rows of the others' best and of the
+// mixed form, D = 128: 24 heads of 21 x 30 x 52 tokens, five anchors, 36 and 34.2: 10.41 -> 9.93 ms (D = 64 7.58 -> 7.20);
+// 18 heads of 4 x 30 x 32, five anchors, 176 -> 141 us; not taken: 12 heads of 8 x 32 x 75, four anchors, 12 and 11.7: 1.93
+// and 2.02 ms.
+constexpr int SIM_THREE_COST = 46, SIM_MIXED_GAIN = 96;  // tenths of a row, per cent
+
 // ---- lists of the grouped form -------------------------------------------------------------------
 // int32 words: [0..2] numbers of 2-token groups, 3-token groups and lone tokens, [4 ..] the 3-token
 // groups (4 words each: partner, tokens; -1 = none), the 2-token groups (likewise) and the lone tokens,
 // room for n_tok of each.  A partner that takes its own triple from this group is stored as ~partner.
+// The mixed form cuts a run into threes and, at its end, up to two twos, without an empty place: its groups lie at the
+// far ends of the two segments, the last one first (a run of two tokens or more leaves the room), their numbers in word 3
+// and in the last word of the lone tokens.  A run of one token, which has no such cut, sets the sign of word 3.
 struct SimilarityLists {
-  static constexpr int SEGMENT = 64;  // rows at which a run ends in any case: bounds the walks below
+  // Rows at which a run ends in any case: bounds the walks below (0.1 us a row where a run is that long) and lies beyond
+  // the rows of a video, so that no run is cut to a single token there, which has no place in the mixed form.
+  static constexpr int SEGMENT = 1024;
   static __host__ __device__ long long bytes(int n_tok) { return 16 + 36LL * n_tok; }
   static __device__ __forceinline__ int4 *groups(int32_t *lists, int n_tok, int R) {
     return reinterpret_cast<int4 *>(lists + 4) + (R == 3 ? 0 : n_tok);
   }
   static __device__ __forceinline__ int32_t *lone(int32_t *lists, int n_tok) { return lists + 4 + 8LL * n_tok; }
+  static __device__ __forceinline__ int32_t *mixed_twos(int32_t *lists, int n_tok) { return lone(lists, n_tok) + n_tok - 1; }
 };
 
-__global__ __launch_bounds__(64) void similarity_clear_kernel(int32_t *__restrict__ lists) {
+__global__ __launch_bounds__(64) void similarity_clear_kernel(int32_t *__restrict__ lists, int n_tok) {
   if (threadIdx.x < 4) lists[threadIdx.x] = 0;
+  if (threadIdx.x == 4) *SimilarityLists::mixed_twos(lists, n_tok) = 0;
 }
 
 __device__ __forceinline__ int similarity_partner(const int32_t *__restrict__ partner, int t, int N) {
@@ -127,6 +141,15 @@ __global__ __launch_bounds__(256) void similarity_group_kernel(const int32_t *__
   const int at3 = append(starts3, lists + 1);
   const int at2 = append(starts2, lists);
   const int at1 = append(lone, lists + 2);
+  // mixed: of the n tokens of the run the first 3 * threes go in threes
+  const int n = before + behind + 1, threes = n % 3 == 1 ? (n - 4) / 3 : n / 3;
+  if (grouped && n == 1) atomicOr(reinterpret_cast<unsigned *>(lists + 3), 0x80000000u);
+  const bool mixed3 = grouped && n > 1 && before < 3 * threes && before % 3 == 0;
+  const bool mixed2 = grouped && n > 1 && before >= 3 * threes && (before - 3 * threes) % 2 == 0;
+  const int at_m3 = append(mixed3, lists + 3) & 0x7fffffff;
+  const int at_m2 = append(mixed2, SimilarityLists::mixed_twos(lists, n_tok));
+  if (mixed3) SimilarityLists::groups(lists, n_tok, 3)[n_tok - 1 - at_m3] = make_int4(stored, t, next[0], next[1]);
+  if (mixed2) SimilarityLists::groups(lists, n_tok, 2)[n_tok - 1 - at_m2] = make_int4(stored, t, next[0], -1);
   if (starts3) SimilarityLists::groups(lists, n_tok, 3)[at3] = make_int4(stored, t, next[0], next[1]);
   if (starts2) SimilarityLists::groups(lists, n_tok, 2)[at2] = make_int4(stored, t, next[0], -1);
   if (lone) SimilarityLists::lone(lists, n_tok)[at1] = t;
@@ -382,29 +405,26 @@ __global__ __launch_bounds__(SIM_BQ * 2, 2) void pair_similarity_kernel(
   pair_similarity<D>(lds, gq, gk, partner, triples, p);
 }
 
+// Unit `unit` of 128 lane groups of head bh: groups of the list at `groups` (step 1, or -1 from its far end), or lone tokens.
 template <int D, int R>
 __device__ __forceinline__ void grouped_similarity(char *lds, const uint16_t *__restrict__ gq,
                                                    const uint16_t *__restrict__ gk, int32_t *__restrict__ lists,
-                                                   float *__restrict__ triples, const SimilarityDims &p, int n_groups,
-                                                   int n_lone) {
+                                                   float *__restrict__ triples, const SimilarityDims &p,
+                                                   const int4 *groups, int step, int n_groups, int n_lone, bool lone,
+                                                   int bh, int unit) {
   using RB = RowBlock<D, SIM_BQ, SIM_BK>;
-  const int n_lone_groups = (n_lone + R) / (R + 1);  // R + 1 tokens that are their own partners per lane
-  const int group_units = (n_groups + SIM_BQ - 1) / SIM_BQ;
-  int bh, r;
-  if (!similarity_unit(p, group_units + (n_lone_groups + SIM_BQ - 1) / SIM_BQ, bh, r)) return;
   RB rb(lds);
-  const bool lone = r >= group_units;
-  const int at = (lone ? r - group_units : r) * SIM_BQ + rb.row_in_block();
+  const int at = unit * SIM_BQ + rb.row_in_block();
   int id[R + 1];
   bool own = false;
-  if (lone) {
+  if (lone) {  // R + 1 tokens that are their own partners per lane
 #pragma unroll
     for (int i = 0; i <= R; ++i) {
       const int j = at * (R + 1) + i;
       id[i] = j < n_lone ? SimilarityLists::lone(lists, p.n_tok)[j] : -1;
     }
   } else if (at < n_groups) {
-    const int4 g = SimilarityLists::groups(lists, p.n_tok, R)[at];
+    const int4 g = groups[(long long)at * step];
     own = g.x < 0;
     id[0] = own ? ~g.x : g.x;
     id[1] = g.y;
@@ -455,12 +475,34 @@ __global__ __launch_bounds__(SIM_BQ * 2, 2) void grouped_similarity_kernel(
     return rows((groups + SIM_BQ - 1) / SIM_BQ + (lone + SIM_BQ - 1) / SIM_BQ, R + 1);
   };
   const long long rows3 = grouped_rows(n3, 3), rows2 = grouped_rows(n2, 2), rows1 = rows(p.nbq, 2);
-  if (rows1 < min(rows2, rows3))
+  auto units = [](int n) { return (n + SIM_BQ - 1) / SIM_BQ; };
+  // Mixed: units of four and of three rows of logits, evenly among each other (an XCD takes a range of them).
+  const int m3 = lists[3], m2 = n_lone < p.n_tok ? *SimilarityLists::mixed_twos(lists, p.n_tok) : 0;
+  const int u3 = m3 < 0 ? 0 : units(m3), u2 = units(m2), u1 = units((n_lone + 3) / 4);
+  const int per_head = u3 + u2 + u1;
+  const bool mixed = u3 > 0 && u2 > 0 && per_head <= p.nbq + 1 &&
+                     rows(per_head, SIM_THREE_COST * (u3 + u1) + 30 * u2) * 10 <
+                         SIM_MIXED_GAIN * per_head * min(rows1, min(rows2, rows3));
+  if (!mixed && rows1 < min(rows2, rows3)) {
     pair_similarity<D>(lds, gq, gk, partner, triples, p);
-  else if (rows2 <= rows3)
-    grouped_similarity<D, 2>(lds, gq, gk, lists, triples, p, n2, n_lone);
-  else
-    grouped_similarity<D, 3>(lds, gq, gk, lists, triples, p, n3, n_lone);
+    return;
+  }
+  const bool twos = !mixed && rows2 <= rows3;
+  const int first = mixed ? u3 : twos ? units(n2) : units(n3);  // units of the first list, then of a second one
+  const int second = mixed ? u2 : 0;
+  int bh, r;
+  if (!similarity_unit(p, first + second + (twos ? units((n_lone + 2) / 3) : u1), bh, r)) return;
+  const bool lone = r >= first + second;
+  const int before = lone ? first : (int)((long long)r * first / (first + second));  // units of the first list
+  const bool of_second = !lone && (long long)(r + 1) * first / (first + second) == before;
+  const int unit = lone ? r - first - second : of_second ? r - before : before;
+  if (twos || of_second) {
+    const int4 *const at = SimilarityLists::groups(lists, p.n_tok, 2) + (mixed ? p.n_tok - 1 : 0);
+    grouped_similarity<D, 2>(lds, gq, gk, lists, triples, p, at, mixed ? -1 : 1, mixed ? m2 : n2, n_lone, lone, bh, unit);
+  } else {
+    const int4 *const at = SimilarityLists::groups(lists, p.n_tok, 3) + (mixed ? p.n_tok - 1 : 0);
+    grouped_similarity<D, 3>(lds, gq, gk, lists, triples, p, at, mixed ? -1 : 1, mixed ? m3 : n3, n_lone, lone, bh, unit);
+  }
 }
 
 // score[b*H + h] = mean over the n_tok / row_len spatial rows of the row's cosine.  A half wavefront adds the

@@ -335,7 +335,7 @@ int launch_similarity(const uint16_t *q, const uint16_t *k, const int32_t *partn
     constexpr int SMEM = SimilarityLds<D, 3>::BYTES;  // not less than the two-token form needs
     static DevInfo info;
     if (int st = prepare(grouped_similarity_kernel<D>, SIM_BQ * 2, SMEM, info, slots)) return st;
-    if (int st = launch_kernel(similarity_clear_kernel, 1, 64, 0, stream, lists)) return st;
+    if (int st = launch_kernel(similarity_clear_kernel, 1, 64, 0, stream, lists, p.n_tok)) return st;
     if (int st = launch_kernel(similarity_group_kernel, (unsigned)((p.n_tok + 255) / 256), 256, 0, stream, partner,
                                lists, p.N, p.n_tok, p.row_len))
       return st;
