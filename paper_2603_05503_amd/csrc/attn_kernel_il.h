@@ -4,8 +4,8 @@
 // Same computation per query block as attn_kernel_2wg.h (paper, Section 2
 // Eq. 1-4 under the block mask of Section 3.2, repeated query blocks written
 // as copies, Section 3.3 / 3.4); the online softmax moves the reference of
-// its exponentials lazily (see IlRow::softmax_op), which changes roundings but
-// not what is computed.
+// its exponentials lazily (see IlRow::softmax_op and IL_SUM_MOVE), which changes
+// roundings but not what is computed.
 //
 // Why.  On this hardware a wavefront issues a vector-ALU instruction only
 // every 5-8 cycles, and the softmax of a 128-key tile is ~225 of them: with
@@ -21,7 +21,7 @@
 //     the MFMAs of  O += P V  of the sub-tile before the previous one,
 //     the MFMAs of  S = K Q^T of the next sub-tile,
 //     the vector instructions of the softmax of the previous sub-tile
-// (about four vector instructions behind every MFMA).  The chain of one
+// (about three vector instructions behind every MFMA).  The chain of one
 // wavefront per tile is then little longer than its MFMAs alone, and the two
 // wavefronts per SIMD (two workgroups per CU, as in attn_kernel_2wg.h)
 // together keep the matrix pipe fed.  One workgroup barrier per stage.
@@ -56,6 +56,14 @@ namespace calibatt_dev {
 // than this (log2 domain): probabilities stay below 2^8, far inside the bf16 /
 // fp16 range, and keep their full relative precision.
 constexpr float IL_REF_SLACK = 8.0f;
+// bf16 probabilities have the range of fp32, and a reference may as well move one sub-tile late: the fast form of a stage
+// looks for no maximum.  A lane whose sum over the sub-tile exceeds 2^8 moves the reference for the sub-tiles that
+// follow; one of 2^64 or more (a logit that far above everything before it in its row), or a result that is not finite
+// after such a move, ends in the row's second run, in the exact form (what that row takes twice as long for).  That
+// leaves out 28 of some 120 vector instructions of a stage: 480p 5.46 -> 5.25 ms, all blocks kept 19.29 -> 18.61, 720p
+// 25.90 -> 24.93, key blocks of 96 3.00 -> 2.82, D = 64 1.69 -> 1.58.  fp16 probabilities have to stay below 2^16: always
+// exact.
+constexpr float IL_SUM_MOVE = 0x1p8f, IL_SUM_BAD = 0x1p64f;
 constexpr int IL_VGPRS = 72;  // arch VGPRs left to the compiler; the named ones follow
 constexpr int IL_STAGES = 6;  // operand staging slots
 constexpr int IL_AHEAD = 4;   // MFMAs between the issue of an operand's LDS reads and its use
@@ -103,6 +111,10 @@ struct IlRow : RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T> {
   float psum[2];     // row sum of the sub-tile being exponentiated
   float part[4], rm, neg_ref;
   float x[8];
+  // fast form: the reference that the next softmax takes, whether it moved there, whether it ever did, and whether a sum
+  // was out of range (the same for all lanes of the wave)
+  float m_next;
+  bool pending, late, bad;
 
   __device__ __forceinline__ IlRow(char *lds_, uint32_t kv_row_bytes_) : RB(lds_, kv_row_bytes_) {
     const uint32_t lds_base = (uint32_t)(uintptr_t)(LDS_PTR(char))lds_;  // a multiple of 1024
@@ -168,9 +180,11 @@ struct IlRow : RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T> {
   static constexpr int N_GROUPS = EL / 8;
   static constexpr int OPS_MAX = EL / 2, OPS_GROUP = 8 + 8 + 4;
   static constexpr int N_OPS = OPS_MAX + 1 + N_GROUPS * OPS_GROUP;
-  template <int PAR, int J>
+  // The fast form leaves out the maxima and the decision.
+  static constexpr __device__ int n_ops(bool exact) { return exact ? N_OPS : N_GROUPS * OPS_GROUP; }
+  template <int PAR, bool EXACT, int J_>
   __device__ __forceinline__ void softmax_op() {
-    constexpr int B = V_S + PAR * EL;
+    constexpr int B = V_S + PAR * EL, J = EXACT ? J_ : J_ + OPS_MAX + 1;
     if constexpr (J < OPS_MAX) {
       if constexpr (J < 4) part[J] = -INFINITY;
       named_max3<B + 2 * J, B + 2 * J + 1>(part[J & 3]);
@@ -211,12 +225,23 @@ struct IlRow : RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T> {
   // behind each (or every second) of the first MFMAs: V rows [v_row0, v_row0 + SUB) into V slot
   // 1 - PAR, then K rows [k_row0, k_row0 + SUB) into K slot 1 - PAR (both slots were released by the
   // stage before).
-  template <int PAR, bool HAS_PV, bool HAS_QK, bool HAS_SM, bool LOADS = false>
+  template <int PAR, bool HAS_PV, bool HAS_QK, bool HAS_SM, bool EXACT, bool LOADS = false>
   __device__ __forceinline__ void stage(const u32x4 &Vres = u32x4{0, 0, 0, 0}, int v_row0 = 0,
                                         const u32x4 &Kres = u32x4{0, 0, 0, 0}, int k_row0 = 0) {
     constexpr int FIRST = HAS_PV ? 0 : N_PV, LAST = HAS_QK ? N_PV + N_QK : N_PV, M = LAST - FIRST;
-    constexpr int OPS = HAS_SM ? N_OPS : 0;
+    constexpr int OPS = HAS_SM ? n_ops(EXACT) : 0;
     static_assert(!LOADS || 2 * LOADS_PER_WAVE <= M, "more load instructions than MFMAs");
+    bool moved = EXACT;
+    if constexpr (HAS_SM && !EXACT) {
+      psum[0] = psum[1] = 0.f;
+      moved = pending;
+      if (pending) {
+        alpha = __builtin_amdgcn_exp2f(this->m_run - m_next);
+        this->m_run = m_next;
+        neg_ref = -m_next;
+        pending = false;
+      }
+    }
     __builtin_amdgcn_s_setprio(1);
     static_unroll<(IL_AHEAD < M ? IL_AHEAD : M)>([&](auto k) { issue_operand_reads<PAR, FIRST + k>(); });
     static_unroll<M>([&](auto k) {
@@ -238,20 +263,30 @@ struct IlRow : RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T> {
                           this->k_lane_off, this->kv_row_bytes);
       // the softmax steps are spread evenly over the MFMAs: step J follows MFMA floor(J * M / OPS)
       constexpr int J0 = (k * OPS + M - 1) / M, J1 = ((k + 1) * OPS + M - 1) / M;
-      static_unroll<J1 - J0>([&](auto q) { softmax_op<1 - PAR, J0 + q>(); });
+      static_unroll<J1 - J0>([&](auto q) { softmax_op<1 - PAR, EXACT, J0 + q>(); });
     });
     __builtin_amdgcn_s_setprio(0);
     // MFMA results are read by vector instructions only behind this (S in the next stage, O below
     // and in the epilogue): the last MFMA's write has to land first
     asm volatile("s_nop 15\n\ts_nop 7");
     if constexpr (HAS_SM) {
-      this->l_run = this->l_run * alpha + (psum[0] + psum[1]);
-      if (__any(alpha != 1.0f)) {
-        static_unroll<2 * DB>([&](auto h) {
-          float o8[8];
-          static_unroll<8>([&](auto i) { o8[i] = acc_read<A_O + 8 * h + i>(); });
-          static_unroll<8>([&](auto i) { acc_write<A_O + 8 * h + i>(o8[i] * alpha); });
-        });
+      const float sum = psum[0] + psum[1];
+      if (moved) {
+        this->l_run *= alpha;
+        if (HAS_PV && __any(alpha != 1.0f)) {  // (nothing in O before the first P V)
+          static_unroll<2 * DB>([&](auto h) {
+            float o8[8];
+            static_unroll<8>([&](auto i) { o8[i] = acc_read<A_O + 8 * h + i>(); });
+            static_unroll<8>([&](auto i) { acc_write<A_O + 8 * h + i>(o8[i] * alpha); });
+          });
+        }
+      }
+      this->l_run += sum;
+      if (!EXACT && __any(!(sum <= IL_SUM_MOVE))) {
+        bad |= __any(!(sum < IL_SUM_BAD));
+        const float most = max_with_other_half(sum);
+        m_next = most > IL_SUM_MOVE ? this->m_run + __builtin_amdgcn_logf(most) : this->m_run;
+        pending = late = true;
       }
     }
   }
@@ -269,6 +304,13 @@ struct IlRow : RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T> {
     });
   }
 
+  // Whether O holds an infinity or a NaN in any lane of the wave.
+  __device__ __forceinline__ bool not_finite() const {
+    float zero = 0.f;
+    static_unroll<16 * DB>([&](auto i) { zero = __builtin_fmaf(acc_read<A_O + i>(), 0.f, zero); });
+    return __any(!(zero == 0.f));
+  }
+
   // Start a row: empty running state, zero accumulators, and the loads of the Q^T operand into the AGPRs (lane (query
   // l32, half g) holds d = 16 s + 8 g + [0,8) of k-slab s), in flight on return.  finish_q, behind their wait, folds a
   // negative scale into the operand's sign.
@@ -281,6 +323,8 @@ struct IlRow : RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T> {
     this->m_run = -FLT_MAX;  // finite: leading keys at -inf have no weight, wherever a row's part begins
     this->l_run = 0.f;
     alpha = 1.f;
+    m_next = this->m_run;
+    pending = late = bad = false;
   }
   __device__ __forceinline__ void finish_q(float scale_log2e) const {
     if (scale_log2e < 0.f)
@@ -321,11 +365,10 @@ __device__ __forceinline__ void il_claim_registers() {
 #undef CALIBATT_R10
 }
 
-// Runs one row of key blocks, or a part of one, from its first loads to the last O += P V.  col_at(i): key block of entry
-// i < n_tiles of the row's list; expand(i): called before entries of the next COLS are asked for, from entry i on (IV).
-// On return the sums lie in the registers and other waves may still read the tile windows.
-template <int BK, bool IV, int COLS, typename Row, typename ColAt, typename Expand>
-__device__ __forceinline__ void il_run_row(Row &rb, const uint16_t *qrow_ptr, const u32x4 &Kres, const u32x4 &Vres,
+// Runs one row of key blocks, or a part of one, from its first loads to the last O += P V, EXACT or in the fast form of the
+// softmax (the first sub-tile, which sets the reference, always exactly).
+template <int BK, bool IV, int COLS, bool EXACT, typename Row, typename ColAt, typename Expand>
+__device__ __forceinline__ void il_stream(Row &rb, const uint16_t *qrow_ptr, const u32x4 &Kres, const u32x4 &Vres,
                                            int N, int n_tiles, float scale_log2e, ColAt col_at, Expand expand) {
   constexpr int SUB = Row::SUB, SPB = Row::SPB, LOADS = Row::LOADS_PER_WAVE;
   // kept key blocks of the row, 64 at a time in one VGPR (lane j = entry j of the current 64)
@@ -377,7 +420,7 @@ __device__ __forceinline__ void il_run_row(Row &rb, const uint16_t *qrow_ptr, co
   rb.finish_q(scale_log2e);
   __syncthreads();
   // stage 0: S of u_0
-  rb.template stage<0, false, true, false>();
+  rb.template stage<0, false, true, false, true>();
   CALIBATT_IL_MASK(0, r0)
   wait_vmem<0>();
   __syncthreads();
@@ -385,7 +428,7 @@ __device__ __forceinline__ void il_run_row(Row &rb, const uint16_t *qrow_ptr, co
   int row_a = r1;            // of u_(k-1) at the start of stage k (k even below)
   int row_b = next_rows();   // of u_k
   rb.issue_k_sub(Kres, row_b, 0);
-  rb.template stage<1, false, true, true>();
+  rb.template stage<1, false, true, true, true>();
   CALIBATT_IL_MASK(1, r1)
   wait_vmem<0>();
   __syncthreads();
@@ -393,7 +436,7 @@ __device__ __forceinline__ void il_run_row(Row &rb, const uint16_t *qrow_ptr, co
   for (int k = 2; k < n_stream; k += 2) {
     // stage k: loads inside the stream: V of u_(k-1), K of u_(k+1) (beyond the stream: zeros into a slot nobody reads)
     const int row_c = next_rows();
-    rb.template stage<0, true, true, true, true>(Vres, row_a, Kres, row_c);
+    rb.template stage<0, true, true, true, EXACT, true>(Vres, row_a, Kres, row_c);
     CALIBATT_IL_MASK(0, row_b)
     wait_vmem<0>();
     __syncthreads();
@@ -401,7 +444,7 @@ __device__ __forceinline__ void il_run_row(Row &rb, const uint16_t *qrow_ptr, co
     if (odd_end) break;
     // stage k + 1: V of u_k, K of u_(k+2)
     const int row_d = next_rows();
-    rb.template stage<1, true, true, true, true>(Vres, row_b, Kres, row_d);
+    rb.template stage<1, true, true, true, EXACT, true>(Vres, row_b, Kres, row_d);
     CALIBATT_IL_MASK(1, row_c)
     wait_vmem<0>();
     __syncthreads();
@@ -413,17 +456,37 @@ __device__ __forceinline__ void il_run_row(Row &rb, const uint16_t *qrow_ptr, co
   // and stage n_stream + 1: O += P V of u_(n_stream-1)
   if (odd_end) {
     rb.issue_v_sub(Vres, row_b, 0);
-    rb.template stage<1, true, false, true>();
+    rb.template stage<1, true, false, true, EXACT>();
     wait_vmem<0>();
     __syncthreads();
-    rb.template stage<0, true, false, false>();
+    rb.template stage<0, true, false, false, EXACT>();
   } else {
     rb.issue_v_sub(Vres, row_a, 1);
-    rb.template stage<0, true, false, true>();
+    rb.template stage<0, true, false, true, EXACT>();
     wait_vmem<0>();
     __syncthreads();
-    rb.template stage<1, true, false, false>();
+    rb.template stage<1, true, false, false, EXACT>();
   }
+}
+
+// The same in whichever form it takes.  col_at(i): key block of entry i < n_tiles of the row's list; expand(i): called before
+// entries of the next COLS are asked for, from entry i on (IV).  votes: LDS, an int per wave.  On return the sums lie in the
+// registers and other waves may still read the tile windows.
+template <int BK, bool IV, int COLS, typename T, typename Row, typename ColAt, typename Expand>
+__device__ __forceinline__ void il_run_row(Row &rb, const uint16_t *qrow_ptr, const u32x4 &Kres, const u32x4 &Vres,
+                                           int N, int n_tiles, float scale_log2e, ColAt col_at, Expand expand,
+                                           volatile int *votes) {
+  if constexpr (std::is_same<T, Bf16>::value) {
+    il_stream<BK, IV, COLS, false>(rb, qrow_ptr, Kres, Vres, N, n_tiles, scale_log2e, col_at, expand);
+    if (rb.late && !rb.bad) rb.bad = rb.not_finite();
+    if (rb.lane == 0) votes[rb.wave] = rb.bad;
+    __syncthreads();  // also: every wave is done with the tile windows
+    int again = 0;
+    for (int w = 0; w < Row::NW; ++w) again |= votes[w];
+    if (!__builtin_amdgcn_readfirstlane(again)) return;
+    if constexpr (IV) expand(0);
+  }
+  il_stream<BK, IV, COLS, true>(rb, qrow_ptr, Kres, Vres, N, n_tiles, scale_log2e, col_at, expand);
 }
 
 // The rows of block r, normalised and rounded, through LDS to the block itself and to the blocks [fan, fan + n_fan) that
@@ -542,8 +605,8 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
     }
     auto col_at = [&](int entry) { return IV ? cols[entry - chunk_lo] : col_idx[cbeg + entry]; };
     const int qrow = min(r * BQ + rb.row_in_block(), N - 1);
-    il_run_row<BK, IV, COLS>(rb, gq + head_off + (size_t)qrow * p.in.n, Kres, Vres, N, n_tiles, p.scale_log2e, col_at,
-                             expand_runs);
+    il_run_row<BK, IV, COLS, T>(rb, gq + head_off + (size_t)qrow * p.in.n, Kres, Vres, N, n_tiles, p.scale_log2e, col_at,
+                                expand_runs, mailbox + 4);
     const int fbeg = fan_ptr[item];
     const int n_fan = fan_ptr[item + 1] - fbeg;
     if (head_ok) il_store_row(rb, lds, p, b, ht, r, fan_dst + fbeg, n_fan, gout, lse);
