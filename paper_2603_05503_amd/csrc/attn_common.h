@@ -74,18 +74,31 @@ __device__ __forceinline__ u32x4 head_rsrc(const uint16_t *base, uint32_t bytes)
 // inline asm so that the compiler keeps no record of LDS being written by an
 // in-flight vector-memory operation (it would otherwise drain vmcnt before
 // every LDS read); completion is tracked by hand with wait_vmem<>().
-// The scalar copy of soff is the wait state between the M0 write and the LDS-DMA that reads it, and the memory
-// instruction then reads a register that the scalar unit wrote: one that the compiler has just brought back from a vector
-// lane would need five wait states (csrc/check_sgpr_waits.py fails the build where they are missing).
+// One wait state lies between the M0 write and the LDS-DMA that reads it.  COPY: it is a scalar copy of soff, so that the
+// memory instruction reads a register that the scalar unit wrote; one that the compiler has just brought back from a
+// vector lane would need five wait states (csrc/check_sgpr_waits.py fails the build where they are missing).  The copy
+// costs the forward and short chains 0.5-1 % (480p 5.34 -> 5.38 ms), so it is made where scalar registers are scarce, and
+// in the energy kernels, which it makes 1 % faster (480p 10.50 -> 10.37 ms).
+template <bool COPY>
 __device__ __forceinline__ void dma_16B_per_lane(const u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds_off) {
-  uint32_t copy;
-  asm volatile(
-      "s_mov_b32 m0, %1\n\t"
-      "s_mov_b32 %0, %4\n\t"
-      "buffer_load_dwordx4 %2, %3, %0 offen lds"
-      : "=&s"(copy)
-      : "s"(lds_off), "v"(voff), "s"(rsrc), "s"(soff)
-      : "m0");
+  if constexpr (COPY) {
+    uint32_t copy;
+    asm volatile(
+        "s_mov_b32 m0, %1\n\t"
+        "s_mov_b32 %0, %4\n\t"
+        "buffer_load_dwordx4 %2, %3, %0 offen lds"
+        : "=&s"(copy)
+        : "s"(lds_off), "v"(voff), "s"(rsrc), "s"(soff)
+        : "m0");
+  } else {
+    asm volatile(
+        "s_mov_b32 m0, %0\n\t"
+        "s_nop 0\n\t"
+        "buffer_load_dwordx4 %1, %2, %3 offen lds"
+        :
+        : "s"(lds_off), "v"(voff), "s"(rsrc), "s"(soff)
+        : "m0");
+  }
 }
 
 // Stream one ROWS x D bf16 tile global -> LDS.  Each instruction fills 1 KB of
@@ -109,16 +122,19 @@ struct TileLoader {
 
   // Instruction `it` of the ITERS that fill the tile.
   // lds_wave_off: LDS byte address of the tile + 1024 * wave index (wave-uniform)
+  // COPY: see dma_16B_per_lane; by default for 64-query blocks at D = 128, many loads in flight of a long stage
+  template <bool COPY = (RPI < 16)>
   static __device__ __forceinline__ void issue_one(int it, const u32x4 rsrc, int row0, uint32_t lds_wave_off, int tid,
                                                    uint32_t lane_off0, uint32_t row_bytes = D * 2) {
     const uint32_t voff = INVARIANT ? lane_off0 : lane_offset(tid, it, row_bytes);
     const uint32_t soff = (uint32_t)(row0 + it * RPI) * row_bytes;
-    dma_16B_per_lane(rsrc, voff, soff, lds_wave_off + it * NT * 16);
+    dma_16B_per_lane<COPY>(rsrc, voff, soff, lds_wave_off + it * NT * 16);
   }
+  template <bool COPY = (RPI < 16)>
   static __device__ __forceinline__ void issue(const u32x4 rsrc, int row0, uint32_t lds_wave_off, int tid,
                                                uint32_t lane_off0, uint32_t row_bytes = D * 2) {
 #pragma unroll
-    for (int it = 0; it < ITERS; ++it) issue_one(it, rsrc, row0, lds_wave_off, tid, lane_off0, row_bytes);
+    for (int it = 0; it < ITERS; ++it) issue_one<COPY>(it, rsrc, row0, lds_wave_off, tid, lane_off0, row_bytes);
   }
 };
 

@@ -101,8 +101,9 @@ struct RowBlock {
     LoadK::issue(Kres, c * BK, ldsK_wave, tid, k_lane_off, kv_row_bytes);
   }
   // K tile c into the LDS window at byte offset `buf_off` (a multiple of TILE_BYTES)
+  template <bool COPY = false>
   __device__ __forceinline__ void issue_k_at(const u32x4 &Kres, int c, uint32_t buf_off) const {
-    LoadK::issue(Kres, c * BK, ldsK_wave + buf_off, tid, k_lane_off, kv_row_bytes);
+    LoadK::template issue<COPY>(Kres, c * BK, ldsK_wave + buf_off, tid, k_lane_off, kv_row_bytes);
   }
   __device__ __forceinline__ void issue_v(const u32x4 &Vres, int c) const {
     LoadV::issue(Vres, c * BK, ldsV_wave, tid, v_lane_off, kv_row_bytes);

@@ -61,7 +61,7 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) void block_energy_kern
   float *const part = reinterpret_cast<float *>(lds + EnergyLds<D, BQ, BK>::PART_OFF);
   const int rows_valid = min(BQ, N - r * BQ);
 
-  rb.issue_k_at(Kres, 0, 0);
+  rb.template issue_k_at<true>(Kres, 0, 0);
   const bool row_valid = rb.row_in_block() < rows_valid;
   rb.begin(gq + head_off + (size_t)(r * BQ + (row_valid ? rb.row_in_block() : 0)) * D);
   const float sc = p.scale_log2e;
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) void block_energy_kern
     const int c = second ? t - p.nbk : t;
     wait_vmem<0>();
     __syncthreads();  // tile t has landed for every wave; everyone is done with the other buffer
-    if (t + 1 < n_steps) rb.issue_k_at(Kres, c + 1 < p.nbk ? c + 1 : 0, ((t + 1) & 1) * TILE_BYTES);
+    if (t + 1 < n_steps) rb.template issue_k_at<true>(Kres, c + 1 < p.nbk ? c + 1 : 0, ((t + 1) & 1) * TILE_BYTES);
     f32x16 s[KB];
     rb.scores((t & 1) * TILE_BYTES, s);
     // Work on the raw products with the scale folded into the exponent's FMA; only the ragged last
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(QW * 2, 2) void block_energy_onepass_kernel(
     const bool row_valid = row < N;
 
     // both K buffers are free: every wave is behind the barrier that followed the last tile of the previous unit
-    rb.issue_k_at(Kres, 0, 0);
+    rb.template issue_k_at<true>(Kres, 0, 0);
     // a lane without a row of its own repeats the first row of its block
     rb.begin(gq + head_off + (size_t)(row_valid ? row : min(row / BQ * BQ, N - 1)) * D);
 
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(QW * 2, 2) void block_energy_onepass_kernel(
       __syncthreads();  // tile c has landed for every wave; everyone is done with the other buffer
       // the value of the previous tile goes out here, a whole tile ahead of the next wait for memory
       if (c > 0 && ((c - 1) & 1) == rb.g) mine[(size_t)(c - 1) * QW] = t_prev;
-      if (c + 1 < p.nbk) rb.issue_k_at(Kres, c + 1, ((c + 1) & 1) * TILE_BYTES);
+      if (c + 1 < p.nbk) rb.template issue_k_at<true>(Kres, c + 1, ((c + 1) & 1) * TILE_BYTES);
       f32x16 s[KB];
       rb.scores((c & 1) * TILE_BYTES, s);
       float sc_t = sc;
@@ -387,7 +387,7 @@ __global__ __launch_bounds__(256, 2) void block_energy_panels_kernel(
     const int row0 = r0 * BQ + rb.wave * 32 * PANELS + rb.l32;  // this lane's row of panel 0; of panel 1: + 32
 
     // both K buffers are free: every wave is behind the barrier that followed the last tile of the previous unit
-    rb.issue_k_at(Kres, 0, 0);
+    rb.template issue_k_at<true>(Kres, 0, 0);
     Operand q[PANELS][DS];
 #pragma unroll
     for (int i = 0; i < PANELS; ++i) {  // a lane without a row of its own repeats the first row of its block
@@ -507,7 +507,7 @@ __global__ __launch_bounds__(256, 2) void block_energy_panels_kernel(
     for (int c = 0; c < nbk; ++c) {
       wait_vmem<0>();
       __syncthreads();  // tile c has landed for every wave; everyone is done with the other buffer
-      if (c + 1 < nbk) rb.issue_k_at(Kres, c + 1, ((c + 1) & 1) * TILE_BYTES);
+      if (c + 1 < nbk) rb.template issue_k_at<true>(Kres, c + 1, ((c + 1) & 1) * TILE_BYTES);
       const uint32_t buf = (c & 1) * TILE_BYTES;
       const bool tail = ragged && c == nbk - 1;
       if (c == 0) {
