@@ -271,12 +271,16 @@ class HostPattern:
         if iv_ptr is not None:
             c.iv_ptr = iv_ptr.ctypes.data
         split = _CSplit()
-        st = lib.calibatt_plan_split(C.byref(c), B, max_blocks, None, 0, C.byref(split))
-        if st == 0 and split.n_parts:
-            parts = np.empty((split.n_parts, 12), np.int32)
-            st = lib.calibatt_plan_split(C.byref(c), B, max_blocks, _ptr(parts, C.c_int32), split.n_parts, C.byref(split))
+        cap = 2 * (self.n_work * B + 1024)  # more than most plans have
+        while True:
+            parts = np.empty((cap, 12), np.int32)
+            st = lib.calibatt_plan_split(C.byref(c), B, max_blocks, _ptr(parts, C.c_int32), cap, C.byref(split))
+            if st != -7 or cap >= split.n_parts:
+                break
+            cap = split.n_parts
         if st != 0:
             raise CalibattError(st, "calibatt_plan_split")
+        parts = parts[:split.n_parts]
         return (split, parts) if split.n_parts else None
 
     def encode_intervals(self):
