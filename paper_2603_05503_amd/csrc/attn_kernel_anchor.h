@@ -187,12 +187,11 @@ __global__ __launch_bounds__(ANCHOR_BQ * 2, 2) __attribute__((amdgpu_num_vgpr(IL
   const int tok = min(max(q_index[qi], 0), N - 1);
   il_run_row<BK, false, 1, Bf16>(
       rb, gq + head_off + (size_t)tok * p.in.n, Kres, Vres, N, c1 - c0, p.scale_log2e,
-      [&](int entry) { return c0 + entry; }, [](int) {}, reinterpret_cast<volatile int *>(lds + L::VOTES_OFF));
+      [&](int entry) { return c0 + entry; }, [](int) {}, reinterpret_cast<int *>(lds + L::VOTES_OFF));
   if (part_out) {
     anchor_store_part(rb, part_out, part_out + BQ * D);
     return;
   }
-  __syncthreads();
   rb.stage_rows(lds);
   __syncthreads();
   anchor_broadcast<D>(lds, tid, r, b, h, gout, dst_ptr, dst_idx, p);

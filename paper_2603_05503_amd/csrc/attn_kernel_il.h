@@ -471,33 +471,34 @@ __device__ __forceinline__ void il_stream(Row &rb, const uint16_t *qrow_ptr, con
 
 // The same in whichever form it takes.  col_at(i): key block of entry i < n_tiles of the row's list; expand(i): called before
 // entries of the next COLS are asked for, from entry i on (IV).  votes: LDS, an int per wave.  On return the sums lie in the
-// registers and other waves may still read the tile windows.
+// registers and every wave is done with the tile windows.
 template <int BK, bool IV, int COLS, typename T, typename Row, typename ColAt, typename Expand>
 __device__ __forceinline__ void il_run_row(Row &rb, const uint16_t *qrow_ptr, const u32x4 &Kres, const u32x4 &Vres,
                                            int N, int n_tiles, float scale_log2e, ColAt col_at, Expand expand,
-                                           volatile int *votes) {
+                                           int *votes_) {
+  LDS_PTR(volatile int) const votes = (LDS_PTR(volatile int))votes_;
   if constexpr (std::is_same<T, Bf16>::value) {
     il_stream<BK, IV, COLS, false>(rb, qrow_ptr, Kres, Vres, N, n_tiles, scale_log2e, col_at, expand);
     if (rb.late && !rb.bad) rb.bad = rb.not_finite();
     if (rb.lane == 0) votes[rb.wave] = rb.bad;
-    __syncthreads();  // also: every wave is done with the tile windows
+    __syncthreads();
     int again = 0;
     for (int w = 0; w < Row::NW; ++w) again |= votes[w];
     if (!__builtin_amdgcn_readfirstlane(again)) return;
     if constexpr (IV) expand(0);
   }
   il_stream<BK, IV, COLS, true>(rb, qrow_ptr, Kres, Vres, N, n_tiles, scale_log2e, col_at, expand);
+  __syncthreads();
 }
 
 // The rows of block r, normalised and rounded, through LDS to the block itself and to the blocks [fan, fan + n_fan) that
-// repeat it; their log-sum-exps likewise.
+// repeat it; their log-sum-exps likewise.  Every wave is done with what LDS held.
 template <typename Row>
 __device__ __forceinline__ void il_store_row(const Row &rb, char *lds, const FwdDims &p, int b, int ht, int r,
                                              const int32_t *fan, int n_fan, uint16_t *__restrict__ gout,
                                              float *__restrict__ lse) {
   constexpr int NT = Row::NT, CH = Row::CH, OST = Row::OST, BQ = NT / 2;
   const int N = p.N;
-  __syncthreads();  // every wave is done with the tile windows
   const float row_lse = rb.stage_rows(lds);
   __syncthreads();
   if (lse && rb.g == 0) {
@@ -606,7 +607,7 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
     auto col_at = [&](int entry) { return IV ? cols[entry - chunk_lo] : col_idx[cbeg + entry]; };
     const int qrow = min(r * BQ + rb.row_in_block(), N - 1);
     il_run_row<BK, IV, COLS, T>(rb, gq + head_off + (size_t)qrow * p.in.n, Kres, Vres, N, n_tiles, p.scale_log2e, col_at,
-                                expand_runs, mailbox + 4);
+                                expand_runs, const_cast<int *>(mailbox) + 4);
     const int fbeg = fan_ptr[item];
     const int n_fan = fan_ptr[item + 1] - fbeg;
     if (head_ok) il_store_row(rb, lds, p, b, ht, r, fan_dst + fbeg, n_fan, gout, lse);

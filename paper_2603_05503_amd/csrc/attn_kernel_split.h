@@ -7,9 +7,9 @@
 // length (split_plan.cpp), one workgroup takes one part, leaves its sums in a workspace, and the one that finds itself
 // last adds them up.  Rows that are not cut go the same way: one workgroup each, the longest first, by the hardware's
 // dispatcher instead of the counters.
-// Measured (us, whole rows -> by plan; density 0.35 where not given): one head of 8 190 tokens 112 -> 34, four 118 -> 64,
-// twelve 180 -> 149; two heads of 16 380 at 0.25 166 -> 85, twelve 470 -> 375; twenty of 5 070, 64-query blocks, D = 64,
-// 150 -> 55.  Adding up costs 0.6 us per part of a row, 67 KB each at D = 128.
+// Measured (us, whole rows -> by plan; density 0.35 where not given): one head of 8 190 tokens 112 -> 33, four 118 -> 61,
+// twelve 180 -> 140; two heads of 16 380 at 0.25 166 -> 77, twelve 470 -> 365; twenty of 5 070, 64-query blocks, D = 64,
+// 150 -> 50.  Adding up costs 0.6 us per part of a row, 67 KB each at D = 128.
 #pragma once
 #include "attn_kernel_il.h"
 
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
   auto col_at = [&](int entry) { return IV ? cols[first + entry - chunk_lo] : col_idx[cbeg + entry]; };
   const int qrow = min(r * BQ + rb.row_in_block(), N - 1);
   il_run_row<BK, IV, COLS, T>(rb, gq + head_off + (size_t)qrow * p.in.n, Kres, Vres, N, n_tiles, p.scale_log2e, col_at,
-                              expand_runs, mailbox + 4);
+                              expand_runs, const_cast<int *>(mailbox) + 4);
   asm volatile("" : "+s"(rec));  // read the rest of the record only here: scalar registers are scarce in the stream
   const int4 where = parts[rec + 2];
   const int part = where.x & 0xffff, n_parts = __builtin_amdgcn_readfirstlane(where.x >> 16);
@@ -174,6 +174,7 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
     if (__builtin_amdgcn_readfirstlane(*mailbox) != n_parts - 1) return;
     asm volatile("" : : : "memory");
     rb.merge_parts(row_parts, n_parts, reinterpret_cast<f32x2 *>(lds));
+    __syncthreads();
   }
   const int4 lists = parts[rec + 1];
   il_store_row(rb, lds, p, where.y, ht, r, fan_dst + lists.z, lists.w, gout, lse);
