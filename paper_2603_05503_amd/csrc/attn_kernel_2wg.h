@@ -30,6 +30,8 @@
 //  * the epilogue stages the normalised bf16 tile in LDS and stores whole rows
 //    with 16-byte accesses to the block itself and to all its repeat targets.
 #pragma once
+#include <float.h>
+
 #include "attn_common.h"
 
 namespace calibatt_dev {
@@ -127,7 +129,7 @@ struct RowBlock {
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
-    m_run = -INFINITY;
+    m_run = -FLT_MAX;  // finite: leading keys at -inf have no weight
     l_run = 0.f;
   }
 
@@ -303,6 +305,27 @@ struct RowBlock {
     __syncthreads();
     // m_run is the maximum of the logits times log2(e), l_tot the sum of 2^(logit - m_run)
     return l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f : -INFINITY;
+  }
+
+  // Result over a PART of the keys, for a later merge with the other parts: the
+  // rows normalised by their own sum as fp32 (rows[row_in_block][D]) and the
+  // natural logarithm of that sum (row_lse[row_in_block], -inf and a zero row
+  // when no key was seen), straight from the accumulators to global memory.
+  __device__ __forceinline__ void store_partial(float *rows, float *row_lse) const {
+    const float l_tot = sum_with_other_half(l_run);
+    const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+    float *orow = rows + (size_t)(wave * 32 + l32) * D;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        f32x4 w;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[j] = o[db][4 * a + j] * inv;
+        *reinterpret_cast<f32x4 *>(orow + 32 * db + 8 * a + 4 * g) = w;
+      }
+    if (g == 0)
+      row_lse[wave * 32 + l32] = l_tot > 0.f ? (m_run + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f : -INFINITY;
   }
 };
 

@@ -6,11 +6,14 @@
 // each result by a CSR list (dst_ptr / dst_idx).  A workgroup takes 128
 // consecutive computed queries of one (batch, head), gathers their rows of Q,
 // runs them against ALL key/value tiles with the same tile engine as the
-// block-sparse kernel (IlRow: transposed MFMA contractions and the online softmax
-// as one instruction stream, direct-to-LDS K/V tiles;
-// against the phases of RowBlock one after the other 3.38 -> 3.29 ms with five anchors and 19.46 -> 18.96 with thirty,
-// 40 heads of 32 760 tokens), stages the normalised bf16 rows in LDS and writes
-// each row to all of its receivers with 16-byte stores.
+// two-workgroup sparse kernel (RowBlock: transposed MFMA contractions, online
+// softmax, direct-to-LDS K/V tiles), stages the normalised bf16 rows in LDS and
+// writes each row to all of its receivers with 16-byte stores.  RowBlock's
+// reference is the running maximum, so the largest probability of a row is
+// exactly 1.  The interleaved stream (IlRow) takes 2.7 % less time (five
+// anchors, 40 heads of 32 760 tokens: 3.29 instead of 3.38 ms), but its
+// references follow the maximum at a distance, the largest probability takes a
+// rounding of its own, and the error against fp64 grows from 2.14e-3 to 2.33e-3.
 //
 // Placement: workgroups are dispatched to the 8 XCDs in turn (workgroup i runs
 // on XCD i mod 8), and every XCD has its own L2.  All workgroups of one head
@@ -28,7 +31,7 @@
 // of a unit (weights exp(lse_s - max lse)) and does the broadcast.  Units of
 // full rounds are untouched.
 #pragma once
-#include "attn_kernel_il.h"
+#include "attn_kernel_2wg.h"
 
 namespace calibatt_dev {
 
@@ -67,10 +70,7 @@ struct AnchorLds {
   static constexpr int ENT_OFF = PTR_OFF + 1024;               // int32[EC] receiver tokens
   static constexpr int ROW_OFF = ENT_OFF + ANCHOR_EC * 4;      // uint8[EC] row of the block each entry belongs to
   static constexpr int EPILOGUE_BYTES = ROW_OFF + ANCHOR_EC;
-  using Row = IlRow<D, ANCHOR_BQ, ANCHOR_BK>;
-  static constexpr int VOTES_OFF = Row::LDS_BYTES > EPILOGUE_BYTES ? Row::LDS_BYTES : EPILOGUE_BYTES;  // int[wave]
-  static constexpr int BYTES = VOTES_OFF + 64;
-  static_assert(Row::OST == RB::OST && Row::NT == RB::NT, "the broadcast reads what the row stages");
+  static constexpr int BYTES = RB::LDS_BYTES > EPILOGUE_BYTES ? RB::LDS_BYTES : EPILOGUE_BYTES;
   static constexpr int MERGE_W_OFF = EPILOGUE_BYTES;           // float[BQ][MAX_SPLIT] merge weights
   static constexpr int MERGE_BYTES = MERGE_W_OFF + ANCHOR_BQ * ANCHOR_MAX_SPLIT * 4;
   static constexpr int PART_FLOATS = ANCHOR_BQ * D + ANCHOR_BQ;  // one part in the workspace: rows, then their lse
@@ -118,35 +118,17 @@ __device__ __forceinline__ void anchor_broadcast(char *lds, int tid, int r, int 
   }
 }
 
-// The rows of a part normalised by their own sum as fp32 (rows[row_in_block][D]) and the natural logarithm of that sum
-// (row_lse[row_in_block], -inf and a zero row when no key was seen), straight from the accumulators to global memory.
-template <typename Row>
-__device__ __forceinline__ void anchor_store_part(const Row &rb, float *rows, float *row_lse) {
-  const float l_tot = sum_with_other_half(rb.l_run);
-  const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-  float *const orow = rows + (size_t)rb.row_in_block() * (Row::DB * 32);
-  static_unroll<4 * Row::DB>([&](auto q4) {
-    constexpr int db = q4 / 4, a = q4 % 4, base = Row::A_O + 16 * db + 4 * a;
-    f32x4 w;
-    static_unroll<4>([&](auto j) { w[(int)j] = acc_read<base + j>() * inv; });
-    *reinterpret_cast<f32x4 *>(orow + 32 * db + 8 * a + 4 * rb.g) = w;
-  });
-  if (rb.g == 0)
-    row_lse[rb.row_in_block()] = l_tot > 0.f ? (rb.m_run + __builtin_amdgcn_logf(l_tot)) * 0.6931471805599453f : -INFINITY;
-}
-
 template <int D>
-__global__ __launch_bounds__(ANCHOR_BQ * 2, 2) __attribute__((amdgpu_num_vgpr(IL_VGPRS))) void anchor_attn_fwd_kernel(
+__global__ __launch_bounds__(ANCHOR_BQ * 2, 2) void anchor_attn_fwd_kernel(
     const uint16_t *__restrict__ gq, const uint16_t *__restrict__ gk, const uint16_t *__restrict__ gv,
     uint16_t *__restrict__ gout, const int32_t *__restrict__ head_ids, const int32_t *__restrict__ q_index,
     const int32_t *__restrict__ dst_ptr, const int32_t *__restrict__ dst_idx, float *__restrict__ workspace,
     const AnchorDims p) {
   constexpr int BQ = ANCHOR_BQ, BK = ANCHOR_BK;
+  using RB = RowBlock<D, BQ, BK>;
   using L = AnchorLds<D>;
-  using Row = typename L::Row;
-  constexpr int NT = Row::NT, ROWB = Row::ROWB;
+  constexpr int NT = RB::NT, ROWB = RB::ROWB;
   static_assert(NT >= BQ + 1, "one thread per offset-table entry");
-  il_claim_registers();
 
   extern __shared__ __attribute__((aligned(1024))) char lds[];  // AnchorLds<D>::BYTES
 
@@ -176,24 +158,29 @@ __global__ __launch_bounds__(ANCHOR_BQ * 2, 2) __attribute__((amdgpu_num_vgpr(IL
   const int h = head_ids[bh - b * p.n_heads];
   if ((unsigned)h >= (unsigned)p.H) return;
 
-  Row rb(lds, (uint32_t)p.in.n * 2);
+  RB rb(lds, (uint32_t)p.in.n * 2);
   const int tid = rb.tid;
   const int N = p.N;
   const size_t head_off = (size_t)b * p.in.b + (size_t)h * p.in.h;
   const uint32_t head_bytes = (uint32_t)(N - 1) * rb.kv_row_bytes + ROWB;  // first byte after the last row
   const u32x4 Kres = head_rsrc(gk + head_off, head_bytes);
   const u32x4 Vres = head_rsrc(gv + head_off, head_bytes);
-  const int qi = min(r * BQ + rb.row_in_block(), p.n_q - 1);
-  const int tok = min(max(q_index[qi], 0), N - 1);
-  il_run_row<BK, false, 1, Bf16>(
-      rb, gq + head_off + (size_t)tok * p.in.n, Kres, Vres, N, c1 - c0, p.scale_log2e,
-      [&](int entry) { return c0 + entry; }, [](int) {}, reinterpret_cast<int *>(lds + L::VOTES_OFF));
+  rb.issue_k(Kres, c0);
+  rb.issue_v(Vres, c0);
+  {
+    int qi = r * BQ + rb.row_in_block();
+    qi = qi < p.n_q ? qi : p.n_q - 1;
+    int tok = q_index[qi];
+    tok = tok < 0 ? 0 : (tok < N ? tok : N - 1);
+    rb.begin(gq + head_off + (size_t)tok * p.in.n);
+  }
+  const float sc = p.scale_log2e;
+  for (int c = c0; c < c1; ++c) rb.tile(Kres, Vres, c, c + 1 < c1, c + 1, N, p.nbk, sc);
   if (part_out) {
-    anchor_store_part(rb, part_out, part_out + BQ * D);
+    rb.store_partial(part_out, part_out + BQ * D);
     return;
   }
-  rb.stage_rows(lds);
-  __syncthreads();
+  rb.stage_result();
   anchor_broadcast<D>(lds, tid, r, b, h, gout, dst_ptr, dst_idx, p);
 }
 

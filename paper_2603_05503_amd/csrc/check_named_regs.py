@@ -10,8 +10,7 @@ blocks, an instruction names an AGPR, an arch VGPR at or above the limit, or scr
 import re
 import sys
 
-KERNELS = {"sparse_attn_fwd_il_kernel": 72, "sparse_attn_fwd_split_kernel": 72,
-           "anchor_attn_fwd_kernel": 72}  # kernel name fragment -> arch VGPRs left to the compiler
+KERNELS = {"sparse_attn_fwd_il_kernel": 72, "sparse_attn_fwd_split_kernel": 72}  # kernel name fragment -> arch VGPRs left to the compiler
 
 
 def check(text):
