@@ -4,8 +4,8 @@
 // Same computation per query block as attn_kernel_2wg.h (paper, Section 2
 // Eq. 1-4 under the block mask of Section 3.2, repeated query blocks written
 // as copies, Section 3.3 / 3.4); the online softmax moves the reference of
-// its exponentials lazily (see IlRow::softmax_op and IL_SUM_MOVE), which changes
-// roundings but not what is computed.
+// its exponentials lazily (see IlRow::softmax_op), which changes roundings but
+// not what is computed.
 //
 // Why.  On this hardware a wavefront issues a vector-ALU instruction only
 // every 5-8 cycles, and the softmax of a 128-key tile is ~225 of them: with
@@ -21,7 +21,7 @@
 //     the MFMAs of  O += P V  of the sub-tile before the previous one,
 //     the MFMAs of  S = K Q^T of the next sub-tile,
 //     the vector instructions of the softmax of the previous sub-tile
-// (about three vector instructions behind every MFMA).  The chain of one
+// (three or four vector instructions behind every MFMA).  The chain of one
 // wavefront per tile is then little longer than its MFMAs alone, and the two
 // wavefronts per SIMD (two workgroups per CU, as in attn_kernel_2wg.h)
 // together keep the matrix pipe fed.  One workgroup barrier per stage.
@@ -56,14 +56,6 @@ namespace calibatt_dev {
 // than this (log2 domain): probabilities stay below 2^8, far inside the bf16 /
 // fp16 range, and keep their full relative precision.
 constexpr float IL_REF_SLACK = 8.0f;
-// bf16 probabilities have the range of fp32, and a reference may as well move one sub-tile late: the fast form of a stage
-// looks for no maximum.  A lane whose sum over the sub-tile exceeds 2^8 moves the reference for the sub-tiles that
-// follow; one of 2^64 or more (a logit that far above everything before it in its row), or a result that is not finite
-// after such a move, ends in the row's second run, in the exact form (what that row takes twice as long for).  That
-// leaves out 28 of some 120 vector instructions of a stage: 480p 5.46 -> 5.25 ms, all blocks kept 19.29 -> 18.61, 720p
-// 25.90 -> 24.93, key blocks of 96 3.00 -> 2.82, D = 64 1.69 -> 1.58.  fp16 probabilities have to stay below 2^16: always
-// exact.
-constexpr float IL_SUM_MOVE = 0x1p8f, IL_SUM_BAD = 0x1p64f;
 constexpr int IL_VGPRS = 72;  // arch VGPRs left to the compiler; the named ones follow
 constexpr int IL_STAGES = 6;  // operand staging slots
 constexpr int IL_AHEAD = 4;   // MFMAs between the issue of an operand's LDS reads and its use
@@ -109,12 +101,9 @@ struct IlRow : RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T> {
   float sc;          // |scale| * log2(e) (a negative scale is folded into the sign of Q)
   float alpha;       // factor by which O and the row sum shrink at the end of the current stage
   float psum[2];     // row sum of the sub-tile being exponentiated
-  float part[4], rm, neg_ref;
+  float part[2], neg_ref;
   float x[8];
-  // fast form: the reference that the next softmax takes, whether it moved there, whether it ever did, and whether a sum
-  // was out of range (the same for all lanes of the wave)
-  float m_next;
-  bool pending, late, bad;
+  bool moved;        // whether some lane's reference moved in the current stage (the same for all lanes of the wave)
 
   __device__ __forceinline__ IlRow(char *lds_, uint32_t kv_row_bytes_) : RB(lds_, kv_row_bytes_) {
     const uint32_t lds_base = (uint32_t)(uintptr_t)(LDS_PTR(char))lds_;  // a multiple of 1024
@@ -168,41 +157,46 @@ struct IlRow : RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T> {
   }
 
   // ---- the vector side of a stage: softmax of the sub-tile in S buffer PAR, as a list of N_OPS steps
-  // Steps [0, EL/2): running maxima of the logits (four chains).  Step EL/2: the row's largest logit
-  // of this sub-tile and the decision about the reference: m_run is the value subtracted in the
-  // exponent; any value works as long as the exponentials stay in range, since numerator and
-  // denominator carry the same factor.  It moves up to the running maximum only when that exceeds
-  // it by more than IL_REF_SLACK (always on a row's first sub-tile, whose reference is the lowest float); then
-  // alpha = 2^(old - new) < 1 and O and the row sum are rescaled at the end of the stage, else
-  // alpha = 1 and they are left alone (O sits in AGPRs, where rescaling costs three instructions
-  // per element).  Then, per group of 8 keys: 8 x (sc * s - m_run), 8 x exp2, 4 x round-and-pack
-  // into the named registers over the logits plus add the packed pair to the row sum.
+  // Steps [0, EL/2): maximum of the lane's logits, in two chains that the last step joins.  Step EL/2: the decision about
+  // the reference: m_run is the value subtracted in the exponent; any value works as long as the exponentials stay in
+  // range, since numerator and denominator carry the same factor.  It moves up to the row's largest logit of this
+  // sub-tile only when that exceeds it by more than IL_REF_SLACK (always on a row's first sub-tile, whose reference is
+  // the lowest float); then alpha = 2^(old - new) < 1 and O and the row sum are rescaled at the end of the stage (O sits
+  // in AGPRs, where rescaling costs three instructions per element).  The logit that a reference moves to has a
+  // probability of exactly 1.  Most sub-tiles move no reference, and the decision is a branch over the wave: two
+  // instructions tell whether any lane could, instead of twelve that work out what moves.  Together with one LDS wait
+  // for two MFMAs' operands: 480p 5.44 -> 5.36 ms, all blocks kept 19.32 -> 18.97, 720p 25.95 -> 25.59, the same bits.
+  // (Without the maxima, a reference that moves one sub-tile late by the logarithm of the sub-tile's sum takes 3 % off
+  // that again, 480p 5.21 ms; but then the largest probability is rounded like any other, and rows that two keys share
+  // are up to 3.4e-3 off instead of 1.4e-3.)  Then, per group of 8 keys: 8 x (sc * s - m_run), 8 x exp2, 4 x
+  // round-and-pack into the named registers over the logits plus add the packed pair to the row sum.
   static constexpr int N_GROUPS = EL / 8;
   static constexpr int OPS_MAX = EL / 2, OPS_GROUP = 8 + 8 + 4;
   static constexpr int N_OPS = OPS_MAX + 1 + N_GROUPS * OPS_GROUP;
-  // The fast form leaves out the maxima and the decision.
-  static constexpr __device__ int n_ops(bool exact) { return exact ? N_OPS : N_GROUPS * OPS_GROUP; }
-  template <int PAR, bool EXACT, int J_>
+  template <int PAR, int J>
   __device__ __forceinline__ void softmax_op() {
-    constexpr int B = V_S + PAR * EL, J = EXACT ? J_ : J_ + OPS_MAX + 1;
-    if constexpr (J < OPS_MAX) {
-      if constexpr (J < 4) part[J] = -INFINITY;
-      named_max3<B + 2 * J, B + 2 * J + 1>(part[J & 3]);
+    constexpr int B = V_S + PAR * EL;
+    if constexpr (J == 0) {
+      part[0] = named_max_of<B, B + 1>();
+    } else if constexpr (J == 1) {
+      part[1] = named_max3_of<B + 2, B + 3, B + 4>();
+    } else if constexpr (J < OPS_MAX - 1) {
+      named_max3<B + 2 * J + 1, B + 2 * J + 2>(part[J & 1]);
+    } else if constexpr (J == OPS_MAX - 1) {
+      named_max3_with<B + EL - 1>(part[0], part[1]);
     } else if constexpr (J == OPS_MAX) {
-      // (plain asm maxima: the compiler would first canonicalise every operand that came out of an asm)
-      asm volatile("v_max3_f32 %0, %0, %1, %2" : "+v"(part[0]) : "v"(part[1]), "v"(part[2]));
-      asm volatile("v_max_f32 %0, %0, %1" : "+v"(part[0]) : "v"(part[3]));
-      float other;
-      halves_of(part[0], rm, other);
-      asm volatile("v_max_f32 %0, %0, %1" : "+v"(rm) : "v"(other));
-      rm *= sc;
-      const float m_old = this->m_run;
-      const float m_new = rm - m_old > IL_REF_SLACK ? rm : m_old;  // rm > m_old where it is taken
-      alpha = __builtin_amdgcn_exp2f(m_old - m_new);  // 0 on the first sub-tile; 1 when nothing moves
-      this->m_run = m_new;
-      neg_ref = -m_new;
       psum[0] = 0.f;
       psum[1] = 0.f;
+      // a little less than IL_REF_SLACK: the product is not rounded here as it is below
+      moved = __any(__builtin_fmaf(part[0], sc, neg_ref) > IL_REF_SLACK - 0.01f);
+      if (moved) {
+        const float rm = max_with_other_half(part[0]) * sc;
+        const float m_old = this->m_run;
+        const float m_new = rm - m_old > IL_REF_SLACK ? rm : m_old;  // rm > m_old where it is taken
+        alpha = __builtin_amdgcn_exp2f(m_old - m_new);  // 0 on the first sub-tile; 1 where nothing moves
+        this->m_run = m_new;
+        neg_ref = -m_new;
+      }
     } else {
       constexpr int g = (J - OPS_MAX - 1) / OPS_GROUP, o = (J - OPS_MAX - 1) % OPS_GROUP;
       if constexpr (o < 8) {
@@ -225,23 +219,12 @@ struct IlRow : RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T> {
   // behind each (or every second) of the first MFMAs: V rows [v_row0, v_row0 + SUB) into V slot
   // 1 - PAR, then K rows [k_row0, k_row0 + SUB) into K slot 1 - PAR (both slots were released by the
   // stage before).
-  template <int PAR, bool HAS_PV, bool HAS_QK, bool HAS_SM, bool EXACT, bool LOADS = false>
+  template <int PAR, bool HAS_PV, bool HAS_QK, bool HAS_SM, bool LOADS = false>
   __device__ __forceinline__ void stage(const u32x4 &Vres = u32x4{0, 0, 0, 0}, int v_row0 = 0,
                                         const u32x4 &Kres = u32x4{0, 0, 0, 0}, int k_row0 = 0) {
     constexpr int FIRST = HAS_PV ? 0 : N_PV, LAST = HAS_QK ? N_PV + N_QK : N_PV, M = LAST - FIRST;
-    constexpr int OPS = HAS_SM ? n_ops(EXACT) : 0;
+    constexpr int OPS = HAS_SM ? N_OPS : 0;
     static_assert(!LOADS || 2 * LOADS_PER_WAVE <= M, "more load instructions than MFMAs");
-    bool moved = EXACT;
-    if constexpr (HAS_SM && !EXACT) {
-      psum[0] = psum[1] = 0.f;
-      moved = pending;
-      if (pending) {
-        alpha = __builtin_amdgcn_exp2f(this->m_run - m_next);
-        this->m_run = m_next;
-        neg_ref = -m_next;
-        pending = false;
-      }
-    }
     __builtin_amdgcn_s_setprio(1);
     static_unroll<(IL_AHEAD < M ? IL_AHEAD : M)>([&](auto k) { issue_operand_reads<PAR, FIRST + k>(); });
     static_unroll<M>([&](auto k) {
@@ -263,16 +246,19 @@ struct IlRow : RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T> {
                           this->k_lane_off, this->kv_row_bytes);
       // the softmax steps are spread evenly over the MFMAs: step J follows MFMA floor(J * M / OPS)
       constexpr int J0 = (k * OPS + M - 1) / M, J1 = ((k + 1) * OPS + M - 1) / M;
-      static_unroll<J1 - J0>([&](auto q) { softmax_op<1 - PAR, EXACT, J0 + q>(); });
+      static_unroll<J1 - J0>([&](auto q) { softmax_op<1 - PAR, J0 + q>(); });
     });
     __builtin_amdgcn_s_setprio(0);
     // MFMA results are read by vector instructions only behind this (S in the next stage, O below
-    // and in the epilogue): the last MFMA's write has to land first
-    asm volatile("s_nop 15\n\ts_nop 7");
-    if constexpr (HAS_SM) {
+    // and in the epilogue): the last MFMA's write has to land first, and the last dot product's, which the asm names so
+    // that nothing reads the sums in front of it (csrc/check_mfma_waits.py)
+    if constexpr (!HAS_SM) {
+      asm volatile("s_nop 15\n\ts_nop 7");
+    } else {
+      asm volatile("s_nop 15\n\ts_nop 7" : "+v"(psum[0]), "+v"(psum[1]));
       const float sum = psum[0] + psum[1];
       if (moved) {
-        this->l_run *= alpha;
+        this->l_run = __builtin_fmaf(this->l_run, alpha, sum);
         if (HAS_PV && __any(alpha != 1.0f)) {  // (nothing in O before the first P V)
           static_unroll<2 * DB>([&](auto h) {
             float o8[8];
@@ -280,13 +266,8 @@ struct IlRow : RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T> {
             static_unroll<8>([&](auto i) { acc_write<A_O + 8 * h + i>(o8[i] * alpha); });
           });
         }
-      }
-      this->l_run += sum;
-      if (!EXACT && __any(!(sum <= IL_SUM_MOVE))) {
-        bad |= __any(!(sum < IL_SUM_BAD));
-        const float most = max_with_other_half(sum);
-        m_next = most > IL_SUM_MOVE ? this->m_run + __builtin_amdgcn_logf(most) : this->m_run;
-        pending = late = true;
+      } else {
+        this->l_run += sum;
       }
     }
   }
@@ -304,13 +285,6 @@ struct IlRow : RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T> {
     });
   }
 
-  // Whether O holds an infinity or a NaN in any lane of the wave.
-  __device__ __forceinline__ bool not_finite() const {
-    float zero = 0.f;
-    static_unroll<16 * DB>([&](auto i) { zero = __builtin_fmaf(acc_read<A_O + i>(), 0.f, zero); });
-    return __any(!(zero == 0.f));
-  }
-
   // Start a row: empty running state, zero accumulators, and the loads of the Q^T operand into the AGPRs (lane (query
   // l32, half g) holds d = 16 s + 8 g + [0,8) of k-slab s), in flight on return.  finish_q, behind their wait, folds a
   // negative scale into the operand's sign.
@@ -322,9 +296,9 @@ struct IlRow : RowBlock<D, BQ, 2 * il_sub(D, BQ, BK), T> {
     sc = fmaxf(fabsf(scale_log2e), 1e-30f);
     this->m_run = -FLT_MAX;  // finite: leading keys at -inf have no weight, wherever a row's part begins
     this->l_run = 0.f;
+    neg_ref = FLT_MAX;
     alpha = 1.f;
-    m_next = this->m_run;
-    pending = late = bad = false;
+    moved = false;
   }
   __device__ __forceinline__ void finish_q(float scale_log2e) const {
     if (scale_log2e < 0.f)
@@ -365,10 +339,11 @@ __device__ __forceinline__ void il_claim_registers() {
 #undef CALIBATT_R10
 }
 
-// Runs one row of key blocks, or a part of one, from its first loads to the last O += P V, EXACT or in the fast form of the
-// softmax (the first sub-tile, which sets the reference, always exactly).
-template <int BK, bool IV, int COLS, bool EXACT, typename Row, typename ColAt, typename Expand>
-__device__ __forceinline__ void il_stream(Row &rb, const uint16_t *qrow_ptr, const u32x4 &Kres, const u32x4 &Vres,
+// Runs one row of key blocks, or a part of one, from its first loads to the last O += P V.  col_at(i): key block of entry
+// i < n_tiles of the row's list; expand(i): called before entries of the next COLS are asked for, from entry i on (IV).  On
+// return the sums lie in the registers; other waves may still be reading the tile windows.
+template <int BK, bool IV, int COLS, typename Row, typename ColAt, typename Expand>
+__device__ __forceinline__ void il_run_row(Row &rb, const uint16_t *qrow_ptr, const u32x4 &Kres, const u32x4 &Vres,
                                            int N, int n_tiles, float scale_log2e, ColAt col_at, Expand expand) {
   constexpr int SUB = Row::SUB, SPB = Row::SPB, LOADS = Row::LOADS_PER_WAVE;
   // kept key blocks of the row, 64 at a time in one VGPR (lane j = entry j of the current 64)
@@ -420,7 +395,7 @@ __device__ __forceinline__ void il_stream(Row &rb, const uint16_t *qrow_ptr, con
   rb.finish_q(scale_log2e);
   __syncthreads();
   // stage 0: S of u_0
-  rb.template stage<0, false, true, false, true>();
+  rb.template stage<0, false, true, false>();
   CALIBATT_IL_MASK(0, r0)
   wait_vmem<0>();
   __syncthreads();
@@ -428,7 +403,7 @@ __device__ __forceinline__ void il_stream(Row &rb, const uint16_t *qrow_ptr, con
   int row_a = r1;            // of u_(k-1) at the start of stage k (k even below)
   int row_b = next_rows();   // of u_k
   rb.issue_k_sub(Kres, row_b, 0);
-  rb.template stage<1, false, true, true, true>();
+  rb.template stage<1, false, true, true>();
   CALIBATT_IL_MASK(1, r1)
   wait_vmem<0>();
   __syncthreads();
@@ -436,7 +411,7 @@ __device__ __forceinline__ void il_stream(Row &rb, const uint16_t *qrow_ptr, con
   for (int k = 2; k < n_stream; k += 2) {
     // stage k: loads inside the stream: V of u_(k-1), K of u_(k+1) (beyond the stream: zeros into a slot nobody reads)
     const int row_c = next_rows();
-    rb.template stage<0, true, true, true, EXACT, true>(Vres, row_a, Kres, row_c);
+    rb.template stage<0, true, true, true, true>(Vres, row_a, Kres, row_c);
     CALIBATT_IL_MASK(0, row_b)
     wait_vmem<0>();
     __syncthreads();
@@ -444,7 +419,7 @@ __device__ __forceinline__ void il_stream(Row &rb, const uint16_t *qrow_ptr, con
     if (odd_end) break;
     // stage k + 1: V of u_k, K of u_(k+2)
     const int row_d = next_rows();
-    rb.template stage<1, true, true, true, EXACT, true>(Vres, row_b, Kres, row_d);
+    rb.template stage<1, true, true, true, true>(Vres, row_b, Kres, row_d);
     CALIBATT_IL_MASK(1, row_c)
     wait_vmem<0>();
     __syncthreads();
@@ -456,39 +431,17 @@ __device__ __forceinline__ void il_stream(Row &rb, const uint16_t *qrow_ptr, con
   // and stage n_stream + 1: O += P V of u_(n_stream-1)
   if (odd_end) {
     rb.issue_v_sub(Vres, row_b, 0);
-    rb.template stage<1, true, false, true, EXACT>();
+    rb.template stage<1, true, false, true>();
     wait_vmem<0>();
     __syncthreads();
-    rb.template stage<0, true, false, false, EXACT>();
+    rb.template stage<0, true, false, false>();
   } else {
     rb.issue_v_sub(Vres, row_a, 1);
-    rb.template stage<0, true, false, true, EXACT>();
+    rb.template stage<0, true, false, true>();
     wait_vmem<0>();
     __syncthreads();
-    rb.template stage<1, true, false, false, EXACT>();
+    rb.template stage<1, true, false, false>();
   }
-}
-
-// The same in whichever form it takes.  col_at(i): key block of entry i < n_tiles of the row's list; expand(i): called before
-// entries of the next COLS are asked for, from entry i on (IV).  votes: LDS, an int per wave.  On return the sums lie in the
-// registers and every wave is done with the tile windows.
-template <int BK, bool IV, int COLS, typename T, typename Row, typename ColAt, typename Expand>
-__device__ __forceinline__ void il_run_row(Row &rb, const uint16_t *qrow_ptr, const u32x4 &Kres, const u32x4 &Vres,
-                                           int N, int n_tiles, float scale_log2e, ColAt col_at, Expand expand,
-                                           int *votes_) {
-  LDS_PTR(volatile int) const votes = (LDS_PTR(volatile int))votes_;
-  if constexpr (std::is_same<T, Bf16>::value) {
-    il_stream<BK, IV, COLS, false>(rb, qrow_ptr, Kres, Vres, N, n_tiles, scale_log2e, col_at, expand);
-    if (rb.late && !rb.bad) rb.bad = rb.not_finite();
-    if (rb.lane == 0) votes[rb.wave] = rb.bad;
-    __syncthreads();
-    int again = 0;
-    for (int w = 0; w < Row::NW; ++w) again |= votes[w];
-    if (!__builtin_amdgcn_readfirstlane(again)) return;
-    if constexpr (IV) expand(0);
-  }
-  il_stream<BK, IV, COLS, true>(rb, qrow_ptr, Kres, Vres, N, n_tiles, scale_log2e, col_at, expand);
-  __syncthreads();
 }
 
 // The rows of block r, normalised and rounded, through LDS to the block itself and to the blocks [fan, fan + n_fan) that
@@ -606,8 +559,9 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
     }
     auto col_at = [&](int entry) { return IV ? cols[entry - chunk_lo] : col_idx[cbeg + entry]; };
     const int qrow = min(r * BQ + rb.row_in_block(), N - 1);
-    il_run_row<BK, IV, COLS, T>(rb, gq + head_off + (size_t)qrow * p.in.n, Kres, Vres, N, n_tiles, p.scale_log2e, col_at,
-                                expand_runs, const_cast<int *>(mailbox) + 4);
+    il_run_row<BK, IV, COLS>(rb, gq + head_off + (size_t)qrow * p.in.n, Kres, Vres, N, n_tiles, p.scale_log2e, col_at,
+                             expand_runs);
+    __syncthreads();  // every wave is done with the tile windows
     const int fbeg = fan_ptr[item];
     const int n_fan = fan_ptr[item + 1] - fbeg;
     if (head_ok) il_store_row(rb, lds, p, b, ht, r, fan_dst + fbeg, n_fan, gout, lse);

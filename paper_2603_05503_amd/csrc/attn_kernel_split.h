@@ -146,8 +146,9 @@ __global__ __launch_bounds__(BQ * 2, (BQ >= 128 ? 2 : 1)) __attribute__((amdgpu_
   if constexpr (IV) expand_runs(0);
   auto col_at = [&](int entry) { return IV ? cols[first + entry - chunk_lo] : col_idx[cbeg + entry]; };
   const int qrow = min(r * BQ + rb.row_in_block(), N - 1);
-  il_run_row<BK, IV, COLS, T>(rb, gq + head_off + (size_t)qrow * p.in.n, Kres, Vres, N, n_tiles, p.scale_log2e, col_at,
-                              expand_runs, const_cast<int *>(mailbox) + 4);
+  il_run_row<BK, IV, COLS>(rb, gq + head_off + (size_t)qrow * p.in.n, Kres, Vres, N, n_tiles, p.scale_log2e, col_at,
+                           expand_runs);
+  __syncthreads();  // every wave is done with the tile windows
   asm volatile("" : "+s"(rec));  // read the rest of the record only here: scalar registers are scarce in the stream
   const int4 where = parts[rec + 2];
   const int part = where.x & 0xffff, n_parts = __builtin_amdgcn_readfirstlane(where.x >> 16);

@@ -78,6 +78,22 @@ __device__ __forceinline__ void mfma_named() {
 }
 // Vector ALU on named arch VGPRs (volatile: executed in the order written).
 template <int R0, int R1>
+__device__ __forceinline__ float named_max_of() {
+  float m;
+  asm volatile("v_max_f32 %0, v[%1], v[%2]" : "=v"(m) : "n"(R0), "n"(R1));
+  return m;
+}
+template <int R0, int R1, int R2>
+__device__ __forceinline__ float named_max3_of() {
+  float m;
+  asm volatile("v_max3_f32 %0, v[%1], v[%2], v[%3]" : "=v"(m) : "n"(R0), "n"(R1), "n"(R2));
+  return m;
+}
+template <int R>
+__device__ __forceinline__ void named_max3_with(float &m, float other) {
+  asm volatile("v_max3_f32 %0, %0, %1, v[%2]" : "+v"(m) : "v"(other), "n"(R));
+}
+template <int R0, int R1>
 __device__ __forceinline__ void named_max3(float &m) {
   asm volatile("v_max3_f32 %0, %0, v[%1], v[%2]" : "+v"(m) : "n"(R0), "n"(R1));
 }

@@ -83,3 +83,26 @@ def test_anchor_rows_behind_keys_without_mass(lib, D, split):
     want = dense_rows(qf, kf[first:], vf[first:], 1.0)
     got = bits_to_f64(from_dev(out))[0, 0]
     assert np.isfinite(got).all() and np.abs(got - want).max() <= 2e-2 and np.linalg.norm(got - want) <= 8e-3 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("D,bq,bk", [(128, 128, 128), (128, 128, 192), (128, 128, 96), (128, 64, 64), (64, 128, 64), (64, 64, 128)])
+@pytest.mark.parametrize("max_blocks", [None, 2])
+def test_sparse_rows(lib, D, bq, bk, max_blocks):
+    import torch
+
+    print(f"dominant key, sparse rows D={D} {bq}x{bk} max_blocks={max_blocks}", flush=True)
+    N = 1600
+    (q, k, v), scale, want = two_keys(D, N, 700, 1100, 5)
+    nbq, nbk = -(-N // bq), -(-N // bk)
+    dp = lib.compile_pattern(np.ones((1, nbq, nbk), np.uint8), None, 1, N, bq, bk).to_device(intervals=True)
+    if max_blocks is None:
+        dp._plans = {}
+        dp._own.splits = {}
+    else:
+        dp._plan(True, max_blocks)
+    out = torch.full((1, 1, N, D), math.nan, dtype=torch.bfloat16, device="cuda")
+    lib.sparse_attn_fwd(to_dev(q), to_dev(k), to_dev(v), out, dp, scale)
+    torch.cuda.synchronize()
+    err = np.abs(bits_to_f64(from_dev(out))[0, 0] - want).max()
+    print(f"  largest error {err:.3e}, bound {BOUND:.3e}", flush=True)
+    assert err <= BOUND

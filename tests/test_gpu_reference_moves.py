@@ -1,5 +1,5 @@
-"""Logits that leave the reference of a row's exponentials behind, by little, by much and by more than the fast form of
-the softmax can take in one sub-tile (the row then runs again in the exact form), rising, falling and late in the row."""
+"""Logits that leave the reference of a row's exponentials behind, by little, by much and by more than the range of an
+exponential, rising, falling and late in the row."""
 import math
 
 import numpy as np
@@ -57,7 +57,7 @@ def test_reference_moves(lib, D, bq, bk, steps, max_blocks):
 
 
 def test_large_values_behind_a_move(lib):
-    """Values so large that probabilities above 2^8 would overflow their products: the row runs again."""
+    """Values so large that probabilities far above 2^8 would overflow their products."""
     import torch
 
     print("reference large values", flush=True)
