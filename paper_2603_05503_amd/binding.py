@@ -266,9 +266,11 @@ class HostPattern:
         c = _CPattern()
         for f in ("H", "N", "block_q", "block_k", "nbq", "nbk", "n_work", "n_repeat", "order", "max_row", "nnz"):
             setattr(c, f, getattr(self, f))
-        c.row_ptr, c.work, c.fan_ptr, c.col_idx = (
-            a.ctypes.data for a in (self.row_ptr, self.work, self.fan_ptr, self.col_idx))
+        # the library reads packed int32; `lists` keeps what is copied for that
+        lists = [np.ascontiguousarray(a, np.int32) for a in (self.row_ptr, self.work, self.fan_ptr, self.col_idx)]
+        c.row_ptr, c.work, c.fan_ptr, c.col_idx = (a.ctypes.data for a in lists)
         if iv_ptr is not None:
+            iv_ptr = np.ascontiguousarray(iv_ptr, np.int32)
             c.iv_ptr = iv_ptr.ctypes.data
         split = _CSplit()
         cap = 2 * (self.n_work * B + 1024)  # more than most plans have

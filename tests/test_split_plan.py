@@ -79,3 +79,24 @@ def test_workspace_and_refusals(lib):
         buf = np.empty(12, np.int32)
         assert raw.calibatt_plan_split(C.byref(c), B, max_blocks, binding._ptr(buf, C.c_int32), 1, C.byref(out)) == status
     assert raw.calibatt_plan_split(None, 1, 0, None, 0, C.byref(out)) == -1
+
+
+def test_plan_of_lists_that_are_views(lib):
+    """Host lists that are strided views or of another integer type give the plan of their values."""
+    import dataclasses
+
+    mask, repeat = random_mask(6, 3, 20, 20, 0.5, 0.2, keep_diagonal=True)
+    hp = lib.compile_pattern(mask, repeat, 3, 20 * 128, 128, 128)
+
+    def view(a):  # every second entry of an array whose others are zero
+        wide = np.full((a.size, 2), 0, np.int32)
+        wide[:, 0] = a
+        return wide[:, 0]
+
+    lists = ("row_ptr", "col_idx", "work", "fan_ptr")
+    want = hp.plan_split(1, 3)
+    for change in (view, lambda a: a.astype(np.int64)):
+        got = dataclasses.replace(hp, **{n: change(getattr(hp, n)) for n in lists}).plan_split(1, 3)
+        assert (got[1] == want[1]).all() and got[0].n_slots == want[0].n_slots
+    backwards = dataclasses.replace(hp, work=np.ascontiguousarray(hp.work[::-1])[::-1])
+    assert (backwards.plan_split(1, 3)[1] == want[1]).all()
