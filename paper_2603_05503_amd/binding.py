@@ -456,7 +456,7 @@ def sparse_attn_fwd(q, k, v, out, pattern: DevicePattern, scale: float,
     strides.  ``lse``: optional contiguous fp32 CUDA tensor [B, H, N] that receives the log-sum-exp of
     every query's kept logits.  ``kernel``: KERNEL_AUTO, KERNEL_TWO_WORKGROUPS or KERNEL_INTERLEAVED (the
     ``kernel`` field of calibatt_fwd_options).  Calls that the pattern has a split for (``DevicePattern``)
-    go through calibatt_sparse_attn_fwd_split, other packed bf16 calls without ``lse`` and with the automatic
+    go through calibatt_sparse_attn_fwd_split (with whole rows where its workspace cannot be had), other packed bf16 calls without ``lse`` and with the automatic
     kernel choice through calibatt_sparse_attn_fwd, everything else through calibatt_sparse_attn_fwd_ex."""
     import torch
 
@@ -481,7 +481,7 @@ def sparse_attn_fwd(q, k, v, out, pattern: DevicePattern, scale: float,
     bk = pattern.host.block_k if block_k is None else block_k
     stream, other = _stream_of(stream, q.device)
     state = pattern._for_stream(stream)
-    split = None if kernel == KERNEL_TWO_WORKGROUPS else state.splits.get(B)
+    split = state.splits.get(B) if kernel != KERNEL_TWO_WORKGROUPS and bq == pattern.host.block_q else None
     packed = q.is_contiguous() and out.is_contiguous()
     args = (q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), B, H, N, D, bq, bk, state.c_ref, float(scale))
     if split is None and packed and lse is None and dtype == torch.bfloat16 and kernel == KERNEL_AUTO:
@@ -490,28 +490,37 @@ def sparse_attn_fwd(q, k, v, out, pattern: DevicePattern, scale: float,
         si, so = _CStrides(*strides[:3]), _CStrides(*out_strides[:3])
         opt = _CFwdOptions(None if packed else C.pointer(si), None if packed else C.pointer(so),
                            0 if dtype == torch.bfloat16 else 1, None if lse is None else lse.data_ptr(), int(kernel))
+        st = None
         if split is None:
-            st = lib.calibatt_sparse_attn_fwd_ex(*args, C.byref(opt), stream)
+            pass
         elif other is None:
             st = _split_call(lib, args, opt, split, bq, D, q.device, stream)
         else:
             with torch.cuda.stream(other):
                 st = _split_call(lib, args, opt, split, bq, D, q.device, stream)
+        if st is None:
+            st = lib.calibatt_sparse_attn_fwd_ex(*args, C.byref(opt), stream)
     if st != 0:
         raise CalibattError(st, "calibatt_sparse_attn_fwd")
     return out
 
 
 def _split_call(lib, args, opt, split, block_q, D, device, stream):
-    """calibatt_sparse_attn_fwd_split with a workspace of torch's current stream, which is the call's."""
+    """calibatt_sparse_attn_fwd_split with a workspace of torch's current stream, which is the call's; None where the
+    memory for it is not there (the call then runs with whole rows, which take none)."""
     import torch
 
+    if not split.n_slots:  # no row is cut: nothing is left anywhere
+        return lib.calibatt_sparse_attn_fwd_split(*args, C.byref(opt), C.byref(split), None, 0, stream)
     nbytes = split.n_slots * _part_bytes(block_q, D)
-    workspace = torch.empty(nbytes // 4, dtype=torch.float32, device=device)
-    if torch.cuda.is_current_stream_capturing():
-        # a captured call counts in memory of its own graph: replays may overlap calls of the stream it is captured on
-        arrivals = torch.zeros(max(split.n_rows, 1), dtype=torch.int32, device=device)
-        split = _CSplit(split.B, split.n_parts, split.n_rows, split.n_slots, split.parts, arrivals.data_ptr())
+    try:
+        workspace = torch.empty(nbytes // 4, dtype=torch.float32, device=device)
+        if torch.cuda.is_current_stream_capturing():
+            # a captured call counts in memory of its own graph: replays may overlap calls of the stream it is captured on
+            arrivals = torch.zeros(split.n_rows, dtype=torch.int32, device=device)
+            split = _CSplit(split.B, split.n_parts, split.n_rows, split.n_slots, split.parts, arrivals.data_ptr())
+    except torch.OutOfMemoryError:
+        return None
     return lib.calibatt_sparse_attn_fwd_split(*args, C.byref(opt), C.byref(split), workspace.data_ptr(), nbytes, stream)
 
 

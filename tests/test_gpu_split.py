@@ -143,3 +143,38 @@ def test_streams_and_graphs(lib):
         torch.cuda.synchronize()
         assert torch.equal(captured.view(torch.int16), want.view(torch.int16))
         assert torch.equal(eager.view(torch.int16), want.view(torch.int16))
+
+
+def test_no_memory_for_the_workspace(lib):
+    """A call whose workspace cannot be had runs with whole rows; one that has gone wrong otherwise says so as without a
+    plan."""
+    import torch
+
+    from paper_2603_05503_amd.binding import CalibattError
+
+    print("split without memory", flush=True)
+    H, N, D = 4, 2000, 128
+    q, k, v = (to_dev(x) for x in _qkv(15, 1, H, N, D))
+    mask, repeat = random_mask(16, H, 16, 16, 0.6, 0.2, keep_diagonal=True, tail_partial=True)
+    hp = lib.compile_pattern(mask, repeat, H, N, 128, 128)
+    want, out = torch.empty_like(q), torch.empty_like(q)
+    lib.sparse_attn_fwd(q, k, v, want, hp.to_device(persistent=False), 0.088)
+    dp = _pattern(lib, mask, repeat, H, N, 128, 128, 2)
+    assert dp._plans[1][0].n_slots * 67584 > 4 << 20  # more than what the allocator's small blocks could hold
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    try:
+        torch.cuda.set_per_process_memory_fraction(torch.cuda.memory_reserved() / total)
+        held = []
+        with pytest.raises(torch.OutOfMemoryError):  # take what is left of the blocks that the allocator has
+            for _ in range(1000):
+                held.append(torch.empty(1 << 20, dtype=torch.float32, device="cuda"))
+        lib.sparse_attn_fwd(q, k, v, out, dp, 0.088)
+        torch.cuda.synchronize()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.equal(out.view(torch.int16), want.view(torch.int16))
+    for block_q in (-128, 64, 1 << 30):
+        with pytest.raises(CalibattError):
+            lib.sparse_attn_fwd(q, k, v, out, dp, 0.088, block_q=block_q)
