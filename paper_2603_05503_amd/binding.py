@@ -424,7 +424,7 @@ class DevicePattern:
                 if self._spare:
                     words = self._spare.pop()
                 else:  # cleared on the stream that uses it: nothing orders a fill on another one before the call
-                    with torch.cuda.stream(torch.cuda.ExternalStream(stream_handle, device=self.counter.device)):
+                    with torch.cuda.stream(_torch_stream(stream_handle, self.counter.device)):
                         words = torch.zeros(self._words, dtype=torch.int32, device=self.counter.device)
                 clone.work_counter = words.data_ptr()
                 self._per_stream[stream_handle] = _StreamState(clone, words, self._splits_with(words))
@@ -623,6 +623,13 @@ def anchor_attn_fwd(q, k, v, out, head_ids, amap: DeviceAnchorMap, scale: float,
     return out
 
 
+def _torch_stream(handle: int, device):
+    """The torch stream of a handle (ExternalStream(0) is not the default stream but one of torch's own)."""
+    import torch
+
+    return torch.cuda.ExternalStream(handle, device=device) if handle else torch.cuda.default_stream(device)
+
+
 def _stream_of(stream, device):
     """(handle, other): the stream handle of a call (None = torch's current stream), and that stream as a torch stream
     where it is not the current one.  What a call allocates is allocated under ``torch.cuda.stream(other)`` (None = the
@@ -634,7 +641,7 @@ def _stream_of(stream, device):
     current = torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
     if stream is None or int(stream) == current:
         return current, None
-    return int(stream), torch.cuda.ExternalStream(int(stream), device=device)
+    return int(stream), _torch_stream(int(stream), device)
 
 
 def _empty(shape, dtype, device, other, returned=False):

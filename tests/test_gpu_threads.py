@@ -94,3 +94,34 @@ def test_first_calls_on_streams_do_not_wait_for_another(lib):
     torch.cuda.synchronize()
     for i, out in enumerate(outs):
         assert torch.equal(out.view(torch.int16), want), i
+
+
+def test_default_stream_by_its_handle(lib):
+    """Handle 0 names the default stream also where another one is current: what a call allocates and clears lies there."""
+    import torch
+
+    from paper_2603_05503_amd import binding
+
+    print("default stream by its handle", flush=True)
+    H, N, D, blk = 4, 2000, 128, 128
+    q, k, v = (to_dev(x) for x in _qkv(905, 1, H, N, D, 2.0))
+    mask, repeat = random_mask(906, H, 16, 16, 0.6, 0.2, tail_partial=True)
+    dp = lib.compile_pattern(mask, repeat, H, N, blk, blk).to_device()
+    dp._plan(True, 2)
+    want = lib.sparse_attn_fwd(q, k, v, torch.empty_like(q), dp, 0.09).view(torch.int16).clone()
+    dp._plan(True, 2)
+    dp._spare.clear()
+    side, out = torch.cuda.Stream(), torch.empty_like(q)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        lib.sparse_attn_fwd(q, k, v, out, dp, 0.09)  # the pattern's own words go to the side stream
+        side.synchronize()
+        handle, other = binding._stream_of(0, q.device)
+        assert handle == 0 and other.cuda_stream == 0
+        for _ in range(2):
+            lib.sparse_attn_fwd(q, k, v, out.zero_(), dp, 0.09, stream=side.cuda_stream)
+            side.synchronize()
+            lib.sparse_attn_fwd(q, k, v, out, dp, 0.09, stream=0)
+            torch.cuda.synchronize()
+            assert torch.equal(out.view(torch.int16), want)
+    assert list(dp._per_stream) == [0]
