@@ -325,6 +325,7 @@ class _StreamState:
 
     def __init__(self, c, words, splits):
         self.c, self.c_ref, self.words, self.splits = c, C.byref(c), words, splits
+        self.stream = None  # as a torch stream, for calls while another one is current
 
 
 class DevicePattern:
@@ -479,7 +480,8 @@ def sparse_attn_fwd(q, k, v, out, pattern: DevicePattern, scale: float,
         raise ValueError("lse must be a contiguous fp32 CUDA tensor [B, H, N]")
     bq = pattern.host.block_q if block_q is None else block_q
     bk = pattern.host.block_k if block_k is None else block_k
-    stream, other = _stream_of(stream, q.device)
+    current = _current_handle(q.device)
+    stream = current if stream is None else int(stream)
     state = pattern._for_stream(stream)
     split = state.splits.get(B) if kernel != KERNEL_TWO_WORKGROUPS and bq == pattern.host.block_q else None
     packed = q.is_contiguous() and out.is_contiguous()
@@ -491,13 +493,24 @@ def sparse_attn_fwd(q, k, v, out, pattern: DevicePattern, scale: float,
         opt = _CFwdOptions(None if packed else C.pointer(si), None if packed else C.pointer(so),
                            0 if dtype == torch.bfloat16 else 1, None if lse is None else lse.data_ptr(), int(kernel))
         st = None
-        if split is None:
-            pass
-        elif other is None:
-            st = _split_call(lib, args, opt, split, bq, D, q.device, stream)
-        else:
-            with torch.cuda.stream(other):
-                st = _split_call(lib, args, opt, split, bq, D, q.device, stream)
+        if split is not None:
+            split_args = lib, args, opt, split, bq, D, q.device, stream
+            if stream == current or not split.n_slots:
+                st = _split_call(*split_args)
+            else:
+                if state.stream is None:
+                    state.stream = _torch_stream(stream, q.device)
+                if torch.cuda.current_device() == q.device.index:
+                    # torch.cuda.stream() takes 3 us more: it looks after the device as well
+                    back = torch.cuda.current_stream()
+                    torch.cuda.set_stream(state.stream)
+                    try:
+                        st = _split_call(*split_args)
+                    finally:
+                        torch.cuda.set_stream(back)
+                else:
+                    with torch.cuda.stream(state.stream):
+                        st = _split_call(*split_args)
         if st is None:
             st = lib.calibatt_sparse_attn_fwd_ex(*args, C.byref(opt), stream)
     if st != 0:
@@ -630,15 +643,20 @@ def _torch_stream(handle: int, device):
     return torch.cuda.ExternalStream(handle, device=device) if handle else torch.cuda.default_stream(device)
 
 
+def _current_handle(device) -> int:
+    """Handle of torch's current stream (a stream object costs 2 us, as much as half a launch)."""
+    import torch
+
+    index = device.index
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
+
+
 def _stream_of(stream, device):
     """(handle, other): the stream handle of a call (None = torch's current stream), and that stream as a torch stream
     where it is not the current one.  What a call allocates is allocated under ``torch.cuda.stream(other)`` (None = the
     current one): free memory of the current stream may still be in use by work of its last owner there, which nothing
     orders before another stream."""
-    import torch
-
-    index = device.index  # the raw handle: a stream object costs 2 us, as much as half a launch
-    current = torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
+    current = _current_handle(device)
     if stream is None or int(stream) == current:
         return current, None
     return int(stream), _torch_stream(int(stream), device)

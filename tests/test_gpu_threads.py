@@ -125,3 +125,33 @@ def test_default_stream_by_its_handle(lib):
             torch.cuda.synchronize()
             assert torch.equal(out.view(torch.int16), want)
     assert list(dp._per_stream) == [0]
+
+
+def test_stream_objects_are_made_once(lib, monkeypatch):
+    """A call on another than the current stream makes a torch stream of the handle the first time that it needs one
+    (rows that are not cut need none), and leaves the current stream and device as they were, also when it is refused."""
+    import torch
+
+    from paper_2603_05503_amd import binding
+
+    print("stream objects", flush=True)
+    H, N, D, blk = 4, 2000, 128, 128
+    q, k, v = (to_dev(x) for x in _qkv(907, 1, H, N, D, 2.0))
+    mask, repeat = random_mask(908, H, 16, 16, 0.6, 0.2, tail_partial=True)
+    hp = lib.compile_pattern(mask, repeat, H, N, blk, blk)
+    made, plain = [], torch.cuda.ExternalStream
+    monkeypatch.setattr(torch.cuda, "ExternalStream", lambda *a, **kw: made.append(a) or plain(*a, **kw))
+    side, current, out = torch.cuda.Stream(), torch.cuda.current_stream(), torch.empty_like(q)
+    for max_blocks, most in ((2, 1), (1000, 0)):
+        dp = hp.to_device()
+        dp._plan(True, max_blocks)
+        assert (dp._plans[1][0].n_slots > 0) == (most > 0)
+        made.clear()
+        for _ in range(3):
+            lib.sparse_attn_fwd(q, k, v, out, dp, 0.09, stream=side.cuda_stream)
+            assert torch.cuda.current_stream() == current
+        assert len(made) == most
+        with pytest.raises(binding.CalibattError):
+            lib.sparse_attn_fwd(q, k, v, out, dp, 0.09, block_k=7, stream=side.cuda_stream)
+        assert torch.cuda.current_stream() == current and torch.cuda.current_device() == 0
+    torch.cuda.synchronize()
