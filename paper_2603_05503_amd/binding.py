@@ -328,6 +328,27 @@ class _StreamState:
         self.stream = None  # as a torch stream, for calls while another one is current
 
 
+def _upload(arrays, device):
+    """{name: int32 tensor on ``device``} of host integer arrays; an empty one becomes one zero.  A copy takes 8 us however
+    little it moves, so small arrays go together, each at a cache line of its own; from 64 KB on an array goes by itself."""
+    import torch
+
+    out, small, n = {}, [], 0
+    for name, a in arrays.items():
+        if a.size > 1 << 14:
+            out[name] = torch.from_numpy(np.ascontiguousarray(a, np.int32)).to(device)
+        else:
+            small.append((name, a, n))
+            n += -(-max(a.size, 1) // 32) * 32
+    flat = np.zeros(n, np.int32)
+    for _, a, at in small:
+        flat[at:at + a.size] = a.reshape(-1)
+    dev = torch.from_numpy(flat).to(device)
+    for name, a, at in small:
+        out[name] = dev[at:at + max(a.size, 1)].view(a.shape if a.size else (1,))
+    return out
+
+
 class DevicePattern:
     """The six index arrays as int32 torch tensors on the GPU plus the C struct
     that points at them."""
@@ -335,65 +356,48 @@ class DevicePattern:
     _NAMES = ("row_ptr", "col_idx", "repeat_src", "work", "fan_ptr", "fan_dst")
 
     def __init__(self, hp: HostPattern, device="cuda", persistent=True, intervals=False, head_map=None):
-        import torch
-
         self.host = hp
-        self.tensors = {}
+        self.device = device
         self.intervals = bool(intervals)
         self._iv_ptr = None
-        for name in self._NAMES:
-            if intervals and name == "col_idx":
-                continue
-            a = getattr(hp, name)
-            t = torch.from_numpy(np.ascontiguousarray(a if a.size else np.zeros(1, np.int32)))
-            self.tensors[name] = t.to(device)
+        lists = {name: getattr(hp, name) for name in self._NAMES if not (intervals and name == "col_idx")}
+        if intervals:
+            self._iv_ptr, iv = hp.encode_intervals()
+            lists["iv_ptr"], lists["iv"] = self._iv_ptr, iv.view(np.int32)
+        if head_map is not None:
+            lists["head_map"] = np.asarray(head_map).reshape(-1)
+            if lists["head_map"].size != hp.H:
+                raise ValueError(f"head_map has {lists['head_map'].size} entries, the pattern has {hp.H} heads")
         c = _CPattern()
         for f in ("H", "N", "block_q", "block_k", "nbq", "nbk", "n_work", "n_repeat", "order", "max_row", "nnz"):
             setattr(c, f, getattr(hp, f))
-        for name in self._NAMES:
-            setattr(c, name, self.tensors[name].data_ptr() if name in self.tensors else None)
-        if intervals:
-            iv_ptr, iv = hp.encode_intervals()
-            self.tensors["iv_ptr"] = torch.from_numpy(iv_ptr).to(device)
-            self.tensors["iv"] = torch.from_numpy(iv.view(np.int32)).to(device)
-            self._iv_ptr = iv_ptr
-            c.iv_ptr = self.tensors["iv_ptr"].data_ptr()
-            c.iv = self.tensors["iv"].data_ptr()
-        else:
-            c.iv_ptr = None
-            c.iv = None
-        if head_map is not None:
-            hm = np.ascontiguousarray(head_map, dtype=np.int32).reshape(-1)
-            if hm.size != hp.H:
-                raise ValueError(f"head_map has {hm.size} entries, the pattern has {hp.H} heads")
-            self.tensors["head_map"] = torch.from_numpy(hm).to(device)
-            c.head_map = self.tensors["head_map"].data_ptr()
-        else:
-            c.head_map = None
-        self.device = device
-        self.c = c
-        self._plan(persistent)
         c.n_groups = hp.n_groups
         gp = hp.group_ptr if hp.group_ptr is not None else np.array([0] + [hp.n_work] * 8, np.int32)
         for i in range(9):
             c.group_ptr[i] = int(gp[i])
+        self.c = c
+        self.tensors = self._plan(persistent, lists=lists)
+        for name in (*self._NAMES, "iv_ptr", "iv", "head_map"):
+            setattr(c, name, self.tensors[name].data_ptr() if name in self.tensors else None)
 
-    def _plan(self, persistent, max_blocks=0):
+    def _plan(self, persistent, max_blocks=0, lists=None):
         """Plans of the calls cut along the keys (batches of one and, for two guidance branches, two), and the counters:
         per stream an int32[16] workspace of the persistent-workgroup scheduler and the arrivals of the cut rows' parts,
-        both kept zero between calls, here for eight streams, cleared so that no call has to."""
-        import torch
-
-        self._plans = {}
+        both kept zero between calls, here for eight streams.  All of it goes to the GPU together with ``lists`` and is there
+        when the call returns; the tensors of the lists are returned."""
+        host, plans = dict(lists or {}), {}
         if persistent:
             for B in (1, 2):
                 plan = self.host.plan_split(B, max_blocks, self._iv_ptr)
                 if plan:
-                    self._plans[B] = (plan[0], torch.from_numpy(plan[1]).to(self.device))
-        # the arrivals behind the scheduler's words, whole cache lines for every stream
-        arrivals = max((p.n_rows for p, _ in self._plans.values()), default=0)
-        self._words = 32 + -(-arrivals // 32) * 32
-        self._spare = list(torch.zeros((8, self._words), dtype=torch.int32, device=self.device)) if persistent else []
+                    plans[B], host[B] = plan
+            # the arrivals behind the scheduler's words, whole cache lines for every stream
+            arrivals = max((p.n_rows for p in plans.values()), default=0)
+            self._words = 32 + -(-arrivals // 32) * 32
+            host["words"] = np.zeros((8, self._words), np.int32)
+        tensors = _upload(host, self.device)
+        self._plans = {B: (plan, tensors.pop(B)) for B, plan in plans.items()}
+        self._spare = list(tensors.pop("words")) if persistent else []
         words = self._spare.pop(0) if persistent else None
         self.counter = words[:16] if persistent else None
         self.c.work_counter = self.counter.data_ptr() if persistent else None
@@ -401,6 +405,7 @@ class DevicePattern:
         self._own = _StreamState(self.c, words, self._splits_with(words))
         self._per_stream = {}     # other streams: clone of the struct, its own words, splits with its own arrivals
         self._lock = threading.Lock()
+        return tensors
 
     def _splits_with(self, words):
         """{B: struct of the planned split whose arrivals are counted behind the scheduler's ``words``}"""

@@ -35,16 +35,22 @@ int32_t parts_of(int32_t len, int32_t longest) {
 // that 512 equal rows fill the device exactly (4 heads of 16 380 tokens, all blocks kept: 483 us, cut in two 496).
 int32_t choose_longest(const std::vector<int32_t> &rows_of_length, int B, double stages, int slots) {
   const int32_t max_row = (int32_t)rows_of_length.size() - 1;
+  std::vector<std::pair<int32_t, int32_t>> lengths;  // (length, rows)
+  double blocks = 0.0;
+  for (int32_t len = 0; len <= max_row; ++len)
+    if (const int32_t rows = rows_of_length[(size_t)len]) {
+      lengths.push_back({len, rows});
+      blocks += (double)len * rows;
+    }
   int32_t best = max_row;
   double best_cost = 0.0;
   for (int32_t longest = max_row;; longest = longest * 7 / 8) {
-    double parts = 0.0, blocks = 0.0, chain = 0.0;
-    for (int32_t len = 0; len <= max_row; ++len) {
-      if (!rows_of_length[(size_t)len]) continue;
-      const int32_t k = parts_of(len, longest);
-      parts += (double)k * rows_of_length[(size_t)len];
-      blocks += (double)len * rows_of_length[(size_t)len];
-      chain = std::max(chain, (double)((len + k - 1) / k));
+    int64_t parts = 0;
+    int32_t chain = 0;
+    for (const auto &l : lengths) {
+      const int32_t k = parts_of(l.first, longest);
+      parts += (int64_t)k * l.second;
+      chain = std::max(chain, (l.first + k - 1) / k);
     }
     const double share = B * (blocks * stages + PART_COST * parts) / slots, cost = share * share +
         CHAIN_WEIGHT * chain * stages * CHAIN_WEIGHT * chain * stages;
@@ -52,6 +58,17 @@ int32_t choose_longest(const std::vector<int32_t> &rows_of_length, int B, double
     else if (cost < best_cost) best = longest, best_cost = cost;
     if (longest <= 1) return best;
   }
+}
+
+// Sorts by key(x), in [0, n_keys), and keeps equals in order.  (Comparing instead takes 50 ns an entry and sort, most of a
+// plan: 704 rows of 64 blocks 45 us.)
+template <typename KeyOf>
+void sort_by(std::vector<int32_t> &a, int32_t n_keys, KeyOf key) {
+  std::vector<int32_t> at((size_t)n_keys + 1, 0), sorted(a.size());
+  for (int32_t x : a) ++at[(size_t)key(x) + 1];
+  for (int32_t k = 0; k < n_keys; ++k) at[(size_t)k + 1] += at[(size_t)k];
+  for (int32_t x : a) sorted[(size_t)at[(size_t)key(x)]++] = x;
+  a.swap(sorted);
 }
 
 }  // namespace
@@ -71,56 +88,60 @@ extern "C" int calibatt_plan_split(const calibatt_pattern *pattern, int B, int m
   auto length = [&](int32_t id) { return row_ptr[id + 1] - row_ptr[id]; };
   try {
     // rows in the order of heads and query blocks
-    std::vector<std::pair<int32_t, int32_t>> rows((size_t)n);
-    int32_t max_row = 1;
+    std::vector<int32_t> rows((size_t)n);  // items
+    int32_t max_row = 1, max_id = 0;
     for (int i = 0; i < n; ++i) {
-      rows[(size_t)i] = {pattern->work[i], i};
+      rows[(size_t)i] = i;
+      max_id = std::max(max_id, pattern->work[i]);
       max_row = std::max(max_row, length(pattern->work[i]));
     }
-    std::sort(rows.begin(), rows.end());
+    sort_by(rows, max_id + 1, [&](int32_t i) { return pattern->work[i]; });
     int32_t longest = max_blocks;
     if (longest == 0) {
       std::vector<int32_t> rows_of_length((size_t)max_row + 1, 0);
-      for (const auto &r : rows) ++rows_of_length[(size_t)length(r.first)];
+      for (int32_t i : rows) ++rows_of_length[(size_t)length(pattern->work[i])];
       longest = choose_longest(rows_of_length, B, stages, slots);
     }
     // cut into parts of nearly equal length
     std::vector<Part> all;
+    all.reserve((size_t)n * B);
     int32_t n_slots = 0, n_rows = 0;
     double total = 0.0;
     auto cost = [&](const Part &p) { return p.count * stages + PART_COST; };
     for (int b = 0; b < B; ++b)
-      for (const auto &r : rows) {
-        const int32_t len = length(r.first), k = parts_of(len, longest);
+      for (int32_t i : rows) {
+        const int32_t id = pattern->work[i], len = length(id), k = parts_of(len, longest);
         for (int32_t j = 0; j < k; ++j) {
           const int32_t lo = (int32_t)((int64_t)len * j / k), hi = (int32_t)((int64_t)len * (j + 1) / k);
-          all.push_back({r.second, r.first, lo, hi - lo, j, k, k > 1 ? n_slots : 0, k > 1 ? n_rows : 0, b});
+          all.push_back({i, id, lo, hi - lo, j, k, k > 1 ? n_slots : 0, k > 1 ? n_rows : 0, b});
           total += cost(all.back());
         }
         if (k > 1) n_slots += k, ++n_rows;
       }
     // eight ranges of equal cost, one per XCD, of the parts ordered by batch, head and the keys in their middle, so that
     // an XCD's workgroups share keys in its L2; in each the longest parts first
+    std::vector<int32_t> order(all.size());
+    for (size_t i = 0; i < all.size(); ++i) order[i] = (int32_t)i;
     if (pattern->col_idx) {
-      auto middle = [&](const Part &p) {
-        return p.count ? pattern->col_idx[row_ptr[p.id] + p.first + p.count / 2] : 0;
-      };
-      const int nbq = pattern->nbq;
-      std::stable_sort(all.begin(), all.end(), [&](const Part &a, const Part &b) {
-        if (a.b != b.b) return a.b < b.b;
-        return a.id / nbq != b.id / nbq ? a.id / nbq < b.id / nbq : middle(a) < middle(b);
+      const int32_t nbq = pattern->nbq, heads = max_id / nbq + 1, last = std::max(pattern->nbk, 1) - 1;
+      sort_by(order, last + 1, [&](int32_t i) {
+        const Part &p = all[(size_t)i];
+        const int32_t middle = p.count ? pattern->col_idx[row_ptr[p.id] + p.first + p.count / 2] : 0;
+        return std::min(std::max(middle, 0), last);
       });
+      sort_by(order, B * heads, [&](int32_t i) { return all[(size_t)i].b * heads + all[(size_t)i].id / nbq; });
     }
-    std::vector<Part> list[CALIBATT_GROUPS];
+    std::vector<int32_t> list[CALIBATT_GROUPS];
     double before = 0.0;
-    for (const Part &p : all) {
+    for (int32_t i : order) {
+      const Part &p = all[(size_t)i];
       const int x = (int)((before + 0.5 * cost(p)) * CALIBATT_GROUPS / total);
-      list[std::min(x, CALIBATT_GROUPS - 1)].push_back(p);
+      list[std::min(x, CALIBATT_GROUPS - 1)].push_back(i);
       before += cost(p);
     }
     size_t most = 0;
     for (auto &l : list) {
-      std::stable_sort(l.begin(), l.end(), [](const Part &a, const Part &b) { return a.count > b.count; });
+      sort_by(l, max_row + 1, [&](int32_t i) { return max_row - all[(size_t)i].count; });
       most = std::max(most, l.size());
     }
     const int64_t n_parts = (int64_t)most * CALIBATT_GROUPS;
@@ -139,7 +160,7 @@ extern "C" int calibatt_plan_split(const calibatt_pattern *pattern, int B, int m
           std::fill(rec, rec + CALIBATT_PART_WORDS, -1);
           continue;
         }
-        const Part &p = list[x][i];
+        const Part &p = all[(size_t)list[x][i]];
         const int32_t fan = pattern->fan_ptr[p.item];
         const int32_t words[CALIBATT_PART_WORDS] = {
             p.id, p.first, p.count, row_ptr[p.id] + p.first,

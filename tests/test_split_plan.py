@@ -100,3 +100,42 @@ def test_plan_of_lists_that_are_views(lib):
         assert (got[1] == want[1]).all() and got[0].n_slots == want[0].n_slots
     backwards = dataclasses.replace(hp, work=np.ascontiguousarray(hp.work[::-1])[::-1])
     assert (backwards.plan_split(1, 3)[1] == want[1]).all()
+
+
+@pytest.mark.parametrize("intervals,head_map,persistent", [(False, None, True), (True, [5, 0, 2], True), (True, None, False)])
+def test_a_small_pattern_is_one_copy(lib, monkeypatch, intervals, head_map, persistent):
+    """Lists, plans and counters of a pattern go to the device in one copy, long lists in one of their own, with the values
+    of the host."""
+    import torch
+
+    copies, plain = [], torch.from_numpy
+    monkeypatch.setattr(torch, "from_numpy", lambda a: copies.append(a.size) or plain(a))
+    for n, more in ((20, 0), (130, 0 if intervals else 1)):
+        mask, repeat = random_mask(n, 3, n, n, 0.5, 0.2, keep_diagonal=True)
+        mask[1, 3] = 0
+        hp = lib.compile_pattern(mask, repeat, 3, n * 128, 128, 128)
+        copies.clear()
+        dp = hp.to_device("cpu", persistent=persistent, intervals=intervals, head_map=head_map)
+        assert len(copies) == 1 + more + (n == 130 and persistent) * sum(p.n_parts * 12 > 1 << 14 for p, _ in dp._plans.values())
+        want = {name: getattr(hp, name) for name in dp._NAMES if not (intervals and name == "col_idx")}
+        if intervals:
+            want["iv_ptr"], want["iv"] = hp.encode_intervals()
+        if head_map:
+            want["head_map"] = np.array(head_map, np.int32)
+        assert sorted(dp.tensors) == sorted(want)
+        for name, a in want.items():
+            t = dp.tensors[name]
+            assert t.dtype == torch.int32 and t.is_contiguous() and t.data_ptr() % 16 == 0
+            assert getattr(dp.c, name) == t.data_ptr()
+            assert (t.numpy().view(a.dtype) == a).all() if a.size else t.tolist() == [0]
+        assert bool(dp._plans) == persistent
+        for B, (split, parts) in dp._plans.items():
+            host = hp.plan_split(B, 0, dp._iv_ptr)
+            assert (parts.numpy() == host[1]).all() and parts.data_ptr() % 16 == 0 and split.n_rows == host[0].n_rows
+        if persistent:
+            words = [dp._own.words, *dp._spare]
+            assert len(words) == 8 and all(len(w) == dp._words and not w.any() and w.data_ptr() % 128 == words[0].data_ptr() % 128
+                                           for w in words)
+            assert dp.c.work_counter == dp.counter.data_ptr() == words[0].data_ptr()
+        else:
+            assert dp.counter is None and dp.c.work_counter is None
