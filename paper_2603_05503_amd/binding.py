@@ -448,9 +448,18 @@ class DevicePattern:
 
     @property
     def index_bytes(self) -> int:
-        """Bytes of the kept-block lists on the GPU (col_idx, or iv_ptr + iv in the interval form)."""
+        """Bytes of the kept-block lists on the GPU (col_idx, or iv_ptr + iv in the interval form), without ``plan_bytes``."""
         names = ("iv_ptr", "iv") if self.intervals else ("col_idx",)
         return sum(self.tensors[n].numel() * 4 for n in names)
+
+    @property
+    def plan_bytes(self) -> int:
+        """Bytes on the GPU that calls cut along the keys need beside the lists: the records of the plans, and the arrivals
+        of the streams so far."""
+        if self.counter is None:
+            return 0
+        streams = 1 + len(self._spare) + len(self._per_stream)
+        return sum(parts.numel() * 4 for _, parts in self._plans.values()) + streams * (self._words - 32) * 4
 
 
 def sparse_attn_fwd(q, k, v, out, pattern: DevicePattern, scale: float,

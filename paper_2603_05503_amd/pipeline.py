@@ -210,8 +210,16 @@ class CalibAttention:
     @property
     def index_bytes(self) -> int:
         """Bytes of kept-block lists resident on the GPU (a pattern shared by several keys counts once)."""
+        return sum(p.index_bytes for p in self._patterns())
+
+    @property
+    def plan_bytes(self) -> int:
+        """Bytes that the plans of calls cut along the keys take beside them."""
+        return sum(p.plan_bytes for p in self._patterns())
+
+    def _patterns(self):
         unique = {id(e): e for e in self.entries.values()}
-        return sum(e.pattern.index_bytes for e in unique.values() if e.pattern is not None)
+        return [e.pattern for e in unique.values() if e.pattern is not None]
 
     @property
     def index_bytes_unshared(self) -> int:

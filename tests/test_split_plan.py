@@ -139,3 +139,22 @@ def test_a_small_pattern_is_one_copy(lib, monkeypatch, intervals, head_map, pers
             assert dp.c.work_counter == dp.counter.data_ptr() == words[0].data_ptr()
         else:
             assert dp.counter is None and dp.c.work_counter is None
+
+
+def test_plan_bytes(lib):
+    """What the plans take on the GPU is reported, for a pattern and for a dictionary whose keys share one."""
+    from paper_2603_05503_amd.pipeline import CalibAttention
+
+    mask, repeat = random_mask(3, 2, 64, 64, 0.4, 0.1, keep_diagonal=True)
+    hp = lib.compile_pattern(mask, repeat, 2, 64 * 128, 128, 128)
+    dp = hp.to_device("cpu", intervals=True)
+    plans = [hp.plan_split(B) for B in (1, 2)]
+    rows = max(p[0].n_rows for p in plans)
+    assert rows > 0
+    want = sum(p[1].nbytes for p in plans) + 8 * -(-rows // 32) * 32 * 4
+    assert dp.plan_bytes == want and want > dp.index_bytes
+    assert hp.to_device("cpu", persistent=False).plan_bytes == 0
+    att = CalibAttention(2, 64 * 128, 128, device="cpu")
+    att.add("a", mask, repeat=repeat)
+    att.entries["b"] = att.entries["a"]
+    assert att.plan_bytes == want and att.index_bytes == dp.index_bytes
