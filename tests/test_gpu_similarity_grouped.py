@@ -230,3 +230,47 @@ def test_temporaries_belong_to_the_stream_of_the_call(lib):
     assert torch.equal(score, want) and torch.equal(triples, want_triples)
     for t in (score, energy, mask):
         assert any(s["address"] <= t.data_ptr() < s["address"] + s["total_size"] for s in segments())
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_long_runs_are_cut(lib, D):
+    """Runs of up to 64 rows stay whole wherever they lie; longer ones, whose tokens would walk past all of their rows, end
+    at every 64th row."""
+    import torch
+
+    print(f"grouped similarity: long runs D={D}", flush=True)
+    raw = lib.load_library()
+    lengths = [64, 65, 63, 3, 200, 1, 64, 66, 129, 30, 64, 1, 2, 128, 70]
+    rows, cols, H = sum(lengths), 7, 1
+    n = rows * cols
+    N = n + len(lengths)
+    rng = np.random.default_rng(8)
+    partner, want = np.empty((rows, cols), np.int64), np.zeros(3, np.int64)
+    for x in range(cols):
+        y = 0
+        for i in rng.permutation(len(lengths)):
+            end = y + lengths[i]
+            kind = rng.integers(3)  # the partner is a token of the run, a token of another column or one behind the grid
+            row = int(rng.integers(y, end)) if kind == 0 else -1
+            partner[y:end, x] = row * cols + x if kind == 0 else y * cols + (x + 1) % cols if kind == 1 else n + i
+            cuts = [y] + ([c for c in range(y + 1, end) if c % 64 == 0] if end - y > 64 else []) + [end]
+            for lo, hi in zip(cuts, cuts[1:]):
+                inside = lo <= row < hi
+                tokens = hi - lo - inside
+                want += [-(-tokens // 2), -(-tokens // 3), inside and tokens == 0]
+            y = end
+    partner = torch.from_numpy(partner.reshape(-1).astype(np.int32)).cuda()
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q, k = (torch.randn(1, H, N, D, device="cuda", generator=gen).mul_(2.0).to(torch.bfloat16) for _ in range(2))
+    out = []
+    for lists in (None, torch.full((36 * n + 16,), 0x5A, dtype=torch.uint8, device="cuda")):
+        triples = torch.full((1, H, n, 3), float("nan"), device="cuda")
+        score = torch.full((1, H), float("nan"), device="cuda")
+        assert raw.calibatt_spatial_similarity_grouped(
+            q.data_ptr(), k.data_ptr(), 1, H, N, D, partner.data_ptr(), n, cols, 1 / math.sqrt(D), triples.data_ptr(),
+            None if lists is None else lists.data_ptr(), 0 if lists is None else lists.numel(), score.data_ptr(),
+            C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+        torch.cuda.synchronize()
+        out.append((triples, score))
+    assert np.frombuffer(lists[:12].cpu().numpy().tobytes(), np.int32).tolist() == want.tolist()
+    assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for a, b in zip(*out))

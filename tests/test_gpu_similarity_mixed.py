@@ -41,7 +41,7 @@ def _mixed(lists, H, n, cus):
 @pytest.mark.parametrize("kind,frames,rows,cols,mixed", [
     ("l6", 3, 29, 41, True), ("o5", 4, 40, 40, True), ("f6", 4, 30, 40, False), ("f8", 3, 40, 40, False),
     ("a5", 18, 30, 32, None), ("f9", 4, 46, 40, None), ("o8", 3, 64, 33, None),
-    ("f6", 1, 1100, 5, None),  # longer than a segment
+    ("f6", 1, 1100, 5, None),  # many runs in a column
     ("f2", 4, 30, 40, False),  # runs of one token
 ])
 def test_mixed_groups(lib, D, kind, frames, rows, cols, mixed):
