@@ -384,10 +384,11 @@ class DevicePattern:
         """Plans of the calls cut along the keys (batches of one and, for two guidance branches, two), and the counters:
         per stream an int32[16] workspace of the persistent-workgroup scheduler and the arrivals of the cut rows' parts,
         both kept zero between calls, here for eight streams.  All of it goes to the GPU together with ``lists`` and is there
-        when the call returns; the tensors of the lists are returned."""
+        when the call returns; the tensors of the lists are returned.  ``max_blocks``: as of ``plan_split``, None = no plans,
+        every call takes whole rows."""
         host, plans = dict(lists or {}), {}
         if persistent:
-            for B in (1, 2):
+            for B in (1, 2) if max_blocks is not None else ():
                 plan = self.host.plan_split(B, max_blocks, self._iv_ptr)
                 if plan:
                     plans[B], host[B] = plan

@@ -5,7 +5,7 @@ import math
 import numpy as np
 import pytest
 
-from tests.parity_utils import bits_to_f64, from_dev, to_dev
+from tests.parity_utils import bits_to_f64, cut_rows, from_dev, to_dev, whole_rows
 from workloads import f32_to_bf16_bits
 
 pytestmark = pytest.mark.gpu
@@ -95,11 +95,7 @@ def test_sparse_rows(lib, D, bq, bk, max_blocks):
     (q, k, v), scale, want = two_keys(D, N, 700, 1100, 5)
     nbq, nbk = -(-N // bq), -(-N // bk)
     dp = lib.compile_pattern(np.ones((1, nbq, nbk), np.uint8), None, 1, N, bq, bk).to_device(intervals=True)
-    if max_blocks is None:
-        dp._plans = {}
-        dp._own.splits = {}
-    else:
-        dp._plan(True, max_blocks)
+    dp = whole_rows(dp) if max_blocks is None else cut_rows(dp, max_blocks)
     out = torch.full((1, 1, N, D), math.nan, dtype=torch.bfloat16, device="cuda")
     lib.sparse_attn_fwd(to_dev(q), to_dev(k), to_dev(v), out, dp, scale)
     torch.cuda.synchronize()

@@ -6,7 +6,7 @@ import math
 import numpy as np
 import pytest
 
-from tests.parity_utils import from_dev, to_dev
+from tests.parity_utils import cut_rows, from_dev, queues_ran, to_dev, whole_rows
 from workloads import f32_to_bf16_bits, random_mask
 
 pytestmark = pytest.mark.gpu
@@ -24,7 +24,7 @@ def test_graph_replays_match_eager(lib):
     mask, repeat = random_mask(18, H - 2, nb, nb, 0.3, 0.2, keep_diagonal=True, tail_partial=True)
     hp = lib.compile_pattern(mask, repeat, H - 2, N, blk, blk, 3)
     dp = hp.to_device(persistent=True, intervals=True, head_map=list(range(2, H)))
-    assert hp.n_work * B > 512
+    assert hp.n_work * B > 512 and B not in dp._plans
     amap = lib.anchor_map(N, F, Hs, Ws, 3).to_device()
     heads = torch.tensor([0, 1], dtype=torch.int32, device="cuda")
     tq, tk, tv = to_dev(q), to_dev(k), to_dev(v)
@@ -57,14 +57,16 @@ def test_graph_replays_match_eager(lib):
         torch.cuda.synchronize()
         assert (from_dev(out) == want).all(), f"replay {i}"
         assert (from_dev(eager) == want).all()
+    assert all(queues_ran(s.words) for s in (dp._own, *dp._per_stream.values())) and len(dp._per_stream) == 1
 
 
-def test_calls_on_two_streams_overlap_safely(lib):
+@pytest.mark.parametrize("rows", ["queues", "cut"])
+def test_calls_on_two_streams_overlap_safely(lib, rows):
     """No state is shared between calls except the caller's workspaces: two patterns, each with its
     own workspace, launched on two streams at the same time give the bits of the serial runs."""
     import torch
 
-    print("two streams", flush=True)
+    print(f"two streams: {rows}", flush=True)
     B, H, N, D, blk = 2, 16, 3000, 128, 128
     rng = np.random.default_rng(19)
     q, k, v = (f32_to_bf16_bits((2.0 * rng.standard_normal((B, H, N, D))).astype(np.float32)) for _ in range(3))
@@ -73,7 +75,8 @@ def test_calls_on_two_streams_overlap_safely(lib):
     pats = []
     for seed, dens in ((20, 0.3), (21, 0.6)):
         mask, repeat = random_mask(seed, H, nb, nb, dens, 0.2, keep_diagonal=True, tail_partial=True)
-        pats.append(lib.compile_pattern(mask, repeat, H, N, blk, blk, 3).to_device(persistent=True, intervals=seed == 21))
+        dp = lib.compile_pattern(mask, repeat, H, N, blk, blk, 3).to_device(persistent=True, intervals=seed == 21)
+        pats.append(whole_rows(dp) if rows == "queues" else cut_rows(dp, 4))
     assert all(dp.host.n_work * B > 512 for dp in pats)
     serial = []
     for dp in pats:
@@ -92,6 +95,8 @@ def test_calls_on_two_streams_overlap_safely(lib):
         torch.cuda.synchronize()
         for out, want in zip(outs, serial):
             assert (from_dev(out) == want).all(), rep
+    for dp in pats:
+        assert queues_ran(dp._per_stream[streams[pats.index(dp)].cuda_stream].words) == (rows == "queues")
 
 
 def test_workspace_calls_replay_under_a_graph(lib):

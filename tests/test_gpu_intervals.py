@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 from oracle import sparse_attention, sparse_attention_blocks
-from tests.parity_utils import MAX_ABS, assert_parity, assert_repeats_bitwise, bits_to_f64, from_dev, to_dev
+from tests.parity_utils import MAX_ABS, assert_parity, assert_repeats_bitwise, bits_to_f64, from_dev, to_dev, whole_rows
 from workloads import f32_to_bf16_bits, make_workload, random_mask
 
 pytestmark = pytest.mark.gpu
@@ -21,13 +21,13 @@ def _qkv(seed, B, H, N, D, gain=1.0):
     return q, k, v
 
 
-def _both(lib, q, k, v, hp, scale, persistent=True):
+def _both(lib, q, k, v, hp, scale, persistent=True, prepare=lambda dp: dp):
     import torch
 
     tq, tk, tv = to_dev(q), to_dev(k), to_dev(v)
     outs = []
     for intervals in (False, True):
-        dp = hp.to_device(persistent=persistent, intervals=intervals)
+        dp = prepare(hp.to_device(persistent=persistent, intervals=intervals))
         out = torch.empty_like(tq)
         out.view(torch.int16).fill_(0x7FC1)
         lib.sparse_attn_fwd(tq, tk, tv, out, dp, scale)
@@ -61,27 +61,41 @@ def test_intervals_equal_indices(lib, B, H, N, D, bq, bk, density, rep, persiste
     assert_repeats_bitwise(by_interval, repeat, bq, N)
 
 
-def test_row_longer_than_one_lds_chunk(lib):
-    """More than 2048 kept blocks in a row: the column list is expanded in pieces."""
-    print("intervals long row", flush=True)
-    B, H, N, D, blk = 1, 1, 140000, 64, 64
-    nb = -(-N // blk)  # 2188
+@pytest.mark.parametrize("block_q,piece", [(64, 1024), (128, 2048)])
+@pytest.mark.parametrize("rows", ["whole", "one part", "two parts"])
+def test_row_longer_than_one_lds_chunk(lib, block_q, piece, rows):
+    """More kept blocks in a row, or in a part of one, than the piece of the column list that is expanded at a time."""
+    print(f"intervals long row block_q={block_q} {rows}", flush=True)
+    B, H, D, blk = 1, 1, 64, 64
+    N = 140000 if block_q == 64 or rows != "two parts" else 270000  # 2188 or 4219 key blocks
+    nbq, nb = -(-N // block_q), -(-N // blk)
     q, k, v = _qkv(47, B, H, N, D, 1.5)
     rng = np.random.default_rng(48)
-    mask = np.zeros((H, nb, nb), np.uint8)
-    mask[0, np.arange(nb), np.arange(nb)] = 1
-    mask[0, 5, :] = 1                                   # one run of 2188 blocks
-    mask[0, 9, :] = (rng.random(nb) < 0.97)             # many runs, more than 2048 kept blocks
-    mask[0, 9, 2047:2052] = [1, 0, 1, 1, 0]
-    mask[0, nb - 1, ::2] = 1                            # the ragged last block, alternating
-    assert mask[0, 9].sum() > 2048
-    hp = lib.compile_pattern(mask, None, H, N, blk, blk, 1)
-    by_index, by_interval = _both(lib, q, k, v, hp, 0.125)
-    assert (by_index == by_interval).all()
-    items = [(0, 0, 5), (0, 0, 9), (0, 0, nb - 1), (0, 0, 100)]
-    want = sparse_attention_blocks(q, k, v, mask, None, 0.125, blk, blk, items)
+    mask = np.zeros((H, nbq, nb), np.uint8)
+    mask[0, np.arange(nb) * blk // block_q, np.arange(nb)] = 1
+    mask[0, 5, :] = 1                                   # one run of all blocks
+    mask[0, 9, :] = (rng.random(nb) < 0.985)            # many runs, more kept blocks than a piece
+    for end in (1024, 2048):                            # the ends of the pieces of whole rows fall into short runs
+        at = int(np.searchsorted(np.cumsum(mask[0, 9]), end))
+        mask[0, 9, at - 1:at + 4] = [1, 0, 1, 1, 0]
+    mask[0, nbq - 1, ::2] = 1                           # the ragged last block, alternating
+    hp = lib.compile_pattern(mask, None, H, N, block_q, blk, 1)
+    longest = 5000 if rows == "one part" else -(-nb // 2)
+
+    def prepare(dp):
+        if rows == "whole":
+            return whole_rows(dp)
+        dp._plan(True, longest)
+        parts = dp._plans[1][1].cpu().numpy()
+        assert np.sort(parts[:, 2])[-2 if rows == "one part" else -4] > piece  # rows 5 and 9, or both their parts
+        return dp
+
+    by_index, by_interval = _both(lib, q, k, v, hp, 0.125, prepare=prepare)
+    assert mask[0, 9].sum() > piece and (by_index == by_interval).all()
+    items = [(0, 0, 5), (0, 0, 9), (0, 0, nbq - 1), (0, 0, 100)]
+    want = sparse_attention_blocks(q, k, v, mask, None, 0.125, block_q, blk, items)
     for (b, h, r), w in zip(items, want):
-        got = bits_to_f64(by_interval[b, h, r * blk : r * blk + w.shape[0]])
+        got = bits_to_f64(by_interval[b, h, r * block_q : r * block_q + w.shape[0]])
         assert np.abs(got - w).max() <= MAX_ABS, r
 
 

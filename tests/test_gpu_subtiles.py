@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from oracle import sparse_attention
-from tests.parity_utils import assert_parity
+from tests.parity_utils import assert_parity, from_dev, to_dev, whole_rows
 from workloads import f32_to_bf16_bits
 
 pytestmark = pytest.mark.gpu
@@ -14,13 +14,12 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("D,bq,bk", [(128, 128, 64), (64, 128, 64), (64, 64, 64), (128, 64, 64), (128, 128, 128),
                                      (128, 64, 128), (128, 128, 192), (128, 128, 96), (128, 128, 160)])
-@pytest.mark.parametrize("intervals", [False, True])
-def test_every_short_row(lib, D, bq, bk, intervals):
+@pytest.mark.parametrize("intervals,rows", [(False, "whole"), (True, "whole"), (False, "one part"), (True, "one part"),
+                                            (False, "planned")])
+def test_every_short_row(lib, D, bq, bk, intervals, rows):
     import torch
 
-    from tests.parity_utils import from_dev, to_dev
-
-    print(f"sub-tiles D={D} {bq}x{bk} intervals={intervals}", flush=True)
+    print(f"sub-tiles D={D} {bq}x{bk} intervals={intervals} {rows}", flush=True)
     counts = [0, 1, 2, 3, 4, 5, 6, 63, 64, 65, 66]
     nbk = 67
     N = nbk * bk - 29  # short last key block
@@ -37,7 +36,13 @@ def test_every_short_row(lib, D, bq, bk, intervals):
         mask[0, r, cols] = 1
     assert set(mask[0].sum(1).tolist()) == set(counts)
     hp = lib.compile_pattern(mask, None, 1, N, bq, bk)
+    dp = hp.to_device(intervals=intervals)
+    if rows == "whole":
+        whole_rows(dp)
+    elif rows == "one part":
+        dp._plan(True, 1000)
+        assert set(dp._plans[1][1].cpu().numpy()[:, 2].tolist()) - {-1} == set(counts)
     out = torch.full((1, 1, N, D), math.nan, dtype=torch.bfloat16, device="cuda")
-    lib.sparse_attn_fwd(to_dev(q), to_dev(k), to_dev(v), out, hp.to_device(intervals=intervals), 1 / math.sqrt(D))
+    lib.sparse_attn_fwd(to_dev(q), to_dev(k), to_dev(v), out, dp, 1 / math.sqrt(D))
     torch.cuda.synchronize()
     assert_parity(from_dev(out), sparse_attention(q, k, v, mask, np.full((1, nbq), -1, np.int32), 1 / math.sqrt(D), bq, bk))

@@ -6,21 +6,23 @@ import threading
 import numpy as np
 import pytest
 
+from tests.parity_utils import cut_rows, queues_ran, whole_rows
 from tests.test_gpu_parity import _qkv
 from workloads import random_mask, to_dev
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("kernel", ["auto", "2wg"])
-def test_four_threads_four_streams(lib, kernel):
+@pytest.mark.parametrize("kernel,H", [("auto", 6), ("queues", 30), ("2wg", 30)])
+def test_four_threads_four_streams(lib, kernel, H):
     import torch
 
     from paper_2603_05503_amd import binding
 
     print(f"threads kernel={kernel}", flush=True)
-    which = binding.KERNEL_AUTO if kernel == "auto" else binding.KERNEL_TWO_WORKGROUPS
-    B, H, N, D, blk = 1, 6, 128 * 24 + 50, 128, 128
+    which = binding.KERNEL_TWO_WORKGROUPS if kernel == "2wg" else binding.KERNEL_AUTO
+    prepare = (lambda dp: cut_rows(dp, 4)) if kernel == "auto" else whole_rows
+    B, N, D, blk = 1, 128 * 24 + 50, 128, 128
     nb = -(-N // blk)
     n_threads, rounds = 4, 6
     cases = []
@@ -28,12 +30,13 @@ def test_four_threads_four_streams(lib, kernel):
         q, k, v = _qkv(700 + i, B, H, N, D, 2.0)
         mask, repeat = random_mask(800 + i, H, nb, nb, 0.3 + 0.1 * i, 0.2, tail_partial=True)
         hp = lib.compile_pattern(mask, repeat, H, N, blk, blk, 4)
+        assert kernel == "auto" or hp.n_work > 512  # more rows than workgroups
         cases.append((to_dev(q), to_dev(k), to_dev(v), hp))
     # serial reference bits, each case with a workspace of its own
     want = []
     for tq, tk, tv, hp in cases:
         out = torch.empty_like(tq)
-        lib.sparse_attn_fwd(tq, tk, tv, out, hp.to_device(), 0.09, kernel=which)
+        lib.sparse_attn_fwd(tq, tk, tv, out, prepare(hp.to_device()), 0.09, kernel=which)
         torch.cuda.synchronize()
         want.append(out.view(torch.int16).clone())
     errors = []
@@ -43,7 +46,7 @@ def test_four_threads_four_streams(lib, kernel):
         try:
             tq, tk, tv, hp = cases[i]
             stream = torch.cuda.Stream()
-            dp = hp.to_device()  # own index tensors and own work counters
+            dp = prepare(hp.to_device())  # own index tensors and own work counters
             outs = [torch.empty_like(tq) for _ in range(rounds)]
             torch.cuda.synchronize()
             barrier.wait()
@@ -55,6 +58,8 @@ def test_four_threads_four_streams(lib, kernel):
             for r in range(rounds):
                 if not torch.equal(outs[r].view(torch.int16), want[i]):
                     errors.append((i, r, "bits differ from the serial call"))
+            if queues_ran(dp.counter) != (kernel != "auto"):
+                errors.append((i, -1, "another launch than the one meant"))
         except Exception as e:  # noqa: BLE001
             errors.append((i, -1, repr(e)))
 
@@ -67,23 +72,25 @@ def test_four_threads_four_streams(lib, kernel):
     assert not errors, errors
 
 
-def test_first_calls_on_streams_do_not_wait_for_another(lib):
-    """A pattern that is in use gets cleared work counters for every further stream, also while the stream that was
-    current when the call was made is busy and its free memory holds other values."""
+@pytest.mark.parametrize("rows", ["queues", "cut"])
+def test_first_calls_on_streams_do_not_wait_for_another(lib, rows):
+    """A pattern that is in use gets cleared work counters and arrivals for every further stream, also while the stream
+    that was current when the call was made is busy and its free memory holds other values."""
     import torch
 
-    print("first calls on ten streams", flush=True)
+    print(f"first calls on ten streams: {rows}", flush=True)
     B, H, N, D, blk = 2, 16, 3000, 128, 128
     nb = -(-N // blk)
     tq, tk, tv = (to_dev(x) for x in _qkv(900, B, H, N, D, 2.0))
     mask, repeat = random_mask(901, H, nb, nb, 0.3, 0.2, tail_partial=True)
     dp = lib.compile_pattern(mask, repeat, H, N, blk, blk, 3).to_device(persistent=True)
-    assert dp.host.n_work * B > 512  # more items than workgroups: the counters are used
+    dp = whole_rows(dp) if rows == "queues" else cut_rows(dp, 4)
+    assert dp.host.n_work * B > 512  # more items than workgroups: whole rows use the counters
     want = lib.sparse_attn_fwd(tq, tk, tv, torch.empty_like(tq), dp, 0.09).view(torch.int16).clone()
     streams = [torch.cuda.Stream() for _ in range(10)]
     outs = [torch.full_like(tq, float("nan")) for _ in streams]
     for _ in range(64):
-        torch.full((16,), 1 << 24, dtype=torch.int32, device="cuda")
+        torch.full((dp._words,), 1 << 24, dtype=torch.int32, device="cuda")
     torch.cuda.synchronize()
     torch.cuda._sleep(200_000_000)
     for out, s in zip(outs, streams):
@@ -94,6 +101,9 @@ def test_first_calls_on_streams_do_not_wait_for_another(lib):
     torch.cuda.synchronize()
     for i, out in enumerate(outs):
         assert torch.equal(out.view(torch.int16), want), i
+    states = [dp._own, *dp._per_stream.values()]
+    assert len(states) == 11 and not dp._spare
+    assert all(queues_ran(s.words) == (rows == "queues") and not s.words[32:].any() for s in states)
 
 
 def test_default_stream_by_its_handle(lib):
@@ -106,11 +116,9 @@ def test_default_stream_by_its_handle(lib):
     H, N, D, blk = 4, 2000, 128, 128
     q, k, v = (to_dev(x) for x in _qkv(905, 1, H, N, D, 2.0))
     mask, repeat = random_mask(906, H, 16, 16, 0.6, 0.2, tail_partial=True)
-    dp = lib.compile_pattern(mask, repeat, H, N, blk, blk).to_device()
-    dp._plan(True, 2)
+    dp = cut_rows(lib.compile_pattern(mask, repeat, H, N, blk, blk).to_device(), 2)
     want = lib.sparse_attn_fwd(q, k, v, torch.empty_like(q), dp, 0.09).view(torch.int16).clone()
-    dp._plan(True, 2)
-    dp._spare.clear()
+    cut_rows(dp, 2)._spare.clear()
     side, out = torch.cuda.Stream(), torch.empty_like(q)
     torch.cuda.synchronize()
     with torch.cuda.stream(side):
