@@ -34,7 +34,6 @@ def test_cut_rows(lib, D, bq, bk, max_blocks, intervals):
 
     print(f"split D={D} {bq}x{bk} max_blocks={max_blocks} intervals={intervals}", flush=True)
     B, H, N = 2, 2, 13 * bk - 37
-    q, k, v = _qkv(D + bq + bk, B, H, N, D)
     nbq, nbk = -(-N // bq), -(-N // bk)
     mask, repeat = random_mask(bk, H, nbq, nbk, 0.6, 0.2, tail_partial=N % bq != 0)
     mask[0, 1, :] = 0
@@ -43,19 +42,23 @@ def test_cut_rows(lib, D, bq, bk, max_blocks, intervals):
     dp = _pattern(lib, mask, repeat, H, N, bq, bk, max_blocks, intervals)
     lse = torch.full((B, H, N), math.nan, dtype=torch.float32, device="cuda")
     out = torch.full((B, H, N, D), math.nan, dtype=torch.bfloat16, device="cuda")
-    want = sparse_attention(q, k, v, mask, repeat, scale, bq, bk)
-    want_lse = sparse_attention_lse(q, k, mask, repeat, scale, bq, bk)
+    # Other inputs from call to call, whose workspaces the allocator puts in one place: parts that a call left would show in the
+    # next one's result.  The third call has the bits of the first (the arrivals were re-armed).
     first = None
-    for _ in range(3):  # later calls also check that the arrivals were re-armed
+    for seed in (0, 1, 0):
+        q, k, v = _qkv(D + bq + bk + seed, B, H, N, D)
         lib.sparse_attn_fwd(to_dev(q), to_dev(k), to_dev(v), out, dp, scale, lse=lse)
         torch.cuda.synchronize()
-        got = from_dev(out)
+        got, got_lse = from_dev(out), lse.cpu().numpy()
+        if seed == 0 and first is not None:
+            assert (got == first).all()
+            break
         first = got if first is None else first
-        assert (got == first).all()
-    assert_parity(first, want)
-    assert_repeats_bitwise(first, repeat, bq, N)
-    got_lse, kept = lse.cpu().numpy(), np.isfinite(want_lse)
-    assert (np.isneginf(got_lse) == ~kept).all() and np.abs(got_lse[kept] - want_lse[kept]).max() <= 5e-3
+        assert_parity(got, sparse_attention(q, k, v, mask, repeat, scale, bq, bk))
+        assert_repeats_bitwise(got, repeat, bq, N)
+        want_lse = sparse_attention_lse(q, k, mask, repeat, scale, bq, bk)
+        kept = np.isfinite(want_lse)
+        assert (np.isneginf(got_lse) == ~kept).all() and np.abs(got_lse[kept] - want_lse[kept]).max() <= 5e-3
 
 
 def test_f16_strided_head_subset(lib):
