@@ -7,7 +7,7 @@ import pytest
 
 from oracle import sparse_attention
 from oracle.attention import sparse_attention_lse
-from tests.parity_utils import assert_parity, from_dev, to_dev
+from tests.parity_utils import assert_parity, cut_rows, from_dev, to_dev, whole_rows
 from workloads import f32_to_bf16_bits
 
 pytestmark = pytest.mark.gpu
@@ -41,11 +41,7 @@ def test_reference_moves(lib, D, bq, bk, steps, max_blocks):
     mask[1, :, 1::3] = 0
     none = np.full((H, nbq), -1, np.int32)
     dp = lib.compile_pattern(mask, None, H, N, bq, bk).to_device(intervals=max_blocks is None)
-    if max_blocks is None:
-        dp._plans = {}
-        dp._own.splits = {}
-    else:
-        dp._plan(True, max_blocks)
+    dp = whole_rows(dp) if max_blocks is None else cut_rows(dp, max_blocks)
     out = torch.full((1, H, N, D), math.nan, dtype=torch.bfloat16, device="cuda")
     lse = torch.full((1, H, N), math.nan, dtype=torch.float32, device="cuda")
     lib.sparse_attn_fwd(to_dev(q), to_dev(k), to_dev(v), out, dp, scale, lse=lse)
@@ -54,6 +50,33 @@ def test_reference_moves(lib, D, bq, bk, steps, max_blocks):
     want = sparse_attention_lse(q, k, mask, none, scale, bq, bk)
     # fp32 logits of up to 300 carry an error of some 2^-24 of their size and of that of the products they are summed from
     assert np.abs(lse.cpu().numpy() - want).max() <= 5e-3
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("steps", list(STEPS))
+@pytest.mark.parametrize("split", [False, True], ids=["whole", "split"])
+def test_reference_moves_in_anchor_rows(lib, D, steps, split):
+    import torch
+
+    print(f"reference, anchor rows D={D} {steps} split={split}", flush=True)
+    H, (F, Hs, Ws) = 2, (2, 20, 50)
+    N = F * Hs * Ws
+    rng = np.random.default_rng(D)
+    scale = 1 / math.sqrt(D)
+    x = [rng.standard_normal((1, H, N, D)).astype(np.float32) for _ in range(3)]
+    x[0][..., 0] = np.where(np.arange(N) % 3 == 0, 4.0, 2.0)
+    x[1][..., 0] = (STEPS[steps] * math.log(2) / (4.0 * scale))[np.arange(N) * 16 // N]
+    q, k, v = (f32_to_bf16_bits(a) for a in x)
+    amap = lib.anchor_map(N, F, Hs, Ws, Hs).to_device()  # every row is an anchor
+    n_split, nbytes = lib.anchor_split_plan(1, N, D, H, amap.n_q)
+    assert n_split > 1
+    workspace = torch.full((nbytes // 4,), math.nan, dtype=torch.float32, device="cuda") if split else None
+    out = torch.full((1, H, N, D), math.nan, dtype=torch.bfloat16, device="cuda")
+    lib.anchor_attn_fwd(to_dev(q), to_dev(k), to_dev(v), out, torch.arange(H, dtype=torch.int32, device="cuda"), amap, scale,
+                        workspace=workspace)
+    torch.cuda.synchronize()
+    mask, none = np.ones((H, 16, 16), np.uint8), np.full((H, 16), -1, np.int32)
+    assert_parity(from_dev(out), sparse_attention(q, k, v, mask, none, scale, 128, 128))
 
 
 def test_large_values_behind_a_move(lib):
