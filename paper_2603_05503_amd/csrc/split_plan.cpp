@@ -14,11 +14,13 @@ struct Part {
   int32_t item, id, first, count, part, n_parts, slot, row, b;
 };
 
-// Costs in stages of 64 keys, fitted to sweeps of the longest part over 41 shapes (1 to 40 heads of 1 024 to 35 100
-// tokens, densities 0.15 to 0.9, every block size and head dimension): what a part costs beside its stages (its start, its
-// sums to memory and back) and how the longest part weighs against an even share of the whole.  The lengths chosen
-// take 1.6 % more time than the best ones of the sweeps, 14 % at most.
-constexpr double PART_COST = 8.0, CHAIN_WEIGHT = 0.4;
+// Costs in stages of 64 keys, fitted to sweeps of the longest part over 1 624 calls (1 to 40 heads of 1 000 to 70 000 tokens,
+// densities 0.12 to 1, banded and uniform masks, every block size and head dimension): what a part costs beside its stages
+// (its start, its sums to memory and back), and how the longest part and the rounds weigh against an even share of the whole.
+// The lengths chosen take 1.5 % more time than the best ones of the sweeps.  Without the rounds it was 3 %, and 10 of 1 469
+// planned calls took over 5 % longer than whole rows, 13 % at most, now one: near-equal rows cut in two to a few more parts
+// than there are slots.  2 heads of 16 320 tokens, 256 rows of 48 blocks: whole 130 us, in 520 parts 147, in 768 128.
+constexpr double PART_COST = 10.0, CHAIN_WEIGHT = 0.7, ROUNDS_WEIGHT = 0.6;
 // Workgroups that the device holds at a time: 256 CUs, two each of 128 queries, four of 64.
 constexpr int slots_of(int block_q) { return block_q >= 128 ? 512 : 1024; }
 // Above so many stages per slot whole rows are the better choice: their workgroups pop from queues that keep an XCD at one head,
@@ -30,31 +32,38 @@ int32_t parts_of(int32_t len, int32_t longest) {
   return std::max(1, std::min<int32_t>(CALIBATT_MAX_PARTS, len / longest + (len % longest != 0)));
 }
 
-// The longest part, in key blocks, whose estimated time is least: an even share of all work and the longest part,
-// whichever is larger, smoothly.  Rows stay whole where cutting them promises less than 3 %: the estimate does not see
-// that 512 equal rows fill the device exactly (4 heads of 16 380 tokens, all blocks kept: 483 us, cut in two 496).
+// The longest part, in key blocks, whose estimated time is least: an even share of all work, the longest part, and the
+// rounds, whichever is largest, smoothly.  Rounds: of k * slots + 1 parts some slot takes k + 1, none of them shorter than
+// the last of these when they are sorted by length.  Rows stay whole where cutting them promises less than 3 %.
 int32_t choose_longest(const std::vector<int32_t> &rows_of_length, int B, double stages, int slots) {
   const int32_t max_row = (int32_t)rows_of_length.size() - 1;
-  std::vector<std::pair<int32_t, int32_t>> lengths;  // (length, rows)
-  double blocks = 0.0;
+  std::vector<std::pair<int32_t, int64_t>> lengths;  // (length, rows of it over the batch)
   for (int32_t len = 0; len <= max_row; ++len)
-    if (const int32_t rows = rows_of_length[(size_t)len]) {
-      lengths.push_back({len, rows});
-      blocks += (double)len * rows;
-    }
+    if (rows_of_length[(size_t)len]) lengths.push_back({len, (int64_t)B * rows_of_length[(size_t)len]});
+  std::vector<int64_t> parts((size_t)max_row + 1);  // by length
+  auto cube = [](double x) { return x * x * x; };
   int32_t best = max_row;
   double best_cost = 0.0;
   for (int32_t longest = max_row;; longest = longest * 7 / 8) {
-    int64_t parts = 0;
+    std::fill(parts.begin(), parts.end(), 0);
     int32_t chain = 0;
     for (const auto &l : lengths) {
-      const int32_t k = parts_of(l.first, longest);
-      parts += (int64_t)k * l.second;
-      chain = std::max(chain, (l.first + k - 1) / k);
+      const int32_t k = parts_of(l.first, longest), less = l.first / k, more = l.first % k;
+      parts[(size_t)less] += (k - more) * l.second;
+      if (more) parts[(size_t)less + 1] += more * l.second;
+      chain = std::max(chain, less + (more != 0));
     }
-    const double share = B * (blocks * stages + PART_COST * parts) / slots, cost = share * share +
-        CHAIN_WEIGHT * chain * stages * CHAIN_WEIGHT * chain * stages;
-    if (longest == max_row) best_cost = 0.97 * 0.97 * cost;
+    double total = 0.0, rounds = 0.0;
+    int64_t n = 0;
+    for (int32_t len = chain; len >= 0; --len)
+      if (parts[(size_t)len]) {
+        const double cost = len * stages + PART_COST;
+        total += cost * (double)parts[(size_t)len];
+        n += parts[(size_t)len];
+        if (n > slots) rounds = std::max(rounds, (double)((n - 1) / slots + 1) * cost);
+      }
+    const double cost = cube(total / slots) + cube(CHAIN_WEIGHT * chain * stages) + cube(ROUNDS_WEIGHT * rounds);
+    if (longest == max_row) best_cost = cube(0.97) * cost;
     else if (cost < best_cost) best = longest, best_cost = cost;
     if (longest <= 1) return best;
   }

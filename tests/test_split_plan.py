@@ -158,3 +158,13 @@ def test_plan_bytes(lib):
     att.add("a", mask, repeat=repeat)
     att.entries["b"] = att.entries["a"]
     assert att.plan_bytes == want and att.index_bytes == dp.index_bytes
+
+
+@pytest.mark.parametrize("H,n,density", [(2, 128, 0.376), (2, 128, 0.25), (3, 95, 0.75), (2, 128, 0.46), (3, 90, 0.4)])
+def test_no_round_for_a_few_parts(lib, H, n, density):
+    """Rows of nearly one length are not cut into a few more parts than the 512 workgroups that the device holds."""
+    for seed in range(3):
+        mask, _ = random_mask(seed, H, n, n, density)
+        plan = lib.compile_pattern(mask, None, H, n * 128, 128, 128).plan_split(1)
+        n_parts = 0 if plan is None else len(_records(plan)[1])
+        assert not 512 < n_parts < 600, n_parts
