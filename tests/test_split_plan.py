@@ -168,3 +168,33 @@ def test_no_round_for_a_few_parts(lib, H, n, density):
         plan = lib.compile_pattern(mask, None, H, n * 128, 128, 128).plan_split(1)
         n_parts = 0 if plan is None else len(_records(plan)[1])
         assert not 512 < n_parts < 600, n_parts
+
+
+@pytest.mark.parametrize("H,n,density,bq", [(12, 85, 0.686, 128), (4, 128, 0.5, 128), (2, 512, 0.1, 64), (20, 60, 0.6, 128), (5, 77, 1.0, 64)])
+@pytest.mark.parametrize("max_blocks", [0, 7, 1000])
+@pytest.mark.parametrize("with_columns", [True, False])
+def test_no_xcd_has_a_round_more(lib, H, n, density, bq, max_blocks, with_columns):
+    """An XCD, with an eighth of the workgroups, gets no more parts than it takes in the rounds that all parts need."""
+    mask, _ = random_mask(n, H, n, n, density)
+    mask[0] = np.tril(mask[0])  # uneven rows: shares of equal cost hold different numbers of parts
+    hp = lib.compile_pattern(mask, None, H, n * bq, bq, bq)
+    if not with_columns:
+        c = binding._CPattern()
+        for f in ("H", "N", "block_q", "block_k", "nbq", "nbk", "n_work", "n_repeat", "order", "max_row", "nnz"):
+            setattr(c, f, getattr(hp, f))
+        c.row_ptr, c.work, c.fan_ptr = (a.ctypes.data for a in (hp.row_ptr, hp.work, hp.fan_ptr))
+        split, buf = binding._CSplit(), np.empty((200000, 12), np.int32)
+        assert binding.load_library().calibatt_plan_split(C.byref(c), 1, max_blocks, binding._ptr(buf, C.c_int32), len(buf),
+                                                          C.byref(split)) == 0
+        plan = (split, buf[:split.n_parts]) if split.n_parts else None
+    else:
+        plan = hp.plan_split(1, max_blocks)
+    if plan is None:
+        return
+    slots = 512 if bq == 128 else 1024
+    _, live = _records(plan)
+    of_xcd = [int((plan[1][x::8, 0] >= 0).sum()) for x in range(8)]
+    assert max(of_xcd) <= slots // 8 * -(-len(live) // slots)
+    # every row is there, once
+    assert sorted(set(live[:, 0].tolist())) == sorted(hp.work.tolist())
+    assert (np.bincount(live[:, 0], live[:, 2], minlength=H * n)[hp.work] == (hp.row_ptr[1:] - hp.row_ptr[:-1])[hp.work]).all()
