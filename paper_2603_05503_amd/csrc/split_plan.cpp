@@ -21,8 +21,9 @@ struct Part {
 // planned calls took over 5 % longer than whole rows, 13 % at most, now one: near-equal rows cut in two to a few more parts
 // than there are slots.  2 heads of 16 320 tokens, 256 rows of 48 blocks: whole 130 us, in 520 parts 147, in 768 128.
 constexpr double PART_COST = 10.0, CHAIN_WEIGHT = 0.7, ROUNDS_WEIGHT = 0.6;
-// Workgroups that the device holds at a time: 256 CUs, two each of 128 queries, four of 64.
-constexpr int slots_of(int block_q) { return block_q >= 128 ? 512 : 1024; }
+constexpr int CUS = 256;
+// Workgroups that the device holds at a time: two per CU of 128 queries, four of 64.
+constexpr int slots_of(int block_q) { return CUS * (block_q >= 128 ? 2 : 4); }
 // Above so many stages per slot whole rows are the better choice: their workgroups pop from queues that keep an XCD at one head,
 // and their tail is small beside the call.  128-key blocks, us whole / by plan: 44 000 blocks (172 stages a slot) 470 /
 // 369, 59 600 514 / 491, 70 300 636 / 641, 141 000 1 112 / 1 123; 64-query blocks: 117 000 833 / 742.
@@ -143,7 +144,11 @@ extern "C" int calibatt_plan_split(const calibatt_pattern *pattern, int B, int m
     // An XCD has an eighth of the slots, and no XCD gets more parts than its slots take in the rounds that all parts need:
     // 1 020 rows of 58 blocks (10 846 tokens, 12 heads) 507 us where one XCD had a third round for a few of them, and 709
     // for 1 024 rows of 116 with 64-query blocks, against 459 and 564 for whole rows from the queues.
-    const int32_t n_all = (int32_t)order.size(), most_of_xcd = slots / CALIBATT_GROUPS * ((n_all - 1) / slots + 1);
+    // Of parts that fit at a time no XCD gets more than its CUs take by ones, by twos and so on: of 255 rows (15 heads of
+    // 2 115 tokens) an XCD got 33 for its 32 CUs, uncut 49.6 us against 41.1 and 42.0 whole; one head of 30 679, 240 rows,
+    // 543 against 474 and 492.
+    const int32_t n_all = (int32_t)order.size(), step = n_all <= slots ? CUS : slots,
+                  most_of_xcd = step / CALIBATT_GROUPS * ((n_all - 1) / step + 1);
     std::vector<int32_t> list[CALIBATT_GROUPS];
     double before = 0.0;
     int xcd = 0;
