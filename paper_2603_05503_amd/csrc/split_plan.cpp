@@ -14,28 +14,36 @@ struct Part {
   int32_t item, id, first, count, part, n_parts, slot, row, b;
 };
 
-// Costs in stages of 64 keys, fitted to sweeps of the longest part over 1 624 calls (1 to 40 heads of 1 000 to 70 000 tokens,
-// densities 0.12 to 1, banded and uniform masks, every block size and head dimension): what a part costs beside its stages
-// (its start, its sums to memory and back), and how the longest part and the rounds weigh against an even share of the whole.
-// The lengths chosen take 1.5 % more time than the best ones of the sweeps.  Without the rounds it was 3 %, and 10 of 1 469
-// planned calls took over 5 % longer than whole rows, 13 % at most, now one: near-equal rows cut in two to a few more parts
-// than there are slots.  2 heads of 16 320 tokens, 256 rows of 48 blocks: whole 130 us, in 520 parts 147, in 768 128.
-constexpr double PART_COST = 10.0, CHAIN_WEIGHT = 0.7, ROUNDS_WEIGHT = 0.6;
+// Costs in stages of 64 keys, fitted to every second of 2 487 calls for which the longest part was swept (1 to 40 heads of 900
+// to 40 000 tokens, densities 0.12 to 1, banded and uniform masks, every block size and head dimension): what a part costs
+// beside its stages (its start, its sums to memory); what adding up costs the longest row, once and for each of its parts;
+// and how the longest part, the part that is the first to share a CU, and the rounds weigh against an even share of the
+// whole.  Over all of them the lengths chosen take 1.6 % more time than the best ones of the sweep, and 12 calls over 2 % more
+// than whole rows; without adding up and shared CUs 2.5 %, and 33: 24 heads of 992 tokens 12.6 us whole, 14.9 with 10 rows
+// cut; one head of 8 190 tokens 34.9 us in 288 parts, 30.5 in 256.  Without the rounds 2 heads of 16 320 tokens, 256 rows of 48
+// blocks, were cut into a few more parts than there are slots: whole 130 us, in 520 parts 147, in 768 128.
+constexpr double PART_COST = 10.0, CHAIN_WEIGHT = 0.75, SHARED_WEIGHT = 0.2, ROUNDS_WEIGHT = 0.8;
+constexpr double MERGE_COST = 1.5, MERGE_COST_PER_PART = 0.9;
 constexpr int CUS = 256;
 // Workgroups that the device holds at a time: two per CU of 128 queries, four of 64.
 constexpr int slots_of(int block_q) { return CUS * (block_q >= 128 ? 2 : 4); }
-// Above so many stages per slot whole rows are the better choice: their workgroups pop from queues that keep an XCD at one head,
-// and their tail is small beside the call.  128-key blocks, us whole / by plan: 44 000 blocks (172 stages a slot) 470 /
-// 369, 59 600 514 / 491, 70 300 636 / 641, 141 000 1 112 / 1 123; 64-query blocks: 117 000 833 / 742.
+// Above so many stages per slot every call takes whole rows: their workgroups pop from queues that keep an XCD at one head,
+// which outweighs an even end where there are many rows for every slot.  The line is a coarse one.  It goes by the work, not
+// by what the last round leaves idle, and above it calls of 1 to 1.5 rows a slot would gain from cutting.  us, whole rows /
+// by the plan if this line were not there, with stages a slot: 40 heads of 10 000 tokens (6.2 rows a slot) 449 / 440 at 206,
+// 565 / 563 at 273, 956 / 989 at 494; 8 heads of 33 000 (4.0) 1 216 / 1 267 at 628; 12 heads of 16 380 (3.0) 520 / 499 at 257,
+// 573 / 557 at 287; 2 heads of 33 000 (1.01) 648 / 592 at 262, 789 / 661 at 313, 1 216 / 955 at 468; one of 75 600 (1.15)
+// 814 / 696 at 341; 64-query blocks, 2 heads of 33 000 (1.01) 506 / 375 at 261, 682 / 498 at 364.
 constexpr int64_t MAX_STAGES_PER_SLOT = 270;
 
 int32_t parts_of(int32_t len, int32_t longest) {
   return std::max(1, std::min<int32_t>(CALIBATT_MAX_PARTS, len / longest + (len % longest != 0)));
 }
 
-// The longest part, in key blocks, whose estimated time is least: an even share of all work, the longest part, and the
-// rounds, whichever is largest, smoothly.  Rounds: of k * slots + 1 parts some slot takes k + 1, none of them shorter than
-// the last of these when they are sorted by length.  Rows stay whole where cutting them promises less than 3 %.
+// The longest part, in key blocks, whose estimated time is least: an even share of all work, the longest row's way, and
+// the rounds, whichever is largest, smoothly.  Sorted by length, the part behind one for every CU shares the CU of a longer
+// one, and of k * slots + 1 parts some slot takes k + 1, none of them shorter than the last of these.  Rows stay whole
+// where cutting them promises less than 3 %.
 int32_t choose_longest(const std::vector<int32_t> &rows_of_length, int B, double stages, int slots) {
   const int32_t max_row = (int32_t)rows_of_length.size() - 1;
   std::vector<std::pair<int32_t, int64_t>> lengths;  // (length, rows of it over the batch)
@@ -54,16 +62,18 @@ int32_t choose_longest(const std::vector<int32_t> &rows_of_length, int B, double
       if (more) parts[(size_t)less + 1] += more * l.second;
       chain = std::max(chain, less + (more != 0));
     }
-    double total = 0.0, rounds = 0.0;
+    double total = 0.0, rounds = 0.0, way = CHAIN_WEIGHT * chain * stages;
+    if (longest < max_row) way += MERGE_COST + MERGE_COST_PER_PART * parts_of(max_row, longest);
     int64_t n = 0;
     for (int32_t len = chain; len >= 0; --len)
       if (parts[(size_t)len]) {
         const double cost = len * stages + PART_COST;
         total += cost * (double)parts[(size_t)len];
+        if (n <= CUS && n + parts[(size_t)len] > CUS) way += SHARED_WEIGHT * cost;
         n += parts[(size_t)len];
         if (n > slots) rounds = std::max(rounds, (double)((n - 1) / slots + 1) * cost);
       }
-    const double cost = cube(total / slots) + cube(CHAIN_WEIGHT * chain * stages) + cube(ROUNDS_WEIGHT * rounds);
+    const double cost = cube(total / slots) + cube(way) + cube(ROUNDS_WEIGHT * rounds);
     if (longest == max_row) best_cost = cube(0.97) * cost;
     else if (cost < best_cost) best = longest, best_cost = cost;
     if (longest <= 1) return best;

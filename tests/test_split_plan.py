@@ -203,3 +203,18 @@ def test_no_xcd_has_a_round_more(lib, H, n, density, bq, max_blocks, with_column
     # every row is there, once
     assert sorted(set(live[:, 0].tolist())) == sorted(hp.work.tolist())
     assert (np.bincount(live[:, 0], live[:, 2], minlength=H * n)[hp.work] == (hp.row_ptr[1:] - hp.row_ptr[:-1])[hp.work]).all()
+
+
+@pytest.mark.parametrize("H,n,band", [(24, 8, 0.22), (28, 8, 0.24), (1, 64, 0.35), (3, 35, 0.31)])
+def test_cuts_count_adding_up_and_shared_cus(lib, H, n, band):
+    """Rows of one to four blocks are not cut to be added up for little, nor longer ones into a few more parts than there are
+    CUs (256)."""
+    for seed in range(3):
+        if n == 8:  # a band and a few blocks beside it
+            i = np.arange(n) / n
+            mask = (np.abs(i[:, None] - i) < band / 2) | (np.random.default_rng(seed).random((H, n, n)) < band / 5)
+            mask[:, np.arange(n), np.arange(n)] = 1
+        else:
+            mask, _ = random_mask(seed, H, n, n, band, keep_diagonal=True)
+        split, live = _records(lib.compile_pattern(mask.astype(np.uint8), None, H, n * 128, 128, 128).plan_split(1))
+        assert split.n_rows == 0 if n == 8 else len(live) <= 256, (split.n_rows, len(live))
