@@ -275,7 +275,8 @@ int calibatt_sparse_attn_fwd_ex(const void *q, const void *k, const void *v, voi
  * idles.  Here every row is cut into parts of about equal length, one workgroup
  * takes a part, and the last of a row's parts to finish adds up their sums in
  * the order of the keys.  Same result up to fp32 rounding, the same bits on
- * every run and for every schedule order of the pattern.
+ * every run and for every schedule order of the pattern; they depend on where a
+ * row is cut, which the other rows and the batch size decide.
  *
  * calibatt_plan_split (HOST): the parts of a pattern for batch B.
  *   pattern     as calibatt_compile_pattern filled it (HOST pointers row_ptr,

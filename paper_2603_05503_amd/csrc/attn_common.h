@@ -78,7 +78,7 @@ __device__ __forceinline__ u32x4 head_rsrc(const uint16_t *base, uint32_t bytes)
 // memory instruction reads a register that the scalar unit wrote; one that the compiler has just brought back from a
 // vector lane would need five wait states (csrc/check_sgpr_waits.py fails the build where they are missing).  The copy
 // costs the forward and short chains 0.5-1 % (480p 5.34 -> 5.38 ms), so it is made where scalar registers are scarce, and
-// in the energy kernels, which it makes 1 % faster (480p 10.50 -> 10.37 ms).
+// in the energy kernels, which it does not slow (480p 10.74 and 10.66 ms, within what two runs differ by).
 template <bool COPY>
 __device__ __forceinline__ void dma_16B_per_lane(const u32x4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds_off) {
   if constexpr (COPY) {

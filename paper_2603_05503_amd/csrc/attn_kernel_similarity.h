@@ -26,7 +26,7 @@
 // bits do not depend on how the tokens were grouped.
 //
 // Measured, 24 heads of 21 x 30 x 52 tokens, D = 128, five anchors, in turn on one box: 13.87 ms with every token
-// beside its own partner over whole tiles and one wavefront per head in the reduction, 9.84 ms in twos, 5 % less mixed.
+// beside its own partner over whole tiles and one wavefront per head in the reduction, 9.84 ms in twos, 2 % less mixed.
 //
 // Without groups, us with one score buffer (and before it, with whole tiles of 128 keys) -> with two: 210 units of 3840
 // keys, D = 128 95 (92) -> 81, D = 64 78 (73) -> 69; 480 units 148 (156) -> 141; 1800 units of 9600 keys 1299 (1427) ->
@@ -63,7 +63,7 @@ constexpr int SIM_GROUP_TOKENS = 512;
 
 // The mixed form is taken where the busiest CU has less than 96 % of the rows of the best other form to do, a row of
 // threes counted 1.15 times (their partner's operand comes from LDS).  Either side, rows of the others' best and of the
-// mixed form, D = 128: 24 heads of 21 x 30 x 52 tokens, five anchors, 36 and 34.2: 10.41 -> 9.93 ms (D = 64 7.58 -> 7.20);
+// mixed form, D = 128: 24 heads of 21 x 30 x 52 tokens, five anchors, 36 and 34.2: 10.20 -> 10.01 ms (D = 64 7.49 -> 7.19);
 // 18 heads of 4 x 30 x 32, five anchors, 176 -> 141 us; not taken: 12 heads of 8 x 32 x 75, four anchors, 12 and 11.7: 1.93
 // and 2.02 ms.
 constexpr int SIM_THREE_COST = 46, SIM_MIXED_GAIN = 96;  // tenths of a row, per cent

@@ -1,15 +1,15 @@
 // The interleaved forward (attn_kernel_il.h) with its rows cut along the keys.
 //
-// A row of key blocks is a chain: its sub-tiles go through one workgroup one after the other, 0.95 us per 64 keys at
-// D = 128 where the workgroup has its CU to itself (a wavefront's issue of some 260 instructions; windows of four
-// sub-tiles, loaded two stages earlier, change nothing) and 1.2 where two share it.  A call of few rows, or of a few long
+// A row of key blocks is a chain: its sub-tiles go through one workgroup one after the other, 0.97 us per 64 keys at
+// D = 128 where the workgroup has its CU to itself (a wavefront's issue of some 280 instructions; windows of four
+// sub-tiles, loaded two stages earlier, change nothing) and more where two share it.  A call of few rows, or of a few long
 // ones, lasts as long as the longest chain while most CUs idle.  Here the host cuts every row into parts of about equal
 // length (split_plan.cpp), one workgroup takes one part, leaves its sums in a workspace, and the one that finds itself
 // last adds them up.  Rows that are not cut go the same way: one workgroup each, the longest first, by the hardware's
 // dispatcher instead of the counters.
-// Measured (us, whole rows -> by plan; density 0.35 where not given): one head of 8 190 tokens 112 -> 33, four 118 -> 61,
-// twelve 180 -> 140; two heads of 16 380 at 0.25 166 -> 77, twelve 470 -> 365; twenty of 5 070, 64-query blocks, D = 64,
-// 150 -> 50.  Adding up costs 0.6 us per part of a row, 67 KB each at D = 128.
+// Measured (us, whole rows -> by plan; uniform masks, density 0.35 where not given): one head of 8 190 tokens 68 -> 31, four
+// 77 -> 70, twelve 184 -> 161; two heads of 16 380 at 0.25 98 -> 84, one with all blocks kept 246 -> 137; twenty of 5 070,
+// 64-query blocks, D = 64, 162 -> 70.  Adding up costs 0.6 us per part of a row, 67 KB each at D = 128.
 #pragma once
 #include "attn_kernel_il.h"
 
